@@ -6,26 +6,63 @@
 // vertex (bit-parallel multi-source BFS).  Every level is one bottom-up sweep:
 // a vertex ORs the frontier words of its neighbours, and the bits it had not
 // seen yet are the sources that reach it at this level.  A vertex stops
-// reading neighbours as soon as every source of the group has reached it, so
-// late levels touch little memory.  Vertices of degree above kHeavy are swept
-// by a whole wavefront (lanes split the neighbour list, then OR-reduce), the
-// rest by one lane each.  Counts are integers and the OR is order-free, so
-// the result does not depend on scheduling.
+// reading neighbours as soon as every source whose search still goes on has
+// reached it, so late levels touch little memory.
+//
+// The sweep is bound by the L2 requests of the random reads of the
+// neighbours' frontier words, so most of them are answered on the CU: a
+// coarse bitmap of the vertices with a nonempty word (at most 2^18 bits, one
+// per 2^k vertices) is held in LDS and looked up first, then an exact bitmap,
+// then the word; in a level with a sparse frontier nearly every lookup ends
+// in LDS.  The work is split by degree to keep the wavefronts busy: up to
+// kSmallDeg edges two lanes take a vertex (16 edges in flight), up to kMidDeg
+// 16 lanes, up to kHugeDeg a wavefront, and above that kSplit wavefronts share
+// it (a hub's list of 10^5 edges on one wavefront took most of a level).  The
+// levels are enqueued kBatch at a time and end themselves when the level
+// before reached nothing, so the host waits once per batch and not once per
+// level.  Measured against one lane per vertex up to 64 edges, one wavefront
+// above, no bitmaps and a wait per level: 8.35 -> 1.27 ms for 64 sources over an
+// R-MAT graph of 2 million vertices and 30 million entries (the same without
+// the bitmaps 2.9 ms), 332 -> 289 ms over a PBA graph of 2^27 vertices, whose
+// words (1 GB) are read from memory.
+// Counts are integers and the OR is order-free, so the result does not depend
+// on scheduling.
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 
 namespace sfg {
 namespace {
 
-constexpr int kPathThreads = 256;
-constexpr uint32_t kHeavy = 64;      // degree above which a wavefront sweeps the vertex
+constexpr int kPathThreads = 512;
 constexpr int kGroup = 64;           // sources per bit-parallel search
+constexpr uint64_t kSmallDeg = 16;   // degree above which 16 lanes take the vertex, not 2
+constexpr uint64_t kMidDeg = 256;    // degree above which a wavefront takes the vertex
+constexpr uint64_t kHugeDeg = 4096;  // degree above which kSplit wavefronts share it
+constexpr int kSplit = 64;
+constexpr int kBatch = 8;         // levels between two waits of the host
+constexpr int kCountSlots = 4;    // words a level's count is spread over (workgroup b adds to word b mod 4)
+constexpr int kListChunk = 16;    // vertices per thread of ps_init
+constexpr int kCoarseWords = 8192;  // 32-bit words of the LDS bitmap
+// The bitmaps are looked up while fewer than n / kDense vertices have a
+// nonempty word; in a denser level most lookups would go on to the word.
+constexpr uint64_t kDense = 8;
+
+// Control words of a search (64-bit).
+enum : int {
+    kCtlMid = 0,     // vertices above kMidDeg in the list
+    kCtlHuge = 1,    // vertices above kHugeDeg in the list
+    kCtlAlive = 2,   // sources that reached a vertex in the level before the batch (bits)
+    kCtlFront = 3,   // vertices with a nonempty word in that level
+    kCtlLevel = 4,   // then the same two words for each level of the batch
+    kCtlWords = kCtlLevel + 2 * kBatch,
+};
 
 struct PsPlan {
-    size_t off_vis, off_f0, off_f1, off_heavy, off_nheavy, off_cnt, total;
+    size_t off_vis, off_f0, off_f1, off_list, off_ctl, off_cnt, total;
 };
 
 PsPlan ps_plan(uint64_t n) {
@@ -39,20 +76,98 @@ PsPlan ps_plan(uint64_t n) {
     p.off_vis = take(n * 8);
     p.off_f0 = take(n * 8);
     p.off_f1 = take(n * 8);
-    p.off_heavy = take(n * 8);
-    p.off_nheavy = take(8);
-    p.off_cnt = take(8);
+    p.off_list = take(n * 8);  // 32-bit lists and, behind them, the bitmaps; or 64-bit lists
+    p.off_ctl = take(kCtlWords * 8);
+    p.off_cnt = take(kBatch * kCountSlots * 8);
     p.total = o;
     return p;
 }
 
-// Compact list of the heavy vertices (order irrelevant: every use is an OR or
-// an integer sum per vertex).
-__global__ __launch_bounds__(kPathThreads) void ps_heavy_list(const uint64_t *rp, uint64_t n, uint64_t *heavy,
-                                                            unsigned long long *nheavy) {
-    const uint64_t stride = (uint64_t)gridDim.x * kPathThreads;
-    for (uint64_t v = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x; v < n; v += stride)
-        if (rp[v + 1] - rp[v] > kHeavy) heavy[atomicAdd(nheavy, 1ull)] = v;
+// The searches' device state.  BITS (n <= 2^32): list entries are 32-bit and
+// the second half of the list region holds the bitmaps -- of the current
+// frontier, of the next one, and one being cleared for the level after.
+// Without BITS list entries are 64-bit, which leaves no room for bitmaps.
+struct Bitmap {
+    uint32_t *fine;    // one bit per vertex
+    uint32_t *coarse;  // one bit per 2^shift vertices; null when shift is 0 (fine fits the LDS words)
+};
+
+template <bool BITS> struct Search {
+    using ListT = typename std::conditional<BITS, uint32_t, uint64_t>::type;
+    uint64_t n;
+    const uint64_t *rp;
+    const void *col;
+    uint64_t *vis, *front, *next;  // next is written for every vertex
+    ListT *list;                   // middle degrees from the start, huge ones from the end
+    unsigned long long *ctl;
+    const unsigned long long *before;  // alive sources and frontier size of the level before
+    unsigned long long *now;           // the same of this level
+    unsigned long long *cnt;           // [kCountSlots] pairs found by this level
+    Bitmap f, x, z;                    // of the frontier, the next one, the one to clear
+    uint32_t shift;
+
+    __device__ __forceinline__ uint64_t words() const { return (n + 31) / 32; }
+    __device__ __forceinline__ uint64_t coarse_words() const { return ((n - 1) >> shift) / 32 + 1; }
+    __device__ __forceinline__ void mark(uint64_t v) const {
+        if (!BITS) return;
+        atomicOr(&x.fine[v >> 5], 1u << (v & 31));
+        if (shift) atomicOr(&x.coarse[v >> (shift + 5)], 1u << ((v >> shift) & 31));
+    }
+};
+
+// Per group of sources: no vertex reached, empty words and bitmaps.  The first
+// group also lists the vertices above kMidDeg (order irrelevant: every use is
+// an OR or an integer sum per vertex), one reservation per workgroup chunk.
+template <bool BITS>
+__global__ __launch_bounds__(kPathThreads) void ps_init(Search<BITS> a, bool lists) {
+    __shared__ uint32_t s_n[2];
+    __shared__ unsigned long long s_base[2];
+    constexpr uint64_t chunk = (uint64_t)kPathThreads * kListChunk;
+    if (BITS) {
+        const uint64_t stride = (uint64_t)gridDim.x * kPathThreads, words = a.words(), cw = a.coarse_words();
+        const uint64_t i0 = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x;
+        for (uint64_t w = i0; w < words; w += stride) a.f.fine[w] = a.x.fine[w] = a.z.fine[w] = 0;
+        if (a.shift)
+            for (uint64_t w = i0; w < cw; w += stride) a.f.coarse[w] = a.x.coarse[w] = a.z.coarse[w] = 0;
+    }
+    for (uint64_t c0 = (uint64_t)blockIdx.x * chunk; c0 < a.n; c0 += (uint64_t)gridDim.x * chunk) {
+        if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+        __syncthreads();
+        uint32_t mid = 0, huge = 0;  // bit i: vertex c0 + i kPathThreads + threadIdx.x
+#pragma unroll
+        for (int i = 0; i < kListChunk; ++i) {
+            const uint64_t v = c0 + (uint64_t)i * kPathThreads + threadIdx.x;
+            if (v < a.n) {
+                const uint64_t deg = a.rp[v + 1] - a.rp[v];
+                mid |= (uint32_t)(deg > kMidDeg && deg <= kHugeDeg) << i;
+                huge |= (uint32_t)(deg > kHugeDeg) << i;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kListChunk; ++i) {
+            const uint64_t v = c0 + (uint64_t)i * kPathThreads + threadIdx.x;
+            if (v < a.n) {
+                a.vis[v] = 0;
+                a.front[v] = 0;
+                if ((huge >> i) & 1u) a.next[v] = 0;  // (several wavefronts OR into it)
+            }
+        }
+        if (lists) {
+            uint32_t at[2] = {0, 0};
+            if (mid) at[0] = atomicAdd(&s_n[0], (uint32_t)__popc(mid));
+            if (huge) at[1] = atomicAdd(&s_n[1], (uint32_t)__popc(huge));
+            __syncthreads();
+            if (threadIdx.x < 2 && s_n[threadIdx.x])
+                s_base[threadIdx.x] = atomicAdd(&a.ctl[kCtlMid + threadIdx.x], (unsigned long long)s_n[threadIdx.x]);
+            __syncthreads();
+            for (int i = 0; i < kListChunk; ++i) {
+                const uint64_t v = c0 + (uint64_t)i * kPathThreads + threadIdx.x;
+                if ((mid >> i) & 1u) a.list[s_base[0] + at[0]++] = (typename Search<BITS>::ListT)v;
+                if ((huge >> i) & 1u) a.list[a.n - 1 - (s_base[1] + at[1]++)] = (typename Search<BITS>::ListT)v;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 struct Sources {
@@ -60,150 +175,372 @@ struct Sources {
     uint32_t count;
 };
 
-__global__ void ps_seed(Sources s, uint64_t *vis, uint64_t *front) {
-    // One thread: sources may repeat, and their bits then share a word.
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        for (uint32_t i = 0; i < s.count; ++i) {
-            vis[s.v[i]] |= 1ull << i;
-            front[s.v[i]] |= 1ull << i;
-        }
+// One wavefront: sources may repeat, and their bits then share a word, which
+// every one of them writes.  (The sources are marked in the bitmap of this
+// launch's `x`, which the first level takes as its frontier.)
+template <bool BITS> __global__ __launch_bounds__(64) void ps_seed(Search<BITS> a, Sources s) {
+    const uint32_t i = threadIdx.x;
+    const bool in = i < s.count;
+    const int64_t v = in ? s.v[i] : 0;
+    uint64_t word = 0;
+    bool spreads = false;
+    if (in) {
+        for (uint32_t j = 0; j < s.count; ++j) word |= (uint64_t)(s.v[j] == v) << j;
+        a.vis[v] = word;
+        a.front[v] = word;
+        a.mark((uint64_t)v);
+        spreads = a.rp[v + 1] > a.rp[v];
+    }
+    const uint64_t alive = __ballot(spreads);
+    if (i == 0) {
+        a.ctl[kCtlAlive] = alive;
+        a.ctl[kCtlFront] = s.count;
+    }
 }
 
-__device__ __forceinline__ void add_count(unsigned long long *cnt, uint64_t x) {
-    __shared__ unsigned long long s_acc[kPathThreads / 64];
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    if ((threadIdx.x & 63) == 0) s_acc[threadIdx.x >> 6] = x;
-    __syncthreads();
+__device__ __forceinline__ uint64_t or_lanes(uint64_t x, int lanes) {
+    for (int off = 1; off < lanes; off <<= 1) x |= __shfl_xor(x, off, 64);
+    return x;
+}
+
+// How a level looks its neighbours up.
+struct Lookup {
+    const uint32_t *lds;  // the coarse bitmap of the frontier
+    uint32_t shift;
+    bool bits;            // look the bitmaps up at all
+};
+
+// OR of the frontier words of the neighbours e, e + step, .. (N of them,
+// those below end).  The loads of a stage go out together.
+template <typename IdT, bool BITS, int N>
+__device__ __forceinline__ uint64_t gather(const Search<BITS> &a, const Lookup &q, uint64_t e, uint64_t end,
+                                           uint32_t step) {
+    using U = typename std::conditional<sizeof(IdT) == 4, uint32_t, uint64_t>::type;
+    const U *col = static_cast<const U *>(a.col);
+    U x[N];
+    uint32_t on = 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) x[u] = e + (uint64_t)u * step < end ? col[e + (uint64_t)u * step] : (U)~(U)0;
+#pragma unroll
+    for (int u = 0; u < N; ++u)  // ids at or above n are not vertices
+        on |= (uint32_t)(e + (uint64_t)u * step < end && (uint64_t)x[u] < a.n) << u;
+    if (BITS && q.bits) {
+        uint32_t b[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const uint32_t c = (uint32_t)x[u] >> q.shift;
+            b[u] = (on >> u) & 1u ? q.lds[c >> 5] >> (c & 31) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) on &= ~((uint32_t)!(b[u] & 1u) << u);
+        if (q.shift) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) b[u] = (on >> u) & 1u ? a.f.fine[(uint32_t)x[u] >> 5] : 0u;
+#pragma unroll
+            for (int u = 0; u < N; ++u) on &= ~((uint32_t)!((b[u] >> ((uint32_t)x[u] & 31)) & 1u) << u);
+        }
+    }
+    uint64_t w[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) w[u] = (on >> u) & 1u ? a.front[x[u]] : 0;
+    uint64_t acc = 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) acc |= w[u];
+    return acc;
+}
+
+// OR over the neighbours [e0, e1) of one vertex, by a whole wavefront; the
+// result is in every lane.  done: the sources that need not be looked for.
+template <typename IdT, bool BITS>
+__device__ __forceinline__ uint64_t gather_wave(const Search<BITS> &a, const Lookup &q, uint64_t e0, uint64_t e1,
+                                                uint64_t done, uint32_t lane) {
+    uint64_t acc = 0;
+    for (uint64_t e = e0; e < e1; e += 512) {
+        acc |= gather<IdT, BITS, 8>(a, q, e + lane, e1, 64);
+        acc = or_lanes(acc, 64);
+        if ((acc | done) == ~0ull) break;
+    }
+    return acc;
+}
+
+// The wavefront's vertices with `act`, 64 / LANES at a time, LANES lanes each,
+// LANES N edges per step.  e0, e1 and done are those of the lane's own
+// vertex, whose OR is returned (0 without act).  Called by whole wavefronts.
+template <typename IdT, bool BITS, int LANES, int N>
+__device__ __forceinline__ uint64_t sweep_class(const Search<BITS> &a, const Lookup &q, bool act, uint64_t e0,
+                                                uint64_t e1, uint64_t done, uint32_t lane) {
+    constexpr uint32_t kAtOnce = 64 / LANES;
+    const uint64_t mask = __ballot(act);
+    if (!mask) return 0;
+    // Lane i learns the lane of the i-th vertex to sweep.
+    const uint32_t nact = (uint32_t)__popcll(mask);
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+    const uint32_t rank = act ? before : nact + (lane - before);
+    const int from = __builtin_amdgcn_ds_permute((int)rank * 4, (int)lane);
+    uint64_t mine = 0;
+    for (uint32_t base = 0; base < nact; base += kAtOnce) {
+        const uint32_t gi = base + lane / LANES;
+        const int sl = __shfl(from, (int)(gi & 63), 64);
+        uint64_t e = __shfl(e0, sl, 64);
+        const uint64_t e1s = __shfl(e1, sl, 64), dn = __shfl(done, sl, 64);
+        const uint64_t end = gi < nact ? e1s : 0;
+        uint64_t acc = 0;
+        bool go = e < end;
+        do {
+            if (go) acc |= gather<IdT, BITS, N>(a, q, e + lane % LANES, end, LANES);
+            acc = or_lanes(acc, LANES);
+            e += LANES * N;
+            go = e < end && (acc | dn) != ~0ull;
+        } while (__any(go));
+        const uint64_t got = __shfl(acc, (int)((rank - base) % kAtOnce) * LANES, 64);
+        if (act && rank >= base && rank < base + kAtOnce) mine = got;
+    }
+    return mine;
+}
+
+// Adds a workgroup's (pairs found, vertices reached, sources that reached
+// one) to the level's words.
+template <bool BITS>
+__device__ __forceinline__ void add_level(const Search<BITS> &a, uint64_t found, uint32_t reached, uint64_t alive) {
+    __shared__ unsigned long long s_found, s_alive;
+    __shared__ uint32_t s_reached;
     if (threadIdx.x == 0) {
-        unsigned long long t = 0;
-        for (int i = 0; i < kPathThreads / 64; ++i) t += s_acc[i];
-        if (t) atomicAdd(cnt, t);
+        s_found = s_alive = 0;
+        s_reached = 0;
+    }
+    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) {
+        found += __shfl_xor(found, off, 64);
+        reached += __shfl_xor(reached, off, 64);
+        alive |= __shfl_xor(alive, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0 && found) {
+        atomicAdd(&s_found, (unsigned long long)found);
+        atomicAdd(&s_reached, reached);
+        atomicOr(&s_alive, (unsigned long long)alive);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_found) {
+        atomicAdd(&a.cnt[blockIdx.x % kCountSlots], s_found);
+        atomicOr(&a.now[0], s_alive);
+        atomicAdd(&a.now[1], (unsigned long long)s_reached);
     }
 }
 
-// Light vertices, one lane each.  next[v] is written for every vertex.
-template <typename IdT>
-__global__ __launch_bounds__(kPathThreads) void ps_level_light(const uint64_t *rp, const IdT *col, uint64_t n,
-                                                              uint64_t all, uint64_t *vis, const uint64_t *front,
-                                                              uint64_t *next, unsigned long long *cnt) {
-    uint64_t found = 0;
-    const uint64_t stride = (uint64_t)gridDim.x * kPathThreads;
-    for (uint64_t v = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x; v < n; v += stride) {
-        const uint64_t e0 = rp[v], e1 = rp[v + 1];
-        if (e1 - e0 > kHeavy) continue;  // swept by ps_level_heavy
-        const uint64_t seen = vis[v];
-        uint64_t acc = 0;
-        if (seen != all)
-            for (uint64_t e = e0; e < e1; ++e) {
-                const uint64_t x = (uint64_t)col[e];
-                if (x < n) acc |= front[x];  // ids at or above n are not vertices
-                if ((acc | seen) == all) break;
-            }
-        const uint64_t fresh = acc & ~seen;
-        next[v] = fresh;
-        if (fresh) {
-            vis[v] = seen | fresh;
-            found += (uint64_t)__popcll(fresh);
-        }
+// One level.  The long lists come first, so that they do not end the sweep.
+template <typename IdT, bool BITS>
+__global__ __launch_bounds__(kPathThreads) void ps_sweep(Search<BITS> a) {
+    __shared__ uint32_t s_bits[BITS ? kCoarseWords : 1];
+    const uint64_t dead = ~a.before[0];  // sources whose search has ended
+    if (dead == ~0ull) return;
+    Lookup q{s_bits, a.shift, BITS && (a.shift == 0 || a.before[1] < a.n / kDense)};
+    const uint64_t gtid = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x;
+    if (BITS) {
+        const uint32_t cw = (uint32_t)a.coarse_words();  // at most kCoarseWords
+        const uint32_t *c = a.shift ? a.f.coarse : a.f.fine;
+        if (q.bits)
+            for (uint32_t i = threadIdx.x; i < cw; i += kPathThreads) s_bits[i] = c[i];
+        if (a.shift && gtid < cw) a.z.coarse[gtid] = 0;
+        __syncthreads();
     }
-    add_count(cnt, found);
-}
-
-// Heavy vertices, one wavefront each.
-template <typename IdT>
-__global__ __launch_bounds__(kPathThreads) void ps_level_heavy(const uint64_t *rp, const IdT *col, uint64_t n,
-                                                              const uint64_t *heavy, const unsigned long long *nheavy,
-                                                              uint64_t all, uint64_t *vis, const uint64_t *front,
-                                                              uint64_t *next, unsigned long long *cnt) {
     const uint32_t lane = threadIdx.x & 63;
-    const uint64_t nh = *nheavy;
-    const uint64_t waves = (uint64_t)gridDim.x * (kPathThreads / 64);
-    uint64_t found = 0;
-    for (uint64_t h = (uint64_t)blockIdx.x * (kPathThreads / 64) + (threadIdx.x >> 6); h < nh; h += waves) {
-        const uint64_t v = heavy[h];
-        const uint64_t e0 = rp[v], e1 = rp[v + 1];
-        const uint64_t seen = vis[v];
-        uint64_t acc = 0;
-        if (seen != all)
-            for (uint64_t base = e0; base < e1; base += 64) {
-                const uint64_t e = base + lane;
-                if (e < e1) {
-                    const uint64_t x = (uint64_t)col[e];
-                    if (x < n) acc |= front[x];
-                }
-                // OR over the wave; the whole wave stops once the group is
-                // complete for v.
-                for (int off = 32; off > 0; off >>= 1) acc |= __shfl_xor(acc, off, 64);
-                if ((acc | seen) == all) break;
-            }
-        const uint64_t fresh = acc & ~seen;
+    const uint64_t wave = gtid >> 6, waves = (uint64_t)gridDim.x * (kPathThreads / 64);
+    const uint64_t nmid = a.ctl[kCtlMid], nhuge = a.ctl[kCtlHuge];
+    uint64_t found = 0, alive = 0;
+    uint32_t reached = 0;
+    // Huge vertices: raw ORs into next (ps_commit takes out what was seen).
+    for (uint64_t it = wave; it < nhuge * kSplit; it += waves) {
+        const uint64_t v = a.list[a.n - 1 - it / kSplit];
+        const uint64_t seen = a.vis[v];
+        if ((seen | dead) == ~0ull) continue;
+        const uint64_t r0 = a.rp[v], r1 = a.rp[v + 1];
+        const uint64_t per = ((r1 - r0) / kSplit + 64) & ~63ull;  // (kSplit parts of at least deg / kSplit)
+        const uint64_t e0 = r0 + (it % kSplit) * per;
+        const uint64_t acc = gather_wave<IdT, BITS>(a, q, e0, min(r1, e0 + per), seen | dead, lane) & ~seen;
+        if (lane == 0 && acc) atomicOr((unsigned long long *)&a.next[v], (unsigned long long)acc);
+    }
+    for (uint64_t it = wave; it < nmid; it += waves) {
+        const uint64_t v = a.list[it];
+        const uint64_t seen = a.vis[v];
+        uint64_t fresh = 0;
+        if ((seen | dead) != ~0ull)
+            fresh = gather_wave<IdT, BITS>(a, q, a.rp[v], a.rp[v + 1], seen | dead, lane) & ~seen;
         if (lane == 0) {
-            next[v] = fresh;
+            a.next[v] = fresh;
             if (fresh) {
-                vis[v] = seen | fresh;
+                a.vis[v] = seen | fresh;
+                a.mark(v);
                 found += (uint64_t)__popcll(fresh);
+                alive |= fresh;
+                ++reached;
             }
         }
     }
-    add_count(cnt, found);
+    // 64 consecutive vertices per wavefront: lane l reads the row and the word
+    // of vertex l, then the vertices still to be swept are taken several at a
+    // time.
+    const uint64_t tasks = (a.n + 63) / 64;
+    for (uint64_t t = wave; t < tasks; t += waves) {
+        const uint64_t v = t * 64 + lane;
+        uint64_t e0 = 0, e1 = 0, seen = 0;
+        if (v < a.n) {
+            e0 = a.rp[v];
+            e1 = a.rp[v + 1];
+            seen = a.vis[v];
+        }
+        if (BITS && lane < 2 && t * 2 + lane < a.words()) a.z.fine[t * 2 + lane] = 0;
+        const uint64_t deg = e1 - e0, done = seen | dead;
+        const bool light = v < a.n && deg <= kMidDeg, act = light && deg > 0 && done != ~0ull;
+        const uint64_t mine = sweep_class<IdT, BITS, 2, 8>(a, q, act && deg <= kSmallDeg, e0, e1, done, lane) |
+                              sweep_class<IdT, BITS, 16, 4>(a, q, act && deg > kSmallDeg, e0, e1, done, lane);
+        const uint64_t fresh = mine & ~seen;
+        if (light) a.next[v] = fresh;
+        const uint64_t nonempty = __ballot(fresh != 0);
+        if (!nonempty) continue;
+        if (fresh) {
+            a.vis[v] = seen | fresh;
+            found += (uint64_t)__popcll(fresh);
+            alive |= fresh;
+            ++reached;
+        }
+        if (BITS) {
+            const uint32_t half = (uint32_t)(nonempty >> (32 * (lane & 1)));
+            if (lane < 2 && half) atomicOr(&a.x.fine[t * 2 + lane], half);
+            if (a.shift) {
+                uint32_t m = fresh ? 1u << ((v >> a.shift) & 31) : 0u;  // (64 vertices share a word: shift >= 1)
+                for (int off = 1; off < 64; off <<= 1) m |= __shfl_xor(m, off, 64);
+                if (lane == 0) atomicOr(&a.x.coarse[v >> (a.shift + 5)], m);
+            }
+        }
+    }
+    add_level(a, found, reached, alive);
 }
 
-__global__ void ps_accumulate(const unsigned long long *cnt, uint64_t level, uint64_t *out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0 && *cnt) {
-        out[0] += level * (uint64_t)*cnt;
-        out[1] += (uint64_t)*cnt;
-        out[2] = out[2] > level ? out[2] : level;
+// The huge vertices' level: what was not seen before stays in next; their
+// words of the frontier just swept are cleared for the level after.
+template <bool BITS> __global__ __launch_bounds__(kPathThreads) void ps_commit(Search<BITS> a) {
+    if (a.before[0] == 0) return;
+    const uint64_t nhuge = a.ctl[kCtlHuge];
+    uint64_t found = 0, alive = 0;
+    uint32_t reached = 0;
+    for (uint64_t h = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x; h < nhuge; h += (uint64_t)gridDim.x * kPathThreads) {
+        const uint64_t v = a.list[a.n - 1 - h];
+        const uint64_t seen = a.vis[v], fresh = a.next[v] & ~seen;
+        a.next[v] = fresh;
+        a.front[v] = 0;
+        if (fresh) {
+            a.vis[v] = seen | fresh;
+            a.mark(v);
+            found += (uint64_t)__popcll(fresh);
+            alive |= fresh;
+            ++reached;
+        }
     }
+    add_level(a, found, reached, alive);
+}
+
+// A batch's counts into the totals; the last level's words go to the start of
+// the next batch, whose own are cleared.
+__global__ void ps_fold(unsigned long long *ctl, unsigned long long *cnt, uint64_t level0, uint64_t *out) {
+    for (int i = 0; i < kBatch; ++i) {
+        unsigned long long c = 0;
+        for (int q = 0; q < kCountSlots; ++q) {
+            c += cnt[i * kCountSlots + q];
+            cnt[i * kCountSlots + q] = 0;
+        }
+        ctl[kCtlAlive] = ctl[kCtlLevel + 2 * i];
+        ctl[kCtlFront] = ctl[kCtlLevel + 2 * i + 1];
+        ctl[kCtlLevel + 2 * i] = ctl[kCtlLevel + 2 * i + 1] = 0;
+        if (!c) break;  // (nor did any later level run)
+        out[0] += (level0 + i) * (uint64_t)c;
+        out[1] += (uint64_t)c;
+        out[2] = out[2] > level0 + i ? out[2] : level0 + i;
+    }
+}
+
+__global__ void ps_clear(uint64_t *out, unsigned long long *ctl, unsigned long long *cnt) {
+    const uint32_t i = threadIdx.x;
+    if (i < 3) out[i] = 0;
+    if (i < kCtlWords) ctl[i] = 0;
+    if (i < kBatch * kCountSlots) cnt[i] = 0;
 }
 
 int grid_of(uint64_t items) {
     return (int)std::max<uint64_t>(1, std::min<uint64_t>((items + kPathThreads - 1) / kPathThreads,
-                                                         (uint64_t)device_cu_count() * 8));
+                                                         (uint64_t)device_cu_count() * 4));
 }
 
-template <typename T> __global__ void ps_fill(T *p, uint64_t n, T v) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
-
-template <typename IdT>
+template <typename IdT, bool BITS>
 int run_paths(uint64_t n, const uint64_t *rp, const IdT *col, const int64_t *sources, uint32_t num_sources,
               uint64_t *out, char *ws, const PsPlan &P, hipStream_t s) {
-    uint64_t *vis = reinterpret_cast<uint64_t *>(ws + P.off_vis);
-    uint64_t *fa = reinterpret_cast<uint64_t *>(ws + P.off_f0);
-    uint64_t *fb = reinterpret_cast<uint64_t *>(ws + P.off_f1);
-    uint64_t *heavy = reinterpret_cast<uint64_t *>(ws + P.off_heavy);
-    auto *nheavy = reinterpret_cast<unsigned long long *>(ws + P.off_nheavy);
-    auto *cnt = reinterpret_cast<unsigned long long *>(ws + P.off_cnt);
-    const int g = grid_of(n);
-    ps_fill<uint64_t><<<1, 64, 0, s>>>(out, 3, 0);
-    ps_fill<unsigned long long><<<1, 64, 0, s>>>(nheavy, 1, 0);
-    { ProfScope _ps("path_level", s); ps_heavy_list<<<g, kPathThreads, 0, s>>>(rp, n, heavy, nheavy); }
+    Search<BITS> a;
+    memset(&a, 0, sizeof(a));
+    a.n = n;
+    a.rp = rp;
+    a.col = col;
+    a.vis = reinterpret_cast<uint64_t *>(ws + P.off_vis);
+    a.front = reinterpret_cast<uint64_t *>(ws + P.off_f0);
+    a.next = reinterpret_cast<uint64_t *>(ws + P.off_f1);
+    a.list = reinterpret_cast<typename Search<BITS>::ListT *>(ws + P.off_list);
+    a.ctl = reinterpret_cast<unsigned long long *>(ws + P.off_ctl);
+    unsigned long long *cnt = reinterpret_cast<unsigned long long *>(ws + P.off_cnt);
+    if (BITS) {
+        // Behind the n list entries: 3 ceil(n / 32) words, and above 2^18
+        // vertices 3 x 2^13 more, within the region's max(8 n, 256) bytes.
+        const uint64_t words = (n + 31) / 32;
+        while (((n - 1) >> a.shift) / 32 >= kCoarseWords) ++a.shift;
+        uint32_t *b = reinterpret_cast<uint32_t *>(ws + P.off_list) + n;
+        a.f.fine = b;
+        a.x.fine = b + words;
+        a.z.fine = b + 2 * words;
+        if (a.shift) {
+            a.f.coarse = b + 3 * words;
+            a.x.coarse = a.f.coarse + kCoarseWords;
+            a.z.coarse = a.x.coarse + kCoarseWords;
+        }
+    }
+    const int g = grid_of(n), gi = grid_of((n + kListChunk - 1) / kListChunk);
+    ps_clear<<<1, 64, 0, s>>>(out, a.ctl, cnt);
     for (uint32_t g0 = 0; g0 < num_sources; g0 += kGroup) {
         Sources src;
         memset(&src, 0, sizeof(src));
         src.count = std::min<uint32_t>(kGroup, num_sources - g0);
         for (uint32_t i = 0; i < src.count; ++i) src.v[i] = sources[g0 + i];
-        const uint64_t all = src.count == 64 ? ~0ull : ((1ull << src.count) - 1);
-        ps_fill<uint64_t><<<g, kPathThreads, 0, s>>>(vis, n, 0);
-        ps_fill<uint64_t><<<g, kPathThreads, 0, s>>>(fa, n, 0);
-        ps_seed<<<1, 64, 0, s>>>(src, vis, fa);
-        // A level finds at least one new (source, vertex) pair or ends the
+        { ProfScope _ps("path_level", s); ps_init<BITS><<<gi, kPathThreads, 0, s>>>(a, g0 == 0); }
+        ps_seed<BITS><<<1, 64, 0, s>>>(a, src);
+        std::swap(a.f, a.x);  // the seeds' bitmap is the first level's frontier
+        // A level reaches at least one new (source, vertex) pair or ends the
         // search, so at most n levels run.
-        for (uint64_t level = 1; level <= n; ++level) {
-            ps_fill<unsigned long long><<<1, 64, 0, s>>>(cnt, 1, 0);
-            { ProfScope _ps("path_level", s); ps_level_light<IdT><<<g, kPathThreads, 0, s>>>(rp, col, n, all, vis, fa, fb, cnt); }
-            { ProfScope _ps("path_level", s); ps_level_heavy<IdT><<<g, kPathThreads, 0, s>>>(rp, col, n, heavy, nheavy, all, vis, fa, fb, cnt); }
-            ps_accumulate<<<1, 1, 0, s>>>(cnt, level, out);
-            unsigned long long found = 0;
-            if (hipMemcpyAsync(&found, cnt, sizeof(found), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        for (uint64_t level = 1;; level += kBatch) {
+            a.before = a.ctl + kCtlAlive;
+            for (int i = 0; i < kBatch; ++i) {
+                a.cnt = cnt + i * kCountSlots;
+                a.now = a.ctl + kCtlLevel + 2 * i;
+                { ProfScope _ps("path_level", s); ps_sweep<IdT, BITS><<<g, kPathThreads, 0, s>>>(a); }
+                { ProfScope _ps("path_level", s); ps_commit<BITS><<<8, kPathThreads, 0, s>>>(a); }
+                a.before = a.now;
+                std::swap(a.front, a.next);
+                const Bitmap f = a.f;
+                a.f = a.x;
+                a.x = a.z;
+                a.z = f;
+            }
+            ps_fold<<<1, 1, 0, s>>>(a.ctl, cnt, level, out);
+            unsigned long long alive = 0;
+            if (hipMemcpyAsync(&alive, a.ctl + kCtlAlive, sizeof(alive), hipMemcpyDeviceToHost, s) != hipSuccess ||
                 hipStreamSynchronize(s) != hipSuccess)
                 return fail(SFG_EDEVICE, "path_stats: %s", hipGetErrorString(hipGetLastError()));
-            if (found == 0) break;
-            std::swap(fa, fb);
+            if (alive == 0) break;
         }
     }
     return check_launch("path_stats");
+}
+
+template <typename IdT>
+int run_paths_any(uint64_t n, const uint64_t *rp, const IdT *col, const int64_t *sources, uint32_t num_sources,
+                  uint64_t *out, char *ws, const PsPlan &P, hipStream_t s) {
+    if (n <= (1ull << 32)) return run_paths<IdT, true>(n, rp, col, sources, num_sources, out, ws, P, s);
+    return run_paths<IdT, false>(n, rp, col, sources, num_sources, out, ws, P, s);
 }
 
 }  // namespace
@@ -229,6 +566,6 @@ extern "C" int path_stats(uint64_t n, const uint64_t *row_ptr, const void *col, 
     hipStream_t s = as_stream(stream);
     char *ws = static_cast<char *>(workspace);
     if (id_bytes == 4)
-        return run_paths<int32_t>(n, row_ptr, static_cast<const int32_t *>(col), sources, num_sources, out, ws, P, s);
-    return run_paths<int64_t>(n, row_ptr, static_cast<const int64_t *>(col), sources, num_sources, out, ws, P, s);
+        return run_paths_any<int32_t>(n, row_ptr, static_cast<const int32_t *>(col), sources, num_sources, out, ws, P, s);
+    return run_paths_any<int64_t>(n, row_ptr, static_cast<const int64_t *>(col), sources, num_sources, out, ws, P, s);
 }

@@ -83,3 +83,22 @@ def test_errors(sfg):
     with pytest.raises(SfgenError):
         sfg.path_stats(4, rp_d, col_d, [0], ws=sfg.workspace(8))
     assert _gpu(sfg, 4, rp, col, []) == (0, 0, 0)
+
+
+@pytest.mark.parametrize("hub", [16, 17, 255, 256, 257, 4095, 4096, 4097, 8200])
+def test_degree_classes_match_oracle(sfg, orc, hub):
+    """Hubs on both sides of the degrees above which more lanes, a wavefront
+    and several wavefronts sweep a vertex; a path behind each, so that the search runs
+    over several batches of levels; two groups of sources, the second ragged
+    and with repeats."""
+    rng = np.random.default_rng(hub)
+    n = hub + 90
+    pairs = [(0, i) for i in range(1, hub + 1)]          # vertex 0: degree hub (+ 1 below)
+    pairs += [(hub + i, hub + i + 1) for i in range(40)]  # a path that starts at a leaf
+    pairs += [(n - 2, n - 1)]                             # a component of its own
+    extra = rng.integers(1, hub + 1, size=(hub, 2))
+    rp, col = _undirected_csr(n, pairs + [tuple(p) for p in extra])
+    srcs = np.concatenate([rng.integers(0, n, 70), [0, hub + 40, n - 1, n - 1]])
+    exp = orc.path_stats(n, rp, col, srcs)
+    for id_bytes in (4, 8):
+        assert _gpu(sfg, n, rp, col, srcs, id_bytes) == tuple(int(x) for x in exp)
