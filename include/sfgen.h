@@ -537,7 +537,7 @@ int adam_step_device(uint64_t count, float *params, const float *grad, float *m,
  * (with the learning rate and the step counter in device memory, as
  * adam_step_device), with the rounding points above.  The first launch
  * rounds the weights to bfloat16 (row-major and transposed); the second
- * runs, for every block of 64 rows, the forward pass, the loss gradient and
+ * runs, for every block of 16 to 64 rows, the forward pass, the loss gradient and
  * the chain of activation gradients on the matrix cores with the layer
  * operand in LDS; the third computes every weight-gradient tile over each
  * 256-row slice of the batch on the matrix cores; the fourth sums the

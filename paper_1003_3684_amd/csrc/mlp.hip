@@ -276,253 +276,320 @@ __global__ void adam_kernel_dev(uint64_t n, float *p, const float *g, float *m, 
 
 // ----------------------------------------------------------------------------- fused training step
 // One training step in four launches.  mlp_round writes the bf16 weights,
-// row-major and transposed.  mlp_rows runs, for a block of 64 rows, the
-// forward pass, the loss gradient and the whole backward chain of activation
+// row-major and transposed.  mlp_rows runs, for a block of rows, the forward
+// pass, the loss gradient and the whole backward chain of activation
 // gradients -- all of it row-local -- on the matrix cores, keeping the
 // current layer's bf16 operand in LDS; it leaves the bf16 layer inputs, the
 // bf16 gradients dZb and per-block column sums of dZ.  mlp_wgrad computes
-// every weight-gradient tile over a 256-row slice of the batch (dW = dZb^T
-// Xb) into per-slice partials; mlp_update sums the partials and the
-// per-block bias sums in a fixed order, applies Adam and sums the loss.  The
+// every weight-gradient tile over a slice of the batch (dW = dZb^T Xb) into
+// per-slice partials, and sums the per-block column sums and losses;
+// mlp_update sums the partials in a fixed order and applies Adam.  The
 // rounding points are those of mlp_forward / mlp_backward.
 //
-// The saved activations are feature-major, [feature][Bp], with the feature
-// count padded to a multiple of 16 and the batch to Bp, a multiple of 64:
-// a lane's four consecutive rows of one feature (the matrix-core output
-// layout) are one vector store, the weight-gradient operands (contiguous in
-// the batch) are direct fragment loads, and every element of the padding is
-// written by every step -- zero in Xb and dZb for rows beyond the batch and
-// features beyond the layer, so that they add exact zeros to dW.
-constexpr int kFR = 64;       // rows per block of mlp_rows
+// The saved layer inputs and gradients are kept in tiles of 16 rows,
+// [row tile][feature][16 rows], with the feature count padded to a multiple
+// of 16 and the batch to Bp, a multiple of 64: a block writes one contiguous
+// range per layer, a lane's four rows of one feature (the matrix-core output
+// layout) are one vector store, and the weight-gradient operands (8 rows of a
+// feature) are direct fragment loads.  Every element of the padding is written
+// by every step -- zero in Xb and dZb for rows beyond the batch and features
+// beyond the layer, so that they add exact zeros to dW.
+constexpr int kFR = 64;       // multiple the batch is padded to
 constexpr int kFMax = 256;    // widest layer the fused step takes
 constexpr int kFMaxL = 8;     // deepest network the fused step takes
 constexpr int kWSlice = 256;  // batch rows per weight-gradient partial
 constexpr int kRW = 8;        // waves per block of mlp_rows
 constexpr int kCT = 2;        // column tiles per wave of mlp_rows
+constexpr int kKSteps = kFMax / kKStep;
 
 struct TrainArgs {
     int L, B, Bp;          // Bp: the batch rounded up to kFR
     int dims[kFMaxL + 1];  // dims[0] = d_in, dims[l + 1] = outputs of layer l
     size_t w_off[kFMaxL], b_off[kFMaxL];
     float *params;
-    // bf16 weights of layer l, zero-padded: wb + wp_off[l] is [pad16(out)][pad32(in)],
-    // wbt + wtp_off[l] is [pad16(in)][pad32(out)] (W transposed)
+    // bf16 weights of layer l, zero-padded, in fragment order (see mlp_round):
+    // wb + wp_off[l] is [pad16(out)][pad32(in)], wbt + wtp_off[l] is
+    // [pad16(in)][pad32(out)] (W transposed)
     const bf16 *wb, *wbt;
     size_t wp_off[kFMaxL], wtp_off[kFMaxL];
     const float *x, *target, *mask, *cw;
     const int64_t *rows;  // batch row r is row rows[r] of x, target and mask (null: row r)
-    bf16 *xb[kFMaxL];     // [pad16(dims[l])][Bp] layer inputs
-    float *z[kFMaxL];     // [pad16(dims[l + 1])][Bp] pre-activations (hidden layers)
-    bf16 *dzb[kFMaxL];    // [pad16(dims[l + 1])][Bp]
+    bf16 *xb[kFMaxL];     // [Bp / 16][pad16(dims[l])][16] layer inputs
+    float *z[kFMaxL];     // pre-activations (hidden layers), each lane's own values together
+    bf16 *dzb[kFMaxL];    // [Bp / 16][pad16(dims[l + 1])][16]
     float *dbp[kFMaxL];   // [blocks][dims[l + 1]] column sums of dZ per block
+    float *db[kFMaxL];    // [dims[l + 1]] their sums
     float *lossp;         // [blocks]
     uint32_t *step;       // advanced by block 0 of mlp_rows
 };
 
 __host__ __device__ __forceinline__ int round16(int x) { return (x + 15) & ~15; }
-__device__ __forceinline__ int round32(int x) { return (x + 31) & ~31; }
+__host__ __device__ __forceinline__ int round32(int x) { return (x + 31) & ~31; }
 
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 
-// The zero-padded bf16 weight copies wb and wbt of every layer.
-__global__ void mlp_round(TrainArgs a) {
-    for (int l = 0; l < a.L; ++l) {
-        const int in = a.dims[l], out = a.dims[l + 1];
-        const int ki = round32(in), ko = round32(out), n1 = round16(out) * ki, n2 = round16(in) * ko;
-        const float *W = a.params + a.w_off[l];
-        bf16 *wb = const_cast<bf16 *>(a.wb) + a.wp_off[l], *wbt = const_cast<bf16 *>(a.wbt) + a.wtp_off[l];
-        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n1 + n2; i += gridDim.x * blockDim.x) {
-            if (i < n1) {
-                const int n = i / ki, k = i % ki;
-                wb[i] = f2bf(n < out && k < in ? W[n * in + k] : 0.f);
-            } else {
-                const int k = (i - n1) / ko, n = (i - n1) % ko;
-                wbt[i - n1] = f2bf(n < out && k < in ? W[n * in + k] : 0.f);
-            }
-        }
+// The zero-padded bf16 weight copies wb and wbt of every layer, in fragment
+// order: the 16 x 32 block of 16 columns of the product (rows of M) and 32 k
+// that one matrix-core operand takes is 1 KB, lane by lane, so that a wave
+// loads it as eight whole cache lines (with rows of M kept together it is 16
+// pieces of 64 bytes).  A workgroup takes a 32 x 32 tile of one layer, read
+// along its rows; its threads then write one lane's 16 bytes of either copy.
+__global__ __launch_bounds__(256) void mlp_round(TrainArgs a) {
+    __shared__ float s_t[32][33];
+    int l = 0, rem = (int)blockIdx.x;
+    for (; l < a.L; ++l) {
+        const int t = (round32(a.dims[l]) / 32) * (round32(a.dims[l + 1]) / 32);
+        if (rem < t) break;
+        rem -= t;
     }
+    const int in = a.dims[l], out = a.dims[l + 1], ki = round32(in), ko = round32(out);
+    const int n0 = rem / (ki / 32) * 32, k0 = rem % (ki / 32) * 32;
+    const float *W = a.params + a.w_off[l];
+    const int c = threadIdx.x % 32, r0 = threadIdx.x / 32;
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = n0 + r0 + 8 * i, k = k0 + c;
+        v[i] = n < out && k < in ? W[(size_t)n * in + k] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_t[r0 + 8 * i][c] = v[i];
+    __syncthreads();
+    const bool tr = threadIdx.x >= 128;  // the transposed copy: rows of M are the layer's inputs
+    const int j = (threadIdx.x / 64) % 2, lane = threadIdx.x % 64, r = 16 * j + lane % 16, q = 8 * (lane / 16);
+    bf16x8 x;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = f2bf(tr ? s_t[q + e][r] : s_t[r][q + e]);
+    const int m0 = tr ? k0 : n0, kk = tr ? n0 : k0, M = round16(tr ? in : out), K = tr ? ko : ki;
+    bf16 *to = const_cast<bf16 *>(tr ? a.wbt + a.wtp_off[l] : a.wb + a.wp_off[l]);
+    if (m0 + 16 * j < M)
+        *reinterpret_cast<bf16x8 *>(to + ((size_t)((m0 / 16 + j) * (K / 32) + kk / 32) * 64 + lane) * 8) = x;
 }
 
-// C (64 rows x N) = A (64 x K, bf16 in LDS, row stride kFMax + 8) * M^T with
-// M [pad16(N)][K] the zero-padded bf16 weights (K a multiple of 32).  Wave w
-// of the kRW waves takes the column tiles w and w + kRW (N <= 256).  All of
-// the wave's M fragments for the layer (K <= 256: at most 8 k-steps) are
-// loaded before the first product, so a layer costs one round trip to L2
-// instead of one per k-step.
-__device__ __forceinline__ void rows_gemm(const bf16 (*sA)[kFMax + 8], int K, const bf16 *M, int N,
-                                          floatx4 (&acc)[4][kCT]) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int r = lane % 16, kq = 8 * (lane / 16);
-    const int ntiles = (N + 15) / 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < kCT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 fb[kFMax / kKStep][kCT];
-#pragma unroll
-    for (int st = 0; st < kFMax / kKStep; ++st)
+// The wave of a thread, as a scalar.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+// A wave's weight fragments of one layer: M [pad16(N)][K] the zero-padded bf16
+// weights in fragment order (K a multiple of 32, at most kKSteps k-steps),
+// column tiles w and w + kRW (N <= 256).  Loaded together, so that a layer
+// costs one round trip to L2 instead of one per k-step.  Nothing is
+// predicated: a fragment beyond the layer is a copy of its last one, which no
+// result uses (under a branch every load waited for the one before it, since
+// its registers might still have been on their way: 5 us per layer).
+struct Weights {
+    bf16x8 f[kKSteps][kCT];
+    __device__ __forceinline__ void load(const bf16 *M, int K, int N) {
+        const int w = wave_id(), ntiles = (N + 15) / 16, steps = K / kKStep;
 #pragma unroll
         for (int j = 0; j < kCT; ++j) {
-            const int ct = w + kRW * j;
-            if (st * kKStep < K && ct < ntiles)
-                fb[st][j] = *reinterpret_cast<const bf16x8 *>(M + (size_t)(16 * ct + r) * K + st * kKStep + kq);
+            const bf16 *p = M + ((size_t)(min(w + kRW * j, ntiles - 1) * steps) * 64 + (threadIdx.x & 63)) * 8;
+#pragma unroll
+            for (int st = 0; st < kKSteps; ++st)
+                f[st][j] = *reinterpret_cast<const bf16x8 *>(p + min(st, steps - 1) * 512);
         }
+    }
+};
+
+// C (16 MT rows x N) = A (16 MT x K, bf16 in LDS, row stride kFMax + 8) * M^T.
+// (A wave without a column tile multiplies too; its results are not used.)
+template <int MT>
+__device__ __forceinline__ void rows_gemm(const bf16 (*sA)[kFMax + 8], int K, const Weights &wt,
+                                          floatx4 (&acc)[MT][kCT]) {
+    const int lane = threadIdx.x & 63;
+    const int r = lane % 16, kq = 8 * (lane / 16);
 #pragma unroll
-    for (int st = 0; st < kFMax / kKStep; ++st) {
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < kCT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < kKSteps; ++st) {
         if (st * kKStep >= K) break;
-        bf16x8 fa[4];
+        bf16x8 fa[MT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) fa[i] = *reinterpret_cast<const bf16x8 *>(&sA[16 * i + r][st * kKStep + kq]);
+        for (int i = 0; i < MT; ++i) fa[i] = *reinterpret_cast<const bf16x8 *>(&sA[16 * i + r][st * kKStep + kq]);
 #pragma unroll
         for (int j = 0; j < kCT; ++j)
-            if (w + kRW * j < ntiles)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[st][j], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < MT; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], wt.f[st][j], acc[i][j], 0, 0, 0);
     }
 }
 
-// Column sums over the block's 64 rows of v (a lane's 4 x 4 values per
-// column tile), in a fixed order, written to out[c].
-__device__ __forceinline__ void block_col_sums(const float (&v)[4][kCT][4], int N, float *out) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// Column sums over the block's rows of v (a lane's MT x 4 values per column
+// tile), in a fixed order, written to out[c].
+template <int MT> __device__ __forceinline__ void block_col_sums(const float (&v)[MT][kCT][4], int N, float *out) {
+    const int lane = threadIdx.x & 63, w = wave_id();
     const int ntiles = (N + 15) / 16;
 #pragma unroll
     for (int j = 0; j < kCT; ++j) {
         const int ct = w + kRW * j;
+        if (ct >= ntiles) break;
         float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) s += v[i][j][e];
         s += __shfl_xor(s, 16, 64);
         s += __shfl_xor(s, 32, 64);
         const int c = 16 * ct + lane % 16;
-        if (ct < ntiles && lane < 16 && c < N) out[c] = s;
+        if (lane < 16 && c < N) out[c] = s;
     }
 }
 
-// Lane layout of the 64 x 16 output tile (i, column tile ct) of rows_gemm:
+// MT row tiles of 16 per block of 8 waves.  A block is a chain of 2 L - 1
+// small products with a barrier and an epilogue between them, so its time is
+// latency, and what shortens the step is more blocks and nothing waited for
+// in sequence: at batch 4,096 57 us with 64-row blocks that loaded a layer's
+// weights after the barrier, 38 us with 16-row blocks, 35 us with the weights
+// in fragment order, 23 us with unpredicated loads (see Weights) and the
+// targets loaded at the start.
+// Lane layout of the 16 x 16 output tile (i, column tile ct) of rows_gemm:
 // column c = 16 ct + lane % 16, rows 16 i + 4 (lane / 16) + e, e = 0..3.
-// Each epilogue issues its global loads before any of its global stores (a
-// load issued after a store waits for that store's completion too), and
-// branches only on wave-uniform tile indices.
-__global__ __launch_bounds__(64 * kRW) void mlp_rows(TrainArgs a) {
-    __shared__ __align__(16) bf16 sA[kFR][kFMax + 8];
-    __shared__ int64_t s_src[kFR];  // data row of each batch row (-1 beyond the batch)
+// A layer's weights (and what its epilogue reads) are loaded before the
+// epilogue of the layer before, which covers their latency; each epilogue's
+// global loads come before its global stores (a load issued after a store
+// waits for that store's completion too).
+template <int MT> __global__ __launch_bounds__(64 * kRW) void mlp_rows(TrainArgs a) {
+    constexpr int kRows = 16 * MT;
+    __shared__ __align__(16) bf16 sA[kRows][kFMax + 8];
+    __shared__ int64_t s_src[kRows];  // data row of each batch row (-1 beyond the batch)
     __shared__ float s_loss[kRW];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int r0 = blockIdx.x * kFR, Bp = a.Bp;
+    const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
+    const int r0 = blockIdx.x * kRows, t0 = blockIdx.x * MT;
     const int L = a.L;
     const int rq = 4 * (lane / 16), cl = lane % 16;
     const bf16 bz = f2bf(0.f);
+    Weights wt;
+    float bj[kCT];
+    auto load_layer = [&](int l) {
+        wt.load(a.wb + a.wp_off[l], round32(a.dims[l]), a.dims[l + 1]);
+#pragma unroll
+        for (int j = 0; j < kCT; ++j) {
+            bj[j] = a.params[a.b_off[l] + min(16 * (w + kRW * j) + cl, a.dims[l + 1] - 1)];
+        }
+    };
+    load_layer(0);
     if (blockIdx.x == 0 && tid == 0) *a.step += 1;
-    if (tid < kFR) s_src[tid] = r0 + tid < a.B ? (a.rows ? a.rows[r0 + tid] : (int64_t)(r0 + tid)) : -1;
+    if (tid < kRows) s_src[tid] = r0 + tid < a.B ? (a.rows ? a.rows[r0 + tid] : (int64_t)(r0 + tid)) : -1;
     __syncthreads();
+    // The targets, mask entries and weights of this lane's outputs (for up to
+    // two row tiles loaded now, above that when the registers are free).
+    float tg[MT][kCT][4], mk[MT][kCT][4], cwj[kCT];
+    auto load_targets = [&]() {
+        const int out = a.dims[L];
+        size_t si[MT][kCT][4];
+#pragma unroll
+        for (int j = 0; j < kCT; ++j) {
+            const int c = min(16 * (w + kRW * j) + cl, out - 1);
+            cwj[j] = a.cw ? a.cw[c] : 1.f;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t src = s_src[16 * i + rq + e];
+                    si[i][j][e] = (size_t)(src >= 0 ? src : 0) * out + c;
+                    tg[i][j][e] = a.target[si[i][j][e]];
+                    mk[i][j][e] = 1.f;
+                }
+        }
+        if (a.mask)
+#pragma unroll
+            for (int j = 0; j < kCT; ++j)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) mk[i][j][e] = a.mask[si[i][j][e]];
+    };
+    if (MT <= 2) load_targets();
     // Xb_0 = bf16(x), zero beyond d_in (up to the padded K) and beyond the batch.
     {
-        const int din = a.dims[0], K = round32(din), n = kFR * K, P = round16(din);
-        for (int i0 = 0; i0 < n; i0 += 64 * kRW * 8) {
-            float v[8];
+        const int din = a.dims[0], K = round32(din), n = kRows * K, P = round16(din);
+        constexpr int kU = 2 * MT;
+        for (int i0 = 0; i0 < n; i0 += 64 * kRW * kU) {
+            float v[kU];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + 64 * kRW * u + tid, c = i / kFR, r = i % kFR;
+            for (int u = 0; u < kU; ++u) {
+                const int i = i0 + 64 * kRW * u + tid, c = i / kRows, r = i % kRows;
                 v[u] = (i < n && c < din && s_src[r] >= 0) ? a.x[(size_t)s_src[r] * din + c] : 0.f;
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + 64 * kRW * u + tid, c = i / kFR, r = i % kFR;
+            for (int u = 0; u < kU; ++u) {
+                const int i = i0 + 64 * kRW * u + tid, c = i / kRows, r = i % kRows;
                 if (i >= n) continue;
                 const bf16 xb = f2bf(v[u]);
                 sA[r][c] = xb;
-                if (c < P) a.xb[0][(size_t)c * Bp + r0 + r] = xb;
+                if (c < P) a.xb[0][((size_t)(t0 + r / 16) * P + c) * 16 + r % 16] = xb;
             }
         }
     }
     __syncthreads();
-    floatx4 acc[4][kCT];
-    float keep[4][kCT][4];  // fp32 dZ of this lane's outputs (loss / activation gradients)
+    floatx4 acc[MT][kCT];
+    float keep[MT][kCT][4];  // fp32 dZ of this lane's outputs (loss / activation gradients)
     float lsum = 0.f;
-    // ---------------- forward: Z = Xb Wb^T + b
-    for (int l = 0; l < L; ++l) {
-        const int in = a.dims[l], out = a.dims[l + 1];
-        const bool last = l == L - 1;
-        const int npad = round32(out), ntiles = (out + 15) / 16;
-        float bj[kCT], cwj[kCT];
+    // ---------------- forward: Z = Xb Wb^T + b, up to the last hidden layer
+    for (int l = 0; l + 1 < L; ++l) {
+        const int out = a.dims[l + 1], npad = round32(out), ntiles = (out + 15) / 16, P = round16(out);
+        rows_gemm<MT>(sA, round32(a.dims[l]), wt, acc);
+        float b[kCT];
+#pragma unroll
+        for (int j = 0; j < kCT; ++j) b[j] = bj[j];
+        load_layer(l + 1);
+        __syncthreads();  // every wave is done reading sA
 #pragma unroll
         for (int j = 0; j < kCT; ++j) {
-            const int c = 16 * (w + kRW * j) + cl;
-            bj[j] = c < out ? a.params[a.b_off[l] + c] : 0.f;
-            cwj[j] = (last && c < out && a.cw) ? a.cw[c] : 1.f;
-        }
-        rows_gemm(sA, round32(in), a.wb + a.wp_off[l], out, acc);
-        __syncthreads();  // every wave is done reading sA
-        if (!last) {
+            const int ct = w + kRW * j, c = 16 * ct + cl;
+            if (16 * ct >= npad) continue;
 #pragma unroll
-            for (int j = 0; j < kCT; ++j) {
-                const int ct = w + kRW * j, c = 16 * ct + cl;
-                if (16 * ct >= npad) continue;
+            for (int i = 0; i < MT; ++i) {
+                floatx4 zv;
+                bf16x4 xv;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    floatx4 zv;
-                    bf16x4 xv;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int r = 16 * i + rq + e;
-                        const float z = acc[i][j][e] + bj[j];
-                        const bf16 xn = (c < out && r0 + r < a.B) ? f2bf(z * sigmoidf_(z)) : bz;
-                        sA[r][c] = xn;
-                        zv[e] = z;
-                        xv[e] = xn;
-                    }
-                    if (ct < ntiles) {
-                        const size_t gi = (size_t)c * Bp + r0 + 16 * i + rq;
-                        *reinterpret_cast<floatx4 *>(a.z[l] + gi) = zv;
-                        *reinterpret_cast<bf16x4 *>(a.xb[l + 1] + gi) = xv;
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * i + rq + e;
+                    const float z = acc[i][j][e] + b[j];
+                    const bf16 xn = (c < out && r0 + r < a.B) ? f2bf(z * sigmoidf_(z)) : bz;
+                    sA[r][c] = xn;
+                    zv[e] = z;
+                    xv[e] = xn;
+                }
+                if (ct < ntiles) {
+                    const size_t tile = (size_t)(t0 + i) * P * 16;
+                    *reinterpret_cast<floatx4 *>(a.z[l] + tile + ct * 256 + lane * 4) = zv;
+                    *reinterpret_cast<bf16x4 *>(a.xb[l + 1] + tile + c * 16 + rq) = xv;
                 }
             }
-        } else {
-            // loss gradient dy = 2 w_c m (y - t) / B and the rows' loss terms;
-            // the targets and mask entries of a column tile, then its stores.
+        }
+        __syncthreads();
+    }
+    // ---------------- output layer: loss gradient dy = 2 w_c m (y - t) / B and
+    // the rows' loss terms.
+    {
+        const int l = L - 1, out = a.dims[L], npad = round32(out), ntiles = (out + 15) / 16, P = round16(out);
+        if (MT > 2) load_targets();
+        rows_gemm<MT>(sA, round32(a.dims[l]), wt, acc);
+        wt.load(a.wbt + a.wtp_off[l], round32(out), a.dims[l]);
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < kCT; ++j) {
-                const int ct = w + kRW * j, c = 16 * ct + cl;
+        for (int j = 0; j < kCT; ++j) {
+            const int ct = w + kRW * j, c = 16 * ct + cl;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < MT; ++i) {
+                bf16x4 gv;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) keep[i][j][e] = 0.f;
-                if (16 * ct >= npad) continue;
-                float tg[4][4], mk[4][4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int64_t src = s_src[16 * i + rq + e];
-                        const bool ok = c < out && src >= 0;
-                        const size_t si = ok ? (size_t)src * out + c : 0;
-                        tg[i][e] = a.target[si];
-                        mk[i][e] = a.mask ? a.mask[si] : 1.f;
-                    }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    bf16x4 gv;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int r = 16 * i + rq + e;
-                        const bool ok = c < out && r0 + r < a.B;
-                        const float wgt = cwj[j] * mk[i][e];
-                        const float d = (acc[i][j][e] + bj[j]) - tg[i][e];
-                        const float dy = (ok && wgt != 0.f) ? 2.f * wgt * d / (float)a.B : 0.f;
-                        lsum += (ok && wgt != 0.f) ? wgt * d * d : 0.f;
-                        keep[i][j][e] = dy;
-                        const bf16 g = f2bf(dy);
-                        sA[r][c] = g;
-                        gv[e] = g;
-                    }
-                    if (ct < ntiles)
-                        *reinterpret_cast<bf16x4 *>(a.dzb[l] + (size_t)c * Bp + r0 + 16 * i + rq) = gv;
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * i + rq + e;
+                    const bool ok = c < out && r0 + r < a.B;
+                    const float wgt = cwj[j] * mk[i][j][e];
+                    const float d = (acc[i][j][e] + bj[j]) - tg[i][j][e];
+                    const float dy = (ok && wgt != 0.f) ? 2.f * wgt * d / (float)a.B : 0.f;
+                    lsum += (ok && wgt != 0.f) ? wgt * d * d : 0.f;
+                    keep[i][j][e] = dy;
+                    const bf16 g = f2bf(dy);
+                    if (16 * ct < npad) sA[r][c] = g;
+                    gv[e] = g;
                 }
+                if (ct < ntiles)
+                    *reinterpret_cast<bf16x4 *>(a.dzb[l] + ((size_t)(t0 + i) * P + c) * 16 + rq) = gv;
             }
         }
         __syncthreads();
@@ -531,39 +598,44 @@ __global__ __launch_bounds__(64 * kRW) void mlp_rows(TrainArgs a) {
     for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
     if (lane == 0) s_loss[w] = lsum;
     // ---------------- backward: dZ_{l-1} = (dZb_l Wb_l) * SiLU'(Z_{l-1})
-    block_col_sums(keep, a.dims[L], a.dbp[L - 1] + (size_t)blockIdx.x * a.dims[L]);
+    block_col_sums<MT>(keep, a.dims[L], a.dbp[L - 1] + (size_t)blockIdx.x * a.dims[L]);
     for (int l = L - 1; l >= 1; --l) {
         const int out = a.dims[l + 1], in = a.dims[l];
-        const int npad = round32(in), ntiles = (in + 15) / 16;
-        // dH (64 x in) = dZb (64 x out) Wb (out x in): M = Wb^T
-        rows_gemm(sA, round32(out), a.wbt + a.wtp_off[l], in, acc);
+        const int npad = round32(in), ntiles = (in + 15) / 16, P = round16(in);
+        floatx4 zv[MT][kCT];
+#pragma unroll
+        for (int j = 0; j < kCT; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int ct = min(w + kRW * j, ntiles - 1);
+                zv[i][j] = *reinterpret_cast<const floatx4 *>(a.z[l - 1] + (size_t)(t0 + i) * P * 16 + ct * 256 + lane * 4);
+            }
+        // dH (rows x in) = dZb (rows x out) Wb (out x in): M = Wb^T
+        rows_gemm<MT>(sA, round32(out), wt, acc);
+        if (l > 1) wt.load(a.wbt + a.wtp_off[l - 1], round32(in), a.dims[l - 1]);
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < kCT; ++j) {
             const int ct = w + kRW * j, c = 16 * ct + cl;
-            floatx4 zv[4];
+            if (16 * ct >= npad) break;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                zv[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (ct < ntiles) zv[i] = *reinterpret_cast<const floatx4 *>(a.z[l - 1] + (size_t)c * Bp + r0 + 16 * i + rq);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < MT; ++i) {
                 bf16x4 gv;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int r = 16 * i + rq + e;
-                    const float zz = zv[i][e], s = sigmoidf_(zz);
+                    const float zz = zv[i][j][e], s = sigmoidf_(zz);
                     const float g = (c < in && r0 + r < a.B) ? acc[i][j][e] * (s * (1.0f + zz * (1.0f - s))) : 0.f;
                     keep[i][j][e] = g;
                     const bf16 gb = f2bf(g);
-                    if (16 * ct < npad) sA[r][c] = gb;
+                    sA[r][c] = gb;
                     gv[e] = gb;
                 }
-                if (ct < ntiles) *reinterpret_cast<bf16x4 *>(a.dzb[l - 1] + (size_t)c * Bp + r0 + 16 * i + rq) = gv;
+                if (ct < ntiles)
+                    *reinterpret_cast<bf16x4 *>(a.dzb[l - 1] + ((size_t)(t0 + i) * P + c) * 16 + rq) = gv;
             }
         }
-        block_col_sums(keep, in, a.dbp[l - 1] + (size_t)blockIdx.x * in);
+        block_col_sums<MT>(keep, in, a.dbp[l - 1] + (size_t)blockIdx.x * in);
         __syncthreads();
     }
     if (tid == 0) {
@@ -573,21 +645,73 @@ __global__ __launch_bounds__(64 * kRW) void mlp_rows(TrainArgs a) {
     }
 }
 
+// Sum of v[0], v[stride], ..., v[(n - 1) stride] in index order, 16 loads in
+// flight at a time.
+__device__ __forceinline__ float ordered_sum(const float *v, int n, size_t stride) {
+    float g = 0.f;
+    for (int z0 = 0; z0 < n; z0 += 16) {
+        float t[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) t[u] = z0 + u < n ? v[(size_t)(z0 + u) * stride] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (z0 + u < n) g += t[u];
+    }
+    return g;
+}
+
+// The per-block sums of one layer's dZ (64 of its columns per workgroup), or
+// the blocks' losses, over all blocks of mlp_rows: four threads per column
+// take a quarter of the blocks each, in block order, and the quarters are
+// added in order.
+__device__ __forceinline__ void sum_blocks(const float *v, int blocks, int cols, int c0, float *out, float scale,
+                                           float (*s_q)[64]) {
+    const int c = c0 + (int)threadIdx.x % 64, q = (int)threadIdx.x / 64;
+    const int per = (blocks + 3) / 4, b0 = min(blocks, q * per), nb = min(blocks, b0 + per) - b0;
+    s_q[q][threadIdx.x % 64] = c < cols ? ordered_sum(v + (size_t)b0 * cols + c, nb, (size_t)cols) : 0.f;
+    __syncthreads();
+    if (q == 0 && c < cols) {
+        const int i = (int)threadIdx.x;
+        out[c] = (((s_q[0][i] + s_q[1][i]) + s_q[2][i]) + s_q[3][i]) * scale;
+    }
+}
+
 // Weight-gradient tile (64 x 64) of one layer over one slice of up to 256
 // batch rows: part[slice][w_off + j * in + i] = sum over the slice's rows r
-// of dZb[j][r] Xb[i][r] (both feature-major: the matrix-core fragments are
-// 16-byte loads, all of a slice's issued before the first product).
-// Workgroup b: tile b / slices (layers in order, each row-major in 64 x 64
-// tiles), slice b % slices.
+// of dZb[j][r] Xb[i][r] (the matrix-core fragments are 16-byte loads, all of a
+// slice's issued before the first product).  Workgroup b < tiles * slices:
+// tile b / slices (layers in order, each row-major in 64 x 64 tiles), slice
+// b % slices; the workgroups after them sum the bias gradients and the loss.
 struct WgradArgs {
     TrainArgs t;
-    int slices;
+    int slices, tiles, blocks;
     size_t nparams;
     float *part;  // [slices][nparams]
+    float *loss;
 };
 
 __global__ __launch_bounds__(256) void mlp_wgrad(WgradArgs a) {
+    __shared__ float s_q[4][64];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if ((int)blockIdx.x >= a.tiles * a.slices) {
+        int rem = (int)blockIdx.x - a.tiles * a.slices;
+        for (int l = 0; l < a.t.L; ++l) {
+            const int groups = (a.t.dims[l + 1] + 63) / 64;
+            if (rem < groups) {
+                sum_blocks(a.t.dbp[l], a.blocks, a.t.dims[l + 1], rem * 64, a.t.db[l], 1.f, s_q);
+                return;
+            }
+            rem -= groups;
+        }
+        // The losses: lane c sums those of blocks c, c + 64, ..
+        float x = 0.f;
+        for (int b = tid; b < a.blocks; b += 256) x += a.t.lossp[b];
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        if (lane == 0) s_q[0][w] = x;
+        __syncthreads();
+        if (tid == 0) *a.loss = (((s_q[0][0] + s_q[0][1]) + s_q[0][2]) + s_q[0][3]) / (float)a.t.B;
+        return;
+    }
     const int slice = (int)blockIdx.x % a.slices;
     int l = 0, rem = (int)blockIdx.x / a.slices;
     for (; l < a.t.L; ++l) {
@@ -611,8 +735,8 @@ __global__ __launch_bounds__(256) void mlp_wgrad(WgradArgs a) {
             const size_t k = (size_t)kb + st * kKStep + kq;
             fa[st][i] = bf16x8{};
             fb[st][i] = bf16x8{};
-            if (st < steps && gm < mp) fa[st][i] = *reinterpret_cast<const bf16x8 *>(A + (size_t)gm * Bp + k);
-            if (st < steps && gn < np) fb[st][i] = *reinterpret_cast<const bf16x8 *>(Bm + (size_t)gn * Bp + k);
+            if (st < steps && gm < mp) fa[st][i] = *reinterpret_cast<const bf16x8 *>(A + ((k / 16) * mp + gm) * 16 + k % 16);
+            if (st < steps && gn < np) fb[st][i] = *reinterpret_cast<const bf16x8 *>(Bm + ((k / 16) * np + gn) * 16 + k % 16);
         }
     floatx4 acc[2][2];
 #pragma unroll
@@ -641,49 +765,31 @@ __global__ __launch_bounds__(256) void mlp_wgrad(WgradArgs a) {
 }
 
 // Every parameter: its gradient (weight: the slice partials in slice order;
-// bias: the per-block sums in block order), Adam, and the loss.
+// bias: summed by mlp_wgrad) and Adam.
 struct UpdateArgs {
     TrainArgs t;
-    int slices, blocks;
+    int slices;
     size_t nparams;
     const float *part;
     float *m, *v, *grad;
     const float *lr;
     float b1, b2, eps;
-    float *loss;
 };
 
-// Sum of v[0], v[stride], ..., v[(n - 1) stride] in index order, 16 loads in
-// flight at a time.
-__device__ __forceinline__ float ordered_sum(const float *v, int n, size_t stride) {
-    float g = 0.f;
-    for (int z0 = 0; z0 < n; z0 += 16) {
-        float t[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) t[u] = z0 + u < n ? v[(size_t)(z0 + u) * stride] : 0.f;
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (z0 + u < n) g += t[u];
-    }
-    return g;
-}
-
 __global__ void mlp_update(UpdateArgs a) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.loss = ordered_sum(a.t.lossp, a.blocks, 1) / (float)a.t.B;
     const float t = (float)*a.t.step, lr = *a.lr;
     const float c1 = 1.f - powf(a.b1, t), c2 = 1.f - powf(a.b2, t);
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.nparams;
          i += (uint64_t)gridDim.x * blockDim.x) {
         int l = 0;
         while (l + 1 < a.t.L && i >= a.t.w_off[l + 1]) ++l;
-        const float g = i < a.t.b_off[l]
-                            ? ordered_sum(a.part + i, a.slices, a.nparams)
-                            : ordered_sum(a.t.dbp[l] + (i - a.t.b_off[l]), a.blocks, (size_t)a.t.dims[l + 1]);
-        const float mi = a.b1 * a.m[i] + (1.f - a.b1) * g;
-        const float vi = a.b2 * a.v[i] + (1.f - a.b2) * g * g;
+        const float m0 = a.m[i], v0 = a.v[i], p0 = a.t.params[i];
+        const float g = i < a.t.b_off[l] ? ordered_sum(a.part + i, a.slices, a.nparams) : a.t.db[l][i - a.t.b_off[l]];
+        const float mi = a.b1 * m0 + (1.f - a.b1) * g;
+        const float vi = a.b2 * v0 + (1.f - a.b2) * g * g;
         a.m[i] = mi;
         a.v[i] = vi;
-        a.t.params[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + a.eps);
+        a.t.params[i] = p0 - lr * (mi / c1) / (sqrtf(vi / c2) + a.eps);
         if (a.grad) a.grad[i] = g;
     }
 }
@@ -880,7 +986,7 @@ namespace {
 
 struct TrainWs {
     TrainArgs t;
-    int blocks, slices;
+    int mt, blocks, slices;
     float *part;
     size_t total;
 };
@@ -892,12 +998,24 @@ bool fused_ok(const Net &net) {
     return true;
 }
 
+// Row tiles per block of mlp_rows: one while that gives every CU of the 256 at
+// most one block, two up to twice that, then four, where the weights that
+// every block reads from L2 cost more than the blocks' latency.  A step of
+// the 3 x 256 network in us with 1 / 2 / 4 tiles: 39 / 44 / 54 at batch 4,096,
+// 56 / 51 / 61 at 8,192, 85 / 87 / 75 at 12,000, 98 / 90 / 78 at 16,384, 428 /
+// 394 / 341 at 65,536.
+int row_tiles(int Bp) {
+    const int tiles = Bp / 16;
+    return tiles <= 256 ? 1 : tiles <= 512 ? 2 : 4;
+}
+
 TrainWs carve_train(const Net &net, uint32_t B, void *base) {
     TrainWs w;
     memset(&w, 0, sizeof(w));
     Carver c(base);
-    w.blocks = (int)((B + kFR - 1) / kFR);
-    const int Bp = w.blocks * kFR;
+    const int Bp = (int)((B + kFR - 1) / kFR * kFR);
+    w.mt = row_tiles(Bp);
+    w.blocks = Bp / (16 * w.mt);
     w.slices = (Bp + kWSlice - 1) / kWSlice;
     w.t.L = net.L;
     w.t.B = (int)B;
@@ -922,6 +1040,7 @@ TrainWs carve_train(const Net &net, uint32_t B, void *base) {
         w.t.z[l] = l + 1 < net.L ? c.take<float>(pout * Bp) : nullptr;
         w.t.dzb[l] = c.take<bf16>(pout * Bp);
         w.t.dbp[l] = c.take<float>((size_t)w.blocks * net.layer[l].out);
+        w.t.db[l] = c.take<float>(net.layer[l].out);
     }
     w.t.lossp = c.take<float>(w.blocks);
     w.part = c.take<float>((size_t)w.slices * net.nparams);
@@ -960,18 +1079,29 @@ extern "C" int mlp_train_step(const sfg_mlp_shape *shape, uint32_t batch, float 
     w.t.rows = rows;
     w.t.step = step;
     hipStream_t s = as_stream(stream);
-    int ntiles = 0;
-    for (int l = 0; l < net.L; ++l)
-        ntiles += ((net.layer[l].out + kTile - 1) / kTile) * ((net.layer[l].in + kTile - 1) / kTile);
-    { ProfScope _ps("mlp_round", s); mlp_round<<<grid_n(2 * net.nparams), 256, 0, s>>>(w.t); }
-    { ProfScope _ps("mlp_rows", s); mlp_rows<<<w.blocks, 64 * kRW, 0, s>>>(w.t); }
-    WgradArgs wa{w.t, w.slices, net.nparams, w.part};
-    { ProfScope _ps("mlp_wgrad", s); mlp_wgrad<<<ntiles * w.slices, 256, 0, s>>>(wa); }
+    int ntiles = 0, nround = 0, nbias = 0;
+    for (int l = 0; l < net.L; ++l) {
+        const int in = net.layer[l].in, out = net.layer[l].out;
+        ntiles += ((out + kTile - 1) / kTile) * ((in + kTile - 1) / kTile);
+        nround += (round32(in) / 32) * (round32(out) / 32);
+        nbias += (out + 63) / 64;
+    }
+    { ProfScope _ps("mlp_round", s); mlp_round<<<nround, 256, 0, s>>>(w.t); }
+    {
+        ProfScope _ps("mlp_rows", s);
+        if (w.mt == 1)
+            mlp_rows<1><<<w.blocks, 64 * kRW, 0, s>>>(w.t);
+        else if (w.mt == 2)
+            mlp_rows<2><<<w.blocks, 64 * kRW, 0, s>>>(w.t);
+        else
+            mlp_rows<4><<<w.blocks, 64 * kRW, 0, s>>>(w.t);
+    }
+    WgradArgs wa{w.t, w.slices, ntiles, w.blocks, net.nparams, w.part, loss};
+    { ProfScope _ps("mlp_wgrad", s); mlp_wgrad<<<ntiles * w.slices + nbias + 1, 256, 0, s>>>(wa); }
     UpdateArgs ua;
     memset(&ua, 0, sizeof(ua));
     ua.t = w.t;
     ua.slices = w.slices;
-    ua.blocks = w.blocks;
     ua.nparams = net.nparams;
     ua.part = w.part;
     ua.m = m;
@@ -981,7 +1111,6 @@ extern "C" int mlp_train_step(const sfg_mlp_shape *shape, uint32_t batch, float 
     ua.b1 = beta1;
     ua.b2 = beta2;
     ua.eps = eps;
-    ua.loss = loss;
     { ProfScope _ps("mlp_update", s); mlp_update<<<grid_n(net.nparams), 256, 0, s>>>(ua); }
     return check_launch("mlp_train_step");
 }

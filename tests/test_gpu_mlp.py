@@ -140,6 +140,20 @@ def test_fused_step_matches_oracle(sfg, shape_t, batch):
     np.testing.assert_allclose(p.cpu().numpy(), po, rtol=1e-5, atol=1e-6)
 
 
+@pytest.mark.parametrize("shape_t,batch", [((10, 200, 34, 2), 4097), ((33, 256, 256, 2), 8192), ((10, 130, 17, 1), 8193)])
+def test_fused_step_row_tiles_match_oracle(sfg, shape_t, batch):
+    """The batches where the rows per block of the fused step change (one,
+    two and four 16-row tiles), ragged, against the oracle at the tolerances
+    of the test above."""
+    shape, params, x, t, g = _setup(sfg, shape_t, batch, 90 + batch)
+    p, grad, loss = _fused_step(sfg, shape, batch, g["params"], g["x"], g["t"])
+    yo, cache = omlp.forward(shape_t, params.astype(np.float64), x.astype(np.float64))
+    dyo, losso = omlp.mse_grad(yo, t.astype(np.float64))
+    go, _ = omlp.backward(shape_t, params.astype(np.float64), cache, dyo)
+    _close(grad.cpu().numpy(), go, 1e-2)
+    assert abs(loss - losso) <= 1e-3 * abs(losso), (loss, losso)
+
+
 def test_fused_step_rows_mask_weights_equal_unfused(sfg):
     """A shuffled batch (rows), a mask and column weights: the fused step's
     gradient and loss equal the unfused kernels' on the gathered batch
