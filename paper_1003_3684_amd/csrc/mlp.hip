@@ -15,6 +15,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -794,6 +795,200 @@ __global__ void mlp_update(UpdateArgs a) {
     }
 }
 
+// ----------------------------------------------------------------------------- fused evaluation
+// mlp_forward, and mlp_backward for the input gradient alone, of networks that
+// the fused step takes: two launches each, the weight copies of the call and
+// one kernel that runs every layer of a block of rows, as mlp_rows does.  (A
+// launch per product and per activation is 10 launches forward and 8
+// backward, and each is a few microseconds at any batch up to a thousand.)
+// 16 rows of the 10 -> 3 x 256 -> 34 network, value and gradient: 73.8 -> 26.5
+// us (10 us of each direction is the one block's chain of layers), the same
+// products in the same order and so the same bits.
+// The workspace is left as the unfused kernels leave it -- row-major bf16
+// weights and layer inputs, pre-activations -- so either backward may follow;
+// the fragment copies live in the split-K scratch, rebuilt by every call.
+struct EvalArgs {
+    int L, B;
+    int dims[kFMaxL + 1];
+    size_t w_off[kFMaxL], b_off[kFMaxL], f_off[kFMaxL];  // f_off: fragments of layer l in frag
+    const float *params;
+    bf16 *wb;    // row-major bf16 parameters (the weights)
+    bf16 *frag;  // this call's fragments: of W forward, of W transposed backward
+    const float *x, *dy;
+    float *y, *dx;
+    bf16 *xb[kFMaxL];  // [B][dims[l]]
+    float *z[kFMaxL];  // [B][dims[l + 1]], hidden layers
+};
+
+// The fragments of every layer (see mlp_round): forward from the float32
+// parameters, which also leaves the row-major bf16 copy, backward (TR) the
+// transposed ones from that copy.
+template <bool TR> __global__ __launch_bounds__(256) void eval_fragments(EvalArgs a) {
+    __shared__ float s_t[32][33];
+    int l = 0, rem = (int)blockIdx.x;
+    for (; l < a.L; ++l) {
+        const int t = (round32(a.dims[l]) / 32) * (round32(a.dims[l + 1]) / 32);
+        if (rem < t) break;
+        rem -= t;
+    }
+    const int in = a.dims[l], out = a.dims[l + 1], ki = round32(in), ko = round32(out);
+    const int n0 = rem / (ki / 32) * 32, k0 = rem % (ki / 32) * 32;
+    const int c = threadIdx.x % 32, r0 = threadIdx.x / 32;
+    bf16 *wb = a.wb + a.w_off[l];
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = n0 + r0 + 8 * i, k = k0 + c;
+        const bool ok = n < out && k < in;
+        const size_t at = ok ? (size_t)n * in + k : 0;
+        v[i] = TR ? bf2f(wb[at]) : a.params[a.w_off[l] + at];
+        if (!ok) v[i] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = n0 + r0 + 8 * i, k = k0 + c;
+        s_t[r0 + 8 * i][c] = v[i];
+        if (!TR && n < out && k < in) wb[(size_t)n * in + k] = f2bf(v[i]);
+    }
+    __syncthreads();
+    if (threadIdx.x >= 128) return;
+    const int j = threadIdx.x / 64, lane = threadIdx.x % 64, r = 16 * j + lane % 16, q = 8 * (lane / 16);
+    bf16x8 x;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = f2bf(TR ? s_t[q + e][r] : s_t[r][q + e]);
+    const int m0 = TR ? k0 : n0, kk = TR ? n0 : k0, M = round16(TR ? in : out), K = TR ? ko : ki;
+    if (m0 + 16 * j < M)
+        *reinterpret_cast<bf16x8 *>(a.frag + a.f_off[l] + ((size_t)((m0 / 16 + j) * (K / 32) + kk / 32) * 64 + lane) * 8) = x;
+}
+
+// Row-major float32 rows [r0, r0 + 16 MT) of v (cols wide) as bf16 into sA,
+// zero beyond the columns up to round32(cols) and beyond the batch; the bf16
+// values also to keep (row-major) when given.
+template <int MT>
+__device__ __forceinline__ void stage_rows(const float *v, int cols, int r0, int B, bf16 (*sA)[kFMax + 8], bf16 *keep) {
+    const int K = round32(cols), n = 16 * MT * K;
+    for (int i0 = 0; i0 < n; i0 += 64 * kRW * 4) {
+        float t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + 64 * kRW * u + (int)threadIdx.x, r = i / K, c = i % K;
+            const bool ok = i < n && c < cols && r0 + r < B;
+            t[u] = v[ok ? (size_t)(r0 + r) * cols + c : 0];
+            if (!ok) t[u] = 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + 64 * kRW * u + (int)threadIdx.x, r = i / K, c = i % K;
+            if (i >= n) break;
+            const bf16 b = f2bf(t[u]);
+            sA[r][c] = b;
+            if (keep && c < cols && r0 + r < B) keep[(size_t)(r0 + r) * cols + c] = b;
+        }
+    }
+}
+
+template <int MT> __global__ __launch_bounds__(64 * kRW) void mlp_eval_forward(EvalArgs a) {
+    __shared__ __align__(16) bf16 sA[16 * MT][kFMax + 8];
+    const int lane = threadIdx.x & 63, w = wave_id();
+    const int r0 = blockIdx.x * 16 * MT, rq = 4 * (lane / 16), cl = lane % 16, L = a.L;
+    Weights wt;
+    float bj[kCT];
+    auto load_layer = [&](int l) {
+        wt.load(a.frag + a.f_off[l], round32(a.dims[l]), a.dims[l + 1]);
+#pragma unroll
+        for (int j = 0; j < kCT; ++j)
+            bj[j] = a.params[a.b_off[l] + min(16 * (w + kRW * j) + cl, a.dims[l + 1] - 1)];
+    };
+    load_layer(0);
+    stage_rows<MT>(a.x, a.dims[0], r0, a.B, sA, a.xb[0]);
+    __syncthreads();
+    floatx4 acc[MT][kCT];
+    for (int l = 0; l < L; ++l) {
+        const int out = a.dims[l + 1], npad = round32(out);
+        const bool last = l == L - 1;
+        rows_gemm<MT>(sA, round32(a.dims[l]), wt, acc);
+        float b[kCT];
+#pragma unroll
+        for (int j = 0; j < kCT; ++j) b[j] = bj[j];
+        load_layer(min(l + 1, L - 1));
+        __syncthreads();  // every wave is done reading sA
+#pragma unroll
+        for (int j = 0; j < kCT; ++j) {
+            const int c = 16 * (w + kRW * j) + cl;
+            if (16 * (w + kRW * j) >= npad) break;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * i + rq + e;
+                    const bool ok = c < out && r0 + r < a.B;
+                    const size_t at = (size_t)(r0 + r) * out + c;
+                    const float z = acc[i][j][e] + b[j];
+                    if (last) {
+                        if (ok) a.y[at] = z;
+                        continue;
+                    }
+                    const bf16 xn = ok ? f2bf(z * sigmoidf_(z)) : f2bf(0.f);
+                    sA[r][c] = xn;
+                    if (ok) {
+                        a.z[l][at] = z;
+                        a.xb[l + 1][at] = xn;
+                    }
+                }
+        }
+        __syncthreads();
+    }
+}
+
+template <int MT> __global__ __launch_bounds__(64 * kRW) void mlp_eval_backward(EvalArgs a) {
+    __shared__ __align__(16) bf16 sA[16 * MT][kFMax + 8];
+    const int lane = threadIdx.x & 63, w = wave_id();
+    const int r0 = blockIdx.x * 16 * MT, rq = 4 * (lane / 16), cl = lane % 16, L = a.L;
+    Weights wt;
+    wt.load(a.frag + a.f_off[L - 1], round32(a.dims[L]), a.dims[L - 1]);
+    stage_rows<MT>(a.dy, a.dims[L], r0, a.B, sA, nullptr);
+    __syncthreads();
+    floatx4 acc[MT][kCT];
+    for (int l = L - 1; l >= 0; --l) {
+        const int in = a.dims[l], npad = round32(in);
+        float z[MT][kCT][4];
+        if (l > 0) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < kCT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        z[i][j][e] = a.z[l - 1][(size_t)min(r0 + 16 * i + rq + e, a.B - 1) * in +
+                                                min(16 * (w + kRW * j) + cl, in - 1)];
+        }
+        rows_gemm<MT>(sA, round32(a.dims[l + 1]), wt, acc);
+        if (l > 0) wt.load(a.frag + a.f_off[l - 1], round32(in), a.dims[l - 1]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kCT; ++j) {
+            const int c = 16 * (w + kRW * j) + cl;
+            if (16 * (w + kRW * j) >= npad) break;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * i + rq + e;
+                    const bool ok = c < in && r0 + r < a.B;
+                    float g = acc[i][j][e];
+                    if (l == 0) {
+                        if (ok) a.dx[(size_t)(r0 + r) * in + c] = g;
+                        continue;
+                    }
+                    const float zz = z[i][j][e], s = sigmoidf_(zz);
+                    g *= s * (1.0f + zz * (1.0f - s));
+                    sA[r][c] = ok ? f2bf(g) : f2bf(0.f);
+                }
+        }
+        __syncthreads();
+    }
+}
+
 // ----------------------------------------------------------------------------- host
 struct Layer {
     int in, out;
@@ -837,6 +1032,10 @@ struct Ws {
     size_t total;
 };
 
+size_t part_floats(const Net &net) {
+    return std::max((size_t)kSplits * net.maxw * net.maxw, (size_t)kColChunks * net.maxw);
+}
+
 Ws carve(const Net &net, uint32_t B, void *base) {
     Ws w;
     memset(&w, 0, sizeof(w));
@@ -848,10 +1047,68 @@ Ws carve(const Net &net, uint32_t B, void *base) {
     w.dz = c.take<float>((size_t)B * net.maxw);
     w.dh = c.take<float>((size_t)B * net.maxw);
     w.dzb = c.take<bf16>((size_t)B * net.maxw);
-    w.part = c.take<float>(std::max((size_t)kSplits * net.maxw * net.maxw, (size_t)kColChunks * net.maxw));
+    w.part = c.take<float>(part_floats(net));
     w.rowloss = c.take<float>(std::max<uint32_t>(B, 1));
     w.total = c.used;
     return w;
+}
+
+// Row tiles per block of mlp_rows: one while that gives every CU of the 256 at
+// most one block, two up to twice that, then four, where the weights that
+// every block reads from L2 cost more than the blocks' latency.  A step of
+// the 3 x 256 network in us with 1 / 2 / 4 tiles: 39 / 44 / 54 at batch 4,096,
+// 56 / 51 / 61 at 8,192, 85 / 87 / 75 at 12,000, 98 / 90 / 78 at 16,384, 428 /
+// 394 / 341 at 65,536.
+int row_tiles(int Bp) {
+    const int tiles = Bp / 16;
+    return tiles <= 256 ? 1 : tiles <= 512 ? 2 : 4;
+}
+
+bool fused_ok(const Net &net) {
+    if (net.L > kFMaxL) return false;
+    for (int l = 0; l < net.L; ++l)
+        if (net.layer[l].in > kFMax || net.layer[l].out > kFMax) return false;
+    return true;
+}
+
+// f(row tiles per block as a type, blocks) for a batch.
+template <typename F> void launch_rows(uint32_t B, F f) {
+    const int Bp = (int)((B + kFR - 1) / kFR * kFR), mt = row_tiles(Bp), blocks = (int)((B + 16 * mt - 1) / (16 * mt));
+    if (mt == 1)
+        f(std::integral_constant<int, 1>(), blocks);
+    else if (mt == 2)
+        f(std::integral_constant<int, 2>(), blocks);
+    else
+        f(std::integral_constant<int, 4>(), blocks);
+}
+
+// The evaluation's arguments for a network and workspace, its fragments in
+// the split-K scratch.  False when the network is not one the fused kernels
+// take, or so narrow that its padded fragments do not fit there (below a width
+// of 32 or so): the unfused kernels run then.
+bool eval_args(const Net &net, uint32_t B, const Ws &w, const float *params, bool transposed, EvalArgs &a, int &tiles) {
+    if (!fused_ok(net)) return false;
+    memset(&a, 0, sizeof(a));
+    a.L = net.L;
+    a.B = (int)B;
+    a.dims[0] = net.layer[0].in;
+    size_t f = 0;
+    tiles = 0;
+    for (int l = 0; l < net.L; ++l) {
+        const int in = net.layer[l].in, out = net.layer[l].out;
+        a.dims[l + 1] = out;
+        a.w_off[l] = net.layer[l].w_off;
+        a.b_off[l] = net.layer[l].b_off;
+        a.f_off[l] = f;
+        f += transposed ? (size_t)round16(in) * round32(out) : (size_t)round16(out) * round32(in);
+        tiles += (round32(in) / 32) * (round32(out) / 32);
+        a.xb[l] = w.xb[l];
+        a.z[l] = w.z[l];
+    }
+    a.params = params;
+    a.wb = w.wb;
+    a.frag = reinterpret_cast<bf16 *>(w.part);
+    return f * sizeof(bf16) <= part_floats(net) * sizeof(float);
 }
 
 int grid_n(uint64_t n) { return (int)std::max<uint64_t>(1, std::min<uint64_t>((n + 255) / 256, 4096)); }
@@ -891,6 +1148,18 @@ extern "C" int mlp_forward(const sfg_mlp_shape *shape, uint32_t batch, const flo
     Ws w = carve(net, batch, workspace);
     if (workspace_bytes < w.total) return fail(SFG_ENOSPACE, "mlp_forward: workspace too small (%zu < %zu)", workspace_bytes, w.total);
     hipStream_t s = as_stream(stream);
+    EvalArgs ea;
+    int tiles;
+    if (eval_args(net, batch, w, params, false, ea, tiles)) {
+        ea.x = x;
+        ea.y = y;
+        { ProfScope _ps("mlp_round", s); eval_fragments<false><<<tiles, 256, 0, s>>>(ea); }
+        ProfScope _ps("mlp_rows", s);
+        launch_rows(batch, [&](auto mt, int blocks) {
+            mlp_eval_forward<decltype(mt)::value><<<blocks, 64 * kRW, 0, s>>>(ea);
+        });
+        return check_launch("mlp_forward");
+    }
     { ProfScope _ps("mlp_elementwise", s); round_weights<<<grid_n(net.nparams), 256, 0, s>>>(params, w.wb, net.nparams); }
     { ProfScope _ps("mlp_elementwise", s); round_input<<<grid_n((uint64_t)batch * net.layer[0].in), 256, 0, s>>>(x, w.xb[0], (uint64_t)batch * net.layer[0].in); }
     for (int l = 0; l < net.L; ++l) {
@@ -916,6 +1185,18 @@ extern "C" int mlp_backward(const sfg_mlp_shape *shape, uint32_t batch, const fl
     if (workspace_bytes < w.total) return fail(SFG_ENOSPACE, "mlp_backward: workspace too small");
     hipStream_t s = as_stream(stream);
     const int B = (int)batch;
+    EvalArgs ea;
+    int tiles;
+    if (!grad && eval_args(net, batch, w, params, true, ea, tiles)) {
+        ea.dy = dy;
+        ea.dx = dx;
+        { ProfScope _ps("mlp_round", s); eval_fragments<true><<<tiles, 256, 0, s>>>(ea); }
+        ProfScope _ps("mlp_rows", s);
+        launch_rows(batch, [&](auto mt, int blocks) {
+            mlp_eval_backward<decltype(mt)::value><<<blocks, 64 * kRW, 0, s>>>(ea);
+        });
+        return check_launch("mlp_backward");
+    }
     for (int l = net.L - 1; l >= 0; --l) {
         const Layer &ly = net.layer[l];
         const uint64_t n = (uint64_t)B * ly.out;
@@ -990,24 +1271,6 @@ struct TrainWs {
     float *part;
     size_t total;
 };
-
-bool fused_ok(const Net &net) {
-    if (net.L > kFMaxL) return false;
-    for (int l = 0; l < net.L; ++l)
-        if (net.layer[l].in > kFMax || net.layer[l].out > kFMax) return false;
-    return true;
-}
-
-// Row tiles per block of mlp_rows: one while that gives every CU of the 256 at
-// most one block, two up to twice that, then four, where the weights that
-// every block reads from L2 cost more than the blocks' latency.  A step of
-// the 3 x 256 network in us with 1 / 2 / 4 tiles: 39 / 44 / 54 at batch 4,096,
-// 56 / 51 / 61 at 8,192, 85 / 87 / 75 at 12,000, 98 / 90 / 78 at 16,384, 428 /
-// 394 / 341 at 65,536.
-int row_tiles(int Bp) {
-    const int tiles = Bp / 16;
-    return tiles <= 256 ? 1 : tiles <= 512 ? 2 : 4;
-}
 
 TrainWs carve_train(const Net &net, uint32_t B, void *base) {
     TrainWs w;
@@ -1089,12 +1352,9 @@ extern "C" int mlp_train_step(const sfg_mlp_shape *shape, uint32_t batch, float 
     { ProfScope _ps("mlp_round", s); mlp_round<<<nround, 256, 0, s>>>(w.t); }
     {
         ProfScope _ps("mlp_rows", s);
-        if (w.mt == 1)
-            mlp_rows<1><<<w.blocks, 64 * kRW, 0, s>>>(w.t);
-        else if (w.mt == 2)
-            mlp_rows<2><<<w.blocks, 64 * kRW, 0, s>>>(w.t);
-        else
-            mlp_rows<4><<<w.blocks, 64 * kRW, 0, s>>>(w.t);
+        launch_rows(batch, [&](auto mt, int) {  // (the padded batch's blocks)
+            mlp_rows<decltype(mt)::value><<<w.blocks, 64 * kRW, 0, s>>>(w.t);
+        });
     }
     WgradArgs wa{w.t, w.slices, ntiles, w.blocks, net.nparams, w.part, loss};
     { ProfScope _ps("mlp_wgrad", s); mlp_wgrad<<<ntiles * w.slices + nbias + 1, 256, 0, s>>>(wa); }

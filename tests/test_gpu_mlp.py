@@ -268,3 +268,29 @@ def test_input_rounding_is_nearest_even(sfg, fused):
         np.testing.assert_array_equal(W0[j] / W0[j, 0], _rne_bf16(x[0]), err_msg=f"call {call}")
         checked += D
     assert checked >= 2000
+
+
+@pytest.mark.parametrize("shape_t,batch", [((10, 256, 34, 3), 15), ((10, 256, 34, 3), 17), ((10, 256, 34, 3), 4097),
+                                           ((10, 256, 34, 3), 8193), ((33, 200, 255, 1), 100), ((256, 256, 256, 7), 33),
+                                           ((10, 257, 34, 2), 65), ((3, 5, 4, 2), 40)])
+def test_forward_and_input_gradient_match_oracle(sfg, shape_t, batch):
+    """mlp_forward and mlp_backward without parameter gradients: the fused
+    kernels at the edges of their row tiles and layers, and the networks that
+    take the unfused ones (wider than 256, narrower than their padding).  The
+    input gradient may be asked for again, also after a backward that used
+    the scratch for parameter gradients."""
+    shape, params, x, t, g = _setup(sfg, shape_t, batch, 30 + batch)
+    rng = np.random.default_rng(batch)
+    dy = rng.normal(size=t.shape).astype(np.float32)
+    import torch
+    dyg = torch.tensor(dy).cuda()
+    y = sfg.mlp_forward(shape, g["params"], g["x"], g["ws"])
+    _, dx = sfg.mlp_backward(shape, g["params"], dyg, g["ws"], want_grad=False, want_dx=True)
+    grad, dx2 = sfg.mlp_backward(shape, g["params"], dyg, g["ws"], want_dx=True)
+    _, dx3 = sfg.mlp_backward(shape, g["params"], dyg, g["ws"], want_grad=False, want_dx=True)
+    yo, cache = omlp.forward(shape_t, params.astype(np.float64), x.astype(np.float64))
+    go, dxo = omlp.backward(shape_t, params.astype(np.float64), cache, dy.astype(np.float64))
+    _close(y.cpu().numpy(), yo, 1e-3)
+    _close(dx.cpu().numpy(), dxo, 1e-2)
+    _close(grad.cpu().numpy(), go, 1e-2)
+    assert torch.equal(dx, dx2) and torch.equal(dx, dx3)  # the same products in the same order
