@@ -41,8 +41,8 @@ namespace {
 constexpr uint32_t kTerm = 0x80000000u;  // bound of a partition's slot count and of a list's length
 constexpr int kXcd = 8;
 constexpr int kResThreads = 256;
-constexpr int kResItems = 16;
-constexpr int kResTile = kResThreads * kResItems;  // slots per resolve tile
+constexpr uint64_t kTicketRounds = 8;
+constexpr int kResItems = 16;  // slots per thread of a resolve tile, at most (see resolve_items)
 constexpr int kSubThreads = 256;
 constexpr uint32_t kMaxParts = 4096;
 constexpr int kScanRows = 256;
@@ -154,6 +154,7 @@ struct ResolveArgs {
     const uint64_t *xtotal;   // [8]
     uint32_t *queues;         // [8] tile tickets
     uint32_t S, xstride;
+    uint32_t items;           // slots per thread of a tile
 };
 
 // Phase-1 parameters of one partition (workgroup-uniform).  F and U are
@@ -203,82 +204,133 @@ __device__ __forceinline__ uint32_t phase2_endpoint(uint64_t t, const Seg2 &sg, 
     }
 }
 
-template <int PHASE> __global__ __launch_bounds__(kResThreads) void pba_resolve(ResolveArgs a) {
+// The segment index of a queue's tile t: the last i with pre[i] <= t.
+__device__ __forceinline__ uint32_t queue_segment(const uint64_t *pre, uint32_t nseg, uint64_t t) {
+    uint32_t lo = 0, hi = nseg;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (pre[mid] <= t)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+// The tiles are dealt out in one of two ways.
+// TICKETS: a workgroup draws its tiles from its XCD's queue until that is
+// empty, then from the others'.  The tiles
+// are then taken in order whatever each costs, which keeps the unresolved
+// window of a segment narrow: at 2^27 vertices, m = 5, phase 1 takes 4.9 ms
+// this way and 7.8 ms with tiles dealt by workgroup id.
+// Otherwise workgroup b, on XCD b mod 8, takes every gridDim.x / 8-th tile of
+// its XCD's queue, in order, or, where the queues differ in length (few
+// partitions, not a multiple of 8), every gridDim.x-th tile of all queues
+// together.  No counter is shared: 2,048 workgroups that each draw from eight
+// counters until they are empty take up to 200 us for that alone, since
+// device-scope atomics on one address run one after the other.
+template <int PHASE, bool TICKETS> __global__ __launch_bounds__(kResThreads) void pba_resolve(ResolveArgs a) {
     __shared__ uint64_t s_tile;
     __shared__ uint32_t s_seg;
     const int tid = threadIdx.x;
     const uint32_t home = blockIdx.x % kXcd;
-    for (uint32_t att = 0; att < kXcd; ++att) {
-        const uint32_t x = (home + att) % kXcd;
-        const uint64_t total = a.xtotal[x];
-        const uint64_t *pre = a.xprefix + (uint64_t)x * a.xstride;
-        const uint32_t nseg = (a.S > x) ? (a.S - x + kXcd - 1) / kXcd : 0;
-        for (;;) {
+    auto segments = [&](uint32_t x) { return a.S > x ? (a.S - x + kXcd - 1) / kXcd : 0; };
+    uint32_t att = 0;                         // TICKETS: queues found empty
+    uint64_t total[kXcd], it = 0, end = 0, step = 0;  // else: next tile, last one, stride
+    bool even = true;
+    if (!TICKETS) {
+        uint64_t sum = 0, longest = 0;
+#pragma unroll
+        for (int x = 0; x < kXcd; ++x) {
+            total[x] = a.xtotal[x];
+            sum += total[x];
+            longest = std::max(longest, total[x]);
+        }
+        even = longest * kXcd <= sum + sum / 8;
+        end = even ? a.xtotal[home] : sum;
+        step = even ? gridDim.x / kXcd : gridDim.x;
+        it = even ? blockIdx.x / kXcd : blockIdx.x;
+    }
+    for (;;) {
+        uint32_t x = home, i;
+        uint64_t t;
+        const uint64_t *pre;
+        if (TICKETS) {
+            x = (home + att) % kXcd;
+            pre = a.xprefix + (uint64_t)x * a.xstride;
+            const uint64_t n = a.xtotal[x];
             if (tid == 0) {
-                const uint64_t t = fetch_add_agent(&a.queues[x], 1u);
-                s_tile = t;
-                if (t < total) {
-                    // last segment index i with pre[i] <= t
-                    uint32_t lo = 0, hi = nseg;
-                    while (hi - lo > 1) {
-                        const uint32_t mid = (lo + hi) / 2;
-                        if (pre[mid] <= t)
-                            lo = mid;
-                        else
-                            hi = mid;
-                    }
-                    s_seg = lo;
-                }
+                const uint64_t mine = fetch_add_agent(&a.queues[x], 1u);
+                s_tile = mine;
+                if (mine < n) s_seg = queue_segment(pre, segments(x), mine);
             }
             __syncthreads();
-            const uint64_t t = s_tile;
-            const uint32_t i = s_seg;
+            t = s_tile;
+            i = s_seg;
             __syncthreads();
-            if (t >= total) break;
-            const uint32_t sgi = x + kXcd * i;
-            const uint64_t b0 = a.base[sgi];
-            const uint64_t len = a.base[sgi + 1] - b0;
-            const uint64_t first = (t - pre[i]) * kResTile;
-            uint32_t g;
-            const PGraph &p = a.G.of_seg(sgi, g);
-            if (PHASE == 1) {
-                Seg1 sg;
-                sg.q = sgi - p.seg0;
-                sg.fs = 1;
-                sg.u = 1;
-                sg.F = sg.U = nullptr;
-                if (a.f.foff) {
-                    sg.F = a.f.fmem + a.f.foff[sg.q];
-                    sg.fs = a.f.foff[sg.q + 1] - a.f.foff[sg.q];
-                    sg.U = a.f.umem + a.f.uoff[sg.q];
-                    sg.u = a.f.uoff[sg.q + 1] - a.f.uoff[sg.q];
-                }
-                sg.nnf = p.P - sg.u;
-                sg.thr_p = p.thr_p;
-                sg.tag = p.tag1;
-                sg.key0 = p.key0;
-                sg.key1 = p.key1;
-                uint16_t *lab = static_cast<uint16_t *>(a.val) + b0;
+            if (t >= n) {
+                if (++att == kXcd) break;
+                continue;
+            }
+        } else {
+            if (it >= end) break;
+            t = it;
+            it += step;
+            if (!even) {
+                x = 0;
+#pragma unroll
+                for (int y = 0; y < kXcd - 1; ++y)
+                    if (x == (uint32_t)y && t >= total[y]) {
+                        t -= total[y];
+                        ++x;
+                    }
+            }
+            pre = a.xprefix + (uint64_t)x * a.xstride;
+            i = queue_segment(pre, segments(x), t);
+        }
+        const uint32_t sgi = x + kXcd * i;
+        const uint64_t b0 = a.base[sgi];
+        const uint64_t len = a.base[sgi + 1] - b0;
+        const uint64_t first = (t - pre[i]) * (a.items * kResThreads);
+        uint32_t g;
+        const PGraph &p = a.G.of_seg(sgi, g);
+        if (PHASE == 1) {
+            Seg1 sg;
+            sg.q = sgi - p.seg0;
+            sg.fs = 1;
+            sg.u = 1;
+            sg.F = sg.U = nullptr;
+            if (a.f.foff) {
+                sg.F = a.f.fmem + a.f.foff[sg.q];
+                sg.fs = a.f.foff[sg.q + 1] - a.f.foff[sg.q];
+                sg.U = a.f.umem + a.f.uoff[sg.q];
+                sg.u = a.f.uoff[sg.q + 1] - a.f.uoff[sg.q];
+            }
+            sg.nnf = p.P - sg.u;
+            sg.thr_p = p.thr_p;
+            sg.tag = p.tag1;
+            sg.key0 = p.key0;
+            sg.key1 = p.key1;
+            uint16_t *lab = static_cast<uint16_t *>(a.val) + b0;
 #pragma unroll 4
-                for (int k = 0; k < kResItems; ++k) {
-                    const uint64_t j = first + (uint64_t)k * kResThreads + tid;
-                    if (j < len) lab[j] = (uint16_t)phase1_label(j, sg, lab);
-                }
-            } else {
-                Seg2 sg;
-                sg.l = sgi - p.seg0;
-                sg.tag = p.tag2;
-                sg.key0 = p.key0;
-                sg.key1 = p.key1;
-                sg.L = part_start(sg.l + 1, p.n, p.P) - part_start(sg.l, p.n, p.P);
-                sg.D = len;
-                sg.magic = len ? ~0ull / len : 0;
-                uint32_t *sel = static_cast<uint32_t *>(a.val) + b0;
+            for (uint32_t k = 0; k < a.items; ++k) {
+                const uint64_t j = first + (uint64_t)k * kResThreads + tid;
+                if (j < len) lab[j] = (uint16_t)phase1_label(j, sg, lab);
+            }
+        } else {
+            Seg2 sg;
+            sg.l = sgi - p.seg0;
+            sg.tag = p.tag2;
+            sg.key0 = p.key0;
+            sg.key1 = p.key1;
+            sg.L = part_start(sg.l + 1, p.n, p.P) - part_start(sg.l, p.n, p.P);
+            sg.D = len;
+            sg.magic = len ? ~0ull / len : 0;
+            uint32_t *sel = static_cast<uint32_t *>(a.val) + b0;
 #pragma unroll 4
-                for (int k = 0; k < kResItems; ++k) {
-                    const uint64_t tt = first + (uint64_t)k * kResThreads + tid;
-                    if (tt < len) sel[tt] = phase2_endpoint(tt, sg, sel);
-                }
+            for (uint32_t k = 0; k < a.items; ++k) {
+                const uint64_t tt = first + (uint64_t)k * kResThreads + tid;
+                if (tt < len) sel[tt] = phase2_endpoint(tt, sg, sel);
             }
         }
     }
@@ -287,7 +339,8 @@ template <int PHASE> __global__ __launch_bounds__(kResThreads) void pba_resolve(
 // Per-XCD queues of resolve tiles: prefix of tile counts over the segments
 // s = x, x+8, ... of each XCD x (one workgroup per XCD queue).
 __global__ __launch_bounds__(1024) void pba_tile_table(const uint64_t *base, uint32_t S, uint32_t xstride,
-                                                       uint64_t *xprefix, uint64_t *xtotal, uint32_t *queues) {
+                                                       uint32_t tile, uint64_t *xprefix, uint64_t *xtotal,
+                                                       uint32_t *queues) {
     __shared__ uint64_t sm[1024];
     const uint32_t x = blockIdx.x;
     const uint32_t nseg = S > x ? (S - x + kXcd - 1) / kXcd : 0;
@@ -296,7 +349,7 @@ __global__ __launch_bounds__(1024) void pba_tile_table(const uint64_t *base, uin
     uint64_t acc = 0;
     for (uint32_t i = lo; i < hi; ++i) {
         const uint32_t sg = x + kXcd * i;
-        acc += (base[sg + 1] - base[sg] + kResTile - 1) / kResTile;
+        acc += (base[sg + 1] - base[sg] + tile - 1) / tile;
     }
     sm[threadIdx.x] = acc;
     __syncthreads();
@@ -311,7 +364,7 @@ __global__ __launch_bounds__(1024) void pba_tile_table(const uint64_t *base, uin
     for (uint32_t i = lo; i < hi; ++i) {
         pre[i] = run;
         const uint32_t sg = x + kXcd * i;
-        run += (base[sg + 1] - base[sg] + kResTile - 1) / kResTile;
+        run += (base[sg + 1] - base[sg] + tile - 1) / tile;
     }
     if (threadIdx.x == 1023) {
         pre[nseg] = sm[1023];
@@ -888,6 +941,19 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
     }
 }
 
+// Slots per thread of a resolve tile, for E slots on `cus` CUs: 16 where that
+// gives all resident workgroups (8 per CU) a tile, else the power of two that
+// does.  A thread walks its slots' chains one after the other, and a walk that
+// finds nothing resolved yet is some ten draws and dependent reads long, so in
+// a small graph the walks of one thread would be the time of the pass.  Where
+// there are tiles enough the larger ones are the better (2,048 slots 70.6 ms
+// against 64.3 for both phases at 2^30 vertices, m = 5).
+uint32_t resolve_items(uint64_t E, int cus) {
+    uint32_t items = kResItems;
+    while (items > 1 && E < (uint64_t)items * kResThreads * 8 * (uint64_t)cus) items /= 2;
+    return items;
+}
+
 uint32_t choose_ct(uint64_t P) {
     // Tiles of the count/substitution passes: large enough that the P x P
     // histogram rows stay a small fraction of the slot arrays.
@@ -1033,8 +1099,14 @@ static int enqueue(const PbaPlan &pl, const Graphs &G, const Factions &fac, uint
     uint64_t *xtot = reinterpret_cast<uint64_t *>(ws + pl.off_xtot);
     uint32_t *queues = reinterpret_cast<uint32_t *>(ws + pl.off_queues);
     const int cus = device_cu_count();
-    const int res_grid = cus * 8;
-    const uint32_t S = pl.S;
+    const int res_grid = cus * 8 / kXcd * kXcd;  // (a multiple of the XCDs)
+    const uint32_t S = pl.S, items = resolve_items(pl.E, cus);
+    // Tickets from kTicketRounds tiles per resident workgroup on.  Both phases
+    // in us, tickets / tiles by workgroup id (m = 5): 404 / 29 at 65,536
+    // vertices (m = 4), 422 / 135 at 10^6, 667 / 369 at 4 10^6, 893 / 760 at
+    // 8 10^6 (4.8 tiles each), 1,304 / 1,414 (64 partitions) and 1,460 / 1,339
+    // (1,024) at 16 10^6, 4,765 / 6,351 at 64 10^6.
+    const bool tickets = pl.E > kTicketRounds * (uint64_t)items * kResThreads * (uint64_t)res_grid;
 
     auto fill32 = [&](void *ptr, uint64_t words, uint32_t v) {
         if (!words) return;
@@ -1048,10 +1120,14 @@ static int enqueue(const PbaPlan &pl, const Graphs &G, const Factions &fac, uint
     // sentinel-initialised labels.
     { ProfScope _ps("pba_tile_table", s); pba_bases1<<<(S + 1 + 255) / 256, 256, 0, s>>>(G, S, pl.E, base1); }
     fill32(lab, (pl.E + 1) / 2, 0xFFFFFFFFu);
-    { ProfScope _ps("pba_tile_table", s); pba_tile_table<<<kXcd, 1024, 0, s>>>(base1, S, pl.xstride, xpre, xtot, queues); }
+    { ProfScope _ps("pba_tile_table", s); pba_tile_table<<<kXcd, 1024, 0, s>>>(base1, S, pl.xstride, items * kResThreads, xpre, xtot, queues); }
     {
         ProfScope _ps("pba_resolve", s);
-        pba_resolve<1><<<res_grid, kResThreads, 0, s>>>(ResolveArgs{G, fac, lab, base1, xpre, xtot, queues, S, pl.xstride});
+        const ResolveArgs ra{G, fac, lab, base1, xpre, xtot, queues, S, pl.xstride, items};
+        if (tickets)
+            pba_resolve<1, true><<<res_grid, kResThreads, 0, s>>>(ra);
+        else
+            pba_resolve<1, false><<<res_grid, kResThreads, 0, s>>>(ra);
     }
 
     // Count exchange.
@@ -1070,10 +1146,14 @@ static int enqueue(const PbaPlan &pl, const Graphs &G, const Factions &fac, uint
 
     // Phase 2: every selection's endpoint, drawn and resolved in one pass.
     fill32(sel, pl.E, kSelNone);
-    { ProfScope _ps("pba_tile_table", s); pba_tile_table<<<kXcd, 1024, 0, s>>>(sbase, S, pl.xstride, xpre, xtot, queues + kXcd); }
+    { ProfScope _ps("pba_tile_table", s); pba_tile_table<<<kXcd, 1024, 0, s>>>(sbase, S, pl.xstride, items * kResThreads, xpre, xtot, queues + kXcd); }
     {
         ProfScope _ps("pba_resolve", s);
-        pba_resolve<2><<<res_grid, kResThreads, 0, s>>>(ResolveArgs{G, fac, sel, sbase, xpre, xtot, queues + kXcd, S, pl.xstride});
+        const ResolveArgs ra{G, fac, sel, sbase, xpre, xtot, queues + kXcd, S, pl.xstride, items};
+        if (tickets)
+            pba_resolve<2, true><<<res_grid, kResThreads, 0, s>>>(ra);
+        else
+            pba_resolve<2, false><<<res_grid, kResThreads, 0, s>>>(ra);
     }
 
     // Substitution.

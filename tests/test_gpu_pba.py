@@ -93,3 +93,17 @@ def test_pba_scale_full(sfg, orc, cfg):
         np.testing.assert_array_equal(dst[s:s + chunk].cpu().numpy().astype(np.int64), od[s:s + chunk])
     del src, dst
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,m,P", [(70_001, 3, 1), (50_003, 4, 9), (4_099, 2, 2_000), (1_500_007, 4, 12),
+                                   (13_500_001, 5, 64)])
+def test_tile_dealing_matches_oracle(sfg, orc, n, m, P):
+    """The ways the resolve tiles are dealt out: one queue, queues of uneven
+    and of even length, one to many slots per thread, and (the last size, more
+    than 8 tiles per resident workgroup) tickets."""
+    import torch
+    src, dst = sfg.pba_generate(n, m, P, 0.2, seed=P)
+    torch.cuda.synchronize()
+    assert sfg.device_error() == 0
+    es, ed = orc.pba_generate(n, m, P, 0.2, P)
+    assert np.array_equal(src.cpu().numpy(), es) and np.array_equal(dst.cpu().numpy(), ed)
