@@ -54,6 +54,7 @@ constexpr int kScanChunk = 4096;  // vertices per chunk of the row fill scan
 constexpr int kPrepUnroll = 4;    // keys per thread in flight in the histogram pass
 constexpr int kPrepCopies = 4;    // interleaved copies of each LDS histogram
 constexpr int kPrepBlocksPerCu = 4;
+constexpr int kPrepMinEdges = 4096;  // edges a workgroup of it has at least
 
 constexpr uint64_t kNoRow = ~0ull;
 
@@ -189,20 +190,6 @@ __global__ __launch_bounds__(256) void csr_prepare(PrepArgs a) {
     }
 }
 
-// Exclusive scan of every pass's digit histogram -> bucket bases.
-__global__ __launch_bounds__(256) void csr_digit_bases(const uint64_t *ghist, uint64_t *gbase) {
-    __shared__ uint64_t s_tmp[4];
-    const int p = blockIdx.x;
-    uint64_t tot;
-    const uint64_t ex = block_exclusive_scan_256(ghist[p * kRadix + threadIdx.x], s_tmp, &tot);
-    gbase[p * kRadix + threadIdx.x] = ex;
-}
-
-template <typename T> __global__ void fill_kernel(T *p, uint64_t n, T v) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
-
 // --------------------------------------------------------------------------- onesweep pass
 
 struct PassArgs {
@@ -211,7 +198,7 @@ struct PassArgs {
     const void *in;         // later passes
     void *out;
     uint64_t *status;       // [tiles][256]
-    const uint64_t *gbase;  // [256] of this pass
+    uint64_t *gbase;        // [256] bucket bases of a FINAL pass, left for csr_run_starts
     const uint64_t *ghist;  // [256] of this pass: digits no entry has skip the look-back
     uint32_t *err;
     uint64_t *csc;          // column starts (BOUND passes only)
@@ -300,9 +287,6 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
         else
             k[i] = valid ? static_cast<const KeyT *>(a.in)[idx] : (KeyT)0;
     }
-    // This thread's digit's base and count of the pass (read only after the
-    // ranking and the look-back), loaded with the keys.
-    const uint64_t my_gbase = tid < kRadix ? a.gbase[tid] : 0;
     const bool used = a.ghist[(uint32_t)tid / kLanesPerDigit] != 0;
     for (int i = tid; i < kPassWaves * kRadix; i += kPassThreads) {
         (&s_cnt[0][0])[i] = 0;
@@ -310,6 +294,17 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     }
     if (FINAL && a.dec && tid < kRadix) s_dec[tid] = a.dec[tid];
     __syncthreads();
+    // The buckets' bases enter the prefixes through tile 0, whose published
+    // counts start from them (a scan of the digit counts that no other tile
+    // needs to do, and no launch of its own).
+    if (tile == 0) {
+        uint64_t entries;
+        const uint64_t base = block_exclusive_scan_256(tid < kRadix ? a.ghist[tid] : 0, s_tmp, &entries);
+        if (tid < kRadix) {
+            s_gpos[tid] = base;
+            if (FINAL) a.gbase[tid] = base;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < kPassItems; ++i) {
         const uint64_t idx = wbase + (uint64_t)i * 64 + lane;
@@ -393,7 +388,8 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     const uint32_t dg = (uint32_t)tid / kLanesPerDigit, part = (uint32_t)tid % kLanesPerDigit;
     const uint64_t my_cnt = s_tot[dg];
     if (part == 0 && used)
-        store_agent(a.status + tile * kRadix + dg, status_word(a.tag, tile == 0 ? kFlagIncl : kFlagAgg, my_cnt));
+        store_agent(a.status + tile * kRadix + dg,
+                    tile == 0 ? status_word(a.tag, kFlagIncl, s_gpos[dg] + my_cnt) : status_word(a.tag, kFlagAgg, my_cnt));
     const bool walk = tile > 0 && used;
 
     uint64_t tot;
@@ -407,7 +403,7 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     for (int i = 0; i < kPassItems; ++i)
         if (d[i] < kRadix) s_keys[s_off[d[i]] + s_cnt[w][d[i]] + r[i]] = k[i];
 
-    uint64_t prefix = 0;
+    uint64_t prefix = tile == 0 && part == 0 ? s_gpos[dg] : 0;
     if (walk) {
         uint64_t j = tile;  // tiles below j are still to be examined
         for (;;) {
@@ -458,7 +454,7 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     }
     if (part == 0) s_gpos[dg] = prefix;
     __syncthreads();
-    if (tid < kRadix) s_gpos[tid] = my_gbase + s_gpos[tid] - ex;
+    if (tid < kRadix) s_gpos[tid] -= ex;
     __syncthreads();
 
     // Write the digit runs out, coalesced.
@@ -518,11 +514,11 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
 // --------------------------------------------------------------------------- run starts
 // After a FINAL pass: the entries that open a digit run of a tile.  The
 // pass's look-back words now hold, for every digit d an entry has and every
-// tile t, the inclusive count incl(t, d) of digit-d entries in tiles <= t, so
-// tile t's run of d starts at gbase[d] + incl(t - 1, d).  Its predecessor in
-// sorted order is the last entry of the nearest earlier tile with a run of d
-// (the first tile whose inclusive count reaches incl(t - 1, d)), or, for the
-// first run of d, the last entry of the previous digit that entries have.
+// tile t, incl(t, d): the bucket base of d plus the count of digit-d entries in
+// tiles <= t, so tile t's run of d starts at incl(t - 1, d).  Its predecessor
+// in sorted order is the last entry of the nearest earlier tile with a run of
+// d (the first tile whose incl reaches incl(t - 1, d)), or, for the first run
+// of d, the last entry of the previous digit that entries have.
 struct RunArgs {
     uint64_t tiles, n;
     const uint64_t *status;  // [tiles][256] of the FINAL pass
@@ -536,9 +532,13 @@ struct RunArgs {
     uint32_t *err;
     int wb;
     uint32_t tag;
+    int run_tiles;  // tiles per workgroup, a multiple of kRunBatch
 };
 
-constexpr int kRunTiles = 16;  // tiles per workgroup of csr_run_starts
+// Tiles per workgroup of csr_run_starts: 16, whose counts then roll along,
+// where that gives every CU a workgroup, else 4 (the passes' tiles are walked
+// one memory latency after the other: 16.4 us for 64 tiles, RUNS_FIGURES).
+constexpr int kRunTiles = 16;
 
 // The FINAL pass has ended, so its look-back words are read with ordinary
 // (cacheable) loads.
@@ -573,7 +573,7 @@ __device__ __forceinline__ uint64_t incl_value(const RunArgs &a, uint64_t v) {
     return v & ((1ull << 56) - 1);
 }
 
-// A workgroup takes kRunTiles consecutive tiles, thread d digit d; the
+// A workgroup takes run_tiles consecutive tiles, thread d digit d; the
 // inclusive counts of the two tiles before the current one roll along.
 // The loads of kRunBatch tiles -- look-back word, first key, and the last
 // key of the tile before (the usual predecessor) -- go out together.
@@ -589,11 +589,12 @@ __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
     if (d == 0) s_dup = 0;
     __syncthreads();
     uint32_t ndup = 0;
-    const uint64_t t0 = (uint64_t)blockIdx.x * kRunTiles;
-    // incl(t - 2, d) and incl(t - 1, d) of the current tile t (0 before tile 0)
-    uint64_t c2 = (used && t0 >= 2) ? incl_of(a, t0 - 2, d) : 0;
-    uint64_t c1 = (used && t0 >= 1) ? incl_of(a, t0 - 1, d) : 0;
-    for (int i0 = 0; i0 < kRunTiles; i0 += kRunBatch) {
+    const uint64_t t0 = (uint64_t)blockIdx.x * a.run_tiles;
+    // incl(t - 2, d) and incl(t - 1, d) of the current tile t (the base before tile 0)
+    const uint64_t base = a.gbase[d];
+    uint64_t c2 = (used && t0 >= 2) ? incl_of(a, t0 - 2, d) : base;
+    uint64_t c1 = (used && t0 >= 1) ? incl_of(a, t0 - 1, d) : base;
+    for (int i0 = 0; i0 < a.run_tiles; i0 += kRunBatch) {
         uint64_t raw[kRunBatch];
         KeyT fk[kRunBatch], lk[kRunBatch];
 #pragma unroll
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
             const KeyT f = fk[u];
             bool has = false;
             KeyT pred = 0;
-            if (before > 0) {
+            if (before > base) {
                 // the nearest earlier tile with a run of d: usually t - 1
                 if (t < 2 || before2 < before) {
                     pred = lk[u];
@@ -631,12 +632,12 @@ __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
                 int dp = (int)d - 1;
                 while (dp >= 0 && a.ghist[dp] == 0) --dp;
                 if (dp >= 0) {
-                    const uint64_t tp = first_tile_reaching(a, (uint32_t)dp, 0, a.tiles - 1, a.ghist[dp]);
+                    const uint64_t tp = first_tile_reaching(a, (uint32_t)dp, 0, a.tiles - 1, a.gbase[dp] + a.ghist[dp]);
                     pred = last[tp * kRadix + dp];
                     has = true;
                 }
             }
-            const uint64_t pos = a.gbase[d] + before;
+            const uint64_t pos = before;
             const uint64_t row = (uint64_t)(f >> a.wb);
             if ((!has || row != (uint64_t)(pred >> a.wb)) && row < a.n) {
                 a.rp[row] = pos;
@@ -899,21 +900,35 @@ __device__ __forceinline__ int log2_bin(uint64_t d) {
     return b > 31 ? 31 : b;
 }
 
-__global__ __launch_bounds__(256) void rowfill_first(const uint64_t *rp, const uint8_t *mark, uint64_t n1,
-                                                     uint64_t *cfirst) {
+// The arrays of a row fill: row starts, then (with a histogram) the sorted
+// positions' row starts and the column starts where the CSR has them.
+struct FillArrays {
+    struct One {
+        uint64_t *A;
+        const uint8_t *mark;
+        uint64_t *cmin;  // [chunks]
+        bool degree;     // A[v + 1] - A[v] counts towards the degree of v
+    } a[3];
+    int count;
+    uint64_t n1, chunks;
+    uint64_t *hist;
+};
+
+__global__ __launch_bounds__(256) void rowfill_first(FillArrays f) {
     __shared__ uint32_t s_first;
     if (threadIdx.x == 0) s_first = ~0u;
     __syncthreads();
+    const FillArrays::One &a = f.a[blockIdx.y];
     constexpr int per = kScanChunk / 256;
     const uint64_t c0 = (uint64_t)blockIdx.x * kScanChunk;
     const uint64_t v0 = c0 + (uint64_t)threadIdx.x * per;
-    const uint32_t bits = v0 < n1 ? load_marks16(mark, v0, n1) : 0u;
+    const uint32_t bits = v0 < f.n1 ? load_marks16(a.mark, v0, f.n1) : 0u;
     if (bits) atomicMin(&s_first, (uint32_t)threadIdx.x * per + (uint32_t)__builtin_ctz(bits));
     __syncthreads();
-    if (threadIdx.x == 0) cfirst[blockIdx.x] = s_first == ~0u ? kNoRow : rp[c0 + s_first];
+    if (threadIdx.x == 0) a.cmin[blockIdx.x] = s_first == ~0u ? kNoRow : a.A[c0 + s_first];
 }
 
-// Exclusive reverse min-scan of the chunk minima (single block).  Thread t
+// Exclusive reverse min-scan of the chunk minima (one block per array).  Thread t
 // takes a contiguous range of whole kChunkBatch batches (128-byte aligned),
 // moved by 16-byte vector loads and stores, so that the range is not walked
 // one memory latency per chunk.
@@ -932,8 +947,10 @@ __device__ __forceinline__ void load_batch(const uint64_t *p, uint64_t b, uint64
     }
 }
 
-__global__ __launch_bounds__(1024) void rowfill_chunks(uint64_t *cmin, uint64_t nchunks) {
+__global__ __launch_bounds__(1024) void rowfill_chunks(FillArrays f) {
     __shared__ uint64_t s[1024];
+    uint64_t *cmin = f.a[blockIdx.x].cmin;
+    const uint64_t nchunks = f.chunks;
     const uint64_t per = ((nchunks + 1023) / 1024 + kChunkBatch - 1) / kChunkBatch * kChunkBatch;
     const uint64_t lo = min((uint64_t)threadIdx.x * per, nchunks), hi = min(lo + per, nchunks);
     const uint64_t nb = (hi - lo + kChunkBatch - 1) / kChunkBatch;
@@ -980,75 +997,118 @@ __global__ __launch_bounds__(1024) void rowfill_chunks(uint64_t *cmin, uint64_t 
     }
 }
 
-// HIST: the fill of the last array also counts the degree histogram (the
-// degrees of the paper's Results section) over rows v < n1 - 1: A[v+1] - A[v]
-// of the filled values, plus other[v+1] - other[v] when other (an array
-// filled before) is given.  other is read only where omark (its marks) is set:
-// an unmarked row of a filled array has other[v+1] = other[v].
-template <bool HIST>
-__global__ __launch_bounds__(256) void rowfill_apply(uint64_t *A, const uint8_t *mark, uint64_t n1,
-                                                     const uint64_t *cnext, const uint64_t *other,
-                                                     const uint8_t *omark, uint64_t *hist) {
+// The first marked value at or after row v (a multiple of 16); kNoRow if there
+// is none.  Whole workgroup; marked rows only ever hold their final value.
+__device__ __forceinline__ uint64_t marked_from(const FillArrays::One &a, uint64_t v, uint64_t n1, uint32_t *s_first) {
+    for (; v < n1; v += kScanChunk) {
+        const uint64_t v0 = v + (uint64_t)threadIdx.x * (kScanChunk / 256);
+        const uint32_t bits = v0 < n1 ? load_marks16(a.mark, v0, n1) : 0u;
+        if (threadIdx.x == 0) *s_first = ~0u;
+        __syncthreads();
+        if (bits) atomicMin(s_first, (uint32_t)threadIdx.x * (kScanChunk / 256) + (uint32_t)__builtin_ctz(bits));
+        __syncthreads();
+        const uint32_t first = *s_first;
+        __syncthreads();
+        if (first != ~0u) return a.A[v + first];
+    }
+    return kNoRow;
+}
+
+// One chunk of every array.  HIST: the degree histogram (the degrees of the
+// paper's Results section) over rows v < n1 - 1 is counted from the filled
+// values, the degree of v being the sum of A[v+1] - A[v] over the arrays that
+// count towards it.  SELF: the value after the chunk is looked for in the
+// marks here, not taken from the chunk scan.
+template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_apply(FillArrays f) {
     constexpr int per = kScanChunk / 256;
     // Thread t owns rows t*per .. t*per+per-1 of the chunk; the results go
     // through LDS (one pad word per `per`) so the stores are coalesced.
     __shared__ uint64_t s_out[kScanChunk + kScanChunk / per];
     __shared__ uint64_t s[256];
     __shared__ uint32_t s_h[32];
+    __shared__ uint32_t s_first;
     const int tid = threadIdx.x;
     const uint32_t lane = tid & 63;
-    const uint64_t c0 = (uint64_t)blockIdx.x * kScanChunk;
+    const uint64_t n1 = f.n1, c0 = (uint64_t)blockIdx.x * kScanChunk;
     const uint64_t v0 = c0 + (uint64_t)tid * per;
-    const uint32_t bits = v0 < n1 ? load_marks16(mark, v0, n1) : 0u;
     if (HIST && tid < 32) s_h[tid] = 0;
-    uint64_t x[per];
-    uint64_t m = kNoRow;
+    uint64_t deg[HIST ? per : 1];  // of row c0 + 256 j + tid
+    if (HIST)
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-        x[j] = ((bits >> j) & 1u) ? A[v0 + j] : kNoRow;  // marked rows only
-        m = min(m, x[j]);
-    }
-    s[tid] = m;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        uint64_t o = tid + off < 256 ? s[tid + off] : kNoRow;
-        __syncthreads();
-        s[tid] = min(s[tid], o);
-        __syncthreads();
-    }
-    const uint64_t next = cnext[blockIdx.x];  // the first marked value after the chunk
-    uint64_t run = min(next, tid + 1 < 256 ? s[tid + 1] : kNoRow);
+        for (int j = 0; j < per; ++j) deg[j] = 0;
+    for (int q = 0; q < f.count; ++q) {
+        const FillArrays::One &a = f.a[q];
+        const uint32_t bits = v0 < n1 ? load_marks16(a.mark, v0, n1) : 0u;
+        uint64_t x[per];
+        uint64_t m = kNoRow;
 #pragma unroll
-    for (int j = per - 1; j >= 0; --j) {
-        run = min(run, x[j]);
-        s_out[tid * (per + 1) + j] = run;
+        for (int j = 0; j < per; ++j) {
+            x[j] = ((bits >> j) & 1u) ? a.A[v0 + j] : kNoRow;  // marked rows only
+            m = min(m, x[j]);
+        }
+        // the first marked value after the chunk
+        const uint64_t next = SELF ? marked_from(a, c0 + kScanChunk, n1, &s_first) : a.cmin[blockIdx.x];
+        s[tid] = m;
+        __syncthreads();
+        for (int off = 1; off < 256; off <<= 1) {
+            uint64_t o = tid + off < 256 ? s[tid + off] : kNoRow;
+            __syncthreads();
+            s[tid] = min(s[tid], o);
+            __syncthreads();
+        }
+        uint64_t run = min(next, tid + 1 < 256 ? s[tid + 1] : kNoRow);
+#pragma unroll
+        for (int j = per - 1; j >= 0; --j) {
+            run = min(run, x[j]);
+            s_out[tid * (per + 1) + j] = run;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            const int i = 256 * j + tid;
+            const uint64_t v = c0 + i;
+            const uint64_t a0 = s_out[(i / per) * (per + 1) + i % per];
+            if (v < n1) a.A[v] = a0;
+            if (HIST && a.degree && v + 1 < n1)  // the row after the chunk's last holds `next` once filled
+                deg[j] += (i + 1 < kScanChunk ? s_out[((i + 1) / per) * (per + 1) + (i + 1) % per] : next) - a0;
+        }
+        __syncthreads();  // s and s_out are rewritten for the next array
     }
-    __syncthreads();
-    for (int i = tid; i < kScanChunk; i += 256) {
-        const uint64_t v = c0 + i;
-        const uint64_t a0 = s_out[(i / per) * (per + 1) + i % per];
-        if (v < n1) A[v] = a0;
-        if (HIST) {
-            // The row after the chunk's last holds `next` once filled.
-            const bool row = v + 1 < n1;
-            int b = 0;
-            if (row) {
-                const uint64_t a1 = i + 1 < kScanChunk ? s_out[((i + 1) / per) * (per + 1) + (i + 1) % per] : next;
-                uint64_t deg = a1 - a0;
-                if (other && omark[v]) deg += other[v + 1] - other[v];
-                b = log2_bin(deg);
-            }
+    if (HIST) {
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            const bool row = c0 + 256 * j + tid + 1 < n1;
+            const int b = row ? log2_bin(deg[j]) : 0;
             // Most vertices of a scale-free graph have small degree: bin 0
             // is counted by ballot, the rest by LDS atomics.
             const uint64_t zero = __ballot(row && b == 0);
             if (lane == 0 && zero) atomicAdd(&s_h[0], (uint32_t)__popcll(zero));
             if (row && b != 0) atomicAdd(&s_h[b], 1u);
         }
-    }
-    if (HIST) {
         __syncthreads();
-        if (tid < 32 && s_h[tid]) atomicAdd((unsigned long long *)&hist[tid], (unsigned long long)s_h[tid]);
+        if (tid < 32 && s_h[tid]) atomicAdd((unsigned long long *)&f.hist[tid], (unsigned long long)s_h[tid]);
     }
+}
+
+// The degree histogram from filled arrays.
+__global__ __launch_bounds__(256) void degree_hist(FillArrays f) {
+    __shared__ uint32_t s_h[32];
+    if (threadIdx.x < 32) s_h[threadIdx.x] = 0;
+    __syncthreads();
+    const uint64_t stride = (uint64_t)gridDim.x * 256;
+    for (uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x; v - (threadIdx.x & 63) < f.n1 - 1; v += stride) {
+        const bool row = v < f.n1 - 1;
+        uint64_t deg = 0;
+        for (int q = 0; q < f.count; ++q)
+            if (row && f.a[q].degree) deg += f.a[q].A[v + 1] - f.a[q].A[v];
+        const int b = row ? log2_bin(deg) : 0;
+        const uint64_t zero = __ballot(row && b == 0);
+        if ((threadIdx.x & 63) == 0 && zero) atomicAdd(&s_h[0], (uint32_t)__popcll(zero));
+        if (row && b != 0) atomicAdd(&s_h[b], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 32 && s_h[threadIdx.x])
+        atomicAdd((unsigned long long *)&f.hist[threadIdx.x], (unsigned long long)s_h[threadIdx.x]);
 }
 
 // --------------------------------------------------------------------------- host
@@ -1137,37 +1197,69 @@ int fill_grid(uint64_t n) {
     return (int)std::max<uint64_t>(1, std::min<uint64_t>(want, (uint64_t)device_cu_count() * 8));
 }
 
-template <typename T> void fill(T *p, uint64_t n, T v, hipStream_t s) {
-    if (n) {
-        ProfScope _ps("fill", s);
-        fill_kernel<T><<<fill_grid(n), 256, 0, s>>>(p, n, v);
+// Everything a build starts from, in one launch (a fill kernel, so the
+// sequence stays valid under stream capture): the counters, histograms and
+// look-back words zeroed, the marks zeroed except that of row n, and the
+// values at row n.  A launch per region was half of a small graph's time.
+struct ClearArgs {
+    struct Region {
+        uint4 *p;        // 16-byte aligned, its length rounded up to 16 bytes
+        uint64_t words;  // 16-byte words
+        uint64_t one;    // byte that is 1 instead of 0, or ~0
+    } r[8];
+    struct Value {
+        uint64_t *p;
+        uint64_t v;
+    } v[4];
+    int regions, values;
+    uint64_t *hist;  // [32], the caller's (8-byte aligned), or null
+    void region(void *p, uint64_t bytes, uint64_t one = ~0ull) { r[regions++] = {static_cast<uint4 *>(p), (bytes + 15) / 16, one}; }
+    void value(uint64_t *p, uint64_t x) { v[values++] = {p, x}; }
+};
+
+__global__ __launch_bounds__(256) void csr_clear(ClearArgs a) {
+    const uint64_t i0 = (uint64_t)blockIdx.x * 256 + threadIdx.x, stride = (uint64_t)gridDim.x * 256;
+    for (int q = 0; q < a.regions; ++q) {
+        const uint64_t at = a.r[q].one;  // (~0 / 16 is no word of any region)
+        for (uint64_t i = i0; i < a.r[q].words; i += stride) {
+            uint4 z = {0, 0, 0, 0};
+            if (i == at / 16) reinterpret_cast<uint8_t *>(&z)[at % 16] = 1;
+            a.r[q].p[i] = z;
+        }
     }
+    if (i0 < (uint64_t)a.values) *a.v[i0].p = a.v[i0].v;
+    if (a.hist && i0 < 32) a.hist[i0] = 0;
 }
 
-// With hist, the last launch also adds the degree histogram (rowfill_apply).
-void row_fill(uint64_t *A, const uint8_t *mark, uint64_t n1, uint64_t *cmin, uint64_t chunks, const uint64_t *other,
-              const uint8_t *omark, uint64_t *hist, hipStream_t s) {
+// The row fill of up to three arrays.  Up to kSelfChunks chunks the marks
+// after a chunk are scanned by its own workgroup, one launch instead of three
+// (a step per chunk in the worst case, against two launches of about 4 us).
+constexpr uint64_t kSelfChunks = 16;
+
+void row_fill(const FillArrays &f, hipStream_t s) {
     ProfScope _ps("csr_rowfill", s);
-    rowfill_first<<<(int)chunks, 256, 0, s>>>(A, mark, n1, cmin);
-    rowfill_chunks<<<1, 1024, 0, s>>>(cmin, chunks);
-    if (hist)
-        rowfill_apply<true><<<(int)chunks, 256, 0, s>>>(A, mark, n1, cmin, other, omark, hist);
+    const unsigned g = (unsigned)f.chunks;
+    if (f.chunks <= kSelfChunks) {
+        if (f.hist)
+            rowfill_apply<true, true><<<g, 256, 0, s>>>(f);
+        else
+            rowfill_apply<false, true><<<g, 256, 0, s>>>(f);
+        return;
+    }
+    rowfill_first<<<dim3(g, f.count), 256, 0, s>>>(f);
+    rowfill_chunks<<<f.count, 1024, 0, s>>>(f);
+    if (f.hist)
+        rowfill_apply<true, false><<<g, 256, 0, s>>>(f);
     else
-        rowfill_apply<false><<<(int)chunks, 256, 0, s>>>(A, mark, n1, cmin, nullptr, nullptr, nullptr);
-}
-
-// Zero the mark bytes of rows [0, n1) (whole 32-bit words; the workspace
-// carving rounds every region up to 256 bytes).
-void clear_marks(uint8_t *mark, uint64_t n1, hipStream_t s) {
-    fill<uint32_t>(reinterpret_cast<uint32_t *>(mark), (n1 + 3) / 4, 0u, s);
+        rowfill_apply<false, false><<<g, 256, 0, s>>>(f);
 }
 
 // The key array the first pass reads when the keys are given (the passes
 // ping-pong so that the last one writes keysA).
 size_t first_input_offset(const Plan &P) { return (P.passes - 1) % 2 == 0 ? P.off_keysB : P.off_keysA; }
 
-// counted: the digit histograms are already in the workspace (counted by the
-// producer of the edges), so the histogram pass is skipped.  keys_given: the
+// counted: the workspace is cleared and the digit histograms are in it
+// (counted by the producer of the edges), so the histogram pass is skipped.  keys_given: the
 // producer also wrote every entry's key at first_input_offset, so the first
 // pass reads keys like any other.
 // Columns of a CSR over packed ids are unpacked by the last pass.
@@ -1175,6 +1267,34 @@ struct Unpack {
     const uint32_t *dec;
     int groups, bits;
 };
+
+// Clears what a build of this plan starts from (see ClearArgs).
+void clear_csr(const Plan &P, uint64_t *row_ptr, uint64_t *hist, uint64_t *dups, char *ws, hipStream_t s) {
+    ClearArgs c;
+    memset(&c, 0, sizeof(c));
+    uint64_t words = 0;
+    auto region = [&](size_t off, uint64_t bytes, uint64_t one = ~0ull) {
+        c.region(ws + off, bytes, one);
+        words = std::max(words, c.r[c.regions - 1].words);
+    };
+    region(P.off_ghist, 8 * kRadix * 8);
+    if (P.N) region(P.off_status, P.pass_tiles * kRadix * 8);
+    if (P.simple && P.N) region(P.off_fstatus, P.fin_tiles * 8);
+    // Row (and column) starts are written only where a row begins and
+    // flagged in the mark bytes; the row fill completes the rest.
+    region(P.off_mark, P.n + 1, P.n);
+    if (P.directed_hist) {
+        region(P.off_cmark, P.n + 1, P.n);
+        c.value(reinterpret_cast<uint64_t *>(ws + P.off_indeg) + P.n, P.N);
+    }
+    c.hist = hist;
+    if (dups) c.value(dups, 0);
+    // (with SIMPLE the finish pass writes the values at row n)
+    if (!P.simple || P.N == 0) c.value(row_ptr + P.n, P.N);
+    if (P.hist && P.simple && P.N == 0) c.value(reinterpret_cast<uint64_t *>(ws + P.off_rpraw) + P.n, 0);
+    ProfScope _ps("fill", s);
+    csr_clear<<<fill_grid(words), 256, 0, s>>>(c);
+}
 
 template <typename IdT, typename KeyT>
 int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, void *col, uint64_t *hist,
@@ -1188,32 +1308,17 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
     uint64_t *gbase = reinterpret_cast<uint64_t *>(ws + P.off_gbase);
     uint64_t *csc = P.directed_hist ? reinterpret_cast<uint64_t *>(ws + P.off_indeg) : nullptr;
     uint64_t *rp_raw_ws = (P.hist && P.simple) ? reinterpret_cast<uint64_t *>(ws + P.off_rpraw) : nullptr;
-    uint64_t *cmin = reinterpret_cast<uint64_t *>(ws + P.off_cmin);
     uint8_t *mark = reinterpret_cast<uint8_t *>(ws + P.off_mark);
     uint8_t *cmark = P.directed_hist ? reinterpret_cast<uint8_t *>(ws + P.off_cmark) : nullptr;
     uint64_t *fstatus = P.simple ? reinterpret_cast<uint64_t *>(ws + P.off_fstatus) : nullptr;
-
-    // Clear counters, histograms and look-back words (fill kernels, so the
-    // sequence stays valid under stream capture).
-    if (!counted) fill<uint64_t>(ghist, 8 * kRadix, 0, s);
-    if (P.N) fill<uint64_t>(status, P.pass_tiles * kRadix, 0, s);
-    if (fstatus && P.N) fill<uint64_t>(fstatus, P.fin_tiles, 0, s);
-    // Row (and column) starts are written only where a row begins and
-    // flagged in the mark bytes; the row fill completes the rest.
-    clear_marks(mark, P.n + 1, s);
-    if (csc) {
-        clear_marks(cmark, P.n + 1, s);
-        fill<uint64_t>(csc + P.n, 1, P.N, s);
-        fill<uint8_t>(cmark + P.n, 1, 1, s);
-    }
-    if (dups) fill<uint64_t>(dups, 1, 0, s);
-    if (hist) fill<uint64_t>(hist, 32, 0, s);
+    if (!counted) clear_csr(P, row_ptr, hist, dups, ws, s);
 
     if (P.N > 0) {
         PrepArgs pa{P.E, P.N, src, dst, ghist, P.db, P.passes, P.tb, P.split,
                     (P.sym && !P.xor_mode && P.db % 8 == 0) ? P.db / 8 : 0};
-        // Every histogram workgroup stays resident (32 KB of LDS each).
-        const int pg = (int)std::max<uint64_t>(1, std::min<uint64_t>((P.E + 255) / 256,
+        // Every histogram workgroup stays resident (32 KB of LDS each); a small
+        // list takes fewer, since each adds its counts to the global ones.
+        const int pg = (int)std::max<uint64_t>(1, std::min<uint64_t>((P.E + kPrepMinEdges - 1) / kPrepMinEdges,
                                                                       (uint64_t)device_cu_count() * kPrepBlocksPerCu));
         if (!counted) {
             ProfScope _ps("csr_prepare", s);
@@ -1222,14 +1327,12 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
             else
                 csr_prepare<IdT, KeyT, false><<<pg, 256, 0, s>>>(pa);
         }
-        { ProfScope _ps("csr_digit_bases", s); csr_digit_bases<<<P.passes, 256, 0, s>>>(ghist, gbase); }
-
         // Ping-pong so that the last pass lands in keysA.
         for (int p = 0; p < P.passes; ++p) {
             const int remaining = P.passes - 1 - p;  // passes after this one
             KeyT *out = (remaining % 2 == 0) ? keysA : keysB;
             KeyT *in = (remaining % 2 == 0) ? keysB : keysA;
-            PassArgs a{P.E, P.N, src, dst, in, out, status, gbase + p * kRadix, ghist + p * kRadix, err,
+            PassArgs a{P.E, P.N, src, dst, in, out, status, gbase, ghist + p * kRadix, err,
                        csc, cmark, P.db, 8 * p, (uint32_t)(p + 1), P.tb, P.split, P.n};
             const int g = (int)P.pass_tiles;
             if (P.fused_finish && p == P.passes - 1) {
@@ -1260,38 +1363,53 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
                    err, P.db};
         if (P.fused_finish) {
             const int last = P.passes - 1;
-            RunArgs ra{P.pass_tiles, P.n, status, gbase + last * kRadix, ghist + last * kRadix, keysA,
+            const int run_tiles = P.pass_tiles >= (uint64_t)kRunTiles * device_cu_count() ? kRunTiles : kRunBatch;
+            RunArgs ra{P.pass_tiles, P.n, status, gbase, ghist + last * kRadix, keysA,
                        keysA + P.pass_tiles * kRadix, reinterpret_cast<const uint32_t *>(keysA + 2 * P.pass_tiles * kRadix),
-                       row_ptr, mark, dups, err, P.db, (uint32_t)(last + 1)};
-            const int rg = (int)((P.pass_tiles + kRunTiles - 1) / kRunTiles);
+                       row_ptr, mark, dups, err, P.db, (uint32_t)(last + 1), run_tiles};
+            const int rg = (int)((P.pass_tiles + run_tiles - 1) / run_tiles);
             { ProfScope _ps("csr_run_starts", s); csr_run_starts<KeyT><<<rg, kRadix, 0, s>>>(ra); }
-            fill<uint64_t>(row_ptr + P.n, 1, P.N, s);
-            fill<uint8_t>(mark + P.n, 1, 1, s);
         } else if (P.xor_mode)
             { ProfScope _ps("csr_finish", s); csr_finish<IdT, KeyT, true><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa); }
         else if (P.simple)
             { ProfScope _ps("csr_finish", s); csr_finish<IdT, KeyT, false><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa); }
         else
             { ProfScope _ps("csr_finish", s); csr_finish_plain<IdT, KeyT><<<fill_grid(P.N), kFinThreads, 0, s>>>(fa); }
-    } else {
-        fill<uint64_t>(row_ptr + P.n, 1, 0, s);
-        if (rp_raw_ws) fill<uint64_t>(rp_raw_ws + P.n, 1, 0, s);
-        fill<uint8_t>(mark + P.n, 1, 1, s);
     }
-    // The degree histogram is counted by the last fill: deg = out (from the
+    // The degree histogram is counted by the fill: deg = out (from the
     // uncompacted row starts) + in (from the column starts, directed).
-    const uint64_t n1 = P.n + 1;
-    if (!hist) {
-        row_fill(row_ptr, mark, n1, cmin, P.chunks, nullptr, nullptr, nullptr, s);
-    } else if (csc) {
-        row_fill(row_ptr, mark, n1, cmin, P.chunks, nullptr, nullptr, nullptr, s);
-        if (rp_raw_ws) row_fill(rp_raw_ws, mark, n1, cmin, P.chunks, nullptr, nullptr, nullptr, s);
-        row_fill(csc, cmark, n1, cmin, P.chunks, rp_raw_ws ? rp_raw_ws : row_ptr, mark, hist, s);
-    } else if (rp_raw_ws) {
-        row_fill(row_ptr, mark, n1, cmin, P.chunks, nullptr, nullptr, nullptr, s);
-        row_fill(rp_raw_ws, mark, n1, cmin, P.chunks, nullptr, nullptr, hist, s);
+    FillArrays f;
+    memset(&f, 0, sizeof(f));
+    f.n1 = P.n + 1;
+    f.chunks = P.chunks;
+    f.hist = hist;
+    auto add = [&](uint64_t *A, const uint8_t *m, bool degree) { f.a[f.count++] = {A, m, nullptr, degree}; };
+    add(row_ptr, mark, hist && !rp_raw_ws);
+    if (rp_raw_ws) add(rp_raw_ws, mark, true);
+    if (csc) add(csc, cmark, true);
+    // The chunk scans of a second and third array go where the look-back words
+    // were (8 bytes per 4,096 rows against 2 KB per tile).
+    f.a[0].cmin = reinterpret_cast<uint64_t *>(ws + P.off_cmin);
+    const uint64_t cpad = (P.chunks + kChunkBatch - 1) / kChunkBatch * kChunkBatch;  // (vector loads)
+    f.a[1].cmin = status;
+    f.a[2].cmin = status + cpad;
+    if ((uint64_t)(f.count - 1) * cpad > std::max<uint64_t>(P.pass_tiles, 1) * kRadix) {
+        // (more rows than 2^19 per tile of entries: one array after the other,
+        // then the histogram from filled arrays)
+        for (int q = 0; q < f.count; ++q) {
+            FillArrays one = f;
+            one.a[0] = f.a[q];
+            one.a[0].cmin = f.a[0].cmin;
+            one.count = 1;
+            one.hist = nullptr;
+            row_fill(one, s);
+        }
+        if (hist) {
+            ProfScope _ps("degree_hist", s);
+            degree_hist<<<fill_grid(P.n), 256, 0, s>>>(f);
+        }
     } else {
-        row_fill(row_ptr, mark, n1, cmin, P.chunks, nullptr, nullptr, hist, s);
+        row_fill(f, s);
     }
     return check_launch("edges_to_csr");
 }
@@ -1499,7 +1617,7 @@ int kron_csr_packed(uint32_t n0, const float *initiator, uint32_t k, uint64_t nu
     bc.pack_groups = groups;
     bc.pack_bits = bits;
     bc.pack_tab = ptab;
-    fill<uint64_t>(bc.hist, 8 * kRadix, 0, s);
+    clear_csr(P, rpc, degree_hist32, num_duplicates, ws, s);
     bool counted = false;
     int rc = kron_generate_counted(n0, initiator, k, num_edges, 0, num_edges, mode, seed, graph_id, id_bytes, src, dst,
                                    s, &bc, &counted);
@@ -1568,7 +1686,7 @@ int kron_csr_build(uint32_t n0, const float *initiator, uint32_t k, uint64_t num
             bc.src_row = P.dpasses;
             bc.src_bytes = P.passes - P.dpasses;
         }
-        fill<uint64_t>(bc.hist, 8 * kRadix, 0, s);
+        clear_csr(P, row_ptr, degree_hist32, num_duplicates, ws, s);
         // 8-byte keys: the sampler writes them too, and the first pass
         // reads them instead of the two id arrays.
         if (P.key_bytes == 8) {

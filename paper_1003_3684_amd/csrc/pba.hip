@@ -111,25 +111,6 @@ __device__ __forceinline__ uint32_t count_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
-// ----------------------------------------------------------------------------- bases
-__global__ void pba_bases1(Graphs G, uint32_t S, uint64_t total, uint64_t *base1) {
-    const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s > S) return;
-    if (s == S) {
-        base1[S] = total;
-        return;
-    }
-    uint32_t g;
-    const PGraph &p = G.of_seg(s, g);
-    base1[s] = p.ebase + (uint64_t)p.m * part_start(s - p.seg0, p.n, p.P);
-}
-
-// ----------------------------------------------------------------------------- sentinels
-__global__ void pba_fill32(uint32_t *p, uint64_t n, uint32_t v) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
-
 // ----------------------------------------------------------------------------- chain resolution
 // A slot's phase-1 label and a selection's phase-2 endpoint are found by
 // following copy pointers to a terminal draw.  Both passes run the draws
@@ -336,21 +317,8 @@ template <int PHASE, bool TICKETS> __global__ __launch_bounds__(kResThreads) voi
     }
 }
 
-// Per-XCD queues of resolve tiles: prefix of tile counts over the segments
-// s = x, x+8, ... of each XCD x (one workgroup per XCD queue).
-__global__ __launch_bounds__(1024) void pba_tile_table(const uint64_t *base, uint32_t S, uint32_t xstride,
-                                                       uint32_t tile, uint64_t *xprefix, uint64_t *xtotal,
-                                                       uint32_t *queues) {
-    __shared__ uint64_t sm[1024];
-    const uint32_t x = blockIdx.x;
-    const uint32_t nseg = S > x ? (S - x + kXcd - 1) / kXcd : 0;
-    const uint32_t per = (nseg + 1023) / 1024;
-    const uint32_t lo = threadIdx.x * per, hi = std::min<uint32_t>(nseg, lo + per);
-    uint64_t acc = 0;
-    for (uint32_t i = lo; i < hi; ++i) {
-        const uint32_t sg = x + kXcd * i;
-        acc += (base[sg + 1] - base[sg] + tile - 1) / tile;
-    }
+// Exclusive prefix of a block's 1,024 per-thread sums; *total their sum.
+__device__ __forceinline__ uint64_t block_prefix_1024(uint64_t acc, uint64_t *sm, uint64_t *total) {
     sm[threadIdx.x] = acc;
     __syncthreads();
     for (int off = 1; off < 1024; off <<= 1) {
@@ -359,18 +327,93 @@ __global__ __launch_bounds__(1024) void pba_tile_table(const uint64_t *base, uin
         sm[threadIdx.x] += o;
         __syncthreads();
     }
-    uint64_t run = threadIdx.x > 0 ? sm[threadIdx.x - 1] : 0;
-    uint64_t *pre = xprefix + (uint64_t)x * xstride;
+    *total = sm[1023];
+    return threadIdx.x > 0 ? sm[threadIdx.x - 1] : 0;
+}
+
+struct TableArgs {
+    uint32_t S, xstride, tile;  // tile: slots per resolve tile
+    uint64_t *xprefix, *xtotal;
+    uint32_t *queues;
+};
+
+// XCD x's queue of resolve tiles: the prefix of the tile counts over its
+// segments s = x, x + 8, ..., whose lengths len(s) gives.  One workgroup of
+// 1,024 threads.
+template <typename Len> __device__ __forceinline__ void tile_table(const TableArgs &t, uint32_t x, Len len, uint64_t *sm) {
+    const uint32_t nseg = t.S > x ? (t.S - x + kXcd - 1) / kXcd : 0;
+    const uint32_t per = (nseg + 1023) / 1024;
+    const uint32_t lo = std::min<uint32_t>(nseg, threadIdx.x * per), hi = std::min<uint32_t>(nseg, lo + per);
+    uint64_t acc = 0, total;
+    for (uint32_t i = lo; i < hi; ++i) acc += (len(x + kXcd * i) + t.tile - 1) / t.tile;
+    uint64_t run = block_prefix_1024(acc, sm, &total);
+    uint64_t *pre = t.xprefix + (uint64_t)x * t.xstride;
     for (uint32_t i = lo; i < hi; ++i) {
         pre[i] = run;
-        const uint32_t sg = x + kXcd * i;
-        run += (base[sg + 1] - base[sg] + tile - 1) / tile;
+        run += (len(x + kXcd * i) + t.tile - 1) / t.tile;
     }
-    if (threadIdx.x == 1023) {
-        pre[nseg] = sm[1023];
-        xtotal[x] = sm[1023];
-        queues[x] = 0;
+    if (threadIdx.x == 0) {
+        pre[nseg] = total;
+        t.xtotal[x] = total;
+        t.queues[x] = 0;
     }
+}
+
+// What the passes start from, in one launch: workgroups 0-7 the phase-1 tile
+// queues; the others the segments' bases and the sentinels that the chain walks
+// test for an unresolved element.
+struct SetupArgs {
+    Graphs G;
+    TableArgs t;
+    uint64_t E;
+    uint64_t *base1;
+    uint32_t *lab, *sel;  // sentinel words of both phases (all bits set)
+    uint64_t lab_words, sel_words;
+};
+
+__global__ __launch_bounds__(1024) void pba_setup(SetupArgs a) {
+    __shared__ uint64_t sm[1024];
+    if (blockIdx.x < kXcd) {
+        tile_table(a.t, blockIdx.x, [&](uint32_t s) {
+            uint32_t g;
+            const PGraph &p = a.G.of_seg(s, g);
+            const uint32_t q = s - p.seg0;
+            return (uint64_t)p.m * (part_start(q + 1, p.n, p.P) - part_start(q, p.n, p.P));
+        }, sm);
+        return;
+    }
+    const uint64_t i0 = (uint64_t)(blockIdx.x - kXcd) * 1024 + threadIdx.x, stride = (uint64_t)(gridDim.x - kXcd) * 1024;
+    for (uint64_t s = i0; s <= a.t.S; s += stride) {
+        if (s == a.t.S) {
+            a.base1[s] = a.E;
+        } else {
+            uint32_t g;
+            const PGraph &p = a.G.of_seg((uint32_t)s, g);
+            a.base1[s] = p.ebase + (uint64_t)p.m * part_start(s - p.seg0, p.n, p.P);
+        }
+    }
+    for (uint64_t i = i0; i < a.lab_words; i += stride) a.lab[i] = 0xFFFFFFFFu;
+    for (uint64_t i = i0; i < a.sel_words; i += stride) a.sel[i] = kSelNone;
+}
+
+// From the list lengths D: workgroups 0-7 the phase-2 tile queues, workgroup 8
+// the list bases (exclusive prefix of D over all segments).
+__global__ __launch_bounds__(1024) void pba_lists(TableArgs t, const uint64_t *D, uint64_t *sbase) {
+    __shared__ uint64_t sm[1024];
+    if (blockIdx.x < kXcd) {
+        tile_table(t, blockIdx.x, [&](uint32_t s) { return D[s]; }, sm);
+        return;
+    }
+    const uint32_t per = (t.S + 1023) / 1024;
+    const uint32_t lo = std::min<uint32_t>(t.S, threadIdx.x * per), hi = std::min<uint32_t>(t.S, lo + per);
+    uint64_t acc = 0, total;
+    for (uint32_t i = lo; i < hi; ++i) acc += D[i];
+    uint64_t run = block_prefix_1024(acc, sm, &total);
+    for (uint32_t i = lo; i < hi; ++i) {
+        sbase[i] = run;
+        run += D[i];
+    }
+    if (threadIdx.x == 0) sbase[t.S] = total;
 }
 
 // ----------------------------------------------------------------------------- counting
@@ -488,29 +531,6 @@ __global__ __launch_bounds__(256) void pba_scan_apply(uint32_t *H, uint64_t R, u
     const uint64_t r0 = (uint64_t)blockIdx.x * kScanRows;
     const uint64_t r1 = std::min<uint64_t>(R, r0 + kScanRows);
     scan_strided(H + r0 * P + col, r1 - r0, P, part[(uint64_t)blockIdx.x * P + col]);
-}
-
-// List bases: sbase = exclusive prefix of D over all segments (single block).
-__global__ __launch_bounds__(1024) void pba_list_bases(const uint64_t *D, uint32_t S, uint64_t *sbase) {
-    __shared__ uint64_t sm[1024];
-    const uint32_t per = (S + 1023) / 1024;
-    const uint32_t lo = threadIdx.x * per, hi = std::min<uint32_t>(S, lo + per);
-    uint64_t acc = 0;
-    for (uint32_t i = lo; i < hi; ++i) acc += D[i];
-    sm[threadIdx.x] = acc;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint64_t o = threadIdx.x >= (uint32_t)off ? sm[threadIdx.x - off] : 0;
-        __syncthreads();
-        sm[threadIdx.x] += o;
-        __syncthreads();
-    }
-    uint64_t run = threadIdx.x > 0 ? sm[threadIdx.x - 1] : 0;
-    for (uint32_t i = lo; i < hi; ++i) {
-        sbase[i] = run;
-        run += D[i];
-    }
-    if (threadIdx.x == 1023) sbase[S] = sm[1023];
 }
 
 // ----------------------------------------------------------------------------- substitution
@@ -1108,19 +1128,15 @@ static int enqueue(const PbaPlan &pl, const Graphs &G, const Factions &fac, uint
     // (1,024) at 16 10^6, 4,765 / 6,351 at 64 10^6.
     const bool tickets = pl.E > kTicketRounds * (uint64_t)items * kResThreads * (uint64_t)res_grid;
 
-    auto fill32 = [&](void *ptr, uint64_t words, uint32_t v) {
-        if (!words) return;
-        ProfScope _ps("pba_fill", s);
-        const uint64_t want = (words + 255) / 256;
-        pba_fill32<<<(unsigned)std::min<uint64_t>(want, (uint64_t)cus * 8), 256, 0, s>>>(static_cast<uint32_t *>(ptr),
-                                                                                      words, v);
-    };
-
     // Phase 1: every slot's label, drawn and resolved in one pass over
     // sentinel-initialised labels.
-    { ProfScope _ps("pba_tile_table", s); pba_bases1<<<(S + 1 + 255) / 256, 256, 0, s>>>(G, S, pl.E, base1); }
-    fill32(lab, (pl.E + 1) / 2, 0xFFFFFFFFu);
-    { ProfScope _ps("pba_tile_table", s); pba_tile_table<<<kXcd, 1024, 0, s>>>(base1, S, pl.xstride, items * kResThreads, xpre, xtot, queues); }
+    {
+        ProfScope _ps("pba_fill", s);
+        const SetupArgs sa{G, {S, pl.xstride, items * kResThreads, xpre, xtot, queues}, pl.E, base1,
+                           reinterpret_cast<uint32_t *>(lab), sel, (pl.E + 1) / 2, pl.E};
+        const uint64_t want = (std::max<uint64_t>(pl.E, S + 1) + 1023) / 1024;
+        pba_setup<<<kXcd + (unsigned)std::min<uint64_t>(want, (uint64_t)cus * 2), 1024, 0, s>>>(sa);
+    }
     {
         ProfScope _ps("pba_resolve", s);
         const ResolveArgs ra{G, fac, lab, base1, xpre, xtot, queues, S, pl.xstride, items};
@@ -1142,11 +1158,12 @@ static int enqueue(const PbaPlan &pl, const Graphs &G, const Factions &fac, uint
     } else {
         { ProfScope _ps("pba_scan", s); pba_scan_columns<<<(S + 255) / 256, 256, 0, s>>>(G, S, H, D, err); }
     }
-    { ProfScope _ps("pba_scan", s); pba_list_bases<<<1, 1024, 0, s>>>(D, S, sbase); }
+    {
+        ProfScope _ps("pba_scan", s);
+        pba_lists<<<kXcd + 1, 1024, 0, s>>>(TableArgs{S, pl.xstride, items * kResThreads, xpre, xtot, queues + kXcd}, D, sbase);
+    }
 
     // Phase 2: every selection's endpoint, drawn and resolved in one pass.
-    fill32(sel, pl.E, kSelNone);
-    { ProfScope _ps("pba_tile_table", s); pba_tile_table<<<kXcd, 1024, 0, s>>>(sbase, S, pl.xstride, items * kResThreads, xpre, xtot, queues + kXcd); }
     {
         ProfScope _ps("pba_resolve", s);
         const ResolveArgs ra{G, fac, sel, sbase, xpre, xtot, queues + kXcd, S, pl.xstride, items};

@@ -135,3 +135,39 @@ def test_entry_count_limit(sfg):
         assert rc == sfg.SFG_ERANGE, (num_edges, flags, rc)
     torch.cuda.synchronize()
     assert int(t.abs().sum().item()) == 0
+
+
+@pytest.mark.parametrize("flags", FLAG_SETS)
+@pytest.mark.parametrize("n,E", [(16 * 4096 - 1, 20_000), (16 * 4096, 20_000), (5 * 4096 - 7, 9), (1 << 22, 100),
+                                 ((1 << 22) + 5, 20_000), (40_000, 0)])
+def test_csr_row_fill_branches(sfg, orc, flags, n, E):
+    """Both sides of the rules of the row fill: its own chunks' next marks (up
+    to 16 chunks of 4,096 rows), the chunk scan, and the arrays one after the
+    other (more than 2^19 rows per tile of entries); long empty stretches."""
+    rng = np.random.default_rng(n + E)
+    src, dst = rng.integers(0, n, size=E), rng.integers(n // 3, n // 2, size=E)
+    src[: E // 2] = src[: E // 2] // 7
+    _check(sfg, orc, n, src, dst, flags, 4)
+
+
+def test_csr_histogram_pointer_of_8_byte_alignment(sfg, orc):
+    """degree_hist32 and num_duplicates need only the alignment of their type."""
+    import ctypes as C
+    import torch
+    rng = np.random.default_rng(8)
+    n, E = 3000, 10_000
+    src, dst = rng.integers(0, n, size=E), rng.integers(0, n, size=E)
+    s, d = (torch.as_tensor(x, dtype=torch.int32).cuda() for x in (src, dst))
+    buf = torch.full((40,), -1, dtype=torch.int64, device="cuda")
+    rp, col = torch.empty(n + 1, dtype=torch.int64, device="cuda"), torch.empty(E, dtype=torch.int32, device="cuda")
+    ws = sfg.workspace(sfg.edges_to_csr_workspace_bytes(n, E, 4, 0))
+    p = lambda t, off=0: C.c_void_p(t.data_ptr() + off)
+    rc = sfg.load().edges_to_csr(n, E, p(s), p(d), 4, 0, p(rp), p(col), p(buf, 8), p(buf, 8 * 35), p(ws), ws.numel(),
+                                 C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    _, hist = orc.degree_histogram(n, src, dst)
+    _, _, dups = orc.edges_to_csr(n, src, dst)
+    np.testing.assert_array_equal(got[1:33].astype(np.uint64), hist)
+    assert got[35] == dups and got[0] == -1 and (got[33:35] == -1).all() and (got[36:] == -1).all()
