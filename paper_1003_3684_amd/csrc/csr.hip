@@ -41,6 +41,14 @@ namespace {
 constexpr int kPassThreads = 1024;
 constexpr int kPassItems = 8;
 constexpr int kPassTile = kPassThreads * kPassItems;  // keys per onesweep tile
+// A list of at most kShortTiles tiles of kShortItems keys per thread is sorted
+// in those: a pass over a few tiles takes as long as one tile, and a tile of two
+// keys per thread is ranked in a quarter of the steps.  The build in us with 8
+// and with 2 keys per thread: 52.8 / 41.1 for 8,192 entries, 63.9 / 61.2 for
+// 65,536, 77.6 / 76.0 for 262,144, 90.2 / 91.2 for 524,288, where the look-back
+// over four times the tiles costs what the ranking saves.
+constexpr int kShortItems = 2;
+constexpr uint64_t kShortTiles = 64;
 constexpr int kPassWaves = kPassThreads / 64;
 constexpr int kRadix = 256;
 constexpr int kLookWindow = 2;  // predecessors read per lane and look-back round trip
@@ -237,11 +245,13 @@ __device__ __forceinline__ uint64_t unpack_id(KeyT packed, const uint32_t *dec, 
 // run follows an entry of another tile (or of another digit's bucket); the
 // run's first and last keys go to the run records, and csr_run_starts
 // settles those entries once every tile is done.
-template <typename IdT, typename KeyT, bool SYM, bool FIRST, bool BOUND, bool FINAL = false>
-__global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassArgs a) {
+template <typename IdT, typename KeyT, bool SYM, bool FIRST, bool BOUND, bool FINAL, bool SHORT>
+__global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix_pass(PassArgs a) {
+    constexpr int kItems = SHORT ? kShortItems : kPassItems, kTile = kPassThreads * kItems;
     // s_keys holds the tile's keys in digit order after ranking; during the
     // ranking its first 32 KB serve as the per-wave lane-match tables.
-    __shared__ KeyT s_keys[kPassTile];
+    constexpr size_t kMatchBytes = sizeof(uint64_t) * kPassWaves * kRadix;
+    __shared__ __align__(16) KeyT s_keys[kTile * sizeof(KeyT) > kMatchBytes ? kTile : kMatchBytes / sizeof(KeyT)];
     // 16-bit per-wave digit counters (8 KB); with the 64 KB key tile the block takes about 77 KB of LDS
     // (8-byte keys): two workgroups per CU.
     __shared__ uint16_t s_cnt[kPassWaves][kRadix];
@@ -251,7 +261,6 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     __shared__ uint64_t s_tmp[4];
     // FINAL over packed ids: the byte -> digit-group table, read once per key.
     __shared__ uint32_t s_dec[FINAL ? kRadix : 1];
-    static_assert(sizeof(KeyT) * kPassTile >= sizeof(uint64_t) * kPassWaves * kRadix, "match tables do not fit");
     static_assert(kPassThreads % kRadix == 0 && 64 % kLanesPerDigit == 0, "look-back lane groups");
     uint64_t *s_match = reinterpret_cast<uint64_t *>(s_keys) + 0;  // [kPassWaves][256]
 
@@ -268,16 +277,16 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     // calls on one device.  (A ticket counter would serialise the tiles on
     // one device-coherent atomic.)
     const uint64_t tile = blockIdx.x;
-    const uint64_t tile_base = tile * kPassTile;
-    const uint64_t wbase = tile_base + (uint64_t)w * 64 * kPassItems;
-    const bool full = tile_base + kPassTile <= a.N;
+    const uint64_t tile_base = tile * kTile;
+    const uint64_t wbase = tile_base + (uint64_t)w * 64 * kItems;
+    const bool full = tile_base + kTile <= a.N;
 
     // The keys' loads go out first; the LDS counters are cleared while they
     // travel.
-    KeyT k[kPassItems];
-    uint32_t d[kPassItems];
+    KeyT k[kItems];
+    uint32_t d[kItems];
 #pragma unroll
-    for (int i = 0; i < kPassItems; ++i) {
+    for (int i = 0; i < kItems; ++i) {
         const uint64_t idx = wbase + (uint64_t)i * 64 + lane;
         const bool valid = full || idx < a.N;
         if (FIRST)
@@ -306,7 +315,7 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
         }
     }
 #pragma unroll
-    for (int i = 0; i < kPassItems; ++i) {
+    for (int i = 0; i < kItems; ++i) {
         const uint64_t idx = wbase + (uint64_t)i * 64 + lane;
         d[i] = (full || idx < a.N) ? (uint32_t)(k[i] >> a.shift) & 255u : (uint32_t)kRadix;
     }
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
         const KeyT *in = static_cast<const KeyT *>(a.in);
         KeyT carry = (wbase > 0 && wbase <= a.N) ? in[wbase - 1] : (KeyT)0;
 #pragma unroll
-        for (int i = 0; i < kPassItems; ++i) {
+        for (int i = 0; i < kItems; ++i) {
             const uint64_t idx = wbase + (uint64_t)i * 64 + lane;
             KeyT prev = __shfl_up(k[i], 1, 64);
             if (lane == 0) prev = carry;
@@ -337,12 +346,12 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     // is exact).  Lanes below this one in the mask come first; the lowest
     // lane of each digit advances the wave's counter and clears the slot.
     // LDS operations of one wave complete in program order.
-    uint32_t r[kPassItems];
+    uint32_t r[kItems];
     uint64_t *match = s_match + w * kRadix;
     uint16_t *wcnt = s_cnt[w];
     const uint64_t my_bit = 1ull << lane;
 #pragma unroll
-    for (int i = 0; i < kPassItems; ++i) {
+    for (int i = 0; i < kItems; ++i) {
         const uint32_t di = d[i];
         const bool valid = di < kRadix;
         const uint32_t slot = valid ? di : 0;
@@ -400,7 +409,7 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
     // Scatter into LDS in digit order (the local order needs no global
     // offsets, and the keys leave the registers before the look-back).
 #pragma unroll
-    for (int i = 0; i < kPassItems; ++i)
+    for (int i = 0; i < kItems; ++i)
         if (d[i] < kRadix) s_keys[s_off[d[i]] + s_cnt[w][d[i]] + r[i]] = k[i];
 
     uint64_t prefix = tile == 0 && part == 0 ? s_gpos[dg] : 0;
@@ -459,7 +468,7 @@ __global__ __launch_bounds__(kPassThreads, BOUND ? 6 : 8) void radix_pass(PassAr
 
     // Write the digit runs out, coalesced.
     const uint64_t rem = a.N - tile_base;
-    const uint32_t nvalid = rem < (uint64_t)kPassTile ? (uint32_t)rem : (uint32_t)kPassTile;
+    const uint32_t nvalid = rem < (uint64_t)kTile ? (uint32_t)rem : (uint32_t)kTile;
     if (FINAL) {
         IdT *col = static_cast<IdT *>(a.col);
         KeyT *rfirst = static_cast<KeyT *>(a.run_first) + tile * kRadix;
@@ -537,7 +546,7 @@ struct RunArgs {
 
 // Tiles per workgroup of csr_run_starts: 16, whose counts then roll along,
 // where that gives every CU a workgroup, else 4 (the passes' tiles are walked
-// one memory latency after the other: 16.4 us for 64 tiles, RUNS_FIGURES).
+// one memory latency after the other: 16.4 us for 64 tiles, 9.7 with 4 per workgroup).
 constexpr int kRunTiles = 16;
 
 // The FINAL pass has ended, so its look-back words are read with ordinary
@@ -1024,7 +1033,7 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
     // Thread t owns rows t*per .. t*per+per-1 of the chunk; the results go
     // through LDS (one pad word per `per`) so the stores are coalesced.
     __shared__ uint64_t s_out[kScanChunk + kScanChunk / per];
-    __shared__ uint64_t s[256];
+    __shared__ uint64_t s_wave[4];
     __shared__ uint32_t s_h[32];
     __shared__ uint32_t s_first;
     const int tid = threadIdx.x;
@@ -1048,15 +1057,16 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
         }
         // the first marked value after the chunk
         const uint64_t next = SELF ? marked_from(a, c0 + kScanChunk, n1, &s_first) : a.cmin[blockIdx.x];
-        s[tid] = m;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            uint64_t o = tid + off < 256 ? s[tid + off] : kNoRow;
-            __syncthreads();
-            s[tid] = min(s[tid], o);
-            __syncthreads();
+        // minimum over the rows of the threads after this one
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint64_t o = __shfl_down(m, off, 64);
+            if (lane + off < 64) m = min(m, o);
         }
-        uint64_t run = min(next, tid + 1 < 256 ? s[tid + 1] : kNoRow);
+        if (lane == 0) s_wave[tid >> 6] = m;
+        __syncthreads();
+        const uint64_t after = __shfl_down(m, 1, 64);
+        uint64_t run = min(next, lane < 63 ? after : kNoRow);
+        for (int w = (tid >> 6) + 1; w < 4; ++w) run = min(run, s_wave[w]);
 #pragma unroll
         for (int j = per - 1; j >= 0; --j) {
             run = min(run, x[j]);
@@ -1072,7 +1082,7 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
             if (HIST && a.degree && v + 1 < n1)  // the row after the chunk's last holds `next` once filled
                 deg[j] += (i + 1 < kScanChunk ? s_out[((i + 1) / per) * (per + 1) + (i + 1) % per] : next) - a0;
         }
-        __syncthreads();  // s and s_out are rewritten for the next array
+        __syncthreads();  // s_wave and s_out are rewritten for the next array
     }
     if (HIST) {
 #pragma unroll
@@ -1125,6 +1135,7 @@ struct Plan {
     bool fused_finish;  // the last pass writes the CSR (FINAL) instead of keys
     int tb;
     uint64_t split;
+    bool short_tiles;  // digit passes over tiles of kShortItems keys per thread
     uint64_t pass_tiles, fin_tiles, chunks;
     // workspace carving
     size_t off_keysA, off_keysB, off_status, off_ghist, off_gbase, off_indeg, off_rpraw, off_mark,
@@ -1160,7 +1171,9 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.kb = p.wb + p.db + p.tb;
     p.passes = (p.kb + 7) / 8;
     p.key_bytes = p.kb <= 32 ? 4 : 8;
-    p.pass_tiles = (p.N + kPassTile - 1) / kPassTile;
+    constexpr uint64_t short_tile = kPassThreads * kShortItems;
+    p.short_tiles = p.N <= kShortTiles * short_tile;
+    p.pass_tiles = p.short_tiles ? (p.N + short_tile - 1) / short_tile : (p.N + kPassTile - 1) / kPassTile;
     p.fin_tiles = (p.N + kFinTile - 1) / kFinTile;
     // Without SIMPLE no entry is dropped, so sorted positions are output
     // positions and the last pass can write the columns itself -- unless it
@@ -1180,7 +1193,7 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.off_keysB = take(p.N * p.key_bytes);
     p.off_status = take(std::max<uint64_t>(p.pass_tiles, 1) * kRadix * 8);
     p.off_ghist = take(8 * kRadix * 8);
-    p.off_gbase = take(8 * kRadix * 8);
+    p.off_gbase = take(kRadix * 8);
     p.off_indeg = take(p.directed_hist ? (n + 1) * 8 : 0);
     p.off_rpraw = take(want_hist && p.simple ? (n + 1) * 8 : 0);
     p.off_mark = take(n + 1);
@@ -1223,7 +1236,10 @@ __global__ __launch_bounds__(256) void csr_clear(ClearArgs a) {
         const uint64_t at = a.r[q].one;  // (~0 / 16 is no word of any region)
         for (uint64_t i = i0; i < a.r[q].words; i += stride) {
             uint4 z = {0, 0, 0, 0};
-            if (i == at / 16) reinterpret_cast<uint8_t *>(&z)[at % 16] = 1;
+            if (i == at / 16) {
+                const uint32_t w = (uint32_t)(at / 4) % 4, x = 1u << (8 * (uint32_t)(at % 4));
+                z = {w == 0 ? x : 0, w == 1 ? x : 0, w == 2 ? x : 0, w == 3 ? x : 0};
+            }
             a.r[q].p[i] = z;
         }
     }
@@ -1296,6 +1312,15 @@ void clear_csr(const Plan &P, uint64_t *row_ptr, uint64_t *hist, uint64_t *dups,
     csr_clear<<<fill_grid(words), 256, 0, s>>>(c);
 }
 
+template <typename IdT, typename KeyT, bool SYM, bool FIRST, bool BOUND, bool FINAL>
+void launch_pass(const PassArgs &a, int grid, bool short_tiles, hipStream_t s) {
+    ProfScope _ps("radix_pass", s);
+    if (short_tiles)
+        radix_pass<IdT, KeyT, SYM, FIRST, BOUND, FINAL, true><<<grid, kPassThreads, 0, s>>>(a);
+    else
+        radix_pass<IdT, KeyT, SYM, FIRST, BOUND, FINAL, false><<<grid, kPassThreads, 0, s>>>(a);
+}
+
 template <typename IdT, typename KeyT>
 int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, void *col, uint64_t *hist,
             uint64_t *dups, char *ws, hipStream_t s, bool counted = false, bool keys_given = false,
@@ -1347,16 +1372,16 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
                     a.dec_groups = up->groups;
                     a.dec_bits = up->bits;
                 }
-                { ProfScope _ps("radix_pass", s); radix_pass<IdT, KeyT, false, false, false, true><<<g, kPassThreads, 0, s>>>(a); }
+                launch_pass<IdT, KeyT, false, false, false, true>(a, g, P.short_tiles, s);
             } else if (csc && p == P.dpasses) {
-                { ProfScope _ps("radix_pass", s); radix_pass<IdT, KeyT, false, false, true><<<g, kPassThreads, 0, s>>>(a); }
+                launch_pass<IdT, KeyT, false, false, true, false>(a, g, P.short_tiles, s);
             } else if (p == 0 && !keys_given) {
                 if (P.sym)
-                    { ProfScope _ps("radix_pass", s); radix_pass<IdT, KeyT, true, true, false><<<g, kPassThreads, 0, s>>>(a); }
+                    launch_pass<IdT, KeyT, true, true, false, false>(a, g, P.short_tiles, s);
                 else
-                    { ProfScope _ps("radix_pass", s); radix_pass<IdT, KeyT, false, true, false><<<g, kPassThreads, 0, s>>>(a); }
+                    launch_pass<IdT, KeyT, false, true, false, false>(a, g, P.short_tiles, s);
             } else {
-                { ProfScope _ps("radix_pass", s); radix_pass<IdT, KeyT, false, false, false><<<g, kPassThreads, 0, s>>>(a); }
+                launch_pass<IdT, KeyT, false, false, false, false>(a, g, P.short_tiles, s);
             }
         }
         FinArgs fa{P.N, P.n, keysA, col, row_ptr, P.simple ? rp_raw_ws : nullptr, mark, dups, fstatus,
@@ -1752,7 +1777,10 @@ extern "C" int edges_to_csr(uint64_t n, uint64_t num_edges, const void *src, con
 namespace sfg {
 namespace {
 constexpr size_t kNoAllocScratch = 64ull << 20;
-__device__ __align__(256) unsigned char scratch[kNoAllocScratch];
+// Room beside it for the look-back words that a list sorted in short tiles has
+// more of, so that the limit is the same for it.
+constexpr size_t kShortExtra = kShortTiles * kRadix * 8;
+__device__ __align__(256) unsigned char scratch[kNoAllocScratch + kShortExtra];
 
 char *noalloc_scratch() {
     static constexpr int kMaxDevs = 64;
@@ -1778,7 +1806,9 @@ extern "C" int edges_to_csr_noalloc(uint64_t n, uint64_t num_edges, const void *
                                     uint64_t *num_duplicates, void *stream) {
     if (n > 0 && (id_bytes == 4 || id_bytes == 8)) {
         const size_t need = sfg::csr_workspace_bytes(n, num_edges, id_bytes, flags);
-        if (need > sfg::kNoAllocScratch)
+        const bool fits_short = num_edges <= sfg::kShortTiles * sfg::kPassThreads * sfg::kShortItems &&
+                                need <= sfg::kNoAllocScratch + sfg::kShortExtra;
+        if (need > sfg::kNoAllocScratch && !fits_short)
             return fail(SFG_ERANGE,
                         "edges_to_csr_noalloc: %llu vertices and %llu edges need %zu scratch bytes, more than the "
                         "%zu of the static scratch array",
@@ -1787,5 +1817,5 @@ extern "C" int edges_to_csr_noalloc(uint64_t n, uint64_t num_edges, const void *
     char *ws = sfg::noalloc_scratch();
     if (!ws) return fail(SFG_EDEVICE, "edges_to_csr_noalloc: scratch address lookup failed");
     return csr_build(n, num_edges, src, dst, id_bytes, flags, row_ptr, col, degree_hist32, num_duplicates, ws,
-                     sfg::kNoAllocScratch, as_stream(stream), nullptr);
+                     sfg::kNoAllocScratch + sfg::kShortExtra, as_stream(stream), nullptr);
 }

@@ -171,3 +171,13 @@ def test_csr_histogram_pointer_of_8_byte_alignment(sfg, orc):
     _, _, dups = orc.edges_to_csr(n, src, dst)
     np.testing.assert_array_equal(got[1:33].astype(np.uint64), hist)
     assert got[35] == dups and got[0] == -1 and (got[33:35] == -1).all() and (got[36:] == -1).all()
+
+
+@pytest.mark.parametrize("id_bytes,n", [(4, 3_000), (8, 300_000)])
+@pytest.mark.parametrize("E", [2047, 2048, 2049, 64 * 2048, 64 * 2048 + 1])
+def test_csr_short_tiles(sfg, orc, E, id_bytes, n):
+    """Directed lists around the short tiles' edges and around the longest
+    list sorted in them, with 4- and 8-byte keys."""
+    rng = np.random.default_rng(E)
+    src = np.minimum(rng.zipf(1.6, size=E) - 1, n - 1)
+    _check(sfg, orc, n, src, rng.integers(0, n, size=E), 0, id_bytes)
