@@ -36,12 +36,24 @@ int csr_build(uint64_t n, uint64_t num_edges, const void *src, const void *dst, 
               uint64_t *row_ptr, void *col, uint64_t *degree_hist32, uint64_t *num_duplicates, void *workspace,
               size_t workspace_bytes, hipStream_t s, const uint64_t **raw_rows);
 
-// CSR of the symmetric difference of two edge sets: entries [0, split) are the
-// first graph (distinct pairs), entries [split, num_entries) the second (pairs
-// may repeat); a pair is kept once when it is in exactly one of them.
-size_t csr_xor_workspace_bytes(uint64_t n, uint64_t num_entries);
-int csr_xor_build(uint64_t n, uint64_t num_entries, uint64_t split, const void *src, const void *dst, int id_bytes,
-                  uint64_t *row_ptr, void *col, void *workspace, size_t workspace_bytes, hipStream_t s);
+// CSR of a Kronecker power XOR a random graph of `num_random` pairs, which may
+// repeat: a pair is kept once when it is in exactly one of the two.
+// csr_xor_begin clears the workspace and says where the caller writes the pairs'
+// sort keys, (row << shift) | column, and adds the counts of their bytes
+// (hist[256 p + byte p], p < passes); csr_xor_finish sorts them and merges
+// the power's entries in.
+struct Power;
+struct PowerSeed;
+struct XorKeys {
+    void *keys;  // num_random of key_bytes (4 or 8) each
+    uint64_t *hist;
+    int key_bytes, shift, passes;
+};
+size_t csr_xor_workspace_bytes(uint64_t n, uint64_t num_random, uint64_t num_power);
+int csr_xor_begin(uint64_t n, uint64_t num_random, Power *power, const PowerSeed &seed, uint64_t *row_ptr, void *workspace,
+                  size_t workspace_bytes, hipStream_t s, XorKeys *keys);
+int csr_xor_finish(uint64_t n, uint64_t num_random, const Power &power, int id_bytes, uint64_t *row_ptr, void *col,
+                   void *workspace, hipStream_t s);
 
 // Counter-word tags of the Philox streams.
 enum : uint32_t { TAG_KRON = 1, TAG_PBA1 = 2, TAG_PBA2 = 3, TAG_WEDGE = 4 };

@@ -34,6 +34,7 @@
 
 #include "common.hpp"
 #include "kron.hpp"
+#include "power.hpp"
 
 namespace sfg {
 namespace {
@@ -54,9 +55,20 @@ constexpr int kRadix = 256;
 constexpr int kLookWindow = 2;  // predecessors read per lane and look-back round trip
 constexpr int kLanesPerDigit = kPassThreads / kRadix;  // look-back lanes per digit
 
-constexpr int kFinThreads = 256;
-constexpr int kFinItems = 12;  // 3,072-entry finish tiles: six workgroups per CU with 8-byte keys
-constexpr int kFinTile = kFinThreads * kFinItems;
+constexpr int kPlainThreads = 256;
+
+// Threads of a finish workgroup and keys of a thread.  Every tile's look-back
+// reads the words of the tiles in flight before it, past the caches, so the
+// words read are the tiles times the tiles in flight and a larger tile saves
+// both ways; two workgroups have to fit a CU's 160 KB of LDS all the same.
+// csr_finish in us at 256 threads x 12 keys / 512 x 12 / 1024 x 6 / 1024 x 8 /
+// 1024 x 9 / 1024 x 12: 333 / 277 / 283 / 269 / 286 / 333 for 6.6e7 8-byte keys
+// (SIMPLE); 15.1 / 14.4 / 12.9 / 12.8 / 14.7 / 16.2 for 524,288.  XOR of 2.1e8
+// and 1e8 entries at 256 x 12 / 512 x 8 / 512 x 12 / 512 x 16 / 1024 x 8: 3,670 /
+// 3,850 / 3,302 / 2,962 / 3,618.
+constexpr int kFinThreads = 1024, kFinItems = 8;  // SIMPLE: two workgroups per CU with 8-byte keys
+constexpr int kXorThreads = 512, kXorItems = 16;  // XOR: twice the registers per thread, and a walk's start shared by more entries
+constexpr int fin_tile(bool xor_mode) { return xor_mode ? kXorThreads * kXorItems : kFinThreads * kFinItems; }
 
 constexpr int kScanChunk = 4096;  // vertices per chunk of the row fill scan
 constexpr int kPrepUnroll = 4;    // keys per thread in flight in the histogram pass
@@ -103,6 +115,30 @@ __device__ uint64_t block_exclusive_scan_256(uint64_t v, uint64_t *s_tmp /*[4]*/
     return base + x - (tid < 256 ? v : 0);
 }
 
+// Exclusive prefix of v over the THREADS threads of a block, *total their sum.
+// All threads of the block must call it; s_tmp may be used again after.
+template <int THREADS> __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s_tmp /*[THREADS / 64]*/, uint32_t *total) {
+    const uint32_t lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6;
+    uint32_t x = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(x, off, 64);
+        if (lane >= (uint32_t)off) x += y;
+    }
+    if (lane == 63) s_tmp[w] = x;
+    __syncthreads();
+    uint32_t base = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < THREADS / 64; ++i) {
+        if (i < w) base += s_tmp[i];
+        tot += s_tmp[i];
+    }
+    __syncthreads();
+    *total = tot;
+    return base + x - v;
+}
+
 // (u << wb) | v, with v cut to wb bits: an id outside [0, 2^wb) then changes
 // only its own field, so the key digits always agree with what the histogram
 // pass counts (whichever way it counts them) and no pass writes out of range.
@@ -119,23 +155,12 @@ __device__ __forceinline__ KeyT entry_key(const IdT *src, const IdT *dst, uint64
     return pack<IdT, KeyT>(dst[j], src[j], wb);
 }
 
-// Key of entry idx with tb origin bits below it: entries at or after `split`
-// come from the second graph (origin 1).
-template <typename IdT, typename KeyT, bool SYM>
-__device__ __forceinline__ KeyT tagged_key(const IdT *src, const IdT *dst, uint64_t E, uint64_t idx, int wb, int tb,
-                                           uint64_t split) {
-    const KeyT k = entry_key<IdT, KeyT, SYM>(src, dst, E, idx, wb);
-    return tb ? (KeyT)((k << 1) | (KeyT)(idx >= split ? 1u : 0u)) : k;
-}
-
 // --------------------------------------------------------------------------- prepare
 struct PrepArgs {
     uint64_t E, N;
     const void *src, *dst;
     uint64_t *ghist;   // [passes][256]
     int wb, passes;    // wb: width of the destination field
-    int tb;            // origin bits below the entry (XOR mode)
-    uint64_t split;    // first entry of origin 1
     int dbytes;        // SYM with a whole-byte destination field: its bytes, else 0
 };
 
@@ -176,8 +201,7 @@ __global__ __launch_bounds__(256) void csr_prepare(PrepArgs a) {
                 }
                 continue;
             }
-            KeyT k = pack<IdT, KeyT>(su[u], du[u], a.wb);
-            if (a.tb) k = (KeyT)((k << 1) | (KeyT)(i >= a.split ? 1u : 0u));
+            const KeyT k = pack<IdT, KeyT>(su[u], du[u], a.wb);
             for (int p = 0; p < a.passes; ++p)
                 atomicAdd(&s_h[(p * kRadix + (uint32_t)((k >> (8 * p)) & 255)) * kPrepCopies + copy], 1u);
             if (SYM) {
@@ -213,8 +237,6 @@ struct PassArgs {
     uint8_t *cmark;         // 1 where a column start was written (BOUND passes only)
     int wb, shift;          // wb: width of the destination field
     uint32_t tag;
-    int tb;                 // origin bits below the entry (first pass, XOR mode)
-    uint64_t split;         // first entry of origin 1
     uint64_t nv;            // vertices (BOUND passes write column starts below it)
     // FINAL pass only: the CSR outputs and the run records (see radix_pass).
     void *col;
@@ -290,8 +312,8 @@ __global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix
         const uint64_t idx = wbase + (uint64_t)i * 64 + lane;
         const bool valid = full || idx < a.N;
         if (FIRST)
-            k[i] = valid ? tagged_key<IdT, KeyT, SYM>(static_cast<const IdT *>(a.src), static_cast<const IdT *>(a.dst),
-                                                       a.E, idx, a.wb, a.tb, a.split)
+            k[i] = valid ? entry_key<IdT, KeyT, SYM>(static_cast<const IdT *>(a.src), static_cast<const IdT *>(a.dst),
+                                                      a.E, idx, a.wb)
                          : (KeyT)0;
         else
             k[i] = valid ? static_cast<const KeyT *>(a.in)[idx] : (KeyT)0;
@@ -674,6 +696,11 @@ struct FinArgs {
     uint64_t *status;   // [tiles] look-back words (SIMPLE)
     uint32_t *err;
     int wb;
+    // XOR: `keys` are the random graph's `random` sorted pairs; N counts them
+    // and the power's entries together.  split[t]: how many of the random pairs
+    // come before merged position t kFinTile.
+    uint64_t random;
+    const uint64_t *split;
 };
 
 __device__ __forceinline__ int fin_slot(int i) { return i + (i >> 4); }
@@ -682,16 +709,16 @@ __device__ __forceinline__ int fin_slot(int i) { return i + (i >> 4); }
 // owns positions base + j*256 + t; the key before position idx comes from the
 // previous lane (or, for lane 0, from memory).
 template <typename IdT, typename KeyT>
-__global__ __launch_bounds__(kFinThreads) void csr_finish_plain(FinArgs a) {
-    __shared__ uint32_t s_dups[kFinThreads / 64];
+__global__ __launch_bounds__(kPlainThreads) void csr_finish_plain(FinArgs a) {
+    __shared__ uint32_t s_dups[kPlainThreads / 64];
     const int tid = threadIdx.x;
     const uint32_t lane = tid & 63;
     const KeyT *K = static_cast<const KeyT *>(a.keys);
     IdT *col = static_cast<IdT *>(a.col);
     const KeyT mask = ((KeyT)1 << a.wb) - 1;
     uint32_t ndup = 0;
-    const uint64_t stride = (uint64_t)gridDim.x * kFinThreads;
-    for (uint64_t idx = (uint64_t)blockIdx.x * kFinThreads + tid; idx - lane < a.N; idx += stride) {
+    const uint64_t stride = (uint64_t)gridDim.x * kPlainThreads;
+    for (uint64_t idx = (uint64_t)blockIdx.x * kPlainThreads + tid; idx - lane < a.N; idx += stride) {
         const bool valid = idx < a.N;
         const KeyT key = valid ? K[idx] : (KeyT)0;
         KeyT prev = __shfl_up(key, 1, 64);
@@ -719,53 +746,181 @@ __global__ __launch_bounds__(kFinThreads) void csr_finish_plain(FinArgs a) {
         __syncthreads();
         if (tid == 0) {
             uint32_t t = 0;
-            for (int i = 0; i < kFinThreads / 64; ++i) t += s_dups[i];
+            for (int i = 0; i < kPlainThreads / 64; ++i) t += s_dups[i];
             if (t) atomicAdd((unsigned long long *)a.dups, (unsigned long long)t);
         }
     }
 }
 
+// The merged position of sorted random pair j: a power entry precedes the
+// random pairs equal to it.
+template <typename KeyT>
+__device__ __forceinline__ uint64_t merged_position(const Power &p, const CountTables &t, const KeyT *R, uint64_t j, int wb) {
+    const uint64_t key = R[j];
+    return j + power_count(p.c, t, (uint32_t)(key >> wb), (uint32_t)(key & ((1ull << wb) - 1)));
+}
+
+// split[t] for every tile boundary t = 0 .. tiles, by binary search.
+template <typename KeyT>
+__global__ __launch_bounds__(256) void xor_split(Power p, const KeyT *R, uint64_t random, uint64_t N, uint64_t tiles, int wb,
+                                                 uint64_t *split) {
+    __shared__ CountTables s_t;
+    power_load(p, &s_t);
+    __syncthreads();
+    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t > tiles) return;
+    const uint64_t d = min(t * fin_tile(true), N);
+    uint64_t lo = d > p.entries ? d - p.entries : 0, hi = min(d, random);
+    while (lo < hi) {
+        const uint64_t mid = lo + (hi - lo) / 2;
+        if (merged_position(p, s_t, R, mid, wb) < d)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    split[t] = lo;
+}
+
 // Compacting finish.  SIMPLE (XOR = false): keep the first of every run of
-// equal entries unless it is a self-loop.  XOR: the keys carry an origin bit
-// below the entry (0 = first graph, whose entries are distinct; 1 = second
-// graph, whose entries may repeat), so the first graph's copy of a pair sorts
-// first; keep one copy of a pair present in exactly one of the two graphs.
+// equal entries unless it is a self-loop.  XOR: the sequence is the merge of a
+// Kronecker power, whose entries are computed where they are needed (power.hpp),
+// with the sorted pairs of a random graph, which may repeat; an origin bit below
+// the entry (0 = power) puts the power's copy of a pair first; keep one copy of
+// a pair present in exactly one of the two graphs.
 // Output positions come from a look-back scan of the kept counts.
-template <typename IdT, typename KeyT, bool XOR>
-__global__ __launch_bounds__(kFinThreads) void csr_finish(FinArgs a) {
+// (XOR) Only the random pairs are sorted and read.  With the power's entries
+// written as keys, sorted and read back as well, a graph of 2.1e8 + 1e8 entries
+// took 13.5 ms, 10.4 of it in preparing, sorting and finishing 3.1e8 keys;
+// merged, 8.1 ms: sort 2.3, this kernel 3.0 (bound by the walk's arithmetic and
+// the look-back; it moves 1.7 GB, 0.35 ms at the rate of a copy).
+template <typename IdT, typename RawT, bool XOR>
+__global__ __launch_bounds__(XOR ? kXorThreads : kFinThreads, XOR ? 4 : 8) void csr_finish(FinArgs a, typename std::conditional<XOR, Power, int>::type p_) {
+    constexpr int kThreads = XOR ? kXorThreads : kFinThreads, kItems = XOR ? kXorItems : kFinItems, kTile = fin_tile(XOR);
     constexpr int TB = XOR ? 1 : 0;  // origin bits below the entry
-    // Blocked reads (kFinItems consecutive keys per thread) would hit few LDS
+    using KeyT = typename std::conditional<XOR, uint64_t, RawT>::type;
+    // Blocked reads (kItems consecutive keys per thread) would hit few LDS
     // banks across the wave; one pad slot per 16 keys spreads them.  Slot 0 holds
     // the key before the tile, the last slot the key after it.
     // The same LDS later holds the tile's kept columns in output order, so
     // the column stores are coalesced; it is sized for 8-byte elements.
-    constexpr size_t kKeyBytes = (kFinTile + kFinTile / 16 + 2) * sizeof(KeyT);
-    constexpr size_t kColBytes = kFinTile * sizeof(IdT);
+    constexpr size_t kKeyBytes = (kTile + kTile / 16 + 2) * sizeof(KeyT);
+    constexpr size_t kColBytes = kTile * sizeof(IdT);
     __shared__ uint64_t s_raw[((kKeyBytes > kColBytes ? kKeyBytes : kColBytes) + 7) / 8];
     KeyT *s_keys = reinterpret_cast<KeyT *>(s_raw);
     IdT *s_col = reinterpret_cast<IdT *>(s_raw);
-    __shared__ uint64_t s_tmp[4];
+    __shared__ uint32_t s_tmp[kThreads / 64];
     __shared__ uint64_t s_base;
-    __shared__ uint32_t s_dups[kFinThreads / 64];
+    __shared__ uint32_t s_dups[kThreads / 64];
     const int tid = threadIdx.x;
     const uint64_t tile = blockIdx.x;  // dispatch order (see radix_pass)
-    const uint64_t t0 = tile * kFinTile;
-    const KeyT *K = static_cast<const KeyT *>(a.keys);
-    for (int i = tid; i < kFinTile; i += kFinThreads) {
-        const uint64_t idx = t0 + i;
-        s_keys[fin_slot(i + 1)] = idx < a.N ? K[idx] : (KeyT)0;
-    }
-    if (tid == 0) {
-        s_keys[0] = t0 > 0 ? K[t0 - 1] : (KeyT)0;
-        s_keys[fin_slot(kFinTile + 1)] = t0 + kFinTile < a.N ? K[t0 + kFinTile] : (KeyT)0;
+    const uint64_t t0 = tile * kTile;
+    if constexpr (XOR) {
+        __shared__ CountTables s_ct;
+        __shared__ uint32_t s_taken[(kTile + 31) / 32 + 1];  // positions that hold a random pair
+        const Power &pw = p_;
+        const RawT *R = static_cast<const RawT *>(a.keys);
+        power_load(pw, &s_ct);
+        for (int i = tid; i < (kTile + 31) / 32 + 1; i += kThreads) s_taken[i] = 0;
+        const uint64_t j0 = a.split[tile], j1 = a.split[tile + 1];
+        __syncthreads();
+        const uint64_t idmask = (1ull << a.wb) - 1;
+        auto count_of = [&](uint64_t key) { return power_count(pw.c, s_ct, (uint32_t)(key >> a.wb), (uint32_t)(key & idmask)); };
+        auto pack_at = [&](const PowerWalk &w) { return (((uint64_t)w.u << a.wb) | (w.high + *w.low)) << 1; };
+        for (uint64_t jb = j0; jb < j1; jb += 4 * kThreads) {  // (the loads of a round go out together)
+            uint64_t key[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint64_t j = jb + i * kThreads + tid;
+                key[i] = R[j < j1 ? j : j1 - 1];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint64_t j = jb + i * kThreads + tid;
+                if (j >= j1) break;
+                const uint32_t x = (uint32_t)(j + count_of(key[i]) - t0);
+                s_keys[fin_slot(x + 1)] = (key[i] << 1) | 1u;
+                atomicOr(&s_taken[x / 32], 1u << (x % 32));
+            }
+        }
+        // The neighbours of the tile: either the random pair or the power
+        // entry next to it.
+        if (tid == 0) {
+            uint64_t v = 0;
+            if (t0 > 0) {
+                const uint64_t g0 = t0 - j0;  // power entries before the tile
+                const uint64_t key = j0 > 0 ? (uint64_t)R[j0 - 1] : 0;
+                if (j0 > 0 && j0 - 1 + count_of(key) == t0 - 1) {
+                    v = (key << 1) | 1u;
+                } else {
+                    PowerWalk w;
+                    w.seek(pw.w, *pw.tables, g0 - 1);
+                    v = pack_at(w);
+                }
+            }
+            s_keys[0] = v;
+        }
+        if (tid == 64) {
+            uint64_t v = 0;
+            const uint64_t t1 = t0 + kTile;
+            if (t1 < a.N) {
+                const uint64_t key = j1 < a.random ? (uint64_t)R[j1] : 0;
+                if (j1 < a.random && j1 + count_of(key) == t1) {
+                    v = (key << 1) | 1u;
+                } else {
+                    PowerWalk w;
+                    w.seek(pw.w, *pw.tables, t1 - j1);
+                    v = pack_at(w);
+                }
+            }
+            s_keys[fin_slot(kTile + 1)] = v;
+        }
+        __syncthreads();
+        // The power's entries take the other positions in order.
+        const int p0 = tid * kItems;
+        const uint64_t two = (uint64_t)s_taken[p0 / 32] | ((uint64_t)s_taken[p0 / 32 + 1] << 32);
+        const uint32_t taken = (uint32_t)(two >> (p0 % 32)) & ((1u << kItems) - 1);
+        uint32_t all;
+        const uint32_t before = block_exclusive_scan<kThreads>((uint32_t)__popc(taken), s_tmp, &all);
+        uint64_t g = t0 - j0 + p0 - before;
+        PowerWalk w;
+        bool at = false;
+        uint64_t row[kItems];
+        uint32_t high[kItems], low[kItems];  // (the loads of all items go out together)
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) {
+            row[j] = high[j] = low[j] = 0;
+            if (((taken >> j) & 1u) || t0 + p0 + j >= a.N) continue;
+            if (at)
+                w.next(pw.w, *pw.tables, g);
+            else
+                w.seek(pw.w, *pw.tables, g);
+            at = true;
+            ++g;
+            row[j] = w.u;
+            high[j] = w.high;
+            low[j] = *w.low;
+        }
+#pragma unroll
+        for (int j = 0; j < kItems; ++j)
+            if (!((taken >> j) & 1u)) s_keys[fin_slot(p0 + j + 1)] = ((row[j] << a.wb) | (high[j] + low[j])) << 1;
+    } else {
+        const KeyT *K = static_cast<const KeyT *>(a.keys);
+        for (int i = tid; i < kTile; i += kThreads) {
+            const uint64_t idx = t0 + i;
+            s_keys[fin_slot(i + 1)] = idx < a.N ? K[idx] : (KeyT)0;
+        }
+        if (tid == 0) {
+            s_keys[0] = t0 > 0 ? K[t0 - 1] : (KeyT)0;
+            s_keys[fin_slot(kTile + 1)] = t0 + kTile < a.N ? K[t0 + kTile] : (KeyT)0;
+        }
     }
     __syncthreads();
     const KeyT mask = ((KeyT)1 << a.wb) - 1;
-    // Blocked view: thread t owns positions t*kFinItems .. (t+1)*kFinItems-1.
+    // Blocked view: thread t owns positions t*kItems .. (t+1)*kItems-1.
     uint32_t keep_bits = 0, nkeep = 0, ndup = 0;
 #pragma unroll
-    for (int j = 0; j < kFinItems; ++j) {
-        const int p = tid * kFinItems + j;
+    for (int j = 0; j < kItems; ++j) {
+        const int p = tid * kItems + j;
         const uint64_t idx = t0 + p;
         if (idx < a.N) {
             const KeyT key = s_keys[fin_slot(p + 1)], prev = s_keys[fin_slot(p)];
@@ -788,8 +943,8 @@ __global__ __launch_bounds__(kFinThreads) void csr_finish(FinArgs a) {
     // decoupled look-back in which the first wavefront reads 64 predecessors
     // per round trip: the nearest one with an inclusive prefix ends the walk,
     // the counts of the ones before it are added.
-    uint64_t tot;
-    const uint64_t ex = block_exclusive_scan_256(nkeep, s_tmp, &tot);
+    uint32_t tot;
+    const uint32_t ex = block_exclusive_scan<kThreads>(nkeep, s_tmp, &tot);
     if (tid < 64) {
         const uint32_t lane = tid;
         uint64_t *st = a.status + tile;
@@ -829,10 +984,10 @@ __global__ __launch_bounds__(kFinThreads) void csr_finish(FinArgs a) {
     const uint64_t cbase = s_base + ex;
     IdT *col = static_cast<IdT *>(a.col);
     uint64_t c = cbase;
-    IdT vals[kFinItems];
+    IdT vals[kItems];
 #pragma unroll
-    for (int j = 0; j < kFinItems; ++j) {
-        const int p = tid * kFinItems + j;
+    for (int j = 0; j < kItems; ++j) {
+        const int p = tid * kItems + j;
         const uint64_t idx = t0 + p;
         vals[j] = 0;
         if (idx < a.N) {
@@ -849,12 +1004,12 @@ __global__ __launch_bounds__(kFinThreads) void csr_finish(FinArgs a) {
     }
     // Kept columns to LDS in output order, then coalesced stores.
     __syncthreads();  // every read of the keys is done
-    uint32_t r = (uint32_t)ex;
+    uint32_t r = ex;
 #pragma unroll
-    for (int j = 0; j < kFinItems; ++j)
+    for (int j = 0; j < kItems; ++j)
         if ((keep_bits >> j) & 1u) s_col[r++] = vals[j];
     __syncthreads();
-    for (uint32_t i = tid; i < (uint32_t)tot; i += kFinThreads) __builtin_nontemporal_store(s_col[i], &col[s_base + i]);
+    for (uint32_t i = tid; i < tot; i += kThreads) __builtin_nontemporal_store(s_col[i], &col[s_base + i]);
     if (a.dups) {
         uint32_t x = ndup;
         for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
@@ -862,14 +1017,14 @@ __global__ __launch_bounds__(kFinThreads) void csr_finish(FinArgs a) {
         __syncthreads();
         if (tid == 0) {
             uint32_t t = 0;
-            for (int i = 0; i < kFinThreads / 64; ++i) t += s_dups[i];
+            for (int i = 0; i < kThreads / 64; ++i) t += s_dups[i];
             if (t) atomicAdd((unsigned long long *)a.dups, (unsigned long long)t);
         }
     }
     // The last tile closes row n: total kept = base of this tile + its kept.
-    if (t0 + kFinTile >= a.N && tid == kFinThreads - 1) {
+    if (t0 + kTile >= a.N && tid == kThreads - 1) {
         uint64_t tail = cbase;
-        for (int j = 0; j < kFinItems; ++j) tail += (keep_bits >> j) & 1u;
+        for (int j = 0; j < kItems; ++j) tail += (keep_bits >> j) & 1u;
         a.rp[a.n] = tail;
         if (a.rp_raw) a.rp_raw[a.n] = a.N;
         a.mark[a.n] = 1;
@@ -1133,17 +1288,16 @@ struct Plan {
     int wb, db, kb, passes, key_bytes, dpasses;
     bool sym, simple, hist, directed_hist, xor_mode;
     bool fused_finish;  // the last pass writes the CSR (FINAL) instead of keys
-    int tb;
-    uint64_t split;
+    uint64_t power;  // (XOR) entries of the Kronecker power, beside the N sorted ones
     bool short_tiles;  // digit passes over tiles of kShortItems keys per thread
     uint64_t pass_tiles, fin_tiles, chunks;
     // workspace carving
     size_t off_keysA, off_keysB, off_status, off_ghist, off_gbase, off_indeg, off_rpraw, off_mark,
-        off_cmark, off_cmin, off_fstatus, total;
+        off_cmark, off_cmin, off_fstatus, off_split, off_tables, total;
 };
 
 Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_hist, bool xor_mode = false,
-               uint64_t split = 0) {
+               uint64_t power = 0) {
     Plan p;
     memset(&p, 0, sizeof(p));
     p.n = n;
@@ -1151,8 +1305,7 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.sym = flags & SFG_CSR_SYMMETRIZE;
     p.simple = (flags & SFG_CSR_SIMPLE) || xor_mode;
     p.xor_mode = xor_mode;
-    p.tb = xor_mode ? 1 : 0;
-    p.split = split;
+    p.power = power;
     p.N = p.sym ? 2 * E : E;
     p.wb = bits_for(n);
     p.hist = want_hist;
@@ -1163,22 +1316,22 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     // Symmetrized: a whole-byte destination field lets the histogram pass
     // count bytes of the two endpoints instead of every digit of both keys;
     // taken when it costs no pass and no key width.
-    if (p.sym && !xor_mode) {
+    if (p.sym) {
         const int db8 = 8 * ((p.wb + 7) / 8);
         if ((p.wb + db8 + 7) / 8 == (2 * p.wb + 7) / 8 && (p.wb + db8 <= 32) == (2 * p.wb <= 32)) p.db = db8;
     }
     p.dpasses = p.db / 8;
-    p.kb = p.wb + p.db + p.tb;
+    p.kb = p.wb + p.db;
     p.passes = (p.kb + 7) / 8;
     p.key_bytes = p.kb <= 32 ? 4 : 8;
     constexpr uint64_t short_tile = kPassThreads * kShortItems;
     p.short_tiles = p.N <= kShortTiles * short_tile;
     p.pass_tiles = p.short_tiles ? (p.N + short_tile - 1) / short_tile : (p.N + kPassTile - 1) / kPassTile;
-    p.fin_tiles = (p.N + kFinTile - 1) / kFinTile;
+    p.fin_tiles = (p.N + power + fin_tile(xor_mode) - 1) / fin_tile(xor_mode);
     // Without SIMPLE no entry is dropped, so sorted positions are output
     // positions and the last pass can write the columns itself -- unless it
     // is also the first pass or the pass that marks column starts.
-    p.fused_finish = !p.simple && !p.xor_mode && p.passes >= 2 && !(p.directed_hist && p.passes - 1 == p.dpasses);
+    p.fused_finish = !p.simple && p.passes >= 2 && !(p.directed_hist && p.passes - 1 == p.dpasses);
     p.chunks = (n + 1 + kScanChunk - 1) / kScanChunk;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -1200,6 +1353,8 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.off_cmark = take(p.directed_hist ? n + 1 : 0);
     p.off_cmin = take(std::max<uint64_t>(p.chunks, 1) * 8);
     p.off_fstatus = take(p.simple ? std::max<uint64_t>(p.fin_tiles, 1) * 8 : 0);
+    p.off_split = take(xor_mode ? (p.fin_tiles + 1) * 8 : 0);
+    p.off_tables = take(xor_mode ? sizeof(PowerTables) : 0);
     p.total = o;
     (void)id_bytes;
     return p;
@@ -1295,7 +1450,7 @@ void clear_csr(const Plan &P, uint64_t *row_ptr, uint64_t *hist, uint64_t *dups,
     };
     region(P.off_ghist, 8 * kRadix * 8);
     if (P.N) region(P.off_status, P.pass_tiles * kRadix * 8);
-    if (P.simple && P.N) region(P.off_fstatus, P.fin_tiles * 8);
+    if (P.simple && P.fin_tiles) region(P.off_fstatus, P.fin_tiles * 8);
     // Row (and column) starts are written only where a row begins and
     // flagged in the mark bytes; the row fill completes the rest.
     region(P.off_mark, P.n + 1, P.n);
@@ -1306,7 +1461,7 @@ void clear_csr(const Plan &P, uint64_t *row_ptr, uint64_t *hist, uint64_t *dups,
     c.hist = hist;
     if (dups) c.value(dups, 0);
     // (with SIMPLE the finish pass writes the values at row n)
-    if (!P.simple || P.N == 0) c.value(row_ptr + P.n, P.N);
+    if (!P.simple || P.fin_tiles == 0) c.value(row_ptr + P.n, P.N);
     if (P.hist && P.simple && P.N == 0) c.value(reinterpret_cast<uint64_t *>(ws + P.off_rpraw) + P.n, 0);
     ProfScope _ps("fill", s);
     csr_clear<<<fill_grid(words), 256, 0, s>>>(c);
@@ -1324,7 +1479,7 @@ void launch_pass(const PassArgs &a, int grid, bool short_tiles, hipStream_t s) {
 template <typename IdT, typename KeyT>
 int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, void *col, uint64_t *hist,
             uint64_t *dups, char *ws, hipStream_t s, bool counted = false, bool keys_given = false,
-            const Unpack *up = nullptr) {
+            const Unpack *up = nullptr, const Power *pw = nullptr) {
     uint32_t *err = device_error_word();
     KeyT *keysA = reinterpret_cast<KeyT *>(ws + P.off_keysA);
     KeyT *keysB = reinterpret_cast<KeyT *>(ws + P.off_keysB);
@@ -1339,8 +1494,7 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
     if (!counted) clear_csr(P, row_ptr, hist, dups, ws, s);
 
     if (P.N > 0) {
-        PrepArgs pa{P.E, P.N, src, dst, ghist, P.db, P.passes, P.tb, P.split,
-                    (P.sym && !P.xor_mode && P.db % 8 == 0) ? P.db / 8 : 0};
+        PrepArgs pa{P.E, P.N, src, dst, ghist, P.db, P.passes, (P.sym && P.db % 8 == 0) ? P.db / 8 : 0};
         // Every histogram workgroup stays resident (32 KB of LDS each); a small
         // list takes fewer, since each adds its counts to the global ones.
         const int pg = (int)std::max<uint64_t>(1, std::min<uint64_t>((P.E + kPrepMinEdges - 1) / kPrepMinEdges,
@@ -1358,7 +1512,7 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
             KeyT *out = (remaining % 2 == 0) ? keysA : keysB;
             KeyT *in = (remaining % 2 == 0) ? keysB : keysA;
             PassArgs a{P.E, P.N, src, dst, in, out, status, gbase, ghist + p * kRadix, err,
-                       csc, cmark, P.db, 8 * p, (uint32_t)(p + 1), P.tb, P.split, P.n};
+                       csc, cmark, P.db, 8 * p, (uint32_t)(p + 1), P.n};
             const int g = (int)P.pass_tiles;
             if (P.fused_finish && p == P.passes - 1) {
                 a.col = col;
@@ -1384,22 +1538,31 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
                 launch_pass<IdT, KeyT, false, false, false, false>(a, g, P.short_tiles, s);
             }
         }
-        FinArgs fa{P.N, P.n, keysA, col, row_ptr, P.simple ? rp_raw_ws : nullptr, mark, dups, fstatus,
-                   err, P.db};
-        if (P.fused_finish) {
-            const int last = P.passes - 1;
-            const int run_tiles = P.pass_tiles >= (uint64_t)kRunTiles * device_cu_count() ? kRunTiles : kRunBatch;
-            RunArgs ra{P.pass_tiles, P.n, status, gbase, ghist + last * kRadix, keysA,
-                       keysA + P.pass_tiles * kRadix, reinterpret_cast<const uint32_t *>(keysA + 2 * P.pass_tiles * kRadix),
-                       row_ptr, mark, dups, err, P.db, (uint32_t)(last + 1), run_tiles};
-            const int rg = (int)((P.pass_tiles + run_tiles - 1) / run_tiles);
-            { ProfScope _ps("csr_run_starts", s); csr_run_starts<KeyT><<<rg, kRadix, 0, s>>>(ra); }
-        } else if (P.xor_mode)
-            { ProfScope _ps("csr_finish", s); csr_finish<IdT, KeyT, true><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa); }
-        else if (P.simple)
-            { ProfScope _ps("csr_finish", s); csr_finish<IdT, KeyT, false><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa); }
-        else
-            { ProfScope _ps("csr_finish", s); csr_finish_plain<IdT, KeyT><<<fill_grid(P.N), kFinThreads, 0, s>>>(fa); }
+    }
+    const uint64_t entries = P.N + P.power;
+    FinArgs fa{entries, P.n, keysA, col, row_ptr, P.simple ? rp_raw_ws : nullptr, mark, dups, fstatus, err, P.db,
+               P.N, reinterpret_cast<const uint64_t *>(ws + P.off_split)};
+    if (entries == 0) {
+        // (the clearing kernel wrote the values at row n)
+    } else if (P.fused_finish) {
+        const int last = P.passes - 1;
+        const int run_tiles = P.pass_tiles >= (uint64_t)kRunTiles * device_cu_count() ? kRunTiles : kRunBatch;
+        RunArgs ra{P.pass_tiles, P.n, status, gbase, ghist + last * kRadix, keysA,
+                   keysA + P.pass_tiles * kRadix, reinterpret_cast<const uint32_t *>(keysA + 2 * P.pass_tiles * kRadix),
+                   row_ptr, mark, dups, err, P.db, (uint32_t)(last + 1), run_tiles};
+        const int rg = (int)((P.pass_tiles + run_tiles - 1) / run_tiles);
+        { ProfScope _ps("csr_run_starts", s); csr_run_starts<KeyT><<<rg, kRadix, 0, s>>>(ra); }
+    } else if (P.xor_mode) {
+        ProfScope _ps("csr_finish", s);
+        xor_split<KeyT><<<(int)((P.fin_tiles + 256) / 256), 256, 0, s>>>(
+            *pw, keysA, P.N, entries, P.fin_tiles, P.db, reinterpret_cast<uint64_t *>(ws + P.off_split));
+        csr_finish<IdT, KeyT, true><<<(int)P.fin_tiles, kXorThreads, 0, s>>>(fa, *pw);
+    } else if (P.simple) {
+        ProfScope _ps("csr_finish", s);
+        csr_finish<IdT, KeyT, false><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa, 0);
+    } else {
+        ProfScope _ps("csr_finish", s);
+        csr_finish_plain<IdT, KeyT><<<fill_grid(P.N), kPlainThreads, 0, s>>>(fa);
     }
     // The degree histogram is counted by the fill: deg = out (from the
     // uncompacted row starts) + in (from the column starts, directed).
@@ -1470,8 +1633,8 @@ int csr_check(uint64_t n, uint64_t num_edges, const void *src, const void *dst, 
     const bool sym = flags & SFG_CSR_SYMMETRIZE;
     const uint64_t N = sym ? 2 * num_edges : num_edges;
     // One workgroup per tile: a dispatch's work-item count must stay below 2^32
-    // (2^34 entries are 2^21 digit-pass tiles of 1,024 threads, and 2^34 / 3,072
-    // finish tiles of 256).
+    // (2^34 entries are 2^21 digit-pass tiles of 1,024 threads, and 2^21 finish
+    // tiles of 1,024).
     if (N > (1ull << 34)) return fail(SFG_ERANGE, "edges_to_csr: more than 2^34 entries");
     P = make_plan(n, num_edges, id_bytes, flags, degree_hist32 != nullptr);
     if (P.total > 0 && !workspace) return fail(SFG_EINVAL, "edges_to_csr: workspace is NULL");
@@ -1696,7 +1859,7 @@ int kron_csr_build(uint32_t n0, const float *initiator, uint32_t k, uint64_t num
                          degree_hist32, num_duplicates, ws, workspace_bytes, P, s);
     if (rc != 1) return rc;  // done (SFG_OK) or failed; 1 = not applicable
     ByteCount bc{};
-    const bool bytes = P.db % 8 == 0 && !P.xor_mode && P.N > 0;
+    const bool bytes = P.db % 8 == 0 && P.N > 0;
     if (bytes) {
         bc.hist = reinterpret_cast<uint64_t *>(ws + P.off_ghist);
         bc.rows = P.passes;
@@ -1732,23 +1895,128 @@ int kron_csr_build(uint32_t n0, const float *initiator, uint32_t k, uint64_t num
 
 namespace sfg {
 
-size_t csr_xor_workspace_bytes(uint64_t n, uint64_t num_entries) {
-    return make_plan(n, num_entries, 8, 0, false, true, 0).total;
+namespace {
+// The tables of power.hpp, a workgroup per row of a digit's seed: blocks
+// [0, c.n[0]) and the next c.n[1] the counting rows, then those for walking.
+// Every workgroup derives the seed's own rows from its bits first.
+__global__ __launch_bounds__(64) void power_tables(PowerSeed q, PowerDigits c, PowerDigits w, PowerTables *t) {
+    __shared__ uint8_t s_list[kPowerMaxN0 * kPowerMaxN0];
+    __shared__ uint32_t s_start[kPowerMaxN0 + 1];
+    const uint32_t n0 = q.n0, tid = threadIdx.x;
+    auto cell = [&](uint32_t a, uint32_t b) { return (q.mask[(a * n0 + b) / 32] >> ((a * n0 + b) % 32)) & 1u; };
+    uint32_t deg0 = 0;
+    if (tid < n0)
+        for (uint32_t y = 0; y < n0; ++y) deg0 += cell(tid, y);
+    uint32_t sum = deg0;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(sum, off, 64);
+        if (tid >= (uint32_t)off) sum += o;
+    }
+    s_start[tid + 1] = sum;
+    if (tid == 0) s_start[0] = 0;
+    if (tid < n0) {
+        uint32_t at = sum - deg0;
+        for (uint32_t y = 0; y < n0; ++y)
+            if (cell(tid, y)) s_list[at++] = (uint8_t)y;
+    }
+    __syncthreads();
+    uint32_t x = blockIdx.x;
+    const bool counting = x < c.n[0] + c.n[1];
+    if (!counting) x -= c.n[0] + c.n[1];
+    const PowerDigits &p = counting ? c : w;
+    const uint32_t v = x < p.n[0] ? 0 : 1, n = p.n[v], levels = p.levels[v];
+    if (v) x -= p.n[0];
+    // Entries of row x and of the rows below it, most significant level first.
+    uint32_t start = 0, deg = 1, place = n, entries = 1;
+    for (uint32_t l = 0; l < levels; ++l) entries *= q.e0;
+    for (uint32_t l = 0, xx = x, below = entries; l < levels; ++l) {
+        place /= n0;
+        below /= q.e0;
+        const uint32_t dgt = xx / place;
+        xx -= dgt * place;
+        start += deg * s_start[dgt] * below;
+        deg *= s_start[dgt + 1] - s_start[dgt];
+    }
+    if (counting) {
+        uint8_t *rank = t->count.rank + (v ? p.n[0] * p.n[0] : 0) + x * n;
+        for (uint32_t y = tid; y < n; y += 64) {
+            uint32_t r = 0;
+            bool in = true;
+            uint32_t pl = n, xx = x, yy = y;
+            for (uint32_t l = 0; l < levels; ++l) {
+                pl /= n0;
+                const uint32_t a = xx / pl, b = yy / pl;
+                xx -= a * pl;
+                yy -= b * pl;
+                uint32_t below = 0;
+                for (uint32_t z = 0; z < b; ++z) below += cell(a, z);
+                r = r * (s_start[a + 1] - s_start[a]) + (in ? below : 0);
+                in = in && cell(a, b);
+            }
+            rank[y] = (uint8_t)(r | (in ? 0x80u : 0u));
+        }
+        if (tid == 0) {
+            t->count.start[v][x] = (uint16_t)start;
+            if (x + 1 == n) t->count.start[v][n] = (uint16_t)entries;
+        }
+    } else {
+        for (uint32_t i = tid; i < deg; i += 64) {
+            uint32_t y = 0, ii = i, xx = x, pl = 1;
+            for (uint32_t l = 0; l < levels; ++l) {  // least significant level first
+                const uint32_t a = xx % n0, s = s_start[a], d = s_start[a + 1] - s;
+                y += s_list[s + ii % d] * pl;
+                ii /= d;
+                xx /= n0;
+                pl *= n0;
+            }
+            t->list[v][start + i] = (uint16_t)y;
+            t->rowof[v][start + i] = (uint16_t)x;
+        }
+        if (tid == 0) {
+            t->start[v][x] = (uint16_t)start;
+            t->degmagic[v][x] = deg ? 0xFFFFFFFFu / deg : 0;
+            if (x + 1 == n) t->start[v][n] = (uint16_t)entries;
+        }
+    }
+}
+}  // namespace
+
+size_t csr_xor_workspace_bytes(uint64_t n, uint64_t num_random, uint64_t num_power) {
+    return make_plan(n, num_random, 8, 0, false, true, num_power).total;
 }
 
-int csr_xor_build(uint64_t n, uint64_t num_entries, uint64_t split, const void *src, const void *dst, int id_bytes,
-                  uint64_t *row_ptr, void *col, void *workspace, size_t workspace_bytes, hipStream_t s) {
+int csr_xor_begin(uint64_t n, uint64_t num_random, Power *power, const PowerSeed &seed, uint64_t *row_ptr, void *workspace,
+                  size_t workspace_bytes, hipStream_t s, XorKeys *keys) {
     if (n > (1ull << 31)) return fail(SFG_ERANGE, "xor: n above 2^31 does not fit the tagged key");
-    Plan P = make_plan(n, num_entries, id_bytes, 0, false, true, split);
+    if (!device_error_word()) return fail(SFG_EDEVICE, "xor: no device");
+    const Plan P = make_plan(n, num_random, 8, 0, false, true, power->entries);
     if (workspace_bytes < P.total)
         return fail(SFG_ENOSPACE, "xor: workspace has %zu bytes, needs %zu", workspace_bytes, P.total);
     char *ws = static_cast<char *>(workspace);
+    clear_csr(P, row_ptr, nullptr, nullptr, ws, s);
+    PowerTables *t = reinterpret_cast<PowerTables *>(ws + P.off_tables);
+    power->tables = t;
+    { ProfScope _ps("fill", s); power_tables<<<power->c.n[0] + power->c.n[1] + power->w.n[0] + power->w.n[1], 64, 0, s>>>(seed, power->c, power->w, t); }
+    keys->keys = ws + first_input_offset(P);
+    keys->hist = reinterpret_cast<uint64_t *>(ws + P.off_ghist);
+    keys->key_bytes = P.key_bytes;
+    keys->shift = P.db;
+    keys->passes = P.passes;
+    return SFG_OK;
+}
+
+int csr_xor_finish(uint64_t n, uint64_t num_random, const Power &power, int id_bytes, uint64_t *row_ptr, void *col,
+                   void *workspace, hipStream_t s) {
+    const Plan P = make_plan(n, num_random, 8, 0, false, true, power.entries);
+    char *ws = static_cast<char *>(workspace);
     if (P.key_bytes == 4) {
-        if (id_bytes == 4) return run_csr<int32_t, uint32_t>(P, src, dst, row_ptr, col, nullptr, nullptr, ws, s);
-        return run_csr<int64_t, uint32_t>(P, src, dst, row_ptr, col, nullptr, nullptr, ws, s);
+        if (id_bytes == 4)
+            return run_csr<int32_t, uint32_t>(P, nullptr, nullptr, row_ptr, col, nullptr, nullptr, ws, s, true, true, nullptr, &power);
+        return run_csr<int64_t, uint32_t>(P, nullptr, nullptr, row_ptr, col, nullptr, nullptr, ws, s, true, true, nullptr, &power);
     }
-    if (id_bytes == 4) return run_csr<int32_t, uint64_t>(P, src, dst, row_ptr, col, nullptr, nullptr, ws, s);
-    return run_csr<int64_t, uint64_t>(P, src, dst, row_ptr, col, nullptr, nullptr, ws, s);
+    if (id_bytes == 4)
+        return run_csr<int32_t, uint64_t>(P, nullptr, nullptr, row_ptr, col, nullptr, nullptr, ws, s, true, true, nullptr, &power);
+    return run_csr<int64_t, uint64_t>(P, nullptr, nullptr, row_ptr, col, nullptr, nullptr, ws, s, true, true, nullptr, &power);
 }
 
 }  // namespace sfg

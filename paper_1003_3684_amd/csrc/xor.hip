@@ -1,40 +1,55 @@
 // Randomized PK by exclusive OR (PK section, randomization): the adjacency
 // matrix of the deterministic Kronecker power XOR that of a random graph.
 //
-// The Kronecker power's e0^k edges (enumerate mode, distinct pairs) and the
-// random graph's num_random uniform pair draws are laid side by side in one
-// edge list; the CSR build sorts them with an origin bit below every entry
-// and keeps a pair once when exactly one of the two graphs holds it (repeated
-// draws are one edge of the random graph).
+// Only the random graph is sorted: its num_random uniform pair draws are written
+// as sort keys, their digits counted as they are drawn, and the CSR build
+// merges the sorted pairs with the power's entries, which are in order by
+// construction and computed where they are needed (power.hpp).  A pair is kept
+// once when exactly one of the two graphs holds it (repeated draws are one
+// edge of the random graph).
 #include <string.h>
 
 #include <algorithm>
 
 #include "common.hpp"
-
+#include "power.hpp"
 
 namespace sfg {
 namespace {
 
 constexpr uint32_t TAG_RANDOM = 6;
 constexpr int kXorThreads = 256;
+constexpr int kXorCopies = 4;  // interleaved copies of each LDS digit histogram
 
 // Draw i: Philox block (i, 0, 0, tag 6 | gid << 8); row = uidx(w0 + 2^32 w1,
 // n), column = uidx(w2 + 2^32 w3, n).
-template <typename IdT>
-__global__ __launch_bounds__(kXorThreads) void random_pairs(uint64_t count, uint64_t n, uint32_t key0, uint32_t key1,
-                                                           uint32_t tagword, IdT *src, IdT *dst) {
+template <typename KeyT>
+__global__ __launch_bounds__(kXorThreads) void random_keys(uint64_t count, uint64_t n, uint32_t key0, uint32_t key1,
+                                                          uint32_t tagword, int shift, int passes, KeyT *keys,
+                                                          uint64_t *hist) {
+    __shared__ uint32_t s_h[8 * 256 * kXorCopies];
+    for (int i = threadIdx.x; i < passes * 256 * kXorCopies; i += kXorThreads) s_h[i] = 0;
+    __syncthreads();
+    const uint32_t copy = threadIdx.x % kXorCopies;
     const uint64_t stride = (uint64_t)gridDim.x * kXorThreads;
     for (uint64_t i = (uint64_t)blockIdx.x * kXorThreads + threadIdx.x; i < count; i += stride) {
         const Block4 r = philox((uint32_t)i, (uint32_t)(i >> 32), 0, tagword, key0, key1);
-        src[i] = (IdT)uidx64(make_u64(r.w0, r.w1), n);
-        dst[i] = (IdT)uidx64(make_u64(r.w2, r.w3), n);
+        const KeyT k = ((KeyT)uidx64(make_u64(r.w0, r.w1), n) << shift) | (KeyT)uidx64(make_u64(r.w2, r.w3), n);
+        keys[i] = k;
+        for (int p = 0; p < passes; ++p) atomicAdd(&s_h[(p * 256 + (uint32_t)((k >> (8 * p)) & 255)) * kXorCopies + copy], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < passes * 256; i += kXorThreads) {
+        uint32_t t = 0;
+#pragma unroll
+        for (int c = 0; c < kXorCopies; ++c) t += s_h[i * kXorCopies + c];
+        if (t) atomicAdd((unsigned long long *)&hist[i], (unsigned long long)t);
     }
 }
 
 struct XorSizes {
-    uint64_t n, epk, total;
-    size_t off_src, off_dst, off_csr, bytes;
+    uint64_t n, e0, epk;
+    size_t bytes;
 };
 
 int xor_sizes(uint32_t n0, const float *seed_matrix, uint32_t k, uint64_t num_random, int id_bytes, XorSizes *z) {
@@ -61,18 +76,9 @@ int xor_sizes(uint32_t n0, const float *seed_matrix, uint32_t k, uint64_t num_ra
     // The sort takes one workgroup per tile of entries (see edges_to_csr).
     if (epk + num_random > (1ull << 34)) return fail(SFG_ERANGE, "kron_xor_random: more than 2^34 entries");
     z->n = n;
+    z->e0 = e0;
     z->epk = epk;
-    z->total = epk + num_random;
-    size_t o = 0;
-    auto take = [&](size_t b) {
-        size_t r = o;
-        o += align256(b);
-        return r;
-    };
-    z->off_src = take(z->total * id_bytes);
-    z->off_dst = take(z->total * id_bytes);
-    z->off_csr = take(csr_xor_workspace_bytes(n, z->total));
-    z->bytes = o;
+    z->bytes = csr_xor_workspace_bytes(n, num_random, epk);
     return SFG_OK;
 }
 
@@ -99,24 +105,24 @@ extern "C" int kron_xor_random(uint32_t n0, const float *seed_matrix, uint32_t k
     if (workspace_bytes < z.bytes)
         return fail(SFG_ENOSPACE, "kron_xor_random: workspace has %zu bytes, needs %zu", workspace_bytes, z.bytes);
     hipStream_t s = as_stream(stream);
-    char *ws = static_cast<char *>(workspace);
-    char *src = ws + z.off_src, *dst = ws + z.off_dst;
-    rc = kron_generate(n0, seed_matrix, k, z.epk, SFG_KRON_ENUMERATE, seed, graph_id, id_bytes, src, dst, stream);
+    Power pw;
+    PowerSeed seed_bits;
+    make_power(n0, seed_matrix, z.e0, k, pw, seed_bits);
+    XorKeys keys;
+    rc = csr_xor_begin(z.n, num_random, &pw, seed_bits, row_ptr, workspace, workspace_bytes, s, &keys);
     if (rc != SFG_OK) return rc;
     if (num_random) {
+        // (a few workgroups per CU: each adds its counts to the global ones)
         const int g = (int)std::max<uint64_t>(
-            1, std::min<uint64_t>((num_random + kXorThreads - 1) / kXorThreads, (uint64_t)device_cu_count() * 8));
+            1, std::min<uint64_t>((num_random + 16 * kXorThreads - 1) / (16 * kXorThreads), (uint64_t)device_cu_count() * 5));
         const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32), tagword = TAG_RANDOM | (graph_id << 8);
         ProfScope _ps("random_pairs", s);
-        if (id_bytes == 4)
-            random_pairs<int32_t><<<g, kXorThreads, 0, s>>>(num_random, z.n, key0, key1, tagword,
-                                                            reinterpret_cast<int32_t *>(src) + z.epk,
-                                                            reinterpret_cast<int32_t *>(dst) + z.epk);
+        if (keys.key_bytes == 4)
+            random_keys<uint32_t><<<g, kXorThreads, 0, s>>>(num_random, z.n, key0, key1, tagword, keys.shift, keys.passes,
+                                                            static_cast<uint32_t *>(keys.keys), keys.hist);
         else
-            random_pairs<int64_t><<<g, kXorThreads, 0, s>>>(num_random, z.n, key0, key1, tagword,
-                                                            reinterpret_cast<int64_t *>(src) + z.epk,
-                                                            reinterpret_cast<int64_t *>(dst) + z.epk);
+            random_keys<uint64_t><<<g, kXorThreads, 0, s>>>(num_random, z.n, key0, key1, tagword, keys.shift, keys.passes,
+                                                            static_cast<uint64_t *>(keys.keys), keys.hist);
     }
-    return csr_xor_build(z.n, z.total, z.epk, src, dst, id_bytes, row_ptr, col, ws + z.off_csr,
-                         workspace_bytes - z.off_csr, s);
+    return csr_xor_finish(z.n, num_random, pw, id_bytes, row_ptr, col, workspace, s);
 }

@@ -29,6 +29,38 @@ def test_xor_matches_oracle(sfg, orc, seed_m, k, M, id_bytes):
     np.testing.assert_array_equal(col[:m].cpu().numpy().astype(np.int64), ocol)
 
 
+def _ring(n0, step):
+    m = np.zeros((n0, n0), np.float32)
+    for x in range(n0):
+        m[x, x] = m[x, (x * step + 1) % n0] = 1
+    return m
+
+
+@pytest.mark.parametrize("seed_m,k,M,id_bytes", [
+    (_ring(5, 2), 1, 40, 4),                           # one level, one digit
+    (np.array([[1, 1], [1, 0]]), 11, 5_000, 4),        # several digits, the top one of fewer levels (counting and walking)
+    (np.array([[1, 1], [1, 0]]), 4, 50_000, 8),        # far more draws than cells, 4-byte keys with 64-bit ids
+    (np.array([[1, 1], [0, 0]]), 13, 0, 4),            # exactly one tile, one row, no random pair
+    (np.array([[1, 1], [0, 0]]), 21, 30_000, 8),       # one long row of three walking digits; 8-byte keys
+    (np.array([[0, 0], [1, 1]]), 13, 1, 4),            # one entry more than a tile
+    (np.array([[0, 1], [1, 0]]), 17, 70_000, 4),       # one entry per row
+    (np.array([[0, 0, 0], [0, 0, 1], [0, 0, 0]]), 7, 3_000, 4),  # the power is a single entry
+    (np.array([[1, 0, 1], [0, 0, 0], [1, 1, 1]]), 9, 100_000, 8),  # empty rows
+    (_ring(33, 3), 3, 60_000, 4),                      # more vertices than a grouped counting digit
+    (_ring(64, 5), 2, 20_000, 8),                      # the largest seed
+    (np.ones((64, 64)), 2, 9_000, 4),                  # and all of its cells
+])
+def test_xor_digit_groupings_match_oracle(sfg, orc, seed_m, k, M, id_bytes):
+    import torch
+    seed_m = np.asarray(seed_m, np.float32)
+    rp, col = sfg.kron_xor_random(seed_m.shape[0], seed_m, k, M, seed=17, graph_id=5, id_bytes=id_bytes)
+    torch.cuda.synchronize()
+    assert sfg.device_error() == 0
+    orp, ocol = orc.kron_xor_random(seed_m, k, M, 17, 5)
+    np.testing.assert_array_equal(rp.cpu().numpy().astype(np.uint64), orp)
+    np.testing.assert_array_equal(col[:int(orp[-1])].cpu().numpy().astype(np.int64), ocol)
+
+
 def test_xor_errors(sfg):
     from paper_1003_3684_amd.native import SfgenError
     with pytest.raises(SfgenError):
