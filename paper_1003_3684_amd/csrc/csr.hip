@@ -71,9 +71,17 @@ constexpr int kXorThreads = 512, kXorItems = 16;  // XOR: twice the registers pe
 constexpr int fin_tile(bool xor_mode) { return xor_mode ? kXorThreads * kXorItems : kFinThreads * kFinItems; }
 
 constexpr int kScanChunk = 4096;  // vertices per chunk of the row fill scan
+constexpr int kPrepThreads = 1024;
 constexpr int kPrepUnroll = 4;    // keys per thread in flight in the histogram pass
-constexpr int kPrepCopies = 4;    // interleaved copies of each LDS histogram
-constexpr int kPrepBlocksPerCu = 4;
+// Interleaved copies of each LDS histogram.  Lanes of a wave that count the same
+// digit in the same copy wait for each other, and in a list that comes sorted
+// by source (PBA) whole waves share the high digits of it: csr_prepare in us of
+// 6.7e8 such edges / 2.4e7 unordered ones with 4 copies in four workgroups of
+// 256 threads per CU 4,725 / 96, with 8 in two of 1,024 2,657 / 97, with 16 in one
+// (128 KB of LDS) 1,701 (3.2 TB/s) / 96 (4 TB/s).  Counting a digit that all lanes
+// share with one add cost more instructions than it saved (2,747 -> 3,460).
+constexpr int kPrepCopies = 16;
+constexpr int kPrepBlocksPerCu = 1;
 constexpr int kPrepMinEdges = 4096;  // edges a workgroup of it has at least
 
 constexpr uint64_t kNoRow = ~0ull;
@@ -164,55 +172,54 @@ struct PrepArgs {
     int dbytes;        // SYM with a whole-byte destination field: its bytes, else 0
 };
 
+// One count of every digit of k (all lanes of their copy of the histograms).
+template <typename KeyT> __device__ __forceinline__ void count_digits(uint32_t *s_h, KeyT k, int passes, uint32_t copy) {
+#pragma unroll
+    for (int p = 0; p < (int)sizeof(KeyT); ++p)
+        if (p < passes) atomicAdd(&s_h[(p * kRadix + (uint32_t)((k >> (8 * p)) & 255)) * kPrepCopies + copy], 1u);
+}
+
 template <typename IdT, typename KeyT, bool SYM>
-__global__ __launch_bounds__(256) void csr_prepare(PrepArgs a) {
+__global__ __launch_bounds__(kPrepThreads) void csr_prepare(PrepArgs a) {
     // kPrepCopies interleaved copies of every histogram, lane l counting in
     // copy l mod kPrepCopies: skewed digits (one value drawn by many lanes of
     // a wave) would otherwise serialise the LDS atomics on one address.
     __shared__ uint32_t s_h[8 * kRadix * kPrepCopies];
-    for (int i = threadIdx.x; i < 8 * kRadix * kPrepCopies; i += 256) s_h[i] = 0;
+    const int rows = SYM && a.dbytes ? a.dbytes : a.passes;
+    for (int i = threadIdx.x; i < rows * kRadix * kPrepCopies; i += kPrepThreads) s_h[i] = 0;
     __syncthreads();
     const uint32_t copy = threadIdx.x % kPrepCopies;
     const IdT *src = static_cast<const IdT *>(a.src), *dst = static_cast<const IdT *>(a.dst);
     // kPrepUnroll keys per thread are loaded before any is counted, so that
     // enough loads are in flight to cover the memory latency.
     // Every edge is read once; with SYM its reversed entry is counted too.
-    const uint64_t stride = (uint64_t)gridDim.x * 256 * kPrepUnroll;
-    for (uint64_t i0 = (uint64_t)blockIdx.x * 256 * kPrepUnroll + threadIdx.x; i0 < a.E; i0 += stride) {
+    const uint64_t stride = (uint64_t)gridDim.x * kPrepThreads * kPrepUnroll;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * kPrepThreads * kPrepUnroll + threadIdx.x; i0 < a.E; i0 += stride) {
         IdT su[kPrepUnroll], du[kPrepUnroll];
 #pragma unroll
         for (int u = 0; u < kPrepUnroll; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * 256;
-            su[u] = i < a.E ? src[i] : (IdT)0;
-            du[u] = i < a.E ? dst[i] : (IdT)0;
+            const uint64_t i = min(i0 + (uint64_t)u * kPrepThreads, a.E - 1);
+            su[u] = src[i];
+            du[u] = dst[i];
         }
 #pragma unroll
         for (int u = 0; u < kPrepUnroll; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * 256;
+            const uint64_t i = i0 + (uint64_t)u * kPrepThreads;
             if (i >= a.E) break;
             if (SYM && a.dbytes) {
                 // Key byte p of (u, v) and of (v, u) together is byte p mod
                 // dbytes of u plus that of v: one count per byte of each end.
                 using U = typename std::conditional<sizeof(IdT) == 4, uint32_t, uint64_t>::type;
-                const uint64_t uu = (U)su[u], vv = (U)du[u];
-                for (int q = 0; q < a.dbytes; ++q) {
-                    atomicAdd(&s_h[(q * kRadix + (uint32_t)((uu >> (8 * q)) & 255)) * kPrepCopies + copy], 1u);
-                    atomicAdd(&s_h[(q * kRadix + (uint32_t)((vv >> (8 * q)) & 255)) * kPrepCopies + copy], 1u);
-                }
+                count_digits<U>(s_h, (U)su[u], a.dbytes, copy);
+                count_digits<U>(s_h, (U)du[u], a.dbytes, copy);
                 continue;
             }
-            const KeyT k = pack<IdT, KeyT>(su[u], du[u], a.wb);
-            for (int p = 0; p < a.passes; ++p)
-                atomicAdd(&s_h[(p * kRadix + (uint32_t)((k >> (8 * p)) & 255)) * kPrepCopies + copy], 1u);
-            if (SYM) {
-                const KeyT kr = pack<IdT, KeyT>(du[u], su[u], a.wb);
-                for (int p = 0; p < a.passes; ++p)
-                    atomicAdd(&s_h[(p * kRadix + (uint32_t)((kr >> (8 * p)) & 255)) * kPrepCopies + copy], 1u);
-            }
+            count_digits<KeyT>(s_h, pack<IdT, KeyT>(su[u], du[u], a.wb), a.passes, copy);
+            if (SYM) count_digits<KeyT>(s_h, pack<IdT, KeyT>(du[u], su[u], a.wb), a.passes, copy);
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < a.passes * kRadix; i += 256) {
+    for (int i = threadIdx.x; i < a.passes * kRadix; i += kPrepThreads) {
         // (with dbytes, pass p's histogram is the byte histogram p mod dbytes)
         const int row = (SYM && a.dbytes) ? (i / kRadix) % a.dbytes * kRadix + i % kRadix : i;
         uint32_t t = 0;
@@ -1495,16 +1502,16 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
 
     if (P.N > 0) {
         PrepArgs pa{P.E, P.N, src, dst, ghist, P.db, P.passes, (P.sym && P.db % 8 == 0) ? P.db / 8 : 0};
-        // Every histogram workgroup stays resident (32 KB of LDS each); a small
+        // Every histogram workgroup stays resident (128 KB of LDS each); a small
         // list takes fewer, since each adds its counts to the global ones.
         const int pg = (int)std::max<uint64_t>(1, std::min<uint64_t>((P.E + kPrepMinEdges - 1) / kPrepMinEdges,
                                                                       (uint64_t)device_cu_count() * kPrepBlocksPerCu));
         if (!counted) {
             ProfScope _ps("csr_prepare", s);
             if (P.sym)
-                csr_prepare<IdT, KeyT, true><<<pg, 256, 0, s>>>(pa);
+                csr_prepare<IdT, KeyT, true><<<pg, kPrepThreads, 0, s>>>(pa);
             else
-                csr_prepare<IdT, KeyT, false><<<pg, 256, 0, s>>>(pa);
+                csr_prepare<IdT, KeyT, false><<<pg, kPrepThreads, 0, s>>>(pa);
         }
         // Ping-pong so that the last pass lands in keysA.
         for (int p = 0; p < P.passes; ++p) {
