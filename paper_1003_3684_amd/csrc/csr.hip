@@ -1811,6 +1811,7 @@ int kron_csr_packed(uint32_t n0, const float *initiator, uint32_t k, uint64_t nu
         bc.keys32 = reinterpret_cast<uint32_t *>(ws + first_input_offset(P));
     bc.pack_groups = groups;
     bc.pack_bits = bits;
+    bc.pack_base = r;
     bc.pack_tab = ptab;
     clear_csr(P, rpc, degree_hist32, num_duplicates, ws, s);
     bool counted = false;

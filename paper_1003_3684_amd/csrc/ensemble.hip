@@ -43,9 +43,12 @@ struct KGraph {
     uint64_t edges, ebase, vbase;
     uint64_t lut_row, lut_col;
     uint32_t tm1[15];
+    uint32_t decode;  // kDecodeBits: tm1 holds bit_thresholds; else the thresholds to compare with
     uint32_t k, n0, shift, pow2, tagword, key0, key1;
     uint64_t block0;  // first workgroup of this member
 };
+
+constexpr uint32_t kDecodeBits = 0;
 
 template <int NT> __device__ __forceinline__ uint32_t bucket_of(uint32_t w, const uint32_t *t) {
     uint32_t b = 0;
@@ -63,8 +66,13 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // is the last one <= b; workgroups walk the tiles persistently (b = blockIdx.x,
 // blockIdx.x + gridDim.x, ...).  The member's parameters are the same for the
 // whole tile, so they are moved from LDS into scalar registers: the Philox key
-// schedule and the bucket thresholds then cost no vector instructions.
-template <typename IdT, int NT, int ITEMS>
+// schedule and the bucket thresholds then cost no vector instructions.  The
+// decode is chosen by the tile's own member: a 2 x 2 initiator takes its bits
+// from three comparisons (Form::Bits in kron.hip), others compare with 8 or 15
+// thresholds.  Bound by vector instructions; with 15 comparisons for every word
+// of a batch that holds a 3 x 3 member it took 1.64 ms for the 96 graphs of a
+// table, now 1.18.
+template <typename IdT, int ITEMS>
 __global__ __launch_bounds__(kKronThreads) void kron_batch(const KGraph *G, uint32_t count, uint64_t tiles,
                                                            IdT *__restrict__ src, IdT *__restrict__ dst) {
     __shared__ KGraph s_g;
@@ -84,20 +92,31 @@ __global__ __launch_bounds__(kKronThreads) void kron_batch(const KGraph *G, uint
         const uint64_t edges = uniform64(s_g.edges), ebase = uniform64(s_g.ebase), vbase = uniform64(s_g.vbase);
         const uint64_t lut_row = uniform64(s_g.lut_row), lut_col = uniform64(s_g.lut_col);
         const uint64_t block0 = uniform64(s_g.block0);
-        uint32_t tm1[NT];
+        uint32_t tm1[15];
 #pragma unroll
-        for (int i = 0; i < NT; ++i) tm1[i] = uniform32(s_g.tm1[i]);
+        for (int i = 0; i < 15; ++i) tm1[i] = uniform32(s_g.tm1[i]);
         const uint32_t k = uniform32(s_g.k), n0 = uniform32(s_g.n0), shift = uniform32(s_g.shift);
         const uint32_t pow2 = uniform32(s_g.pow2), tagword = uniform32(s_g.tagword);
         const uint32_t key0 = uniform32(s_g.key0), key1 = uniform32(s_g.key1);
+        const uint32_t decode = uniform32(s_g.decode);
         __syncthreads();  // s_g is rewritten by the next tile
-        // Levels 5 blk .. 5 blk + nlev - 1 of edge e from Philox block blk.
-        auto levels = [&](uint64_t e, uint32_t blk, uint32_t nlev, uint32_t &u, uint32_t &v) {
-            const Block4 r = philox((uint32_t)e, (uint32_t)(e >> 32), blk, tagword, key0, key1);
-            const uint32_t ws[5] = {r.w0, r.w1, r.w2, r.w3, level4_word(r)};
+        const uint32_t full = k / 5, rest = k % 5;
+        const uint64_t e0 = (tile - block0) * (uint64_t)(kKronThreads * ITEMS);
+        auto sample = [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;  // thresholds to compare with, or 0: two bits
+            // Levels 5 blk .. 5 blk + nlev - 1 of edge e from Philox block blk.
+            auto levels = [&](uint64_t e, uint32_t blk, uint32_t nlev, uint32_t &u, uint32_t &v) {
+                const Block4 r = philox((uint32_t)e, (uint32_t)(e >> 32), blk, tagword, key0, key1);
+                const uint32_t ws[5] = {r.w0, r.w1, r.w2, r.w3, level4_word(r)};
 #pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                if ((uint32_t)i < nlev) {
+                for (int i = 0; i < 5; ++i) {
+                    if ((uint32_t)i >= nlev) break;
+                    if (NT == 0) {
+                        const bool t0 = ws[i] > tm1[0], t1 = ws[i] > tm1[1], t2 = ws[i] > tm1[2];
+                        u = u + u + (t1 ? 1u : 0u);
+                        v = v + v + (((t0 != t1) != t2) ? 1u : 0u);
+                        continue;
+                    }
                     const uint32_t b = bucket_of<NT>(ws[i], tm1);
                     const uint32_t rd = (uint32_t)(lut_row >> (4 * b)) & 15u;
                     const uint32_t cd = (uint32_t)(lut_col >> (4 * b)) & 15u;
@@ -109,19 +128,23 @@ __global__ __launch_bounds__(kKronThreads) void kron_batch(const KGraph *G, uint
                         v = v * n0 + cd;
                     }
                 }
+            };
+            for (int it = 0; it < ITEMS; ++it) {
+                const uint64_t e = e0 + (uint64_t)it * kKronThreads + threadIdx.x;
+                if (e >= edges) break;
+                uint32_t u = 0, v = 0;  // below n0^k <= 2^32
+                for (uint32_t blk = 0; blk < full; ++blk) levels(e, blk, 5, u, v);
+                if (rest) levels(e, full, rest, u, v);
+                src[ebase + e] = (IdT)(vbase + u);
+                dst[ebase + e] = (IdT)(vbase + v);
             }
         };
-        const uint32_t full = k / 5, rest = k % 5;
-        const uint64_t e0 = (tile - block0) * (uint64_t)(kKronThreads * ITEMS);
-        for (int it = 0; it < ITEMS; ++it) {
-            const uint64_t e = e0 + (uint64_t)it * kKronThreads + threadIdx.x;
-            if (e >= edges) break;
-            uint32_t u = 0, v = 0;  // below n0^k <= 2^32
-            for (uint32_t blk = 0; blk < full; ++blk) levels(e, blk, 5, u, v);
-            if (rest) levels(e, full, rest, u, v);
-            src[ebase + e] = (IdT)(vbase + u);
-            dst[ebase + e] = (IdT)(vbase + v);
-        }
+        if (decode == kDecodeBits)
+            sample(std::integral_constant<int, 0>{});
+        else if (decode <= 8)
+            sample(std::integral_constant<int, 8>{});
+        else
+            sample(std::integral_constant<int, 15>{});
     }
 }
 
@@ -181,7 +204,7 @@ std::vector<std::pair<uint32_t, uint32_t>> cut_batches(const sfg_graph_desc *d, 
 struct BatchPlan {
     uint32_t b0, b1;
     uint64_t nv, E, E_pba, chunks, kron_tiles;
-    int id_bytes, nt_max;
+    int id_bytes;
     std::vector<PbaGraphSpec> pba;
     std::vector<uint32_t> pba_idx, kron_idx;  // descriptor indices, in batch order
     std::vector<KGraph> kt;
@@ -194,7 +217,6 @@ int plan_batch(const sfg_graph_desc *d, uint32_t b0, uint32_t b1, uint32_t items
     p.b0 = b0;
     p.b1 = b1;
     p.nv = p.E = p.E_pba = p.chunks = p.kron_tiles = 0;
-    p.nt_max = 0;
     // Vertex space and edge order: PBA members first, then Kronecker members.
     for (uint32_t i = b0; i < b1; ++i)
         if (d[i].kind == SFG_GRAPH_PBA) {
@@ -224,6 +246,7 @@ int plan_batch(const sfg_graph_desc *d, uint32_t b0, uint32_t b1, uint32_t items
                 g.lut_row |= (uint64_t)tab.row[b] << (4 * b);
                 g.lut_col |= (uint64_t)tab.col[b] << (4 * b);
             }
+            g.decode = bit_thresholds(d[i].n0, tab, g.tm1) ? kDecodeBits : std::max(tab.nt, 1u);
             g.k = d[i].k;
             g.n0 = d[i].n0;
             g.pow2 = (d[i].n0 & (d[i].n0 - 1)) == 0;
@@ -233,7 +256,6 @@ int plan_batch(const sfg_graph_desc *d, uint32_t b0, uint32_t b1, uint32_t items
             g.key1 = (uint32_t)(d[i].seed >> 32);
             g.block0 = p.kron_tiles;
             p.kron_tiles += (g.edges + tile_edges - 1) / tile_edges;
-            p.nt_max = std::max(p.nt_max, (int)tab.nt);
             p.kt.push_back(g);
             p.kron_idx.push_back(i);
             p.nv += nv;
@@ -306,16 +328,16 @@ void fill_tables(const Ensemble &en, std::vector<char> &blob) {
     }
 }
 
-template <typename IdT, int NT>
+template <typename IdT>
 void launch_kron(int items, unsigned grid, const KGraph *G, uint32_t count, uint64_t tiles, void *src, void *dst,
                  hipStream_t s) {
     IdT *su = static_cast<IdT *>(src), *du = static_cast<IdT *>(dst);
     if (items == 4)
-        kron_batch<IdT, NT, 4><<<grid, kKronThreads, 0, s>>>(G, count, tiles, su, du);
+        kron_batch<IdT, 4><<<grid, kKronThreads, 0, s>>>(G, count, tiles, su, du);
     else if (items == 16)
-        kron_batch<IdT, NT, 16><<<grid, kKronThreads, 0, s>>>(G, count, tiles, su, du);
+        kron_batch<IdT, 16><<<grid, kKronThreads, 0, s>>>(G, count, tiles, su, du);
     else
-        kron_batch<IdT, NT, 8><<<grid, kKronThreads, 0, s>>>(G, count, tiles, su, du);
+        kron_batch<IdT, 8><<<grid, kKronThreads, 0, s>>>(G, count, tiles, su, du);
 }
 
 // Kernel launches of one batch (its tables already on the device).
@@ -334,17 +356,10 @@ int enqueue_batch(const BatchPlan &P, const sfg_ensemble_tuning &tu, uint32_t sa
         const uint32_t kc = (uint32_t)P.kt.size();
         const unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(P.kron_tiles, cap));
         const int items = (int)tu.kron_items;
-        if (P.id_bytes == 4) {
-            if (P.nt_max <= 3)
-                launch_kron<int32_t, 3>(items, grid, ktab, kc, P.kron_tiles, src, dst, s);
-            else
-                launch_kron<int32_t, 15>(items, grid, ktab, kc, P.kron_tiles, src, dst, s);
-        } else {
-            if (P.nt_max <= 3)
-                launch_kron<int64_t, 3>(items, grid, ktab, kc, P.kron_tiles, src, dst, s);
-            else
-                launch_kron<int64_t, 15>(items, grid, ktab, kc, P.kron_tiles, src, dst, s);
-        }
+        if (P.id_bytes == 4)
+            launch_kron<int32_t>(items, grid, ktab, kc, P.kron_tiles, src, dst, s);
+        else
+            launch_kron<int64_t>(items, grid, ktab, kc, P.kron_tiles, src, dst, s);
     }
     // One CSR of the union; its histogram output is scratch (per-member
     // histograms come from the statistics pass).

@@ -82,6 +82,16 @@ int build_sample_table(uint32_t n0, const float *W, SampleTable &tab) {
     return SFG_OK;
 }
 
+bool bit_thresholds(uint32_t n0, const SampleTable &tab, uint32_t *tm1) {
+    if (n0 != 2 || tab.row[0] != 0 || tab.col[0] != 0) return false;
+    for (uint32_t c = 1; c < 4; ++c) {
+        tm1[c - 1] = 0xFFFFFFFFu;
+        // (the first bucket at or past cell c starts at its threshold)
+        for (uint32_t b = tab.nt; b > 0 && tab.row[b] * 2u + tab.col[b] >= c; --b) tm1[c - 1] = tab.tm1[b - 1];
+    }
+    return true;
+}
+
 namespace {
 
 // Kernel arguments of the register path (at most 15 distinct thresholds and
@@ -102,14 +112,25 @@ struct FastArgs {
     int key_shift;
     uint64_t key_sym;  // offset of the reversed entries, or 0
     uint32_t *keys32;  // 4-byte keys (packed ids only)
-    int pack_groups, pack_bits;
+    int pack_bits;
+    uint32_t pack_base;
     const uint16_t *pack_tab;  // [2^pack_bits], see ByteCount
+    uint64_t group_end;        // bit l: level l is the last of its group of packed digits
 };
 
 constexpr int kPackTabMax = 4096;  // group values of a packing table
 
-constexpr int kCountRows = 8;    // byte-count rows a sampler workgroup keeps in LDS
-constexpr int kCountCopies = 4;  // interleaved copies of every counter
+constexpr int kCountRows = 8;  // byte-count rows a sampler workgroup keeps in LDS
+
+// How a word becomes a row and a column digit, and digits become ids.
+// Bits: a 2 x 2 initiator with a nonzero first cell.  The cell is the number of
+// thresholds the word reaches, so the row bit is one comparison and the column
+// bit the parity of three, and both enter the ids as carries.
+// The others draw both digits as one entry (row | column << kColAt):
+// Packed: the digits of a group go into one byte of a row and one of a column
+// (base pack_base), which are what the sort takes; the ids come from the bytes.
+// Narrow: n0 <= 4, five digits of a field fit 10 bits.  Wide: any other n0.
+enum class Form { Bits, Narrow, Wide, Packed };
 
 template <int NT> __device__ __forceinline__ uint32_t bucket_of(uint32_t w, const uint32_t (&t)[15]) {
     uint32_t b = 0;
@@ -119,103 +140,172 @@ template <int NT> __device__ __forceinline__ uint32_t bucket_of(uint32_t w, cons
 }
 
 // Guide table over the top kGuideBits bits of a word: for every prefix the
-// row digit and the column digit of the cell (two byte tables, so that each
-// digit is shifted into its id by a single instruction), unless a threshold
-// falls inside the prefix's range of words (kStraddle in the row byte), where
-// the word is compared against the thresholds.  The bucket count is monotone
-// in the word, so equal buckets at both ends of a range make the entry exact
-// for every word in it.
-constexpr int kGuideBits = 13;
+// entry of the cell, unless a threshold falls inside the prefix's range of
+// words: then kStraddle and the bucket of the range's first word, from which the
+// word is compared with the thresholds that follow.  The bucket count is
+// monotone in the word, so equal buckets at both ends of a range make the entry
+// exact for every word in it.
+constexpr int kGuideBits = 14;
 constexpr uint32_t kGuideSize = 1u << kGuideBits;
-constexpr uint32_t kStraddle = 0x80;
+constexpr uint32_t kStraddle = 0x8000;
 
 // With CNT the kernel also counts the bytes of the ids it writes (ByteCount in
 // kron.hpp): one LDS row of 256 counters per counted byte position, added
 // into the global rows once per workgroup.  The counts are exact integers, so
 // the result does not depend on the order in which lanes add them.
-template <typename IdT, typename AccT, bool POW2, int NT, bool CNT>
+// Bound by vector instructions (0.8 to 0.9 of the issue rate).  Per level the
+// entry takes an index, half of a three-way OR and one multiply-add; with the
+// digits in two byte tables, appended to both ids and packed afterwards, 2^30
+// edges of a padded 3 x 3 initiator took 10.25 ms, 9.75 with one entry per cell and
+// 9.27 with 14 guide bits (13: a third of the waves held a straddling word per
+// block) and the comparison from the range's bucket.  A 2 x 2 initiator's bits from
+// three comparisons instead of a bucket, two 64-bit table shifts and two
+// inserts: 235 -> 187 us for 2^24 edges.
+template <typename IdT, typename AccT, Form FORM, bool POW2, int NT, bool CNT>
 __global__ __launch_bounds__(kFastBlock) void kron_sample_fast(FastArgs a, IdT *__restrict__ src, IdT *__restrict__ dst) {
+    constexpr bool kPacked = FORM == Form::Packed;
+    static_assert(!kPacked || (CNT && POW2), "packed ids are counted");
+    constexpr int kColAt = FORM == Form::Narrow ? 10 : 8;
     // With few thresholds the comparisons are cheaper than the table.
-    constexpr bool kGuide = NT > 3;
-    __shared__ uint8_t s_guide[kGuide ? 2 * kGuideSize : 1];  // row digits | kStraddle, then column digits
-    // Lane l counts in copy l mod kCountCopies: lanes of a wave that draw the
+    constexpr bool kGuide = FORM != Form::Bits && NT > 3;
+    __shared__ uint16_t s_guide[kGuide ? kGuideSize : 1];
+    __shared__ uint32_t s_tm1[kGuide ? NT + 1 : 1];  // thresholds, then one that no word exceeds
+    __shared__ uint16_t s_entry[kGuide ? NT + 1 : 1];
+    // Lane l counts in copy l mod kCopies: lanes of a wave that draw the
     // same byte (frequent for skewed initiators) would otherwise serialise
     // their LDS atomics on one address.
-    __shared__ uint32_t s_cnt[CNT ? kCountRows * 256 * kCountCopies : 1];
-    __shared__ uint8_t s_pack[CNT && POW2 ? kPackTabMax : 1];
-    const uint32_t copy = threadIdx.x % kCountCopies;
+    constexpr uint32_t kCopies = kGuide ? 4 : 8;
+    __shared__ uint32_t s_cnt[CNT ? kCountRows * 256 * kCopies : 1];
+    __shared__ uint16_t s_dec[kPacked ? 256 : 1];  // the group of id bits of a packed byte
+    const uint32_t copy = threadIdx.x % kCopies;
     if (CNT)
-        for (uint32_t i = threadIdx.x; i < kCountRows * 256 * kCountCopies; i += kFastBlock) s_cnt[i] = 0;
-    if (CNT && POW2 && a.pack_groups)
-        for (uint32_t i = threadIdx.x; i < (1u << a.pack_bits); i += kFastBlock) s_pack[i] = (uint8_t)a.pack_tab[i];
+        for (uint32_t i = threadIdx.x; i < kCountRows * 256 * kCopies; i += kFastBlock) s_cnt[i] = 0;
+    if (kPacked)
+        for (uint32_t i = threadIdx.x; i < (1u << a.pack_bits); i += kFastBlock) {
+            const uint32_t t = a.pack_tab[i];
+            if (t & 256u) s_dec[t & 255u] = (uint16_t)i;
+        }
+    auto entry_of = [&](uint32_t b) {
+        return ((uint32_t)(a.lut_row >> (4 * b)) & 15u) | (((uint32_t)(a.lut_col >> (4 * b)) & 15u) << kColAt);
+    };
     if (kGuide) {
         for (uint32_t i = threadIdx.x; i < kGuideSize; i += kFastBlock) {
             const uint32_t lo = i << (32 - kGuideBits), hi = lo | ((1u << (32 - kGuideBits)) - 1u);
             const uint32_t blo = bucket_of<NT>(lo, a.tm1), bhi = bucket_of<NT>(hi, a.tm1);
-            const uint32_t rd = (uint32_t)(a.lut_row >> (4 * blo)) & 15u, cd = (uint32_t)(a.lut_col >> (4 * blo)) & 15u;
-            s_guide[i] = (uint8_t)(rd | (blo == bhi ? 0u : kStraddle));
-            s_guide[kGuideSize + i] = (uint8_t)cd;
+            s_guide[i] = (uint16_t)(blo == bhi ? entry_of(blo) : blo | kStraddle);
+        }
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int i = 0; i <= NT; ++i) {
+                s_tm1[i] = i < NT ? a.tm1[i < NT ? i : 0] : 0xFFFFFFFFu;
+                s_entry[i] = (uint16_t)entry_of((uint32_t)i);
+            }
         }
     }
     if (kGuide || CNT) __syncthreads();
-    // Levels 5 blk .. 5 blk + nlev - 1 of edge (elo, ehi) from Philox block blk.
-    auto levels = [&](uint32_t elo, uint32_t ehi, uint32_t blk, uint32_t nlev, AccT &u, AccT &v) {
+    // The ids so far; (Packed) the packed ids, and the digits of the group so far.
+    AccT u, v, ku, kv;
+    uint32_t group;
+    auto end_group = [&]() {
+        const uint32_t x = group & 255u, y = group >> 8;
+        ku = (AccT)(ku << 8) | (AccT)x;
+        kv = (AccT)(kv << 8) | (AccT)y;
+        u = (AccT)(u << a.pack_bits) | (AccT)s_dec[x];
+        v = (AccT)(v << a.pack_bits) | (AccT)s_dec[y];
+        group = 0;
+    };
+    // Levels 5 blk .. 5 blk + nlev - 1 of edge (elo, ehi) from Philox block
+    // blk; pw = n0^nlev.
+    auto levels = [&](uint32_t elo, uint32_t ehi, uint32_t blk, uint32_t nlev, AccT pw) {
         const Block4 r = philox(elo, ehi, blk, a.tagword, a.key0, a.key1);
         const uint32_t ws[5] = {r.w0, r.w1, r.w2, r.w3, level4_word(r)};
-        // The block's table reads go out together; the rare words whose
-        // prefix holds a threshold are decoded by comparison.
-        uint32_t rd[5], cd[5];
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            const uint32_t g = ws[i] >> (32 - kGuideBits);
-            rd[i] = kGuide ? (uint32_t)s_guide[g] : kStraddle;
-            cd[i] = kGuide ? (uint32_t)s_guide[kGuideSize + g] : 0u;
-        }
-        if ((rd[0] | rd[1] | rd[2] | rd[3] | rd[4]) & kStraddle) {
+        if (FORM == Form::Bits) {
+            uint32_t x = 0, y = 0;
 #pragma unroll
             for (int i = 0; i < 5; ++i)
-                if (rd[i] & kStraddle) {
-                    const uint32_t b = bucket_of<NT>(ws[i], a.tm1);
-                    rd[i] = (uint32_t)(a.lut_row >> (4 * b)) & 15u;
-                    cd[i] = (uint32_t)(a.lut_col >> (4 * b)) & 15u;
+                if ((uint32_t)i < nlev) {
+                    const bool t0 = ws[i] > a.tm1[0], t1 = ws[i] > a.tm1[1], t2 = ws[i] > a.tm1[2];
+                    x = x + x + (t1 ? 1u : 0u);
+                    y = y + y + (((t0 != t1) != t2) ? 1u : 0u);
+                }
+            u = (AccT)(u << nlev) | (AccT)x;
+            v = (AccT)(v << nlev) | (AccT)y;
+            return;
+        }
+        // The block's table reads go out together; the rare words whose
+        // prefix holds a threshold are decoded by comparison.
+        uint32_t e[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) e[i] = kGuide ? (uint32_t)s_guide[ws[i] >> (32 - kGuideBits)] : kStraddle;
+        if ((e[0] | e[1] | e[2] | e[3] | e[4]) & kStraddle) {
+#pragma unroll
+            for (int i = 0; i < 5; ++i)
+                if (e[i] & kStraddle) {
+                    if (kGuide) {
+                        uint32_t b = e[i] & 15u;
+                        while (ws[i] > s_tm1[b]) ++b;
+                        e[i] = s_entry[b];
+                    } else {
+                        e[i] = entry_of(bucket_of<NT>(ws[i], a.tm1));
+                    }
                 }
         }
+        if (FORM == Form::Packed) {
+            const uint32_t ends = (uint32_t)(a.group_end >> (5 * blk)) & 31u;
+            if (nlev == 5 && ends == 16u) {  // the block is a group, or the end of one
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            if ((uint32_t)i < nlev) {
-                if (POW2) {
-                    u = (u << a.shift) | (AccT)rd[i];
-                    v = (v << a.shift) | (AccT)cd[i];
-                } else {
-                    u = u * a.n0 + (AccT)rd[i];
-                    v = v * a.n0 + (AccT)cd[i];
-                }
+                for (int i = 0; i < 5; ++i) group = __umul24(group, a.pack_base) + e[i];
+                end_group();
+            } else {
+#pragma unroll
+                for (int i = 0; i < 5; ++i)
+                    if ((uint32_t)i < nlev) {
+                        group = __umul24(group, a.pack_base) + e[i];
+                        if ((ends >> i) & 1u) end_group();
+                    }
             }
+        } else if (FORM == Form::Narrow) {
+            uint32_t x = 0;
+#pragma unroll
+            for (int i = 0; i < 5; ++i)
+                if ((uint32_t)i < nlev) x = (POW2 ? x << a.shift : __umul24(x, a.n0)) + e[i];
+            const AccT xr = (AccT)(x & 1023u), xc = (AccT)(x >> 10);
+            u = POW2 ? (AccT)(u << (a.shift * nlev)) | xr : u * pw + xr;
+            v = POW2 ? (AccT)(v << (a.shift * nlev)) | xc : v * pw + xc;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 5; ++i)
+                if ((uint32_t)i < nlev) {
+                    const AccT rd = (AccT)(e[i] & 255u), cd = (AccT)(e[i] >> 8);
+                    u = POW2 ? (AccT)(u << a.shift) | rd : u * a.n0 + rd;
+                    v = POW2 ? (AccT)(v << a.shift) | cd : v * a.n0 + cd;
+                }
         }
     };
     // Whole blocks of five levels first (no per-level test), then the rest.
     const uint32_t full = a.k / 5, rest = a.k % 5;
+    AccT pw5 = 1, pwr = 1;
+    if (FORM == Form::Narrow && !POW2) {
+        for (uint32_t i = 0; i < 5; ++i) pw5 *= a.n0;
+        for (uint32_t i = 0; i < rest; ++i) pwr *= a.n0;
+    }
     const uint64_t stride = (uint64_t)gridDim.x * kFastBlock;
     for (uint64_t i = (uint64_t)blockIdx.x * kFastBlock + threadIdx.x; i < a.num_edges; i += stride) {
-        AccT u = 0, v = 0;
+        u = v = ku = kv = 0;
+        group = 0;
         const uint64_t e = a.e_begin + i;  // the edge's index in the whole graph
         const uint32_t elo = (uint32_t)e, ehi = (uint32_t)(e >> 32);
-        for (uint32_t blk = 0; blk < full; ++blk) levels(elo, ehi, blk, 5, u, v);
-        if (rest) levels(elo, ehi, full, rest, u, v);
+        for (uint32_t blk = 0; blk < full; ++blk) levels(elo, ehi, blk, 5, pw5);
+        if (rest) levels(elo, ehi, full, rest, pwr);
         src[i] = (IdT)u;
         dst[i] = (IdT)v;
         if (CNT) {
             // The sort works on packed ids when packing is on, else on the ids.
-            AccT ku = u, kv = v;
-            if (POW2 && a.pack_groups) {
-                const AccT gmask = ((AccT)1 << a.pack_bits) - 1;
-                ku = 0;
-                kv = 0;
-                for (int j = a.pack_groups - 1; j >= 0; --j) {
-                    ku = (ku << 8) | (AccT)s_pack[(uint32_t)((u >> (a.pack_bits * j)) & gmask)];
-                    kv = (kv << 8) | (AccT)s_pack[(uint32_t)((v >> (a.pack_bits * j)) & gmask)];
-                }
-                if (a.keys32) __builtin_nontemporal_store(((uint32_t)ku << a.key_shift) | (uint32_t)kv, &a.keys32[i]);
+            if (!kPacked) {
+                ku = u;
+                kv = v;
+            } else if (a.keys32) {
+                __builtin_nontemporal_store(((uint32_t)ku << a.key_shift) | (uint32_t)kv, &a.keys32[i]);
             }
             if (a.keys) {
                 __builtin_nontemporal_store(((uint64_t)ku << a.key_shift) | (uint64_t)kv, &a.keys[i]);
@@ -225,9 +315,9 @@ __global__ __launch_bounds__(kFastBlock) void kron_sample_fast(FastArgs a, IdT *
 #pragma unroll
             for (int q = 0; q < (int)sizeof(AccT); ++q) {
                 if (q < a.dst_bytes)
-                    atomicAdd(&s_cnt[((a.dst_row + q) * 256 + (uint32_t)((kv >> (8 * q)) & 255u)) * kCountCopies + copy], 1u);
+                    atomicAdd(&s_cnt[((a.dst_row + q) * 256 + (uint32_t)((kv >> (8 * q)) & 255u)) * kCopies + copy], 1u);
                 if (q < a.src_bytes)
-                    atomicAdd(&s_cnt[((a.src_row + q) * 256 + (uint32_t)((ku >> (8 * q)) & 255u)) * kCountCopies + copy], 1u);
+                    atomicAdd(&s_cnt[((a.src_row + q) * 256 + (uint32_t)((ku >> (8 * q)) & 255u)) * kCopies + copy], 1u);
             }
         }
     }
@@ -237,7 +327,7 @@ __global__ __launch_bounds__(kFastBlock) void kron_sample_fast(FastArgs a, IdT *
             const uint32_t slot = ((i >> 8) % (uint32_t)a.row_mod) * 256 + (i & 255u);
             uint32_t t = 0;
 #pragma unroll
-            for (int c = 0; c < kCountCopies; ++c) t += s_cnt[slot * kCountCopies + c];
+            for (uint32_t c = 0; c < kCopies; ++c) t += s_cnt[slot * kCopies + c];
             if (t) atomicAdd((unsigned long long *)&a.hist[i], (unsigned long long)t);
         }
     }
@@ -450,28 +540,41 @@ int grid_fast(uint64_t items) {
     return (int)std::max<uint64_t>(1, std::min(want, cap));
 }
 
-template <typename IdT, typename AccT, bool POW2, bool CNT>
+template <typename IdT, typename AccT, Form FORM, bool POW2, bool CNT>
 void launch_fast(const FastArgs &a, uint32_t nt, void *src, void *dst, hipStream_t s) {
     const int g = grid_fast(a.num_edges);
     IdT *S = static_cast<IdT *>(src), *D = static_cast<IdT *>(dst);
-    if (nt <= 3)
-        { ProfScope _ps("kron_sample", s); kron_sample_fast<IdT, AccT, POW2, 3, CNT><<<g, kFastBlock, 0, s>>>(a, S, D); }
+    ProfScope _ps("kron_sample", s);
+    if (FORM == Form::Bits || (nt <= 3 && FORM != Form::Wide))
+        kron_sample_fast<IdT, AccT, FORM, POW2, FORM == Form::Wide ? 8 : 3, CNT><<<g, kFastBlock, 0, s>>>(a, S, D);
     else if (nt <= 8)
-        { ProfScope _ps("kron_sample", s); kron_sample_fast<IdT, AccT, POW2, 8, CNT><<<g, kFastBlock, 0, s>>>(a, S, D); }
+        kron_sample_fast<IdT, AccT, FORM, POW2, FORM == Form::Bits ? 3 : 8, CNT><<<g, kFastBlock, 0, s>>>(a, S, D);
     else
-        { ProfScope _ps("kron_sample", s); kron_sample_fast<IdT, AccT, POW2, 15, CNT><<<g, kFastBlock, 0, s>>>(a, S, D); }
+        kron_sample_fast<IdT, AccT, FORM, POW2, FORM == Form::Bits ? 3 : 15, CNT><<<g, kFastBlock, 0, s>>>(a, S, D);
+}
+
+template <typename IdT, typename AccT, bool POW2, bool CNT>
+void launch_fast_form(const FastArgs &a, Form form, uint32_t nt, void *src, void *dst, hipStream_t s) {
+    if (form == Form::Bits)
+        launch_fast<IdT, AccT, Form::Bits, POW2, CNT>(a, nt, src, dst, s);
+    else if (form == Form::Packed)
+        launch_fast<IdT, AccT, POW2 && CNT ? Form::Packed : Form::Narrow, POW2, CNT>(a, nt, src, dst, s);
+    else if (form == Form::Narrow)
+        launch_fast<IdT, AccT, Form::Narrow, POW2, CNT>(a, nt, src, dst, s);
+    else
+        launch_fast<IdT, AccT, Form::Wide, POW2, CNT>(a, nt, src, dst, s);
 }
 
 template <typename IdT, typename AccT>
-void launch_fast_any(const FastArgs &a, bool pow2, bool cnt, uint32_t nt, void *src, void *dst, hipStream_t s) {
+void launch_fast_any(const FastArgs &a, Form form, bool pow2, bool cnt, uint32_t nt, void *src, void *dst, hipStream_t s) {
     if (pow2 && cnt)
-        launch_fast<IdT, AccT, true, true>(a, nt, src, dst, s);
+        launch_fast_form<IdT, AccT, true, true>(a, form, nt, src, dst, s);
     else if (pow2)
-        launch_fast<IdT, AccT, true, false>(a, nt, src, dst, s);
+        launch_fast_form<IdT, AccT, true, false>(a, form, nt, src, dst, s);
     else if (cnt)
-        launch_fast<IdT, AccT, false, true>(a, nt, src, dst, s);
+        launch_fast_form<IdT, AccT, false, true>(a, form, nt, src, dst, s);
     else
-        launch_fast<IdT, AccT, false, false>(a, nt, src, dst, s);
+        launch_fast_form<IdT, AccT, false, false>(a, form, nt, src, dst, s);
 }
 
 template <bool VEC>
@@ -618,6 +721,8 @@ int kron_generate_counted(uint32_t n0, const float *initiator, uint32_t k, uint6
             a.lut_row |= (uint64_t)tab.row[b] << (4 * b);
             a.lut_col |= (uint64_t)tab.col[b] << (4 * b);
         }
+        Form form = n0 <= 4 ? Form::Narrow : Form::Wide;
+        if (bit_thresholds(n0, tab, a.tm1)) form = Form::Bits;
         const bool cnt = bc && count_ok(*bc, count, id_bytes) && (pow2 || !bc->pack_groups);
         if (cnt) {
             a.hist = bc->hist;
@@ -630,19 +735,23 @@ int kron_generate_counted(uint32_t n0, const float *initiator, uint32_t k, uint6
             a.keys = bc->keys;
             a.key_shift = bc->key_shift;
             a.key_sym = bc->key_sym ? count : 0;
-            if (pow2) {
+            if (bc->pack_groups) {
+                form = Form::Packed;
                 a.keys32 = bc->keys32;
-                a.pack_groups = bc->pack_groups;
                 a.pack_bits = bc->pack_bits;
+                a.pack_base = bc->pack_base;
                 a.pack_tab = bc->pack_tab;
+                const uint32_t g = (uint32_t)bc->pack_bits / shift;
+                for (uint32_t l = 0; l < k; ++l)
+                    if ((k - 1 - l) % g == 0) a.group_end |= 1ull << l;
             }
         }
         if (id_bytes == 4)
-            launch_fast_any<int32_t, uint32_t>(a, pow2, cnt, tab.nt, src, dst, s);
+            launch_fast_any<int32_t, uint32_t>(a, form, pow2, cnt, tab.nt, src, dst, s);
         else if (acc32)
-            launch_fast_any<int64_t, uint32_t>(a, pow2, cnt, tab.nt, src, dst, s);
+            launch_fast_any<int64_t, uint32_t>(a, form, pow2, cnt, tab.nt, src, dst, s);
         else
-            launch_fast_any<int64_t, uint64_t>(a, pow2, cnt, tab.nt, src, dst, s);
+            launch_fast_any<int64_t, uint64_t>(a, form, pow2, cnt, tab.nt, src, dst, s);
         if (counted) *counted = cnt;
         return check_launch("kron_generate(sample)");
     }

@@ -20,6 +20,12 @@ struct SampleTable {
 // row-major); returns SFG_EINVAL for a negative, non-finite or zero matrix.
 int build_sample_table(uint32_t n0, const float *W, SampleTable &tab);
 
+// For a 2 x 2 initiator whose first cell is drawn: a word w selects the cell
+// number #{c in 1 .. 3 : w > tm1[c - 1]} (a cell of weight zero has the threshold
+// of the next one; where there is no next one, 2^32 - 1, which no word exceeds).
+// False, and tm1 as it was, for any other initiator.
+bool bit_thresholds(uint32_t n0, const SampleTable &tab, uint32_t *tm1);
+
 // Byte counts that a sampler launch can add while it writes the ids, in place
 // of a later pass that reads the edge list to count them: byte q of every
 // destination id is counted in row dst_row + q (q < dst_bytes), byte q of
@@ -51,6 +57,7 @@ struct ByteCount {
     bool key_sym;
     uint32_t *keys32;
     int pack_groups, pack_bits;
+    uint32_t pack_base;  // r
     const uint16_t *pack_tab;
 };
 

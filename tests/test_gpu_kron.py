@@ -168,3 +168,52 @@ def test_kron_enumerate_unaligned_and_ranges(sfg, orc, id_bytes):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(s.cpu().numpy().astype(np.int64), os_[b:b + c])
         np.testing.assert_array_equal(d.cpu().numpy().astype(np.int64), od[b:b + c])
+
+
+def _support(n0, cells, seed):
+    """Random weights on the given cells (row, column)."""
+    W = np.zeros((n0, n0), np.float32)
+    rng = np.random.default_rng(seed)
+    for r, c in cells:
+        W[r, c] = rng.uniform(0.1, 1.0)
+    return W
+
+
+FULL = lambda n: [(r, c) for r in range(n) for c in range(n)]  # noqa: E731
+
+DECODES = [
+    (2, FULL(2), 5), (2, FULL(2), 33), (2, [(0, 0), (1, 0)], 9), (2, [(0, 0), (0, 1)], 11), (2, [(0, 0)], 3),  # bits
+    (2, [(0, 1), (1, 0), (1, 1)], 12),                                 # a 2 x 2 whose first cell is empty
+    (3, FULL(3), 6), (3, FULL(3), 21), (3, [(0, 2), (1, 1)], 5),       # narrow fields, base 3
+    (4, FULL(4), 7), (4, [(0, 3), (3, 0), (2, 2)], 10), (4, FULL(4), 17),  # narrow fields, shifts
+    (5, [(0, 4), (4, 0), (2, 3)], 6), (9, [(8, 8), (0, 0), (3, 5), (7, 1)], 4), (8, [(7, 7), (0, 1), (5, 2)], 11),  # wide
+    (16, [(15, 15), (15, 0), (0, 15)], 9),
+    (4, FULL(3), 5), (4, FULL(3), 7), (4, FULL(3), 14), (4, FULL(2), 8), (8, FULL(3), 6), (8, [(0, 4), (4, 4), (1, 0)], 7),
+]
+
+
+@pytest.mark.parametrize("n0,cells,k", DECODES)
+def test_kron_decodes_match_oracle(sfg, orc, n0, cells, k):
+    """Every way of decoding the levels, at level counts that are and are not
+    whole Philox blocks and whole packing groups: the ids equal the oracle's, and
+    the one-call CSR (which counts, packs and writes keys) equals the CSR of the
+    ids."""
+    import torch
+    W = _support(n0, cells, n0 * 100 + k)
+    E = 30_011
+    id_bytes = 4 if n0 ** k <= 1 << 31 else 8
+    c = dict(n0=n0, initiator=W, k=k, num_edges=E, seed=77 + k, graph_id=9, id_bytes=id_bytes)
+    src, dst = _gpu(sfg, c)
+    os_, od = orc.kron_sample(n0, W, k, E, c["seed"], 9)
+    np.testing.assert_array_equal(src.cpu().numpy().astype(np.int64), os_)
+    np.testing.assert_array_equal(dst.cpu().numpy().astype(np.int64), od)
+    if n0 ** k > 1 << 28:
+        return
+    for ib, flags in ((id_bytes, 0), (8, 0), (id_bytes, sfg.CSR_SYMMETRIZE)):
+        s1, d1, rp1, col1, h1, q1 = sfg.kron_generate_csr(n0, W, k, E, seed=c["seed"], graph_id=9, id_bytes=ib, flags=flags)
+        rp2, col2, h2, q2 = sfg.edges_to_csr(n0 ** k, s1, d1, flags=flags)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(s1.cpu().numpy().astype(np.int64), os_)
+        np.testing.assert_array_equal(d1.cpu().numpy().astype(np.int64), od)
+        assert torch.equal(rp1, rp2) and torch.equal(col1, col2) and torch.equal(h1, h2) and torch.equal(q1, q2)
+    assert sfg.device_error() == 0
