@@ -60,14 +60,13 @@ constexpr int kPlainThreads = 256;
 // Threads of a finish workgroup and keys of a thread.  Every tile's look-back
 // reads the words of the tiles in flight before it, past the caches, so the
 // words read are the tiles times the tiles in flight and a larger tile saves
-// both ways; two workgroups have to fit a CU's 160 KB of LDS all the same.
-// csr_finish in us at 256 threads x 12 keys / 512 x 12 / 1024 x 6 / 1024 x 8 /
-// 1024 x 9 / 1024 x 12: 333 / 277 / 283 / 269 / 286 / 333 for 6.6e7 8-byte keys
-// (SIMPLE); 15.1 / 14.4 / 12.9 / 12.8 / 14.7 / 16.2 for 524,288.  XOR of 2.1e8
-// and 1e8 entries at 256 x 12 / 512 x 8 / 512 x 12 / 512 x 16 / 1024 x 8: 3,670 /
-// 3,850 / 3,302 / 2,962 / 3,618.
-constexpr int kFinThreads = 1024, kFinItems = 8;  // SIMPLE: two workgroups per CU with 8-byte keys
-constexpr int kXorThreads = 512, kXorItems = 16;  // XOR: twice the registers per thread, and a walk's start shared by more entries
+// both ways, as long as two workgroups fit a CU.  csr_finish in us for 4.8e7
+// 8-byte keys (SIMPLE) at 256 threads x 16 keys / 256 x 32 / 512 x 12 / 512 x 16 / 512 x
+// 24 / 1024 x 8 / 1024 x 12: 227 / 200 / 213 / 200 / 201 / 205 / 233.  XOR of 2.1e8 and
+// 1e8 entries at 256 x 12 / 512 x 8 / 512 x 12 / 512 x 16 / 1024 x 8: 3,670 / 3,850 /
+// 3,302 / 2,962 / 3,618.
+constexpr int kFinThreads = 512, kFinItems = 16;
+constexpr int kXorThreads = 512, kXorItems = 16;
 constexpr int fin_tile(bool xor_mode) { return xor_mode ? kXorThreads * kXorItems : kFinThreads * kFinItems; }
 
 constexpr int kScanChunk = 4096;  // vertices per chunk of the row fill scan
@@ -759,6 +758,138 @@ __global__ __launch_bounds__(kPlainThreads) void csr_finish_plain(FinArgs a) {
     }
 }
 
+// The kept entries of all earlier tiles, by a decoupled look-back in which one
+// wavefront reads 64 predecessors per round trip: the nearest one with an
+// inclusive prefix ends the walk, the counts of the ones before it are added.
+// `tot` are the tile's own.  (All 64 lanes call it and get the prefix.)
+__device__ __forceinline__ uint64_t tile_prefix(const FinArgs &a, uint64_t tile, uint32_t tot, uint32_t lane) {
+    uint64_t *st = a.status + tile;
+    uint64_t prefix = 0;
+    if (tile == 0) {
+        if (lane == 0) store_agent(st, status_word(1, kFlagIncl, tot));
+    } else {
+        if (lane == 0) store_agent(st, status_word(1, kFlagAgg, tot));
+        uint64_t j = tile;  // this round reads tiles j-1 .. j-64
+        for (;;) {
+            const bool real = j > lane;
+            const uint64_t *pj = a.status + (real ? j - 1 - lane : 0);
+            uint64_t v = real ? load_agent(pj) : status_word(1, kFlagIncl, 0);
+            uint32_t spins = 0;
+            while ((uint32_t)(v >> 58) != 1u) {
+                if (++spins > kSpinLimit || ((spins & 1023) == 0 && load_agent(a.err) != 0)) {
+                    raise_device_error(a.err, DEVERR_LOOKBACK);
+                    v = status_word(1, kFlagIncl, 0);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                v = load_agent(pj);
+            }
+            const uint64_t incl = __ballot(((v >> 56) & 3) == kFlagIncl);
+            const uint32_t first = incl ? (uint32_t)__builtin_ctzll(incl) : 64u;
+            uint64_t c = lane <= first ? (v & ((1ull << 56) - 1)) : 0;
+            for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+            prefix += c;
+            if (incl) break;
+            j -= 64;  // j > 64 here: a lane past tile 0 reads an inclusive zero
+        }
+        if (lane == 0) store_agent(st, status_word(1, kFlagIncl, prefix + tot));
+    }
+    return prefix;
+}
+
+// One DPP instruction: the value of the lane below, lane 0 that of `first`.
+__device__ __forceinline__ uint32_t lane_below(uint32_t v, uint32_t first) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /*wave_shr:1*/, 0xF, 0xF, false);
+}
+__device__ __forceinline__ uint64_t lane_below(uint64_t v, uint64_t first) {
+    return make_u64(lane_below((uint32_t)v, (uint32_t)first), lane_below((uint32_t)(v >> 32), (uint32_t)(first >> 32)));
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+__device__ __forceinline__ uint64_t last_lane(uint64_t v) {
+    return make_u64(last_lane((uint32_t)v), last_lane((uint32_t)(v >> 32)));
+}
+
+// SIMPLE finish: keep the first of every run of equal entries unless it is a
+// self-loop.  Output positions come from a look-back scan of the kept counts.
+// A wave's keys are consecutive and stay in registers, item i of lane l being
+// key 64 i + l: the entry before a key is the lane below's, kept entries are
+// ranked by ballots, and the columns of an item leave as one run.  With the
+// keys and then the kept columns staged through LDS, a thread's keys consecutive,
+// 4.8e7 8-byte entries took 269 us (333 in tiles of 3,072), now 200: 0.82 GB, 4.1 TB/s.
+template <typename IdT, typename KeyT>
+__global__ __launch_bounds__(kFinThreads, 4) void csr_finish(FinArgs a) {
+    constexpr int kWaves = kFinThreads / 64;
+    __shared__ uint32_t s_counts[kWaves];  // kept entries of a wave | repeats << 16
+    __shared__ uint64_t s_base;
+    static_assert(fin_tile(false) < (1 << 16), "a tile's counts fit 16 bits");
+    const uint32_t lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t tile = blockIdx.x;  // dispatch order (see radix_pass)
+    const uint64_t base = tile * fin_tile(false) + (uint64_t)w * 64 * kFinItems;  // of the wave
+    const KeyT *K = static_cast<const KeyT *>(a.keys);
+    const KeyT mask = ((KeyT)1 << a.wb) - 1;
+    KeyT k[kFinItems];
+    const uint32_t left = base < a.N ? (uint32_t)min(a.N - base, (uint64_t)(64 * kFinItems)) : 0u;  // of the wave's
+    const KeyT *Kw = K + min(base, a.N - 1);
+#pragma unroll
+    for (int i = 0; i < kFinItems; ++i) k[i] = Kw[64 * i + lane < left ? 64 * i + lane : 0];
+    KeyT before = base > 0 ? K[min(base, a.N) - 1] : ~Kw[0];  // (nothing is equal to, or in the row of, the one before the first)
+    uint32_t keeps = 0, starts = 0, counts = 0;  // bit i: of item i
+#pragma unroll
+    for (int i = 0; i < kFinItems; ++i) {
+        const KeyT key = k[i], prev = lane_below(key, before), row = key >> a.wb;
+        before = last_lane(key);
+        const bool in = 64 * i + lane < left, dup = key == prev;
+        const bool keep = in & !dup & (row != (key & mask));
+        counts += (uint32_t)__popcll(__ballot(keep)) | (uint32_t)__popcll(__ballot(in & dup)) << 16;
+        keeps |= (uint32_t)keep << i;
+        starts |= (uint32_t)(in & (row != (prev >> a.wb)) & ((uint64_t)row < a.n)) << i;
+        // (decided here, and the row shifted out again below: of an item only the
+        // key and two bits are held meanwhile)
+        asm volatile("" : "+v"(keeps), "+v"(starts));
+    }
+    if (lane == 0) s_counts[w] = counts;
+    __syncthreads();
+    uint32_t all = 0, below = 0;
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) {
+        below += x < w ? s_counts[x] : 0u;
+        all += s_counts[x];
+    }
+    const uint32_t tot = all & 0xFFFFu;
+    if (w == 0) {
+        const uint64_t prefix = tile_prefix(a, tile, tot, lane);
+        if (lane == 0) s_base = prefix;
+    }
+    __syncthreads();
+    uint64_t c = s_base + (below & 0xFFFFu);
+    IdT *col = static_cast<IdT *>(a.col);
+#pragma unroll
+    for (int i = 0; i < kFinItems; ++i) {
+        const bool keep = (keeps >> i) & 1u;
+        const uint64_t lanes = __ballot(keep);
+        asm volatile("" : "+v"(k[i]));
+        const uint64_t at = c + count_below(lanes);
+        if ((starts >> i) & 1u) {
+            const uint64_t row = (uint64_t)(k[i] >> a.wb);
+            a.rp[row] = at;
+            if (a.rp_raw) a.rp_raw[row] = base + 64 * i + lane;
+            a.mark[row] = 1;
+        }
+        if (keep) __builtin_nontemporal_store((IdT)(k[i] & mask), &col[at]);
+        c += (uint32_t)__popcll(lanes);
+    }
+    if (threadIdx.x == 0) {
+        if (a.dups && (all >> 16)) atomicAdd((unsigned long long *)a.dups, (unsigned long long)(all >> 16));
+        // The last tile closes row n.
+        if ((tile + 1) * fin_tile(false) >= a.N) {
+            a.rp[a.n] = s_base + tot;
+            if (a.rp_raw) a.rp_raw[a.n] = a.N;
+            a.mark[a.n] = 1;
+        }
+    }
+}
+
 // The merged position of sorted random pair j: a power entry precedes the
 // random pairs equal to it.
 template <typename KeyT>
@@ -788,23 +919,20 @@ __global__ __launch_bounds__(256) void xor_split(Power p, const KeyT *R, uint64_
     split[t] = lo;
 }
 
-// Compacting finish.  SIMPLE (XOR = false): keep the first of every run of
-// equal entries unless it is a self-loop.  XOR: the sequence is the merge of a
-// Kronecker power, whose entries are computed where they are needed (power.hpp),
-// with the sorted pairs of a random graph, which may repeat; an origin bit below
-// the entry (0 = power) puts the power's copy of a pair first; keep one copy of
-// a pair present in exactly one of the two graphs.
-// Output positions come from a look-back scan of the kept counts.
-// (XOR) Only the random pairs are sorted and read.  With the power's entries
+// XOR finish.  The sequence is the merge of a Kronecker power, whose entries are
+// computed where they are needed (power.hpp), with the sorted pairs of a random
+// graph, which may repeat; an origin bit below the entry (0 = power) puts the
+// power's copy of a pair first; one copy of a pair present in exactly one of the
+// two graphs is kept.
+// Only the random pairs are sorted and read.  With the power's entries
 // written as keys, sorted and read back as well, a graph of 2.1e8 + 1e8 entries
 // took 13.5 ms, 10.4 of it in preparing, sorting and finishing 3.1e8 keys;
 // merged, 8.1 ms: sort 2.3, this kernel 3.0 (bound by the walk's arithmetic and
 // the look-back; it moves 1.7 GB, 0.35 ms at the rate of a copy).
-template <typename IdT, typename RawT, bool XOR>
-__global__ __launch_bounds__(XOR ? kXorThreads : kFinThreads, XOR ? 4 : 8) void csr_finish(FinArgs a, typename std::conditional<XOR, Power, int>::type p_) {
-    constexpr int kThreads = XOR ? kXorThreads : kFinThreads, kItems = XOR ? kXorItems : kFinItems, kTile = fin_tile(XOR);
-    constexpr int TB = XOR ? 1 : 0;  // origin bits below the entry
-    using KeyT = typename std::conditional<XOR, uint64_t, RawT>::type;
+template <typename IdT, typename RawT>
+__global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Power pw) {
+    constexpr int kThreads = kXorThreads, kItems = kXorItems, kTile = fin_tile(true);
+    using KeyT = uint64_t;
     // Blocked reads (kItems consecutive keys per thread) would hit few LDS
     // banks across the wave; one pad slot per 16 keys spreads them.  Slot 0 holds
     // the key before the tile, the last slot the key after it.
@@ -817,174 +945,120 @@ __global__ __launch_bounds__(XOR ? kXorThreads : kFinThreads, XOR ? 4 : 8) void 
     IdT *s_col = reinterpret_cast<IdT *>(s_raw);
     __shared__ uint32_t s_tmp[kThreads / 64];
     __shared__ uint64_t s_base;
-    __shared__ uint32_t s_dups[kThreads / 64];
     const int tid = threadIdx.x;
     const uint64_t tile = blockIdx.x;  // dispatch order (see radix_pass)
     const uint64_t t0 = tile * kTile;
-    if constexpr (XOR) {
-        __shared__ CountTables s_ct;
-        __shared__ uint32_t s_taken[(kTile + 31) / 32 + 1];  // positions that hold a random pair
-        const Power &pw = p_;
-        const RawT *R = static_cast<const RawT *>(a.keys);
-        power_load(pw, &s_ct);
-        for (int i = tid; i < (kTile + 31) / 32 + 1; i += kThreads) s_taken[i] = 0;
-        const uint64_t j0 = a.split[tile], j1 = a.split[tile + 1];
-        __syncthreads();
-        const uint64_t idmask = (1ull << a.wb) - 1;
-        auto count_of = [&](uint64_t key) { return power_count(pw.c, s_ct, (uint32_t)(key >> a.wb), (uint32_t)(key & idmask)); };
-        auto pack_at = [&](const PowerWalk &w) { return (((uint64_t)w.u << a.wb) | (w.high + *w.low)) << 1; };
-        for (uint64_t jb = j0; jb < j1; jb += 4 * kThreads) {  // (the loads of a round go out together)
-            uint64_t key[4];
+    __shared__ CountTables s_ct;
+    __shared__ uint32_t s_taken[(kTile + 31) / 32 + 1];  // positions that hold a random pair
+    const RawT *R = static_cast<const RawT *>(a.keys);
+    power_load(pw, &s_ct);
+    for (int i = tid; i < (kTile + 31) / 32 + 1; i += kThreads) s_taken[i] = 0;
+    const uint64_t j0 = a.split[tile], j1 = a.split[tile + 1];
+    __syncthreads();
+    const uint64_t idmask = (1ull << a.wb) - 1;
+    auto count_of = [&](uint64_t key) { return power_count(pw.c, s_ct, (uint32_t)(key >> a.wb), (uint32_t)(key & idmask)); };
+    auto pack_at = [&](const PowerWalk &w) { return (((uint64_t)w.u << a.wb) | (w.high + *w.low)) << 1; };
+    for (uint64_t jb = j0; jb < j1; jb += 4 * kThreads) {  // (the loads of a round go out together)
+        uint64_t key[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint64_t j = jb + i * kThreads + tid;
-                key[i] = R[j < j1 ? j : j1 - 1];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint64_t j = jb + i * kThreads + tid;
-                if (j >= j1) break;
-                const uint32_t x = (uint32_t)(j + count_of(key[i]) - t0);
-                s_keys[fin_slot(x + 1)] = (key[i] << 1) | 1u;
-                atomicOr(&s_taken[x / 32], 1u << (x % 32));
-            }
-        }
-        // The neighbours of the tile: either the random pair or the power
-        // entry next to it.
-        if (tid == 0) {
-            uint64_t v = 0;
-            if (t0 > 0) {
-                const uint64_t g0 = t0 - j0;  // power entries before the tile
-                const uint64_t key = j0 > 0 ? (uint64_t)R[j0 - 1] : 0;
-                if (j0 > 0 && j0 - 1 + count_of(key) == t0 - 1) {
-                    v = (key << 1) | 1u;
-                } else {
-                    PowerWalk w;
-                    w.seek(pw.w, *pw.tables, g0 - 1);
-                    v = pack_at(w);
-                }
-            }
-            s_keys[0] = v;
-        }
-        if (tid == 64) {
-            uint64_t v = 0;
-            const uint64_t t1 = t0 + kTile;
-            if (t1 < a.N) {
-                const uint64_t key = j1 < a.random ? (uint64_t)R[j1] : 0;
-                if (j1 < a.random && j1 + count_of(key) == t1) {
-                    v = (key << 1) | 1u;
-                } else {
-                    PowerWalk w;
-                    w.seek(pw.w, *pw.tables, t1 - j1);
-                    v = pack_at(w);
-                }
-            }
-            s_keys[fin_slot(kTile + 1)] = v;
-        }
-        __syncthreads();
-        // The power's entries take the other positions in order.
-        const int p0 = tid * kItems;
-        const uint64_t two = (uint64_t)s_taken[p0 / 32] | ((uint64_t)s_taken[p0 / 32 + 1] << 32);
-        const uint32_t taken = (uint32_t)(two >> (p0 % 32)) & ((1u << kItems) - 1);
-        uint32_t all;
-        const uint32_t before = block_exclusive_scan<kThreads>((uint32_t)__popc(taken), s_tmp, &all);
-        uint64_t g = t0 - j0 + p0 - before;
-        PowerWalk w;
-        bool at = false;
-        uint64_t row[kItems];
-        uint32_t high[kItems], low[kItems];  // (the loads of all items go out together)
-#pragma unroll
-        for (int j = 0; j < kItems; ++j) {
-            row[j] = high[j] = low[j] = 0;
-            if (((taken >> j) & 1u) || t0 + p0 + j >= a.N) continue;
-            if (at)
-                w.next(pw.w, *pw.tables, g);
-            else
-                w.seek(pw.w, *pw.tables, g);
-            at = true;
-            ++g;
-            row[j] = w.u;
-            high[j] = w.high;
-            low[j] = *w.low;
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t j = jb + i * kThreads + tid;
+            key[i] = R[j < j1 ? j : j1 - 1];
         }
 #pragma unroll
-        for (int j = 0; j < kItems; ++j)
-            if (!((taken >> j) & 1u)) s_keys[fin_slot(p0 + j + 1)] = ((row[j] << a.wb) | (high[j] + low[j])) << 1;
-    } else {
-        const KeyT *K = static_cast<const KeyT *>(a.keys);
-        for (int i = tid; i < kTile; i += kThreads) {
-            const uint64_t idx = t0 + i;
-            s_keys[fin_slot(i + 1)] = idx < a.N ? K[idx] : (KeyT)0;
-        }
-        if (tid == 0) {
-            s_keys[0] = t0 > 0 ? K[t0 - 1] : (KeyT)0;
-            s_keys[fin_slot(kTile + 1)] = t0 + kTile < a.N ? K[t0 + kTile] : (KeyT)0;
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t j = jb + i * kThreads + tid;
+            if (j >= j1) break;
+            const uint32_t x = (uint32_t)(j + count_of(key[i]) - t0);
+            s_keys[fin_slot(x + 1)] = (key[i] << 1) | 1u;
+            atomicOr(&s_taken[x / 32], 1u << (x % 32));
         }
     }
+    // The neighbours of the tile: either the random pair or the power
+    // entry next to it.
+    if (tid == 0) {
+        uint64_t v = 0;
+        if (t0 > 0) {
+            const uint64_t g0 = t0 - j0;  // power entries before the tile
+            const uint64_t key = j0 > 0 ? (uint64_t)R[j0 - 1] : 0;
+            if (j0 > 0 && j0 - 1 + count_of(key) == t0 - 1) {
+                v = (key << 1) | 1u;
+            } else {
+                PowerWalk w;
+                w.seek(pw.w, *pw.tables, g0 - 1);
+                v = pack_at(w);
+            }
+        }
+        s_keys[0] = v;
+    }
+    if (tid == 64) {
+        uint64_t v = 0;
+        const uint64_t t1 = t0 + kTile;
+        if (t1 < a.N) {
+            const uint64_t key = j1 < a.random ? (uint64_t)R[j1] : 0;
+            if (j1 < a.random && j1 + count_of(key) == t1) {
+                v = (key << 1) | 1u;
+            } else {
+                PowerWalk w;
+                w.seek(pw.w, *pw.tables, t1 - j1);
+                v = pack_at(w);
+            }
+        }
+        s_keys[fin_slot(kTile + 1)] = v;
+    }
+    __syncthreads();
+    // The power's entries take the other positions in order.
+    const int p0 = tid * kItems;
+    const uint64_t two = (uint64_t)s_taken[p0 / 32] | ((uint64_t)s_taken[p0 / 32 + 1] << 32);
+    const uint32_t taken = (uint32_t)(two >> (p0 % 32)) & ((1u << kItems) - 1);
+    uint32_t all;
+    const uint32_t before = block_exclusive_scan<kThreads>((uint32_t)__popc(taken), s_tmp, &all);
+    uint64_t g = t0 - j0 + p0 - before;
+    PowerWalk w;
+    bool at = false;
+    uint64_t row[kItems];
+    uint32_t high[kItems], low[kItems];  // (the loads of all items go out together)
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        row[j] = high[j] = low[j] = 0;
+        if (((taken >> j) & 1u) || t0 + p0 + j >= a.N) continue;
+        if (at)
+            w.next(pw.w, *pw.tables, g);
+        else
+            w.seek(pw.w, *pw.tables, g);
+        at = true;
+        ++g;
+        row[j] = w.u;
+        high[j] = w.high;
+        low[j] = *w.low;
+    }
+#pragma unroll
+    for (int j = 0; j < kItems; ++j)
+        if (!((taken >> j) & 1u)) s_keys[fin_slot(p0 + j + 1)] = ((row[j] << a.wb) | (high[j] + low[j])) << 1;
     __syncthreads();
     const KeyT mask = ((KeyT)1 << a.wb) - 1;
     // Blocked view: thread t owns positions t*kItems .. (t+1)*kItems-1.
-    uint32_t keep_bits = 0, nkeep = 0, ndup = 0;
+    uint32_t keep_bits = 0, nkeep = 0;
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
         const int p = tid * kItems + j;
         const uint64_t idx = t0 + p;
         if (idx < a.N) {
             const KeyT key = s_keys[fin_slot(p + 1)], prev = s_keys[fin_slot(p)];
-            bool keep;
-            if (XOR) {
-                const KeyT pair = key >> TB, next = s_keys[fin_slot(p + 2)];
-                const bool first = idx == 0 || (prev >> TB) != pair;
-                const bool alone = (key & 1) != 0 || idx + 1 >= a.N || (next >> TB) != pair;
-                keep = first && alone;
-            } else {
-                const bool dup = idx > 0 && key == prev;
-                ndup += dup;
-                keep = !dup && (key >> a.wb) != (key & mask);
-            }
+            const KeyT pair = key >> 1, next = s_keys[fin_slot(p + 2)];
+            const bool first = idx == 0 || (prev >> 1) != pair;
+            const bool alone = (key & 1) != 0 || idx + 1 >= a.N || (next >> 1) != pair;
+            const bool keep = first && alone;
             keep_bits |= (uint32_t)keep << j;
             nkeep += keep;
         }
     }
-    // Exclusive scan of kept counts over the threads, then over tiles by a
-    // decoupled look-back in which the first wavefront reads 64 predecessors
-    // per round trip: the nearest one with an inclusive prefix ends the walk,
-    // the counts of the ones before it are added.
+    // Exclusive scan of kept counts over the threads, then over tiles.
     uint32_t tot;
     const uint32_t ex = block_exclusive_scan<kThreads>(nkeep, s_tmp, &tot);
     if (tid < 64) {
         const uint32_t lane = tid;
-        uint64_t *st = a.status + tile;
-        uint64_t prefix = 0;
-        if (tile == 0) {
-            if (lane == 0) store_agent(st, status_word(1, kFlagIncl, tot));
-        } else {
-            if (lane == 0) store_agent(st, status_word(1, kFlagAgg, tot));
-            uint64_t j = tile;  // this round reads tiles j-1 .. j-64
-            for (;;) {
-                const bool real = j > lane;
-                const uint64_t *pj = a.status + (real ? j - 1 - lane : 0);
-                uint64_t v = real ? load_agent(pj) : status_word(1, kFlagIncl, 0);
-                uint32_t spins = 0;
-                while ((uint32_t)(v >> 58) != 1u) {
-                    if (++spins > kSpinLimit || ((spins & 1023) == 0 && load_agent(a.err) != 0)) {
-                        raise_device_error(a.err, DEVERR_LOOKBACK);
-                        v = status_word(1, kFlagIncl, 0);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                    v = load_agent(pj);
-                }
-                const uint64_t incl = __ballot(((v >> 56) & 3) == kFlagIncl);
-                const uint32_t first = incl ? (uint32_t)__builtin_ctzll(incl) : 64u;
-                uint64_t c = lane <= first ? (v & ((1ull << 56) - 1)) : 0;
-                for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-                prefix += c;
-                if (incl) break;
-                j -= 64;  // j > 64 here: a lane past tile 0 reads an inclusive zero
-            }
-            if (lane == 0) store_agent(st, status_word(1, kFlagIncl, prefix + tot));
-        }
+        const uint64_t prefix = tile_prefix(a, tile, tot, lane);
         if (lane == 0) s_base = prefix;
     }
     __syncthreads();
@@ -998,11 +1072,10 @@ __global__ __launch_bounds__(XOR ? kXorThreads : kFinThreads, XOR ? 4 : 8) void 
         const uint64_t idx = t0 + p;
         vals[j] = 0;
         if (idx < a.N) {
-            const KeyT key = s_keys[fin_slot(p + 1)] >> TB, prev = s_keys[fin_slot(p)] >> TB;
+            const KeyT key = s_keys[fin_slot(p + 1)] >> 1, prev = s_keys[fin_slot(p)] >> 1;
             const uint64_t row = (uint64_t)(key >> a.wb);
             if ((idx == 0 || row != (uint64_t)(prev >> a.wb)) && row < a.n) {
                 a.rp[row] = c;
-                if (a.rp_raw) a.rp_raw[row] = idx;
                 a.mark[row] = 1;
             }
             vals[j] = (IdT)(key & mask);
@@ -1017,23 +1090,11 @@ __global__ __launch_bounds__(XOR ? kXorThreads : kFinThreads, XOR ? 4 : 8) void 
         if ((keep_bits >> j) & 1u) s_col[r++] = vals[j];
     __syncthreads();
     for (uint32_t i = tid; i < tot; i += kThreads) __builtin_nontemporal_store(s_col[i], &col[s_base + i]);
-    if (a.dups) {
-        uint32_t x = ndup;
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        if ((tid & 63) == 0) s_dups[tid >> 6] = x;
-        __syncthreads();
-        if (tid == 0) {
-            uint32_t t = 0;
-            for (int i = 0; i < kThreads / 64; ++i) t += s_dups[i];
-            if (t) atomicAdd((unsigned long long *)a.dups, (unsigned long long)t);
-        }
-    }
     // The last tile closes row n: total kept = base of this tile + its kept.
     if (t0 + kTile >= a.N && tid == kThreads - 1) {
         uint64_t tail = cbase;
         for (int j = 0; j < kItems; ++j) tail += (keep_bits >> j) & 1u;
         a.rp[a.n] = tail;
-        if (a.rp_raw) a.rp_raw[a.n] = a.N;
         a.mark[a.n] = 1;
     }
 }
@@ -1563,10 +1624,10 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
         ProfScope _ps("csr_finish", s);
         xor_split<KeyT><<<(int)((P.fin_tiles + 256) / 256), 256, 0, s>>>(
             *pw, keysA, P.N, entries, P.fin_tiles, P.db, reinterpret_cast<uint64_t *>(ws + P.off_split));
-        csr_finish<IdT, KeyT, true><<<(int)P.fin_tiles, kXorThreads, 0, s>>>(fa, *pw);
+        csr_finish_xor<IdT, KeyT><<<(int)P.fin_tiles, kXorThreads, 0, s>>>(fa, *pw);
     } else if (P.simple) {
         ProfScope _ps("csr_finish", s);
-        csr_finish<IdT, KeyT, false><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa, 0);
+        csr_finish<IdT, KeyT><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa);
     } else {
         ProfScope _ps("csr_finish", s);
         csr_finish_plain<IdT, KeyT><<<fill_grid(P.N), kPlainThreads, 0, s>>>(fa);
@@ -1641,7 +1702,7 @@ int csr_check(uint64_t n, uint64_t num_edges, const void *src, const void *dst, 
     const uint64_t N = sym ? 2 * num_edges : num_edges;
     // One workgroup per tile: a dispatch's work-item count must stay below 2^32
     // (2^34 entries are 2^21 digit-pass tiles of 1,024 threads, and 2^21 finish
-    // tiles of 1,024).
+    // tiles of 512).
     if (N > (1ull << 34)) return fail(SFG_ERANGE, "edges_to_csr: more than 2^34 entries");
     P = make_plan(n, num_edges, id_bytes, flags, degree_hist32 != nullptr);
     if (P.total > 0 && !workspace) return fail(SFG_EINVAL, "edges_to_csr: workspace is NULL");

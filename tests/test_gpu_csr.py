@@ -181,3 +181,29 @@ def test_csr_short_tiles(sfg, orc, E, id_bytes, n):
     rng = np.random.default_rng(E)
     src = np.minimum(rng.zipf(1.6, size=E) - 1, n - 1)
     _check(sfg, orc, n, src, rng.integers(0, n, size=E), 0, id_bytes)
+
+
+@pytest.mark.parametrize("id_bytes", [4, 8])
+@pytest.mark.parametrize("E", [1, 63, 65, 1023, 1025, 8191, 8192, 8193, 16_385, 40_000])
+@pytest.mark.parametrize("shape", ["runs", "one pair", "loops", "one vertex", "sparse"])
+def test_csr_simple_finish_tiles(sfg, orc, shape, E, id_bytes):
+    """Runs of equal entries, self-loops and row starts across the lanes, waves and
+    tiles of the compacting finish, for lists that end inside each of them."""
+    import torch
+    rng = np.random.default_rng(E + id_bytes)
+    n = {"runs": 40, "one pair": 5, "loops": 300, "one vertex": 1, "sparse": 70_001}[shape]
+    src = rng.integers(0, n, E)
+    dst = rng.integers(0, n, E)
+    if shape == "one pair":
+        src[:], dst[:] = 3, 1
+    if shape == "loops":
+        dst = np.where(rng.uniform(size=E) < 0.9, src, dst)
+    t = torch.int32 if id_bytes == 4 else torch.int64
+    rp, col, hist, dups = sfg.edges_to_csr(n, torch.tensor(src, dtype=t, device="cuda"),
+                                           torch.tensor(dst, dtype=t, device="cuda"), flags=sfg.CSR_SIMPLE)
+    torch.cuda.synchronize()
+    assert sfg.device_error() == 0
+    orp, ocol, odups = orc.edges_to_csr(n, src, dst, symmetrize=False, simple=True)
+    np.testing.assert_array_equal(rp.cpu().numpy().astype(np.uint64), orp.astype(np.uint64))
+    np.testing.assert_array_equal(col[:int(orp[-1])].cpu().numpy().astype(np.int64), ocol)
+    assert int(dups.item()) == odups
