@@ -36,6 +36,36 @@ def test_matches_oracle(sfg, orc, seed_m, k, p_add, p_del, id_bytes):
     np.testing.assert_array_equal(dst.cpu().numpy().astype(np.int64), od)
 
 
+@pytest.mark.parametrize("n0,cells,k,p_add,p_del", [
+    (2, 1, 12, 0.4, 0.1), (3, 4, 7, 0.1, 0.2), (4, 16, 5, 0.0, 0.3), (5, 1, 2, 0.0, 0.0),
+    (6, 9, 4, 0.1, 0.0),      # more than 32 cells: 64-bit masks
+    (7, 49, 3, 0.0, 0.5), (8, 3, 4, 0.02, 0.0),
+    (8, 64, 3, 0.0, 0.0),     # the most children of a round: 256 x 64
+])
+def test_granules_and_cell_masks_match_oracle(sfg, orc, n0, cells, k, p_add, p_del):
+    import torch
+    m = np.zeros(n0 * n0, np.float32)
+    m[np.random.default_rng(n0 * 100 + cells).permutation(n0 * n0)[:cells]] = 1
+    m = m.reshape(n0, n0)
+    cap = 2_000_000
+    os_, od = orc.kron_perturbed(m, k, p_add, p_del, 23, 1, cap=cap)
+    for capacity in (max(len(os_), cells), cap):  # (no level is larger than the last one allows, or is stopped below)
+        try:
+            src, dst = sfg.kron_perturbed(n0, m, k, p_add, p_del, capacity, seed=23, graph_id=1)
+        except Exception:
+            assert capacity != cap and p_del > 0  # a level before the last was larger
+            continue
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(src.cpu().numpy().astype(np.int64), os_)
+        np.testing.assert_array_equal(dst.cpu().numpy().astype(np.int64), od)
+
+
+def test_level_too_large_names_its_iteration(sfg):
+    from paper_1003_3684_amd.native import SfgenError
+    with pytest.raises(SfgenError, match=r"iteration 3 has 1331 edges, capacity is 1330"):
+        sfg.kron_perturbed(5, FIG2, 6, 0.0, 0.0, 1330)
+
+
 def test_no_change_equals_enumerate(sfg):
     import torch
     a = sfg.kron_perturbed(5, FIG2, 5, 0.0, 0.0, 11 ** 5, seed=3)
