@@ -16,15 +16,21 @@
 // then the word; in a level with a sparse frontier nearly every lookup ends
 // in LDS.  The work is split by degree to keep the wavefronts busy: up to
 // kSmallDeg edges two lanes take a vertex (16 edges in flight), up to kMidDeg
-// 16 lanes, up to kHugeDeg a wavefront, and above that kSplit wavefronts share
-// it (a hub's list of 10^5 edges on one wavefront took most of a level).  The
+// eight, up to kHugeDeg a wavefront, and above that kSplit wavefronts share
+// it (a hub's list of 10^5 edges on one wavefront took most of a level).  All but
+// the smallest are taken from lists, since vertices of high degree stand
+// together in generated graphs: 64 neighbours of 200 edges each were a chain of
+// 64 round trips for one wavefront.  The bitmaps are written after the sweep, by
+// plain stores from the new frontier's words, and only if the next level looks
+// them up.  The
 // levels are enqueued kBatch at a time and end themselves when the level
 // before reached nothing, so the host waits once per batch and not once per
 // level.  Measured against one lane per vertex up to 64 edges, one wavefront
-// above, no bitmaps and a wait per level: 8.35 -> 1.27 ms for 64 sources over an
-// R-MAT graph of 2 million vertices and 30 million entries (the same without
-// the bitmaps 2.9 ms), 332 -> 289 ms over a PBA graph of 2^27 vertices, whose
-// words (1 GB) are read from memory.
+// above, no bitmaps and a wait per level: 8.35 -> 0.96 ms for 64 sources over an
+// R-MAT graph of 2 million vertices and 30 million entries, 332 -> 126 ms over a
+// PBA graph of 2^27 vertices, whose words (1 GB) are read from memory.  Without
+// the bitmaps the first took 2.9 ms; with the vertices up to kMidDeg swept where
+// they stand and the bitmaps written by atomics 1.27 and 289 ms.
 // Counts are integers and the OR is order-free, so the result does not depend
 // on scheduling.
 #include <string.h>
@@ -39,10 +45,11 @@ namespace {
 
 constexpr int kPathThreads = 512;
 constexpr int kGroup = 64;           // sources per bit-parallel search
-constexpr uint64_t kSmallDeg = 16;   // degree above which 16 lanes take the vertex, not 2
+constexpr uint64_t kSmallDeg = 16;   // degree above which more than 2 lanes take the vertex
 constexpr uint64_t kMidDeg = 256;    // degree above which a wavefront takes the vertex
 constexpr uint64_t kHugeDeg = 4096;  // degree above which kSplit wavefronts share it
 constexpr int kSplit = 64;
+constexpr int kMoreLanes = 8;      // lanes of a vertex above kSmallDeg (8 edges each in flight)
 constexpr int kBatch = 8;         // levels between two waits of the host
 constexpr int kCountSlots = 4;    // words a level's count is spread over (workgroup b adds to word b mod 4)
 constexpr int kListChunk = 16;    // vertices per thread of ps_init
@@ -54,10 +61,11 @@ constexpr uint64_t kDense = 8;
 // Control words of a search (64-bit).
 enum : int {
     kCtlMid = 0,     // vertices above kMidDeg in the list
-    kCtlHuge = 1,    // vertices above kHugeDeg in the list
+    kCtlHuge = 1,    // those above kHugeDeg
     kCtlAlive = 2,   // sources that reached a vertex in the level before the batch (bits)
     kCtlFront = 3,   // vertices with a nonempty word in that level
-    kCtlLevel = 4,   // then the same two words for each level of the batch
+    kCtlMore = 4,    // vertices above kSmallDeg in the list (BITS)
+    kCtlLevel = 5,   // then the words kCtlAlive and kCtlFront for each level of the batch
     kCtlWords = kCtlLevel + 2 * kBatch,
 };
 
@@ -76,69 +84,78 @@ PsPlan ps_plan(uint64_t n) {
     p.off_vis = take(n * 8);
     p.off_f0 = take(n * 8);
     p.off_f1 = take(n * 8);
-    p.off_list = take(n * 8);  // 32-bit lists and, behind them, the bitmaps; or 64-bit lists
+    p.off_list = take(n * 8);  // 32-bit lists and, behind them, the bitmap; or 64-bit lists
     p.off_ctl = take(kCtlWords * 8);
     p.off_cnt = take(kBatch * kCountSlots * 8);
     p.total = o;
     return p;
 }
 
-// The searches' device state.  BITS (n <= 2^32): list entries are 32-bit and
-// the second half of the list region holds the bitmaps -- of the current
-// frontier, of the next one, and one being cleared for the level after.
-// Without BITS list entries are 64-bit, which leaves no room for bitmaps.
-struct Bitmap {
-    uint32_t *fine;    // one bit per vertex
-    uint32_t *coarse;  // one bit per 2^shift vertices; null when shift is 0 (fine fits the LDS words)
-};
-
+// The searches' device state.  BITS (n <= 2^32): list entries are 32-bit, and the
+// second half of the list region holds the frontier's bitmap, the sweep tasks'
+// idle counts and a list of the huge vertices, as many as fit (they are taken by one wavefront each beyond
+// that: it takes a multigraph whose vertices nearly all have more than kHugeDeg
+// edges).  Without BITS list entries are 64-bit, which leaves no room for either;
+// vertices up to kMidDeg are then taken where they stand.
 template <bool BITS> struct Search {
     using ListT = typename std::conditional<BITS, uint32_t, uint64_t>::type;
     uint64_t n;
     const uint64_t *rp;
     const void *col;
     uint64_t *vis, *front, *next;  // next is written for every vertex
-    ListT *list;                   // middle degrees from the start, huge ones from the end
+    ListT *list;                   // BITS: above kSmallDeg from the start, above kMidDeg from the end
+                                   // else: above kMidDeg from the start, huge ones from the end
+    ListT *huge;                   // BITS: [huge_cap]
+    uint64_t huge_cap;
     unsigned long long *ctl;
     const unsigned long long *before;  // alive sources and frontier size of the level before
     unsigned long long *now;           // the same of this level
     unsigned long long *cnt;           // [kCountSlots] pairs found by this level
-    Bitmap f, x, z;                    // of the frontier, the next one, the one to clear
+    uint32_t *fine;                    // one bit per vertex of the frontier
+    uint32_t *coarse;                  // one bit per 2^shift vertices; null when shift is 0 (fine fits the LDS words)
+    uint8_t *idle;                     // BITS: sweeps that found nothing left to look for in 64 vertices, up to 2
     uint32_t shift;
 
     __device__ __forceinline__ uint64_t words() const { return (n + 31) / 32; }
     __device__ __forceinline__ uint64_t coarse_words() const { return ((n - 1) >> shift) / 32 + 1; }
     __device__ __forceinline__ void mark(uint64_t v) const {
         if (!BITS) return;
-        atomicOr(&x.fine[v >> 5], 1u << (v & 31));
-        if (shift) atomicOr(&x.coarse[v >> (shift + 5)], 1u << ((v >> shift) & 31));
+        atomicOr(&fine[v >> 5], 1u << (v & 31));
+        if (shift) atomicOr(&coarse[v >> (shift + 5)], 1u << ((v >> shift) & 31));
     }
+    // Whether a level whose frontier has `size` vertices looks the bitmap up.
+    __device__ __forceinline__ bool sparse(uint64_t size) const { return BITS && (shift == 0 || size < n / kDense); }
+    // Entries of the lists: above kMidDeg, and huge.
+    __device__ __forceinline__ ListT &mid_at(uint64_t i) const { return BITS ? list[n - 1 - i] : list[i]; }
+    __device__ __forceinline__ ListT &huge_at(uint64_t i) const { return BITS ? huge[i] : list[n - 1 - i]; }
 };
 
-// Per group of sources: no vertex reached, empty words and bitmaps.  The first
-// group also lists the vertices above kMidDeg (order irrelevant: every use is
-// an OR or an integer sum per vertex), one reservation per workgroup chunk.
+// Per group of sources: no vertex reached, empty words and bitmap.  The first
+// group also makes the lists (order irrelevant: every use is an OR or an integer
+// sum per vertex), one reservation per list and workgroup chunk.
 template <bool BITS>
 __global__ __launch_bounds__(kPathThreads) void ps_init(Search<BITS> a, bool lists) {
-    __shared__ uint32_t s_n[2];
-    __shared__ unsigned long long s_base[2];
+    __shared__ uint32_t s_n[3];
+    __shared__ unsigned long long s_base[3];
     constexpr uint64_t chunk = (uint64_t)kPathThreads * kListChunk;
     if (BITS) {
         const uint64_t stride = (uint64_t)gridDim.x * kPathThreads, words = a.words(), cw = a.coarse_words();
         const uint64_t i0 = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x;
-        for (uint64_t w = i0; w < words; w += stride) a.f.fine[w] = a.x.fine[w] = a.z.fine[w] = 0;
+        for (uint64_t w = i0; w < words; w += stride) a.fine[w] = 0;
+        for (uint64_t t = i0; t < (a.n + 63) / 64; t += stride) a.idle[t] = 0;
         if (a.shift)
-            for (uint64_t w = i0; w < cw; w += stride) a.f.coarse[w] = a.x.coarse[w] = a.z.coarse[w] = 0;
+            for (uint64_t w = i0; w < cw; w += stride) a.coarse[w] = 0;
     }
     for (uint64_t c0 = (uint64_t)blockIdx.x * chunk; c0 < a.n; c0 += (uint64_t)gridDim.x * chunk) {
-        if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+        if (threadIdx.x < 3) s_n[threadIdx.x] = 0;
         __syncthreads();
-        uint32_t mid = 0, huge = 0;  // bit i: vertex c0 + i kPathThreads + threadIdx.x
+        uint32_t more = 0, mid = 0, huge = 0;  // bit i: vertex c0 + i kPathThreads + threadIdx.x
 #pragma unroll
         for (int i = 0; i < kListChunk; ++i) {
             const uint64_t v = c0 + (uint64_t)i * kPathThreads + threadIdx.x;
             if (v < a.n) {
                 const uint64_t deg = a.rp[v + 1] - a.rp[v];
+                more |= (uint32_t)(BITS && deg > kSmallDeg && deg <= kMidDeg) << i;
                 mid |= (uint32_t)(deg > kMidDeg && deg <= kHugeDeg) << i;
                 huge |= (uint32_t)(deg > kHugeDeg) << i;
             }
@@ -153,17 +170,27 @@ __global__ __launch_bounds__(kPathThreads) void ps_init(Search<BITS> a, bool lis
             }
         }
         if (lists) {
-            uint32_t at[2] = {0, 0};
-            if (mid) at[0] = atomicAdd(&s_n[0], (uint32_t)__popc(mid));
-            if (huge) at[1] = atomicAdd(&s_n[1], (uint32_t)__popc(huge));
+            uint32_t at[3] = {0, 0, 0};
+            if (mid) at[kCtlMid] = atomicAdd(&s_n[kCtlMid], (uint32_t)__popc(mid));
+            if (huge) at[kCtlHuge] = atomicAdd(&s_n[kCtlHuge], (uint32_t)__popc(huge));
+            if (more) at[2] = atomicAdd(&s_n[2], (uint32_t)__popc(more));
             __syncthreads();
-            if (threadIdx.x < 2 && s_n[threadIdx.x])
-                s_base[threadIdx.x] = atomicAdd(&a.ctl[kCtlMid + threadIdx.x], (unsigned long long)s_n[threadIdx.x]);
+            if (threadIdx.x < 3 && s_n[threadIdx.x])
+                s_base[threadIdx.x] = atomicAdd(&a.ctl[threadIdx.x == 2 ? (int)kCtlMore : (int)threadIdx.x],
+                                                (unsigned long long)s_n[threadIdx.x]);
             __syncthreads();
             for (int i = 0; i < kListChunk; ++i) {
                 const uint64_t v = c0 + (uint64_t)i * kPathThreads + threadIdx.x;
-                if ((mid >> i) & 1u) a.list[s_base[0] + at[0]++] = (typename Search<BITS>::ListT)v;
-                if ((huge >> i) & 1u) a.list[a.n - 1 - (s_base[1] + at[1]++)] = (typename Search<BITS>::ListT)v;
+                using ListT = typename Search<BITS>::ListT;
+                if ((more >> i) & 1u) a.list[s_base[2] + at[2]++] = (ListT)v;
+                if ((mid >> i) & 1u) a.mid_at(s_base[kCtlMid] + at[kCtlMid]++) = (ListT)v;
+                if ((huge >> i) & 1u) {
+                    const uint64_t h = s_base[kCtlHuge] + at[kCtlHuge]++;
+                    if (h < a.huge_cap)
+                        a.huge_at(h) = (ListT)v;
+                    else
+                        a.mid_at(atomicAdd(&a.ctl[kCtlMid], 1ull)) = (ListT)v;
+                }
             }
         }
         __syncthreads();
@@ -176,8 +203,7 @@ struct Sources {
 };
 
 // One wavefront: sources may repeat, and their bits then share a word, which
-// every one of them writes.  (The sources are marked in the bitmap of this
-// launch's `x`, which the first level takes as its frontier.)
+// every one of them writes.
 template <bool BITS> __global__ __launch_bounds__(64) void ps_seed(Search<BITS> a, Sources s) {
     const uint32_t i = threadIdx.x;
     const bool in = i < s.count;
@@ -235,7 +261,7 @@ __device__ __forceinline__ uint64_t gather(const Search<BITS> &a, const Lookup &
         for (int u = 0; u < N; ++u) on &= ~((uint32_t)!(b[u] & 1u) << u);
         if (q.shift) {
 #pragma unroll
-            for (int u = 0; u < N; ++u) b[u] = (on >> u) & 1u ? a.f.fine[(uint32_t)x[u] >> 5] : 0u;
+            for (int u = 0; u < N; ++u) b[u] = (on >> u) & 1u ? a.fine[(uint32_t)x[u] >> 5] : 0u;
 #pragma unroll
             for (int u = 0; u < N; ++u) on &= ~((uint32_t)!((b[u] >> ((uint32_t)x[u] & 31)) & 1u) << u);
         }
@@ -333,110 +359,164 @@ __global__ __launch_bounds__(kPathThreads) void ps_sweep(Search<BITS> a) {
     __shared__ uint32_t s_bits[BITS ? kCoarseWords : 1];
     const uint64_t dead = ~a.before[0];  // sources whose search has ended
     if (dead == ~0ull) return;
-    Lookup q{s_bits, a.shift, BITS && (a.shift == 0 || a.before[1] < a.n / kDense)};
-    const uint64_t gtid = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x;
+    Lookup q{s_bits, a.shift, a.sparse(a.before[1])};
     if (BITS) {
         const uint32_t cw = (uint32_t)a.coarse_words();  // at most kCoarseWords
-        const uint32_t *c = a.shift ? a.f.coarse : a.f.fine;
+        const uint32_t *c = a.shift ? a.coarse : a.fine;
         if (q.bits)
             for (uint32_t i = threadIdx.x; i < cw; i += kPathThreads) s_bits[i] = c[i];
-        if (a.shift && gtid < cw) a.z.coarse[gtid] = 0;
         __syncthreads();
     }
     const uint32_t lane = threadIdx.x & 63;
-    const uint64_t wave = gtid >> 6, waves = (uint64_t)gridDim.x * (kPathThreads / 64);
-    const uint64_t nmid = a.ctl[kCtlMid], nhuge = a.ctl[kCtlHuge];
+    const uint64_t wave = ((uint64_t)blockIdx.x * kPathThreads + threadIdx.x) >> 6;
+    const uint64_t waves = (uint64_t)gridDim.x * (kPathThreads / 64);
+    const uint64_t nmid = a.ctl[kCtlMid], nhuge = min((uint64_t)a.ctl[kCtlHuge], a.huge_cap);
     uint64_t found = 0, alive = 0;
     uint32_t reached = 0;
-    // Huge vertices: raw ORs into next (ps_commit takes out what was seen).
-    for (uint64_t it = wave; it < nhuge * kSplit; it += waves) {
-        const uint64_t v = a.list[a.n - 1 - it / kSplit];
-        const uint64_t seen = a.vis[v];
-        if ((seen | dead) == ~0ull) continue;
-        const uint64_t r0 = a.rp[v], r1 = a.rp[v + 1];
-        const uint64_t per = ((r1 - r0) / kSplit + 64) & ~63ull;  // (kSplit parts of at least deg / kSplit)
-        const uint64_t e0 = r0 + (it % kSplit) * per;
-        const uint64_t acc = gather_wave<IdT, BITS>(a, q, e0, min(r1, e0 + per), seen | dead, lane) & ~seen;
-        if (lane == 0 && acc) atomicOr((unsigned long long *)&a.next[v], (unsigned long long)acc);
+    auto reach = [&](uint64_t v, uint64_t seen, uint64_t fresh) {
+        a.vis[v] = seen | fresh;
+        found += (uint64_t)__popcll(fresh);
+        alive |= fresh;
+        ++reached;
+    };
+    // The listed vertices, 64 items of the wavefront at a time: every lane reads
+    // its item's vertex, and only those with sources left to look for are swept.
+    struct Item {
+        uint64_t v, e0, e1, seen;
+        bool in, act;
+    };
+    auto item = [&](bool in, auto at, uint64_t i) {
+        Item x{0, 0, 0, 0, in, false};
+        if (in) {
+            x.v = at(i);
+            x.seen = a.vis[x.v];
+            x.e0 = a.rp[x.v];
+            x.e1 = a.rp[x.v + 1];
+            x.act = (x.seen | dead) != ~0ull;
+        }
+        return x;
+    };
+    // Huge vertices: raw ORs into next (ps_commit takes them into vis).
+    for (uint64_t i0 = wave; i0 < nhuge * kSplit; i0 += 64 * waves) {
+        const uint64_t mine = i0 + lane * waves;
+        const Item x = item(mine < nhuge * kSplit, [&](uint64_t i) { return a.huge_at(i); }, mine / kSplit);
+        for (uint64_t todo = __ballot(x.act); todo; todo &= todo - 1) {
+            const int sl = __builtin_ctzll(todo);
+            const uint64_t r0 = __shfl(x.e0, sl, 64), r1 = __shfl(x.e1, sl, 64), seen = __shfl(x.seen, sl, 64);
+            const uint64_t per = ((r1 - r0) / kSplit + 64) & ~63ull;  // (kSplit parts of at least deg / kSplit)
+            const uint64_t e0 = r0 + ((i0 + sl * waves) % kSplit) * per;
+            const uint64_t acc = gather_wave<IdT, BITS>(a, q, e0, min(r1, e0 + per), seen | dead, lane) & ~seen;
+            if (lane == (uint32_t)sl && acc) atomicOr((unsigned long long *)&a.next[x.v], (unsigned long long)acc);
+        }
     }
-    for (uint64_t it = wave; it < nmid; it += waves) {
-        const uint64_t v = a.list[it];
-        const uint64_t seen = a.vis[v];
+    for (uint64_t i0 = wave; i0 < nmid; i0 += 64 * waves) {
+        const Item x = item(i0 + lane * waves < nmid, [&](uint64_t i) { return a.mid_at(i); }, i0 + lane * waves);
         uint64_t fresh = 0;
-        if ((seen | dead) != ~0ull)
-            fresh = gather_wave<IdT, BITS>(a, q, a.rp[v], a.rp[v + 1], seen | dead, lane) & ~seen;
-        if (lane == 0) {
-            a.next[v] = fresh;
-            if (fresh) {
-                a.vis[v] = seen | fresh;
-                a.mark(v);
-                found += (uint64_t)__popcll(fresh);
-                alive |= fresh;
-                ++reached;
-            }
+        for (uint64_t todo = __ballot(x.act); todo; todo &= todo - 1) {
+            const int sl = __builtin_ctzll(todo);
+            const uint64_t e0 = __shfl(x.e0, sl, 64), e1 = __shfl(x.e1, sl, 64), seen = __shfl(x.seen, sl, 64);
+            const uint64_t acc = gather_wave<IdT, BITS>(a, q, e0, e1, seen | dead, lane) & ~seen;
+            if (lane == (uint32_t)sl) fresh = acc;
+        }
+        if (x.in) a.next[x.v] = fresh;
+        if (fresh) reach(x.v, x.seen, fresh);
+    }
+    if (BITS) {
+        const uint64_t nmore = a.ctl[kCtlMore];
+        constexpr uint32_t run = 64 / kMoreLanes;  // list entries that stand together in an item set
+        for (uint64_t i0 = wave * run; i0 < nmore; i0 += 64 * waves) {
+            const uint64_t mine = i0 + lane / run * run * waves + lane % run;
+            const Item x = item(mine < nmore, [&](uint64_t i) { return a.list[i]; }, mine);
+            const uint64_t fresh = sweep_class<IdT, BITS, kMoreLanes, 8>(a, q, x.act, x.e0, x.e1, x.seen | dead, lane) & ~x.seen;
+            if (x.in) a.next[x.v] = fresh;
+            if (fresh) reach(x.v, x.seen, fresh);
         }
     }
     // 64 consecutive vertices per wavefront: lane l reads the row and the word
     // of vertex l, then the vertices still to be swept are taken several at a
-    // time.
+    // time.  A task whose vertices need no source any more never will: once it
+    // has cleared its words of both frontier buffers it is left out (the flags
+    // of 64 tasks are read together).
     const uint64_t tasks = (a.n + 63) / 64;
-    for (uint64_t t = wave; t < tasks; t += waves) {
-        const uint64_t v = t * 64 + lane;
-        uint64_t e0 = 0, e1 = 0, seen = 0;
-        if (v < a.n) {
-            e0 = a.rp[v];
-            e1 = a.rp[v + 1];
-            seen = a.vis[v];
-        }
-        if (BITS && lane < 2 && t * 2 + lane < a.words()) a.z.fine[t * 2 + lane] = 0;
-        const uint64_t deg = e1 - e0, done = seen | dead;
-        const bool light = v < a.n && deg <= kMidDeg, act = light && deg > 0 && done != ~0ull;
-        const uint64_t mine = sweep_class<IdT, BITS, 2, 8>(a, q, act && deg <= kSmallDeg, e0, e1, done, lane) |
-                              sweep_class<IdT, BITS, 16, 4>(a, q, act && deg > kSmallDeg, e0, e1, done, lane);
-        const uint64_t fresh = mine & ~seen;
-        if (light) a.next[v] = fresh;
-        const uint64_t nonempty = __ballot(fresh != 0);
-        if (!nonempty) continue;
-        if (fresh) {
-            a.vis[v] = seen | fresh;
-            found += (uint64_t)__popcll(fresh);
-            alive |= fresh;
-            ++reached;
-        }
-        if (BITS) {
-            const uint32_t half = (uint32_t)(nonempty >> (32 * (lane & 1)));
-            if (lane < 2 && half) atomicOr(&a.x.fine[t * 2 + lane], half);
-            if (a.shift) {
-                uint32_t m = fresh ? 1u << ((v >> a.shift) & 31) : 0u;  // (64 vertices share a word: shift >= 1)
-                for (int off = 1; off < 64; off <<= 1) m |= __shfl_xor(m, off, 64);
-                if (lane == 0) atomicOr(&a.x.coarse[v >> (a.shift + 5)], m);
+    for (uint64_t t0 = wave; t0 < tasks; t0 += 64 * waves) {
+        const uint64_t mine = t0 + lane * waves;  // this lane's task
+        const uint32_t idle = mine >= tasks ? 2u : BITS ? (uint32_t)a.idle[mine] : 0u;
+        uint64_t todo = __ballot(idle < 2);
+        uint64_t quiet = 0;  // tasks with nothing to look for
+        while (todo) {
+            const uint32_t which = (uint32_t)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            const uint64_t v = (t0 + which * waves) * 64 + lane;
+            uint64_t e0 = 0, e1 = 0, seen = 0;
+            if (v < a.n) {
+                e0 = a.rp[v];
+                e1 = a.rp[v + 1];
+                seen = a.vis[v];
             }
+            const uint64_t deg = e1 - e0, done = seen | dead;
+            const bool here = v < a.n && deg <= (BITS ? kSmallDeg : kMidDeg), act = here && deg > 0 && done != ~0ull;
+            uint64_t got = sweep_class<IdT, BITS, 2, 8>(a, q, act && deg <= kSmallDeg, e0, e1, done, lane);
+            if (!BITS) got |= sweep_class<IdT, BITS, 16, 4>(a, q, act && deg > kSmallDeg, e0, e1, done, lane);
+            const uint64_t fresh = got & ~seen;
+            if (here) a.next[v] = fresh;
+            if (fresh) reach(v, seen, fresh);
+            if (BITS && !__any(act)) quiet |= 1ull << which;
         }
+        if (BITS && ((quiet >> lane) & 1u)) a.idle[mine] = (uint8_t)(idle + 1);
     }
     add_level(a, found, reached, alive);
 }
 
-// The huge vertices' level: what was not seen before stays in next; their
-// words of the frontier just swept are cleared for the level after.
+// After a level's sweep.  The huge vertices' new sources go into vis, and their
+// words of the frontier just swept are cleared for the level after.  (What the
+// sweep ORed into next had been filtered by vis: it is the new frontier's word.)
+// The new frontier's bitmap, if the next level looks it up: a wavefront takes
+// the vertices of a coarse word, or 64 where there is no coarse bitmap.
 template <bool BITS> __global__ __launch_bounds__(kPathThreads) void ps_commit(Search<BITS> a) {
     if (a.before[0] == 0) return;
-    const uint64_t nhuge = a.ctl[kCtlHuge];
+    const uint64_t nhuge = min((uint64_t)a.ctl[kCtlHuge], a.huge_cap);
+    const bool bits = a.sparse(a.now[1]);  // (before the huge vertices are added: at most once too often)
+    const uint64_t gtid = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x, threads = (uint64_t)gridDim.x * kPathThreads;
     uint64_t found = 0, alive = 0;
     uint32_t reached = 0;
-    for (uint64_t h = (uint64_t)blockIdx.x * kPathThreads + threadIdx.x; h < nhuge; h += (uint64_t)gridDim.x * kPathThreads) {
-        const uint64_t v = a.list[a.n - 1 - h];
-        const uint64_t seen = a.vis[v], fresh = a.next[v] & ~seen;
-        a.next[v] = fresh;
+    for (uint64_t h = gtid; h < nhuge; h += threads) {
+        const uint64_t v = a.huge_at(h);
+        const uint64_t seen = a.vis[v], fresh = a.next[v];
         a.front[v] = 0;
         if (fresh) {
             a.vis[v] = seen | fresh;
-            a.mark(v);
             found += (uint64_t)__popcll(fresh);
             alive |= fresh;
             ++reached;
         }
     }
-    add_level(a, found, reached, alive);
+    if (BITS && bits) {
+        const uint32_t lane = threadIdx.x & 63;
+        const uint64_t per = a.shift ? 32ull << a.shift : 64, tasks = (a.n + per - 1) / per;
+        for (uint64_t t = gtid >> 6; t < tasks; t += threads >> 6) {
+            uint32_t m = 0;
+            for (uint64_t v0 = t * per; v0 < min(a.n, (t + 1) * per); v0 += 256) {
+                uint64_t w[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint64_t v = v0 + 64 * u + lane;
+                    w[u] = 64 * u < per && v < a.n ? a.next[v] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint64_t v = v0 + 64 * u + lane, on = __ballot(w[u] != 0);
+                    if (lane < 2 && 64 * u < per && (v0 + 64 * u) / 32 + lane < a.words())
+                        a.fine[(v0 + 64 * u) / 32 + lane] = (uint32_t)(on >> (32 * lane));
+                    m |= w[u] ? 1u << ((v >> a.shift) & 31) : 0u;
+                }
+            }
+            if (a.shift) {
+                for (int off = 1; off < 64; off <<= 1) m |= __shfl_xor(m, off, 64);
+                if (lane == 0) a.coarse[t] = m;
+            }
+        }
+    }
+    if (gtid - threadIdx.x < nhuge) add_level(a, found, reached, alive);  // (whole workgroups)
 }
 
 // A batch's counts into the totals; the last level's words go to the start of
@@ -484,20 +564,24 @@ int run_paths(uint64_t n, const uint64_t *rp, const IdT *col, const int64_t *sou
     a.list = reinterpret_cast<typename Search<BITS>::ListT *>(ws + P.off_list);
     a.ctl = reinterpret_cast<unsigned long long *>(ws + P.off_ctl);
     unsigned long long *cnt = reinterpret_cast<unsigned long long *>(ws + P.off_cnt);
+    a.huge_cap = n;
     if (BITS) {
-        // Behind the n list entries: 3 ceil(n / 32) words, and above 2^18
-        // vertices 3 x 2^13 more, within the region's max(8 n, 256) bytes.
-        const uint64_t words = (n + 31) / 32;
+        // Behind the n list entries: ceil(n / 32) words, above 2^18 vertices
+        // kCoarseWords more, a byte per 64 vertices, and the huge vertices' list
+        // in what is left.
+        const uint64_t words = (n + 31) / 32, region = align256(n * 8) / 4;
         while (((n - 1) >> a.shift) / 32 >= kCoarseWords) ++a.shift;
         uint32_t *b = reinterpret_cast<uint32_t *>(ws + P.off_list) + n;
-        a.f.fine = b;
-        a.x.fine = b + words;
-        a.z.fine = b + 2 * words;
+        uint64_t used = n + words;
+        a.fine = b;
         if (a.shift) {
-            a.f.coarse = b + 3 * words;
-            a.x.coarse = a.f.coarse + kCoarseWords;
-            a.z.coarse = a.x.coarse + kCoarseWords;
+            a.coarse = b + words;
+            used += kCoarseWords;
         }
+        a.idle = reinterpret_cast<uint8_t *>(ws + P.off_list) + used * 4;
+        used += words / 2 / 4 + 1;  // (a byte per 64 vertices)
+        a.huge = reinterpret_cast<typename Search<BITS>::ListT *>(ws + P.off_list) + used;
+        a.huge_cap = region - used;
     }
     const int g = grid_of(n), gi = grid_of((n + kListChunk - 1) / kListChunk);
     ps_clear<<<1, 64, 0, s>>>(out, a.ctl, cnt);
@@ -508,7 +592,6 @@ int run_paths(uint64_t n, const uint64_t *rp, const IdT *col, const int64_t *sou
         for (uint32_t i = 0; i < src.count; ++i) src.v[i] = sources[g0 + i];
         { ProfScope _ps("path_level", s); ps_init<BITS><<<gi, kPathThreads, 0, s>>>(a, g0 == 0); }
         ps_seed<BITS><<<1, 64, 0, s>>>(a, src);
-        std::swap(a.f, a.x);  // the seeds' bitmap is the first level's frontier
         // A level reaches at least one new (source, vertex) pair or ends the
         // search, so at most n levels run.
         for (uint64_t level = 1;; level += kBatch) {
@@ -517,13 +600,9 @@ int run_paths(uint64_t n, const uint64_t *rp, const IdT *col, const int64_t *sou
                 a.cnt = cnt + i * kCountSlots;
                 a.now = a.ctl + kCtlLevel + 2 * i;
                 { ProfScope _ps("path_level", s); ps_sweep<IdT, BITS><<<g, kPathThreads, 0, s>>>(a); }
-                { ProfScope _ps("path_level", s); ps_commit<BITS><<<8, kPathThreads, 0, s>>>(a); }
+                { ProfScope _ps("path_level", s); ps_commit<BITS><<<BITS ? g : 8, kPathThreads, 0, s>>>(a); }
                 a.before = a.now;
                 std::swap(a.front, a.next);
-                const Bitmap f = a.f;
-                a.f = a.x;
-                a.x = a.z;
-                a.z = f;
             }
             ps_fold<<<1, 1, 0, s>>>(a.ctl, cnt, level, out);
             unsigned long long alive = 0;

@@ -102,3 +102,24 @@ def test_degree_classes_match_oracle(sfg, orc, hub):
     exp = orc.path_stats(n, rp, col, srcs)
     for id_bytes in (4, 8):
         assert _gpu(sfg, n, rp, col, srcs, id_bytes) == tuple(int(x) for x in exp)
+
+
+@pytest.mark.parametrize("n,deg,tail", [(64, 4200, 0), (40, 4097, 11), (300, 17, 11), (5000, 40, 11)])
+def test_listed_degrees_match_oracle(sfg, orc, n, deg, tail):
+    """Multigraphs whose vertices are all listed: nearly all above the huge degree
+    (at 64 vertices more than its list holds), or all of a middle degree; a tail of
+    a few vertices, so that most of the search finds nothing left in them."""
+    rng = np.random.default_rng(n + deg)
+    u = np.repeat(np.arange(n), (deg + 1) // 2)
+    v = (u + 1 + rng.integers(0, n - 1, len(u))) % n
+    path = np.arange(n - 1, n + tail)  # behind the last vertex
+    u, v = np.concatenate([u, path[:-1]]), np.concatenate([v, path[1:]])
+    u, v = np.concatenate([u, v]), np.concatenate([v, u])
+    order = np.argsort(u, kind="stable")
+    total = n + tail
+    rp = np.concatenate([[0], np.cumsum(np.bincount(u, minlength=total))]).astype(np.uint64)
+    col = v[order].astype(np.int64)
+    srcs = rng.integers(0, total, 70)
+    exp = orc.path_stats(total, rp, col, srcs)
+    for id_bytes in (4, 8):
+        assert _gpu(sfg, total, rp, col, srcs, id_bytes) == tuple(int(x) for x in exp)
