@@ -752,22 +752,28 @@ constexpr int kTileThreads = 1024;
 constexpr int kTileWaves = kTileThreads / 64;
 constexpr uint32_t kTileMax = 16384;
 constexpr int kTilePer = (int)kTileMax / kTileThreads;  // slots of a thread
+// The same where no tile has more than kTileThreads kTileShort slots: the slots
+// are then spread over all wavefronts (4,096 of them: 16 ranking steps of four
+// wavefronts become four of sixteen; 64 such tiles 17.9 -> 12.5 us).
+constexpr int kTileShort = 4;
 constexpr uint32_t kTilePmax = 1024;
-static_assert(kTilePer == 16 && kTilePmax <= (uint32_t)kTileThreads, "one label per thread in the label scans");
+static_assert(kTilePmax <= (uint32_t)kTileThreads, "one label per thread in the label scans");
 static_assert(kTileMax <= (1u << 14), "a slot fits the permutation word's low 14 bits");
 
-template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_substitute_tile(SubArgs a) {
+template <typename IdT, int PER> __global__ __launch_bounds__(kTileThreads) void pba_substitute_tile(SubArgs a) {
+    constexpr uint32_t kSlots = kTileThreads * PER;       // of a tile
     __shared__ uint64_t s_cur[kTilePmax];                 // list entry of each label's first slot in the tile
     __shared__ uint16_t s_off[kTilePmax];                 // label bases in sorted order
-    __shared__ uint32_t s_r1[kTileMax];  // labels in slot order (u16), then slot | label << 14 of each sorted position
+    __shared__ uint32_t s_r1[kSlots];  // labels in slot order (u16), then slot | label << 14 of each sorted position
     uint16_t *s_lab = reinterpret_cast<uint16_t *>(s_r1);
     uint32_t *s_perm = s_r1;
     __shared__ uint32_t s_part[kTileWaves];
-    __shared__ uint32_t s_u[kTileMax];  // per-wave label counts [kTileWaves][Pm] and ranks [kTileMax], then values
+    // Per-wave label counts [kTileWaves][Pm] and ranks [kSlots], then values.
+    constexpr uint32_t kShared = kTileWaves * kTilePmax / 2 + kSlots / 2;
+    __shared__ uint32_t s_u[kShared > kSlots ? kShared : kSlots];
     uint16_t *s_wcnt = reinterpret_cast<uint16_t *>(s_u);
     uint16_t *s_rank = s_wcnt + kTileWaves * kTilePmax;
     uint32_t *s_val = s_u;
-    static_assert(kTileWaves * kTilePmax * 2 + kTileMax * 2 <= kTileMax * 4, "counts and ranks share the values' space");
     const PGraph &p = a.G.one;  // a single graph
     const uint32_t P = p.P;
     const uint32_t xcd = blockIdx.x % kXcd, nper = gridDim.x / kXcd;
@@ -796,16 +802,16 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
         tn = (uint32_t)std::min<uint64_t>(p.CT, len - tfirst);
         return true;
     };
-    // A tile's labels (thread: 16 slots, wave w holding slots w*1024 ..
-    // w*1024+1023) and the two parts of label tid's list position.
-    uint32_t lr[kTilePer];
+    // A tile's labels (thread: PER slots, wave w holding slots w 64 PER ..
+    // (w + 1) 64 PER - 1) and the two parts of label tid's list position.
+    uint32_t lr[PER];
     uint64_t cur_a = 0;
     uint32_t cur_b = 0;
     auto load_tile = [&](uint32_t tq, uint32_t tn, uint64_t tb0, uint64_t tfirst) {
         const int tid = threadIdx.x;
 #pragma unroll
-        for (int st = 0; st < kTilePer; ++st) {
-            const uint32_t i = (uint32_t)(tid >> 6) * 1024u + (uint32_t)st * 64u + (tid & 63);
+        for (int st = 0; st < PER; ++st) {
+            const uint32_t i = (uint32_t)(tid >> 6) * (64u * PER) + (uint32_t)st * 64u + (tid & 63);
             lr[st] = a.lab[tb0 + tfirst + (i < tn ? i : tn - 1)];
         }
         const uint32_t tau = (uint32_t)(tfirst / p.CT);
@@ -827,8 +833,8 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
         const uint32_t lane = (uint32_t)tid & 63u, w = (uint32_t)tid >> 6;
         // This tile's labels and list positions into LDS, counts cleared.
 #pragma unroll
-        for (int st = 0; st < kTilePer; ++st) {
-            const uint32_t i = w * 1024u + (uint32_t)st * 64u + lane;
+        for (int st = 0; st < PER; ++st) {
+            const uint32_t i = w * (64u * PER) + (uint32_t)st * 64u + lane;
             if (i < nsub) s_lab[i] = (uint16_t)lr[st];
         }
         if ((uint32_t)tid < P) s_cur[tid] = cur_a + cur_b;
@@ -842,16 +848,16 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
         while (lt < lt_end && !(next = tile_of(lt, nq, nn, nb0, nfirst))) lt += nper;
         if (next) load_tile(nq, nn, nb0, nfirst);
         __builtin_amdgcn_wave_barrier();
-        // Stable ranks inside each wave's 1,024 slots: every ballot over one
+        // Stable ranks inside each wave's slots: every ballot over one
         // label bit keeps the lanes that agree with this lane on that bit.
         // Four steps at a time, so that their ballot chains interleave.
-        for (int st = 0; st < kTilePer; st += 4) {
+        for (int st = 0; st < PER; st += 4) {
             uint32_t ii[4], ll[4];
             bool vv[4];
             uint64_t pp[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                ii[u] = w * 1024u + (uint32_t)(st + u) * 64u + lane;
+                ii[u] = w * (64u * PER) + (uint32_t)(st + u) * 64u + lane;
                 vv[u] = ii[u] < nsub;
                 ll[u] = vv[u] ? s_lab[ii[u]] : 0u;
                 pp[u] = __ballot(vv[u]);
@@ -900,16 +906,16 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
         __syncthreads();
         // Sorted position of every slot (its label and rank first taken
         // into registers: the permutation overwrites the labels).
-        uint32_t lk[kTilePer];
+        uint32_t lk[PER];
 #pragma unroll
-        for (int st = 0; st < kTilePer; ++st) {
-            const uint32_t i = w * 1024u + (uint32_t)st * 64u + lane;
+        for (int st = 0; st < PER; ++st) {
+            const uint32_t i = w * (64u * PER) + (uint32_t)st * 64u + lane;
             lk[st] = i < nsub ? (uint32_t)s_lab[i] | ((uint32_t)s_rank[i] << 16) : 0u;
         }
         __syncthreads();
 #pragma unroll 4
-        for (int st = 0; st < kTilePer; ++st) {
-            const uint32_t i = w * 1024u + (uint32_t)st * 64u + lane;
+        for (int st = 0; st < PER; ++st) {
+            const uint32_t i = w * (64u * PER) + (uint32_t)st * 64u + lane;
             if (i < nsub) {
                 const uint32_t l = lk[st] & 0xFFFFu;
                 s_perm[s_off[l] + s_wcnt[w * kTilePmax + l] + (lk[st] >> 16)] = i | (l << 14);
@@ -917,9 +923,9 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
         }
         __syncthreads();  // the counts are dead: their space takes the values
         // Gather in sorted order.
-        uint32_t v[kTilePer];
+        uint32_t v[PER];
 #pragma unroll
-        for (int k = 0; k < kTilePer; ++k) {
+        for (int k = 0; k < PER; ++k) {
             const uint32_t i = (uint32_t)k * kTileThreads + tid;
             const uint32_t ic = i < nsub ? i : nsub - 1;  // a valid address for every lane
             const uint32_t l = s_perm[ic] >> 14;
@@ -931,7 +937,7 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
         // The values stored are the local destinations: the label's first
         // vertex plus the endpoint (below 2^32: checked on the host).
 #pragma unroll
-        for (int k = 0; k < kTilePer; ++k) {
+        for (int k = 0; k < PER; ++k) {
             const uint32_t i = (uint32_t)k * kTileThreads + tid;
             const uint32_t x = s_perm[i < nsub ? i : nsub - 1];
             const uint32_t l = x >> 14;
@@ -942,7 +948,7 @@ template <typename IdT> __global__ __launch_bounds__(kTileThreads) void pba_subs
         // Edges in slot order.
         const uint64_t vstart = p.vbase + part_start(q, p.n, P);
 #pragma unroll 4
-        for (int k = 0; k < kTilePer; ++k) {
+        for (int k = 0; k < PER; ++k) {
             const uint32_t i = (uint32_t)k * kTileThreads + tid;
             if (i < nsub) {
                 const uint64_t j = first + i;
@@ -1183,10 +1189,17 @@ static int enqueue(const PbaPlan &pl, const Graphs &G, const Factions &fac, uint
         ProfScope _ps("pba_substitute", s);
         if (count == 1 && pl.Pmax <= kTilePmax && G.one.n < (1ull << 32)) {
             const unsigned gt = (unsigned)std::min<uint64_t>((uint64_t)cus, (per_xcd) * kXcd) / kXcd * kXcd;
-            if (id_bytes == 4)
-                pba_substitute_tile<int32_t><<<std::max(gt, (unsigned)kXcd), kTileThreads, 0, s>>>(sa);
+            const unsigned gw = std::max(gt, (unsigned)kXcd);
+            const uint64_t longest = (G.one.n + G.one.P - 1) / G.one.P * G.one.m;  // partition, in slots
+            const bool few = std::min<uint64_t>(longest, G.one.CT) <= (uint64_t)kTileThreads * kTileShort;
+            if (id_bytes == 4 && few)
+                pba_substitute_tile<int32_t, kTileShort><<<gw, kTileThreads, 0, s>>>(sa);
+            else if (id_bytes == 4)
+                pba_substitute_tile<int32_t, kTilePer><<<gw, kTileThreads, 0, s>>>(sa);
+            else if (few)
+                pba_substitute_tile<int64_t, kTileShort><<<gw, kTileThreads, 0, s>>>(sa);
             else
-                pba_substitute_tile<int64_t><<<std::max(gt, (unsigned)kXcd), kTileThreads, 0, s>>>(sa);
+                pba_substitute_tile<int64_t, kTilePer><<<gw, kTileThreads, 0, s>>>(sa);
         } else if (id_bytes == 4)
             pba_substitute<int32_t><<<gsub, kSubThreads, lds, s>>>(sa);
         else

@@ -107,3 +107,17 @@ def test_tile_dealing_matches_oracle(sfg, orc, n, m, P):
     assert sfg.device_error() == 0
     es, ed = orc.pba_generate(n, m, P, 0.2, P)
     assert np.array_equal(src.cpu().numpy(), es) and np.array_equal(dst.cpu().numpy(), ed)
+
+
+@pytest.mark.parametrize("id_bytes", [4, 8])
+@pytest.mark.parametrize("n,m,P", [(126, 1, 63), (64 * 1024, 4, 64), (64 * 1024 + 1, 4, 64), (4096, 1, 1), (4097, 1, 1),
+                                   (16_385, 1, 2), (1024 * 40, 3, 1024), (1025 * 9, 7, 1024)])
+def test_substitution_tiles_match_oracle(sfg, orc, n, m, P, id_bytes):
+    """Partitions on both sides of the 4,096 slots up to which the substitution
+    spreads a tile over all wavefronts, up to its 1,024 labels."""
+    import torch
+    src, dst = sfg.pba_generate(n, m, P, 0.3, seed=n, id_bytes=id_bytes)
+    torch.cuda.synchronize()
+    assert sfg.device_error() == 0
+    es, ed = orc.pba_generate(n, m, P, 0.3, n)
+    assert np.array_equal(src.cpu().numpy(), es) and np.array_equal(dst.cpu().numpy(), ed)
