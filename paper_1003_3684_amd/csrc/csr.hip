@@ -761,14 +761,15 @@ __global__ __launch_bounds__(kPlainThreads) void csr_finish_plain(FinArgs a) {
 // The kept entries of all earlier tiles, by a decoupled look-back in which one
 // wavefront reads 64 predecessors per round trip: the nearest one with an
 // inclusive prefix ends the walk, the counts of the ones before it are added.
-// `tot` are the tile's own.  (All 64 lanes call it and get the prefix.)
+// `tot` are the tile's own, published by one lane as early as they are known.
+// (All 64 lanes call tile_prefix and get the prefix.)
+__device__ __forceinline__ void tile_publish(const FinArgs &a, uint64_t tile, uint32_t tot) {
+    store_agent(a.status + tile, status_word(1, tile == 0 ? kFlagIncl : kFlagAgg, tot));
+}
 __device__ __forceinline__ uint64_t tile_prefix(const FinArgs &a, uint64_t tile, uint32_t tot, uint32_t lane) {
     uint64_t *st = a.status + tile;
     uint64_t prefix = 0;
-    if (tile == 0) {
-        if (lane == 0) store_agent(st, status_word(1, kFlagIncl, tot));
-    } else {
-        if (lane == 0) store_agent(st, status_word(1, kFlagAgg, tot));
+    if (tile > 0) {
         uint64_t j = tile;  // this round reads tiles j-1 .. j-64
         for (;;) {
             const bool real = j > lane;
@@ -858,6 +859,7 @@ __global__ __launch_bounds__(kFinThreads, 4) void csr_finish(FinArgs a) {
     }
     const uint32_t tot = all & 0xFFFFu;
     if (w == 0) {
+        if (lane == 0) tile_publish(a, tile, tot);
         const uint64_t prefix = tile_prefix(a, tile, tot, lane);
         if (lane == 0) s_base = prefix;
     }
@@ -895,7 +897,8 @@ __global__ __launch_bounds__(kFinThreads, 4) void csr_finish(FinArgs a) {
 template <typename KeyT>
 __device__ __forceinline__ uint64_t merged_position(const Power &p, const CountTables &t, const KeyT *R, uint64_t j, int wb) {
     const uint64_t key = R[j];
-    return j + power_count(p.c, t, (uint32_t)(key >> wb), (uint32_t)(key & ((1ull << wb) - 1)));
+    bool member;
+    return j + power_count(p.c, t, (uint32_t)(key >> wb), (uint32_t)(key & ((1ull << wb) - 1)), &member);
 }
 
 // split[t] for every tile boundary t = 0 .. tiles, by binary search.
@@ -933,16 +936,11 @@ template <typename IdT, typename RawT>
 __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Power pw) {
     constexpr int kThreads = kXorThreads, kItems = kXorItems, kTile = fin_tile(true);
     using KeyT = uint64_t;
-    // Blocked reads (kItems consecutive keys per thread) would hit few LDS
-    // banks across the wave; one pad slot per 16 keys spreads them.  Slot 0 holds
-    // the key before the tile, the last slot the key after it.
-    // The same LDS later holds the tile's kept columns in output order, so
-    // the column stores are coalesced; it is sized for 8-byte elements.
-    constexpr size_t kKeyBytes = (kTile + kTile / 16 + 2) * sizeof(KeyT);
-    constexpr size_t kColBytes = kTile * sizeof(IdT);
-    __shared__ uint64_t s_raw[((kKeyBytes > kColBytes ? kKeyBytes : kColBytes) + 7) / 8];
-    KeyT *s_keys = reinterpret_cast<KeyT *>(s_raw);
-    IdT *s_col = reinterpret_cast<IdT *>(s_raw);
+    // The walk writes kItems consecutive entries per thread, which would hit few
+    // LDS banks across the wave; one pad slot per 16 entries spreads them.  Slot
+    // 0 holds the entry before the tile, the last slot the one after it.
+    __shared__ KeyT s_keys[kTile + kTile / 16 + 2];
+    __shared__ int32_t s_change[kThreads / 64];
     __shared__ uint32_t s_tmp[kThreads / 64];
     __shared__ uint64_t s_base;
     const int tid = threadIdx.x;
@@ -956,20 +954,29 @@ __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Powe
     const uint64_t j0 = a.split[tile], j1 = a.split[tile + 1];
     __syncthreads();
     const uint64_t idmask = (1ull << a.wb) - 1;
-    auto count_of = [&](uint64_t key) { return power_count(pw.c, s_ct, (uint32_t)(key >> a.wb), (uint32_t)(key & idmask)); };
+    auto count_of = [&](uint64_t key, bool *member) {
+        return power_count(pw.c, s_ct, (uint32_t)(key >> a.wb), (uint32_t)(key & idmask), member);
+    };
+    // The tile keeps its power entries, less those that a random pair takes out
+    // (it follows them), plus the first copies of the other random pairs: known
+    // from the random pairs alone, and published before the walk.
+    int32_t change = 0;
+    bool member;
     auto pack_at = [&](const PowerWalk &w) { return (((uint64_t)w.u << a.wb) | (w.high + *w.low)) << 1; };
     for (uint64_t jb = j0; jb < j1; jb += 4 * kThreads) {  // (the loads of a round go out together)
-        uint64_t key[4];
+        uint64_t key[4], prev[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint64_t j = jb + i * kThreads + tid;
-            key[i] = R[j < j1 ? j : j1 - 1];
+            const uint64_t j = min(jb + i * kThreads + tid, j1 - 1);
+            key[i] = R[j];
+            prev[i] = R[j > 0 ? j - 1 : 0];
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint64_t j = jb + i * kThreads + tid;
             if (j >= j1) break;
-            const uint32_t x = (uint32_t)(j + count_of(key[i]) - t0);
+            const uint32_t x = (uint32_t)(j + count_of(key[i], &member) - t0);
+            if (j == 0 || prev[i] != key[i]) change += member ? (x > 0 ? -1 : 0) : 1;
             s_keys[fin_slot(x + 1)] = (key[i] << 1) | 1u;
             atomicOr(&s_taken[x / 32], 1u << (x % 32));
         }
@@ -981,7 +988,7 @@ __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Powe
         if (t0 > 0) {
             const uint64_t g0 = t0 - j0;  // power entries before the tile
             const uint64_t key = j0 > 0 ? (uint64_t)R[j0 - 1] : 0;
-            if (j0 > 0 && j0 - 1 + count_of(key) == t0 - 1) {
+            if (j0 > 0 && j0 - 1 + count_of(key, &member) == t0 - 1) {
                 v = (key << 1) | 1u;
             } else {
                 PowerWalk w;
@@ -996,8 +1003,9 @@ __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Powe
         const uint64_t t1 = t0 + kTile;
         if (t1 < a.N) {
             const uint64_t key = j1 < a.random ? (uint64_t)R[j1] : 0;
-            if (j1 < a.random && j1 + count_of(key) == t1) {
+            if (j1 < a.random && j1 + count_of(key, &member) == t1) {
                 v = (key << 1) | 1u;
+                if (member && (j1 == 0 || (uint64_t)R[j1 - 1] != key)) --change;  // (its copy ends this tile)
             } else {
                 PowerWalk w;
                 w.seek(pw.w, *pw.tables, t1 - j1);
@@ -1006,95 +1014,117 @@ __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Powe
         }
         s_keys[fin_slot(kTile + 1)] = v;
     }
+    for (int off = 32; off > 0; off >>= 1) change += __shfl_xor(change, off, 64);
+    if ((tid & 63) == 0) s_change[tid >> 6] = change;
     __syncthreads();
+    uint32_t all_kept = (uint32_t)(min(a.N - t0, (uint64_t)kTile) - (j1 - j0));
+#pragma unroll
+    for (int x = 0; x < kThreads / 64; ++x) all_kept += (uint32_t)s_change[x];
+    if (tid == 0) tile_publish(a, tile, all_kept);
     // The power's entries take the other positions in order.
-    const int p0 = tid * kItems;
-    const uint64_t two = (uint64_t)s_taken[p0 / 32] | ((uint64_t)s_taken[p0 / 32 + 1] << 32);
-    const uint32_t taken = (uint32_t)(two >> (p0 % 32)) & ((1u << kItems) - 1);
-    uint32_t all;
-    const uint32_t before = block_exclusive_scan<kThreads>((uint32_t)__popc(taken), s_tmp, &all);
-    uint64_t g = t0 - j0 + p0 - before;
-    PowerWalk w;
-    bool at = false;
-    uint64_t row[kItems];
-    uint32_t high[kItems], low[kItems];  // (the loads of all items go out together)
-#pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        row[j] = high[j] = low[j] = 0;
-        if (((taken >> j) & 1u) || t0 + p0 + j >= a.N) continue;
-        if (at)
-            w.next(pw.w, *pw.tables, g);
-        else
-            w.seek(pw.w, *pw.tables, g);
-        at = true;
-        ++g;
-        row[j] = w.u;
-        high[j] = w.high;
-        low[j] = *w.low;
-    }
-#pragma unroll
-    for (int j = 0; j < kItems; ++j)
-        if (!((taken >> j) & 1u)) s_keys[fin_slot(p0 + j + 1)] = ((row[j] << a.wb) | (high[j] + low[j])) << 1;
-    __syncthreads();
-    const KeyT mask = ((KeyT)1 << a.wb) - 1;
-    // Blocked view: thread t owns positions t*kItems .. (t+1)*kItems-1.
-    uint32_t keep_bits = 0, nkeep = 0;
-#pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        const int p = tid * kItems + j;
-        const uint64_t idx = t0 + p;
-        if (idx < a.N) {
-            const KeyT key = s_keys[fin_slot(p + 1)], prev = s_keys[fin_slot(p)];
-            const KeyT pair = key >> 1, next = s_keys[fin_slot(p + 2)];
-            const bool first = idx == 0 || (prev >> 1) != pair;
-            const bool alone = (key & 1) != 0 || idx + 1 >= a.N || (next >> 1) != pair;
-            const bool keep = first && alone;
-            keep_bits |= (uint32_t)keep << j;
-            nkeep += keep;
+    {
+        const int p0 = tid * kItems;
+        const uint64_t two = (uint64_t)s_taken[p0 / 32] | ((uint64_t)s_taken[p0 / 32 + 1] << 32);
+        const uint32_t taken = (uint32_t)(two >> (p0 % 32)) & ((1u << kItems) - 1);
+        uint32_t all;
+        const uint32_t before = block_exclusive_scan<kThreads>((uint32_t)__popc(taken), s_tmp, &all);
+        // (the first wavefront looks back here, so that no tile waits for a
+        // slower one's walk)
+        if (tid < 64) {
+            const uint64_t prefix = tile_prefix(a, tile, all_kept, tid);
+            if (tid == 0) s_base = prefix;
         }
-    }
-    // Exclusive scan of kept counts over the threads, then over tiles.
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_scan<kThreads>(nkeep, s_tmp, &tot);
-    if (tid < 64) {
-        const uint32_t lane = tid;
-        const uint64_t prefix = tile_prefix(a, tile, tot, lane);
-        if (lane == 0) s_base = prefix;
+        uint64_t g = t0 - j0 + p0 - before;
+        PowerWalk w;
+        bool at = false;
+        uint64_t row[kItems];
+        uint32_t high[kItems], low[kItems];  // (the loads of all items go out together)
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) {
+            row[j] = high[j] = low[j] = 0;
+            if (((taken >> j) & 1u) || t0 + p0 + j >= a.N) continue;
+            if (at)
+                w.next(pw.w, *pw.tables, g);
+            else
+                w.seek(pw.w, *pw.tables, g);
+            at = true;
+            ++g;
+            row[j] = w.u;
+            high[j] = w.high;
+            low[j] = *w.low;
+        }
+#pragma unroll
+        for (int j = 0; j < kItems; ++j)
+            if (!((taken >> j) & 1u)) s_keys[fin_slot(p0 + j + 1)] = ((row[j] << a.wb) | (high[j] + low[j])) << 1;
     }
     __syncthreads();
-    const uint64_t cbase = s_base + ex;
+    // From here on a wave's entries are consecutive, item i of lane l being
+    // entry 64 i + l (as in csr_finish).  eq: lanes whose pair equals the one
+    // before it; an entry is kept if it is the first of its pair and either a
+    // random pair or not followed by the same one.
+    const uint32_t lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t p1 = (uint32_t)w * 64 * kItems;  // the wave's first entry in the tile
+    const uint32_t left = (uint32_t)(t0 + p1 < a.N ? min(a.N - t0 - p1, (uint64_t)(64 * kItems)) : 0);
+    const uint64_t mask = (1ull << a.wb) - 1;
+    KeyT k[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) k[i] = s_keys[fin_slot(p1 + 64 * i + lane + 1)];
+    KeyT before = t0 + p1 > 0 ? s_keys[fin_slot(p1)] : ~0ull;  // (no pair is as large)
+    const KeyT after = s_keys[fin_slot(p1 + 64 * kItems + 1)];
+    uint32_t keeps = 0, starts = 0, kept = 0;
+    uint64_t eq = 0, first = 0;  // of the item before, whose keeping the next item's eq settles
+    bool random = false;
+#pragma unroll
+    for (int i = 0; i <= kItems; ++i) {
+        uint64_t eq_i = 0, first_i = 0;
+        bool random_i = false;
+        if (i < kItems) {
+            const KeyT key = k[i], prev = lane_below(key, before);
+            before = last_lane(key);
+            const bool in = 64 * i + lane < left;
+            eq_i = __ballot(in & ((key ^ prev) <= 1u));
+            first_i = __ballot(in) & ~eq_i;
+            random_i = key & 1u;
+            const uint64_t row = key >> (a.wb + 1);
+            starts |= (uint32_t)(in & (row != prev >> (a.wb + 1)) & (row < a.n)) << i;
+        } else {
+            eq_i = 64 * kItems <= left && t0 + p1 + 64 * kItems < a.N && (after ^ before) <= 1u;
+        }
+        if (i > 0) {
+            const uint64_t lanes = first & (__ballot(random) | ~(eq >> 1 | eq_i << 63));
+            kept += (uint32_t)__popcll(lanes);
+            keeps |= (uint32_t)(lanes >> lane & 1u) << (i - 1);
+        }
+        eq = eq_i;
+        first = first_i;
+        random = random_i;
+        asm volatile("" : "+v"(keeps), "+v"(starts));
+    }
+    if (lane == 0) s_tmp[w] = kept;
+    __syncthreads();
+    uint32_t below = 0;
+#pragma unroll
+    for (int x = 0; x < kThreads / 64; ++x) below += x < w ? s_tmp[x] : 0u;
+    uint64_t c = s_base + below;
     IdT *col = static_cast<IdT *>(a.col);
-    uint64_t c = cbase;
-    IdT vals[kItems];
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        const int p = tid * kItems + j;
-        const uint64_t idx = t0 + p;
-        vals[j] = 0;
-        if (idx < a.N) {
-            const KeyT key = s_keys[fin_slot(p + 1)] >> 1, prev = s_keys[fin_slot(p)] >> 1;
-            const uint64_t row = (uint64_t)(key >> a.wb);
-            if ((idx == 0 || row != (uint64_t)(prev >> a.wb)) && row < a.n) {
-                a.rp[row] = c;
-                a.mark[row] = 1;
-            }
-            vals[j] = (IdT)(key & mask);
-            c += (keep_bits >> j) & 1u;
+    for (int i = 0; i < kItems; ++i) {
+        const bool keep = (keeps >> i) & 1u;
+        const uint64_t lanes = __ballot(keep);
+        asm volatile("" : "+v"(k[i]));
+        const uint64_t at = c + count_below(lanes);
+        if ((starts >> i) & 1u) {
+            const uint64_t row = k[i] >> (a.wb + 1);
+            a.rp[row] = at;
+            a.mark[row] = 1;
         }
+        if (keep) __builtin_nontemporal_store((IdT)(k[i] >> 1 & mask), &col[at]);
+        c += (uint32_t)__popcll(lanes);
     }
-    // Kept columns to LDS in output order, then coalesced stores.
-    __syncthreads();  // every read of the keys is done
-    uint32_t r = ex;
-#pragma unroll
-    for (int j = 0; j < kItems; ++j)
-        if ((keep_bits >> j) & 1u) s_col[r++] = vals[j];
-    __syncthreads();
-    for (uint32_t i = tid; i < tot; i += kThreads) __builtin_nontemporal_store(s_col[i], &col[s_base + i]);
-    // The last tile closes row n: total kept = base of this tile + its kept.
-    if (t0 + kTile >= a.N && tid == kThreads - 1) {
-        uint64_t tail = cbase;
-        for (int j = 0; j < kItems; ++j) tail += (keep_bits >> j) & 1u;
-        a.rp[a.n] = tail;
+    // The last tile closes row n.
+    if (tid == 0 && t0 + kTile >= a.N) {
+        a.rp[a.n] = s_base + all_kept;
         a.mark[a.n] = 1;
     }
 }

@@ -131,8 +131,9 @@ __device__ __forceinline__ void power_load(const Power &p, CountTables *s) {
         for (uint32_t i = threadIdx.x; i <= p.c.n[w]; i += blockDim.x) s->start[w][i] = t.start[w][i];
 }
 
-// The number of the power's entries at or below (u, c), both vertices of it.
-__device__ __forceinline__ uint64_t power_count(const PowerDigits &p, const CountTables &t, uint32_t u, uint32_t c) {
+// The number of the power's entries at or below (u, c), both vertices of it;
+// *member: whether (u, c) is one.
+__device__ __forceinline__ uint64_t power_count(const PowerDigits &p, const CountTables &t, uint32_t u, uint32_t c, bool *member) {
     uint64_t below = 0;     // entries in rows below u
     uint32_t d = 1, r = 0;  // entries that share u's digits so far; columns of u below c so far
     bool in = true;         // c's digits so far are neighbours of u's
@@ -147,6 +148,7 @@ __device__ __forceinline__ uint64_t power_count(const PowerDigits &p, const Coun
         in = in && (f & 0x80u);
         d *= deg;
     }
+    *member = in;
     return below + r + (in ? 1u : 0u);
 }
 
