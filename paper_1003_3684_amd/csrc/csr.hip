@@ -63,8 +63,8 @@ constexpr int kPlainThreads = 256;
 // both ways, as long as two workgroups fit a CU.  csr_finish in us for 4.8e7
 // 8-byte keys (SIMPLE) at 256 threads x 16 keys / 256 x 32 / 512 x 12 / 512 x 16 / 512 x
 // 24 / 1024 x 8 / 1024 x 12: 227 / 200 / 213 / 200 / 201 / 205 / 233.  XOR of 2.1e8 and
-// 1e8 entries at 256 x 12 / 512 x 8 / 512 x 12 / 512 x 16 / 1024 x 8: 3,670 / 3,850 /
-// 3,302 / 2,962 / 3,618.
+// 1e8 entries at 256 x 16 / 512 x 8 / 512 x 12 / 512 x 16: 2,562 / 2,469 / 2,605 /
+// 2,398.
 constexpr int kFinThreads = 512, kFinItems = 16;
 constexpr int kXorThreads = 512, kXorItems = 16;
 constexpr int fin_tile(bool xor_mode) { return xor_mode ? kXorThreads * kXorItems : kFinThreads * kFinItems; }
@@ -930,8 +930,11 @@ __global__ __launch_bounds__(256) void xor_split(Power p, const KeyT *R, uint64_
 // Only the random pairs are sorted and read.  With the power's entries
 // written as keys, sorted and read back as well, a graph of 2.1e8 + 1e8 entries
 // took 13.5 ms, 10.4 of it in preparing, sorting and finishing 3.1e8 keys;
-// merged, 8.1 ms: sort 2.3, this kernel 3.0 (bound by the walk's arithmetic and
-// the look-back; it moves 1.7 GB, 0.35 ms at the rate of a copy).
+// merged, this kernel takes 2.3 ms and the sort 2.3.  It moves 1.7 GB (0.35 ms at
+// the rate of a copy) and is bound by the walk's arithmetic and the latency of
+// its table loads.  Counting what it keeps only after the walk made every tile
+// wait for the slowest one in flight (3.0 ms; 2.4 with the counts published
+// before it), and a walk that waited for each middle column itself 2.4.
 template <typename IdT, typename RawT>
 __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Power pw) {
     constexpr int kThreads = kXorThreads, kItems = kXorItems, kTile = fin_tile(true);
@@ -962,7 +965,7 @@ __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Powe
     // from the random pairs alone, and published before the walk.
     int32_t change = 0;
     bool member;
-    auto pack_at = [&](const PowerWalk &w) { return (((uint64_t)w.u << a.wb) | (w.high + *w.low)) << 1; };
+    auto pack_at = [&](const PowerWalk &w) { return (((uint64_t)w.u << a.wb) | (w.rest + *w.mid * pw.w.midplace + *w.low)) << 1; };
     for (uint64_t jb = j0; jb < j1; jb += 4 * kThreads) {  // (the loads of a round go out together)
         uint64_t key[4], prev[4];
 #pragma unroll
@@ -1037,11 +1040,10 @@ __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Powe
         uint64_t g = t0 - j0 + p0 - before;
         PowerWalk w;
         bool at = false;
-        uint64_t row[kItems];
-        uint32_t high[kItems], low[kItems];  // (the loads of all items go out together)
+        uint32_t row[kItems], rest[kItems], mid[kItems], low[kItems];  // (the loads of all items go out together)
 #pragma unroll
         for (int j = 0; j < kItems; ++j) {
-            row[j] = high[j] = low[j] = 0;
+            row[j] = rest[j] = mid[j] = low[j] = 0;
             if (((taken >> j) & 1u) || t0 + p0 + j >= a.N) continue;
             if (at)
                 w.next(pw.w, *pw.tables, g);
@@ -1050,12 +1052,14 @@ __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Powe
             at = true;
             ++g;
             row[j] = w.u;
-            high[j] = w.high;
+            rest[j] = w.rest;
+            mid[j] = *w.mid;
             low[j] = *w.low;
         }
 #pragma unroll
         for (int j = 0; j < kItems; ++j)
-            if (!((taken >> j) & 1u)) s_keys[fin_slot(p0 + j + 1)] = ((row[j] << a.wb) | (high[j] + low[j])) << 1;
+            if (!((taken >> j) & 1u))
+                s_keys[fin_slot(p0 + j + 1)] = (((uint64_t)row[j] << a.wb) | (rest[j] + mid[j] * pw.w.midplace + low[j])) << 1;
     }
     __syncthreads();
     // From here on a wave's entries are consecutive, item i of lane l being

@@ -36,6 +36,7 @@ struct PowerDigits {
     uint32_t place[kPowerMaxDigits];   // vertices below digit l
     uint32_t pmagic[kPowerMaxDigits];  // floor((2^32 - 1) / place)
     uint64_t below[kPowerMaxDigits];   // entries of the digits below l
+    uint32_t midplace;                 // place of the digit above the lowest one; 0 if there is none
 };
 
 struct PowerSeed {
@@ -85,6 +86,7 @@ inline void group_levels(uint32_t n0, uint64_t e0, uint32_t k, uint64_t max_n, u
     if (top != g)
         for (uint32_t l = p.n[1] = 1; l <= top; ++l) p.n[1] *= n0;
     p.nmagic = 0xFFFFFFFFu / p.n[0];
+    p.midplace = p.digits > 1 ? p.n[0] : 0u;
     uint64_t place = 1, below = 1;
     for (uint32_t l = p.digits; l-- > 0;) {
         p.place[l] = (uint32_t)place;
@@ -155,14 +157,16 @@ __device__ __forceinline__ uint64_t power_count(const PowerDigits &p, const Coun
 // A walk over the power's entries in order.  A row's columns are the sums of
 // the columns of its digits, the lowest digit's running fastest: a step moves
 // a pointer into that digit's row of the list, and where it wraps one into the
-// next digit's.
+// next digit's.  The column of the entry is rest + *mid p.midplace + *low: the
+// two loads are left to the caller, who can issue those of many entries before
+// waiting for one.
 struct PowerWalk {
     uint32_t u;                              // row
     const uint16_t *low;                     // column of the lowest digit
     uint32_t low_left, low_deg;              // entries of its row from here on, and in all
-    const uint16_t *mid;                     // the same for the digit above it (null: there is none)
+    const uint16_t *mid;                     // the same for the digit above it (any entry if there is none)
     uint32_t mid_left, mid_deg;
-    uint32_t high, rest;                     // column of the digits above the lowest, above the middle one
+    uint32_t rest;                           // column of the digits above the middle one
     uint32_t i, d;                           // index of `rest` among those of the row, and their number
 
     // To entry g < entries.
@@ -195,9 +199,9 @@ struct PowerWalk {
         const uint32_t il = r - hi * low_deg;
         low = t.list[v[0]] + s[0] + il;
         low_left = low_deg - il;
-        mid = nullptr;
+        mid = t.list[0];
         i = 0;
-        rest = high = 0;
+        rest = 0;
         mid_left = 1;
         if (p.digits == 1) return;
         i = power_div(hi, mid_deg, t.degmagic[v[1]][x[1]]);
@@ -205,7 +209,6 @@ struct PowerWalk {
         mid = t.list[v[1]] + s[1] + im;
         mid_left = mid_deg - im;
         if (p.digits > 2) above(p, t);
-        high = rest + *mid * p.place[p.digits - 2];
     }
     // rest: the column of index i of row u's digits above the middle one.
     __device__ __forceinline__ void above(const PowerDigits &p, const PowerTables &t) {
@@ -235,9 +238,7 @@ struct PowerWalk {
             above(p, t);
         } else {
             seek(p, t, g);
-            return;
         }
-        high = rest + *mid * p.place[p.digits - 2];
     }
 };
 
