@@ -370,7 +370,7 @@ int enqueue_batch(const BatchPlan &P, const sfg_ensemble_tuning &tu, uint32_t sa
                        col, reinterpret_cast<uint64_t *>(ws + P.off_hist), nullptr, ws + P.off_gen,
                        P.off_rp - P.off_gen, s, &raw);
     if (rc != SFG_OK) return rc;
-    const StatGraph *stab = reinterpret_cast<const StatGraph *>(tables + P.tab_s);
+    StatGraph *stab = reinterpret_cast<StatGraph *>(tables + P.tab_s);
     return stats_enqueue(stab, (uint32_t)P.st.size(), P.chunks, P.nv, raw, rp, col, P.id_bytes, samples, stat_seed,
                          hist, gamma, closed, ws + P.off_scratch, s,
                          (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(P.chunks, cap)));

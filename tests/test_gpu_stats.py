@@ -55,3 +55,17 @@ def test_stats_random(sfg, orc, trial):
 def test_stats_no_wedge(sfg, orc):
     # a single edge and a self-loop: no wedge anywhere
     _check(sfg, orc, 5, np.array([0, 3]), np.array([1, 3]), 100, 1, 0)
+
+
+@pytest.mark.parametrize("samples", [0, 500])
+@pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 1024 * 4096, 1024 * 4096 + 1])
+def test_stats_chunk_edges(sfg, orc, n, samples):
+    """Vertex counts around a chunk and around the 1,024 chunk sums that the
+    workgroups add up themselves; the hub sits in the last chunk, and one list has
+    no wedge."""
+    rng = np.random.default_rng(n + samples)
+    E = min(3 * n, 40_000)
+    src = np.where(rng.uniform(size=E) < 0.3, n - 1, rng.integers(0, n, size=E))
+    dst = rng.integers(0, n, size=E)
+    _check(sfg, orc, n, src, dst, samples, 5, 3)
+    _check(sfg, orc, n, src[:1], dst[:1], samples, 5, 3, 8)
