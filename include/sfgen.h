@@ -320,8 +320,8 @@ int graph_stats(uint64_t n, uint64_t num_edges, const void *src, const void *dst
  * out:           device, 3 u64.
  * workspace:     device, path_stats_workspace_bytes(n) (32 B per vertex).
  * The call searches 64 sources at a time and waits for the stream after
- * every level to decide whether the search is over, so it returns with the
- * work done.
+ * every few levels to decide whether the search is over, so it returns with
+ * the work done.
  * Errors: EINVAL (n == 0, bad id_bytes, NULL buffers, a source outside
  * [0, n)); ENOSPACE.
  * ---------------------------------------------------------------------- */
@@ -347,9 +347,8 @@ int path_stats(uint64_t n, const uint64_t *row_ptr, const void *col, int id_byte
  * n0 <= 8, n0^k <= 2^32.  capacity bounds the edges of every iteration (the
  * output arrays and the workspace are sized by it); an iteration above it
  * fails with ENOSPACE.  *num_edges (device u64) receives the edge count.
- * The call waits for the stream after every iteration (the next size comes
- * from the device).
- * workspace: device, kron_perturbed_workspace_bytes(capacity) (32 B per edge).
+ * The call waits for the stream at the end (the sizes come from the device).
+ * workspace: device, kron_perturbed_workspace_bytes(capacity) (24 B per edge).
  * Errors: EINVAL (n0 outside [2, 8], k == 0, probabilities outside [0, 1],
  * bad seed entry or no edge, bad id_bytes, graph_id >= 2^24, NULL buffers);
  * ERANGE (n0^k > 2^32, k > 255, ids beyond int32 with id_bytes 4); ENOSPACE.
