@@ -371,6 +371,18 @@ struct SetupArgs {
     uint64_t lab_words, sel_words;
 };
 
+// p[0 .. n) = v by all threads (this one's index i0 of `stride`), in 16-byte
+// stores where p is aligned for them (1e9 words: 0.75 ms, 0.78 in 4-byte stores).
+__device__ __forceinline__ void fill_words(uint32_t *p, uint64_t n, uint32_t v, uint64_t i0, uint64_t stride) {
+    if ((uintptr_t)p % 16 == 0) {
+        const uint64_t quads = n / 4;
+        for (uint64_t i = i0; i < quads; i += stride) reinterpret_cast<uint4 *>(p)[i] = make_uint4(v, v, v, v);
+        if (i0 < n % 4) p[4 * quads + i0] = v;
+    } else {
+        for (uint64_t i = i0; i < n; i += stride) p[i] = v;
+    }
+}
+
 __global__ __launch_bounds__(1024) void pba_setup(SetupArgs a) {
     __shared__ uint64_t sm[1024];
     if (blockIdx.x < kXcd) {
@@ -392,8 +404,8 @@ __global__ __launch_bounds__(1024) void pba_setup(SetupArgs a) {
             a.base1[s] = p.ebase + (uint64_t)p.m * part_start(s - p.seg0, p.n, p.P);
         }
     }
-    for (uint64_t i = i0; i < a.lab_words; i += stride) a.lab[i] = 0xFFFFFFFFu;
-    for (uint64_t i = i0; i < a.sel_words; i += stride) a.sel[i] = kSelNone;
+    fill_words(a.lab, a.lab_words, 0xFFFFFFFFu, i0, stride);
+    fill_words(a.sel, a.sel_words, kSelNone, i0, stride);
 }
 
 // From the list lengths D: workgroups 0-7 the phase-2 tile queues, workgroup 8
