@@ -1263,15 +1263,38 @@ __global__ __launch_bounds__(1024) void rowfill_chunks(FillArrays f) {
     }
 }
 
+// The marks of rows v0 .. v0+3 (v0 a multiple of 4).
+__device__ __forceinline__ uint32_t load_marks4(const uint8_t *mark, uint64_t v0, uint64_t n1) {
+    uint32_t bits = 0;
+    if (v0 + 4 <= n1) {
+        const uint32_t m = *reinterpret_cast<const uint32_t *>(mark + v0);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) bits |= ((m >> (8 * b)) & 1u) << b;
+    } else {
+        for (uint64_t v = v0; v < n1; ++v) bits |= (uint32_t)(mark[v] & 1u) << (uint32_t)(v - v0);
+    }
+    return bits;
+}
+
 // The first marked value at or after row v (a multiple of 16); kNoRow if there
-// is none.  Whole workgroup; marked rows only ever hold their final value.
+// is none.  Whole workgroup of 256, 16,384 rows per step; marked rows only ever
+// hold their final value.
 __device__ __forceinline__ uint64_t marked_from(const FillArrays::One &a, uint64_t v, uint64_t n1, uint32_t *s_first) {
-    for (; v < n1; v += kScanChunk) {
-        const uint64_t v0 = v + (uint64_t)threadIdx.x * (kScanChunk / 256);
-        const uint32_t bits = v0 < n1 ? load_marks16(a.mark, v0, n1) : 0u;
+    constexpr int kAhead = 4;
+    for (; v < n1; v += 256 * 16 * kAhead) {
+        uint32_t bits[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const uint64_t v0 = v + (uint64_t)(q * 256 + (int)threadIdx.x) * 16;
+            bits[q] = v0 < n1 ? load_marks16(a.mark, v0, n1) : 0u;
+        }
+        uint32_t mine = ~0u;
+#pragma unroll
+        for (int q = kAhead - 1; q >= 0; --q)
+            if (bits[q]) mine = (uint32_t)(q * 256 + (int)threadIdx.x) * 16 + (uint32_t)__builtin_ctz(bits[q]);
         if (threadIdx.x == 0) *s_first = ~0u;
         __syncthreads();
-        if (bits) atomicMin(s_first, (uint32_t)threadIdx.x * (kScanChunk / 256) + (uint32_t)__builtin_ctz(bits));
+        if (mine != ~0u) atomicMin(s_first, mine);
         __syncthreads();
         const uint32_t first = *s_first;
         __syncthreads();
@@ -1284,18 +1307,21 @@ __device__ __forceinline__ uint64_t marked_from(const FillArrays::One &a, uint64
 // paper's Results section) over rows v < n1 - 1 is counted from the filled
 // values, the degree of v being the sum of A[v+1] - A[v] over the arrays that
 // count towards it.  SELF: the value after the chunk is looked for in the
-// marks here, not taken from the chunk scan.
+// marks here, not taken from the chunk scan, and the chunks are shorter: such a
+// fill has few of them, and each takes as long as its serial steps.
+constexpr int kSelfChunk = 1024;
+
 template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_apply(FillArrays f) {
-    constexpr int per = kScanChunk / 256;
+    constexpr int kChunk = SELF ? kSelfChunk : kScanChunk, per = kChunk / 256;
     // Thread t owns rows t*per .. t*per+per-1 of the chunk; the results go
     // through LDS (one pad word per `per`) so the stores are coalesced.
-    __shared__ uint64_t s_out[kScanChunk + kScanChunk / per];
+    __shared__ uint64_t s_out[kChunk + kChunk / per];
     __shared__ uint64_t s_wave[4];
     __shared__ uint32_t s_h[32];
     __shared__ uint32_t s_first;
     const int tid = threadIdx.x;
     const uint32_t lane = tid & 63;
-    const uint64_t n1 = f.n1, c0 = (uint64_t)blockIdx.x * kScanChunk;
+    const uint64_t n1 = f.n1, c0 = (uint64_t)blockIdx.x * kChunk;
     const uint64_t v0 = c0 + (uint64_t)tid * per;
     if (HIST && tid < 32) s_h[tid] = 0;
     uint64_t deg[HIST ? per : 1];  // of row c0 + 256 j + tid
@@ -1304,7 +1330,7 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
         for (int j = 0; j < per; ++j) deg[j] = 0;
     for (int q = 0; q < f.count; ++q) {
         const FillArrays::One &a = f.a[q];
-        const uint32_t bits = v0 < n1 ? load_marks16(a.mark, v0, n1) : 0u;
+        const uint32_t bits = v0 >= n1 ? 0u : SELF ? load_marks4(a.mark, v0, n1) : load_marks16(a.mark, v0, n1);
         uint64_t x[per];
         uint64_t m = kNoRow;
 #pragma unroll
@@ -1313,7 +1339,7 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
             m = min(m, x[j]);
         }
         // the first marked value after the chunk
-        const uint64_t next = SELF ? marked_from(a, c0 + kScanChunk, n1, &s_first) : a.cmin[blockIdx.x];
+        const uint64_t next = SELF ? marked_from(a, c0 + kChunk, n1, &s_first) : a.cmin[blockIdx.x];
         // minimum over the rows of the threads after this one
         for (int off = 1; off < 64; off <<= 1) {
             const uint64_t o = __shfl_down(m, off, 64);
@@ -1337,7 +1363,7 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
             const uint64_t a0 = s_out[(i / per) * (per + 1) + i % per];
             if (v < n1) a.A[v] = a0;
             if (HIST && a.degree && v + 1 < n1)  // the row after the chunk's last holds `next` once filled
-                deg[j] += (i + 1 < kScanChunk ? s_out[((i + 1) / per) * (per + 1) + (i + 1) % per] : next) - a0;
+                deg[j] += (i + 1 < kChunk ? s_out[((i + 1) / per) * (per + 1) + (i + 1) % per] : next) - a0;
         }
         __syncthreads();  // s_wave and s_out are rewritten for the next array
     }
@@ -1506,17 +1532,21 @@ __global__ __launch_bounds__(256) void csr_clear(ClearArgs a) {
 
 // The row fill of up to three arrays.  Up to kSelfChunks chunks the marks
 // after a chunk are scanned by its own workgroup, one launch instead of three
-// (a step per chunk in the worst case, against two launches of about 4 us).
-constexpr uint64_t kSelfChunks = 16;
+// (eight steps in the worst case, against two launches of about 4 us).  The fill
+// in us with rows all over / in the first five alone: 11.1 / 11.8 at 65,537
+// vertices and 11.3 / 17.4 at 131,000, by three launches 20.8 / 19.4 and 20.3 / 18.9;
+// at 16,384 vertices 10.2 in chunks of 1,024 rows, 14.2 in chunks of 4,096.
+constexpr uint64_t kSelfChunks = 32;
 
 void row_fill(const FillArrays &f, hipStream_t s) {
     ProfScope _ps("csr_rowfill", s);
     const unsigned g = (unsigned)f.chunks;
     if (f.chunks <= kSelfChunks) {
+        const unsigned gs = (unsigned)((f.n1 + kSelfChunk - 1) / kSelfChunk);
         if (f.hist)
-            rowfill_apply<true, true><<<g, 256, 0, s>>>(f);
+            rowfill_apply<true, true><<<gs, 256, 0, s>>>(f);
         else
-            rowfill_apply<false, true><<<g, 256, 0, s>>>(f);
+            rowfill_apply<false, true><<<gs, 256, 0, s>>>(f);
         return;
     }
     rowfill_first<<<dim3(g, f.count), 256, 0, s>>>(f);

@@ -229,3 +229,18 @@ def test_csr_short_tiles_without_their_workspace(sfg, orc):
     from paper_1003_3684_amd.native import SfgenError
     with pytest.raises(SfgenError):
         sfg.edges_to_csr(n, s, d, ws=torch.empty(2 * 4 * E - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("flags", FLAG_SETS)
+@pytest.mark.parametrize("n", [1, 3, 1022, 1023, 1024, 4095, 16_384, 65_537, 131_071, 131_072])
+@pytest.mark.parametrize("rows", ["first", "last", "sparse"])
+def test_csr_row_fill_short_chunks(sfg, orc, rows, n, flags):
+    """Chunks of 1,024 rows (up to 2^17 - 1 vertices) and the chunk scan above:
+    lists whose rows lie at one end, so that the next marked row is far or there
+    is none, or a few rows apart."""
+    rng = np.random.default_rng(n)
+    E = 700
+    src = rng.integers(0, min(n, 5), size=E) if rows != "sparse" else rng.integers(0, n, size=E)
+    src = n - 1 - src if rows == "last" else src
+    dst = rng.integers(0, min(n, 9), size=E)
+    _check(sfg, orc, n, src, dst, flags, 4)
