@@ -89,7 +89,7 @@ struct ChunkArgs {
 // the wedge prefix.  Both read row starts only, and a small graph's time is its
 // launches: with the wedge sums, the exponent, the clearing and the marking of
 // graphs without a wedge in launches of their own, the statistics of 2^18 edges
-// took 132 us, now 117 (of which the CSR about 85).  Rows through LDS, coalesced,
+// took 132 us, together 117 (of which the CSR about 85).  Rows through LDS, coalesced,
 // instead of 16 strided reads per thread: this pass over 1.7e7 vertices 255 -> 71 us,
 // the wedge prefix 287 -> 42.
 __global__ __launch_bounds__(kChunkThreads) void stats_chunks(ChunkArgs a) {
@@ -261,18 +261,36 @@ __global__ __launch_bounds__(kChunkThreads) void stats_apply(ChunkArgs a, double
     }
 }
 
-template <typename IdT>
-__device__ __forceinline__ bool adjacent(const uint64_t *rp, const IdT *col, uint64_t v, uint64_t w) {
-    uint64_t lo = rp[v], hi = rp[v + 1];
-    while (lo < hi) {
-        const uint64_t mid = lo + (hi - lo) / 2;
-        if ((uint64_t)col[mid] < w)
-            lo = mid + 1;
-        else
-            hi = mid;
+// The smallest i in [lo, hi] for which `above` holds (it holds from there on;
+// hi: for none below), by LANES consecutive lanes with the same arguments: every
+// step asks at LANES places, so it takes log_{LANES + 1} of them.  Whole
+// wavefronts call it, a group that need not search with lo = hi.
+template <int LANES, typename Above> __device__ __forceinline__ uint64_t first_above(uint64_t lo, uint64_t hi, Above above) {
+    const uint32_t lane = threadIdx.x & 63, part = lane % LANES;
+    while (LANES == 1 ? lo < hi : __any(lo < hi)) {
+        if (LANES == 1) {
+            const uint64_t mid = lo + (hi - lo) / 2;
+            if (above(mid))
+                hi = mid;
+            else
+                lo = mid + 1;
+            continue;
+        }
+        const uint64_t len = hi - lo, at = lo + len * (part + 1) / (LANES + 1);
+        const bool yes = len > 0 && above(at);
+        const uint32_t mask = (uint32_t)(__ballot(yes) >> (lane - part)) & ((1u << LANES) - 1);
+        const uint32_t first = mask ? (uint32_t)__builtin_ctz(mask) : (uint32_t)LANES;
+        const uint64_t up = __shfl(at, (int)(lane - part + (first < LANES ? first : 0)), 64);
+        const uint64_t down = __shfl(at, (int)(lane - part + (first > 0 ? first - 1 : 0)), 64);
+        if (len > 0) {
+            if (first < LANES) hi = up;
+            if (first > 0) lo = down + 1;
+        }
     }
-    return lo < rp[v + 1] && (uint64_t)col[lo] == w;
+    return lo;
 }
+
+constexpr int kWedgeLanes = 16;  // lanes of a sample, where all of them fit the GPU at once
 
 struct WedgeArgs {
     const StatGraph *G;
@@ -284,44 +302,47 @@ struct WedgeArgs {
     uint64_t nv;                 // vertices of the shared space
 };
 
-// Sample i of graph g: Philox block (i, 0, 0, WEDGE | gid << 8).
-template <typename IdT> __global__ __launch_bounds__(256) void wedge_sample(WedgeArgs a) {
+// Sample i of graph g: Philox block (i, 0, 0, WEDGE | gid << 8).  Two searches,
+// one load after the other: few samples take LANES lanes each, which shortens
+// both (2,000 samples over 16,384 vertices 14.3 us with one lane, 8.3 with 16);
+// more samples than fit the GPU that way hide the latency behind one another
+// (9.6e5 over 1.7e7 vertices: 156 us).
+template <typename IdT, int LANES> __global__ __launch_bounds__(256) void wedge_sample(WedgeArgs a) {
     const uint64_t total_items = (uint64_t)a.count * a.samples;
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
-    for (uint64_t it = (uint64_t)blockIdx.x * 256 + threadIdx.x; it < total_items; it += stride) {
-        const StatGraph &g = a.G[it / a.samples];
+    const uint64_t stride = (uint64_t)gridDim.x * (256 / LANES);
+    const uint64_t it0 = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / LANES, wave0 = it0 - (threadIdx.x & 63) / LANES;
+    for (uint64_t step = 0; wave0 + step < total_items; step += stride) {
+        const uint64_t it = it0 + step;
+        const bool in = it < total_items;
+        const StatGraph &g = a.G[in ? it / a.samples : 0];
         const uint32_t i = (uint32_t)(it % a.samples);
-        if (g.v1 == g.v0) {
-            if (i == 0) a.closed[g.out] = ~0ull;
-            continue;
-        }
         const uint64_t base = g.v0 > 0 ? a.pre[g.v0 - 1] : 0;
-        const uint64_t total = a.pre[g.v1 - 1] - base;
-        if (total == 0) {
-            if (i == 0) a.closed[g.out] = ~0ull;  // -1: no wedge at all, and no other sample adds to it
-            continue;
-        }
+        const uint64_t total = g.v1 > g.v0 ? a.pre[g.v1 - 1] - base : 0;
+        const bool leader = in && threadIdx.x % LANES == 0;
+        if (leader && total == 0 && i == 0) a.closed[g.out] = ~0ull;  // -1: no wedge at all, and no other sample adds to it
+        const bool draw = in && total > 0;
         const Block4 w = philox(i, 0, 0, TAG_WEDGE | (g.gid << 8), a.key0, a.key1);
         const uint64_t target = base + uidx64(make_u64(w.w0, w.w1), total);
         // centre: first v with pre[v] > target
-        uint64_t lo = g.v0, hi = g.v1;
-        while (lo < hi) {
-            const uint64_t mid = lo + (hi - lo) / 2;
-            if (a.pre[mid] > target)
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        const uint64_t v = lo;
+        const uint64_t v = first_above<LANES>(g.v0, draw ? g.v1 : g.v0, [&](uint64_t x) { return a.pre[x] > target; });
         const IdT *col = static_cast<const IdT *>(a.col);
-        const uint32_t d = (uint32_t)(a.rp[v + 1] - a.rp[v]);
-        const uint32_t x = uidx32(w.w2, d);
-        uint32_t y = uidx32(w.w3, d - 1);
-        if (y >= x) ++y;
-        const uint64_t na = (uint64_t)col[a.rp[v] + x], nb = (uint64_t)col[a.rp[v] + y];
-        // (ids outside the vertex space come only from invalid input; they
-        // are never looked up)
-        if (na < a.nv && adjacent<IdT>(a.rp, col, na, nb)) atomicAdd(&a.closed[g.out], 1ull);
+        uint64_t lo = 0, hi = 0, nb = 0;
+        if (draw) {
+            const uint32_t d = (uint32_t)(a.rp[v + 1] - a.rp[v]);
+            const uint32_t x = uidx32(w.w2, d);
+            uint32_t y = uidx32(w.w3, d - 1);
+            if (y >= x) ++y;
+            const uint64_t na = (uint64_t)col[a.rp[v] + x];
+            nb = (uint64_t)col[a.rp[v] + y];
+            // (ids outside the vertex space come only from invalid input; they
+            // are never looked up)
+            if (na < a.nv) {
+                lo = a.rp[na];
+                hi = a.rp[na + 1];
+            }
+        }
+        const uint64_t at = first_above<LANES>(lo, hi, [&](uint64_t x) { return (uint64_t)col[x] >= nb; });
+        if (leader && at < hi && (uint64_t)col[at] == nb) atomicAdd(&a.closed[g.out], 1ull);
     }
 }
 
@@ -399,12 +420,18 @@ int stats_enqueue(StatGraph *G_dev, uint32_t count, uint64_t total_chunks, uint6
         WedgeArgs wa{G_dev, count, samples, rp, pre, col, (uint32_t)seed, (uint32_t)(seed >> 32),
                      reinterpret_cast<unsigned long long *>(closed), nv};
         const uint64_t items = (uint64_t)count * samples;
-        const unsigned g = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((items + 255) / 256, (uint64_t)device_cu_count() * 16));
+        const uint64_t resident = (uint64_t)device_cu_count() * 16;  // workgroups
+        const int lanes = items * kWedgeLanes <= resident * 256 ? kWedgeLanes : 1;
+        const unsigned g = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((items * lanes + 255) / 256, resident));
         ProfScope _ps("stats_wedge", s);
-        if (id_bytes == 4)
-            wedge_sample<int32_t><<<g, 256, 0, s>>>(wa);
+        if (id_bytes == 4 && lanes > 1)
+            wedge_sample<int32_t, kWedgeLanes><<<g, 256, 0, s>>>(wa);
+        else if (id_bytes == 4)
+            wedge_sample<int32_t, 1><<<g, 256, 0, s>>>(wa);
+        else if (lanes > 1)
+            wedge_sample<int64_t, kWedgeLanes><<<g, 256, 0, s>>>(wa);
         else
-            wedge_sample<int64_t><<<g, 256, 0, s>>>(wa);
+            wedge_sample<int64_t, 1><<<g, 256, 0, s>>>(wa);
     }
     else { ProfScope _ps("stats_wedge", s); wedge_mark_empty<<<(count + 255) / 256, 256, 0, s>>>(G_dev, count, pre, cl); }
     return check_launch("graph statistics");

@@ -69,3 +69,14 @@ def test_stats_chunk_edges(sfg, orc, n, samples):
     dst = rng.integers(0, n, size=E)
     _check(sfg, orc, n, src, dst, samples, 5, 3)
     _check(sfg, orc, n, src[:1], dst[:1], samples, 5, 3, 8)
+
+
+@pytest.mark.parametrize("samples", [1, 15, 16, 17, 65_535, 65_536, 65_537, 70_001])
+def test_stats_sample_lanes(sfg, orc, samples):
+    """Sample counts around a wavefront's groups of lanes and around the number
+    from which a sample takes one lane, over rows of every length."""
+    rng = np.random.default_rng(samples)
+    n, E = 20_000, 60_000
+    src = np.minimum(rng.zipf(1.5, size=E) - 1, n - 1)
+    dst = np.minimum(rng.zipf(1.3, size=E) - 1, n - 1)
+    _check(sfg, orc, n, src, dst, samples, 11, 6, 8 if samples % 2 else 4)
