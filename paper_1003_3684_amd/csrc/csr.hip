@@ -770,7 +770,7 @@ __device__ __forceinline__ uint64_t tile_prefix(const FinArgs &a, uint64_t tile,
     uint64_t *st = a.status + tile;
     uint64_t prefix = 0;
     if (tile > 0) {
-        uint64_t j = tile;  // this round reads tiles j-1 .. j-64
+        uint64_t j = tile;  // this step reads tiles j-1 .. j-64
         for (;;) {
             const bool real = j > lane;
             const uint64_t *pj = a.status + (real ? j - 1 - lane : 0);
@@ -1425,7 +1425,7 @@ struct Plan {
 };
 
 Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_hist, bool xor_mode = false,
-               uint64_t power = 0, bool short_tiles = true) {
+               uint64_t power = 0) {
     Plan p;
     memset(&p, 0, sizeof(p));
     p.n = n;
@@ -1453,7 +1453,7 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.passes = (p.kb + 7) / 8;
     p.key_bytes = p.kb <= 32 ? 4 : 8;
     constexpr uint64_t short_tile = kPassThreads * kShortItems;
-    p.short_tiles = short_tiles && p.N <= kShortTiles * short_tile;
+    p.short_tiles = p.N <= kShortTiles * short_tile;
     p.pass_tiles = p.short_tiles ? (p.N + short_tile - 1) / short_tile : (p.N + kPassTile - 1) / kPassTile;
     p.fin_tiles = (p.N + power + fin_tile(xor_mode) - 1) / fin_tile(xor_mode);
     // Without SIMPLE no entry is dropped, so sorted positions are output
@@ -1769,10 +1769,6 @@ int csr_check(uint64_t n, uint64_t num_edges, const void *src, const void *dst, 
     // tiles of 512).
     if (N > (1ull << 34)) return fail(SFG_ERANGE, "edges_to_csr: more than 2^34 entries");
     P = make_plan(n, num_edges, id_bytes, flags, degree_hist32 != nullptr);
-    // (short tiles have up to 84 KB more look-back words: a workspace without
-    // room for those is still enough)
-    if (P.short_tiles && workspace_bytes < P.total)
-        P = make_plan(n, num_edges, id_bytes, flags, degree_hist32 != nullptr, false, 0, false);
     if (P.total > 0 && !workspace) return fail(SFG_EINVAL, "edges_to_csr: workspace is NULL");
     if (workspace_bytes < P.total)
         return fail(SFG_ENOSPACE, "edges_to_csr: workspace has %zu bytes, needs %zu", workspace_bytes, P.total);

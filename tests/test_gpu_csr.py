@@ -209,28 +209,6 @@ def test_csr_simple_finish_tiles(sfg, orc, shape, E, id_bytes):
     assert int(dups.item()) == odups
 
 
-def test_csr_short_tiles_without_their_workspace(sfg, orc):
-    """A workspace that lacks the short tiles' extra look-back words (84 KB at
-    131,072 entries) is taken with the long ones; one without room for the two key
-    arrays is refused."""
-    import torch
-    rng = np.random.default_rng(8)
-    n, E = 5000, 131_072
-    src, dst = rng.integers(0, n, E), rng.integers(0, n, E)
-    s = torch.tensor(src, dtype=torch.int32, device="cuda")
-    d = torch.tensor(dst, dtype=torch.int32, device="cuda")
-    size = sfg.edges_to_csr_workspace_bytes(n, E, 4, 0)
-    rp, col, hist, dups = sfg.edges_to_csr(n, s, d, ws=torch.empty(size - 80_000, dtype=torch.uint8, device="cuda"))
-    torch.cuda.synchronize()
-    orp, ocol, odups = orc.edges_to_csr(n, src, dst, symmetrize=False, simple=False)
-    np.testing.assert_array_equal(rp.cpu().numpy().astype(np.uint64), orp)
-    np.testing.assert_array_equal(col.cpu().numpy().astype(np.int64), ocol)
-    assert int(dups.item()) == odups
-    from paper_1003_3684_amd.native import SfgenError
-    with pytest.raises(SfgenError):
-        sfg.edges_to_csr(n, s, d, ws=torch.empty(2 * 4 * E - 256, dtype=torch.uint8, device="cuda"))
-
-
 @pytest.mark.parametrize("flags", FLAG_SETS)
 @pytest.mark.parametrize("n", [1, 3, 1022, 1023, 1024, 4095, 16_384, 65_537, 131_071, 131_072])
 @pytest.mark.parametrize("rows", ["first", "last", "sparse"])
