@@ -203,21 +203,20 @@ struct Sources {
 };
 
 // One wavefront: sources may repeat, and their bits then share a word, which
-// every one of them writes.
+// every one of them writes.  Every source's search starts alive: that its own
+// row is empty does not say that no row lists it.
 template <bool BITS> __global__ __launch_bounds__(64) void ps_seed(Search<BITS> a, Sources s) {
     const uint32_t i = threadIdx.x;
     const bool in = i < s.count;
     const int64_t v = in ? s.v[i] : 0;
     uint64_t word = 0;
-    bool spreads = false;
     if (in) {
         for (uint32_t j = 0; j < s.count; ++j) word |= (uint64_t)(s.v[j] == v) << j;
         a.vis[v] = word;
         a.front[v] = word;
         a.mark((uint64_t)v);
-        spreads = a.rp[v + 1] > a.rp[v];
     }
-    const uint64_t alive = __ballot(spreads);
+    const uint64_t alive = __ballot(in);
     if (i == 0) {
         a.ctl[kCtlAlive] = alive;
         a.ctl[kCtlFront] = s.count;

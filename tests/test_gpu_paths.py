@@ -123,3 +123,22 @@ def test_listed_degrees_match_oracle(sfg, orc, n, deg, tail):
     exp = orc.path_stats(total, rp, col, srcs)
     for id_bytes in (4, 8):
         assert _gpu(sfg, total, rp, col, srcs, id_bytes) == tuple(int(x) for x in exp)
+
+
+@pytest.mark.parametrize("id_bytes", [4, 8])
+def test_listed_only_by_others_matches_oracle(sfg, orc, id_bytes):
+    """Rows that list a source whose own row is empty: a level ORs the words of
+    the neighbours a row lists, so the source reaches those rows (a breadth-first
+    search of the transposed graph)."""
+    rng = np.random.default_rng(11)
+    n = 400
+    pairs = [(v, 0) for v in range(1, 60)]                    # row 0 is empty
+    pairs += [(v, int(rng.integers(1, 60))) for v in range(60, 300)]
+    pairs += [(v, v - 1) for v in range(301, n)]              # a chain read from its head, whose row is empty
+    a = np.array(sorted(pairs), np.int64)
+    t = a[np.argsort(a[:, 1], kind="stable")][:, ::-1]
+    rp, trp = (np.concatenate([[0], np.cumsum(np.bincount(x[:, 0], minlength=n))]).astype(np.uint64) for x in (a, t))
+    for srcs in ([0], [300], [0, 300, 7, 0]):
+        exp = orc.path_stats(n, trp, t[:, 1], np.array(srcs))
+        assert exp[1] > 50
+        assert _gpu(sfg, n, rp, a[:, 1], srcs, id_bytes) == tuple(int(x) for x in exp)
