@@ -1082,12 +1082,20 @@ template <typename F> void launch_rows(uint32_t B, F f) {
         f(std::integral_constant<int, 4>(), blocks);
 }
 
-// The evaluation's arguments for a network and workspace, its fragments in
-// the split-K scratch.  False when the network is not one the fused kernels
-// take, or so narrow that its padded fragments do not fit there (below a width
-// of 32 or so): the unfused kernels run then.
-bool eval_args(const Net &net, uint32_t B, const Ws &w, const float *params, bool transposed, EvalArgs &a, int &tiles) {
-    if (!fused_ok(net)) return false;
+bool overlap(const float *a, size_t na, const float *b, size_t nb) {
+    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+    return pa < pb + nb * sizeof(float) && pb < pa + na * sizeof(float);
+}
+
+// The evaluation's arguments for a network and workspace, its fragments in the
+// split-K scratch; in and out are the call's, [B][cin] and [B][cout].  False, and
+// the unfused kernels run, when the network is not one the fused kernels take or
+// so narrow that its padded fragments do not fit there (below a width of 32 or
+// so), or when out shares memory with in (a block of the fused kernel writes its
+// rows of out while others still have theirs of in to read).
+bool eval_args(const Net &net, uint32_t B, const Ws &w, const float *params, bool transposed, const float *in, int cin,
+               const float *out, int cout, EvalArgs &a, int &tiles) {
+    if (!fused_ok(net) || overlap(in, (size_t)B * cin, out, (size_t)B * cout)) return false;
     memset(&a, 0, sizeof(a));
     a.L = net.L;
     a.B = (int)B;
@@ -1150,7 +1158,7 @@ extern "C" int mlp_forward(const sfg_mlp_shape *shape, uint32_t batch, const flo
     hipStream_t s = as_stream(stream);
     EvalArgs ea;
     int tiles;
-    if (eval_args(net, batch, w, params, false, ea, tiles)) {
+    if (eval_args(net, batch, w, params, false, x, net.layer[0].in, y, net.layer[net.L - 1].out, ea, tiles)) {
         ea.x = x;
         ea.y = y;
         { ProfScope _ps("mlp_round", s); eval_fragments<false><<<tiles, 256, 0, s>>>(ea); }
@@ -1187,7 +1195,7 @@ extern "C" int mlp_backward(const sfg_mlp_shape *shape, uint32_t batch, const fl
     const int B = (int)batch;
     EvalArgs ea;
     int tiles;
-    if (!grad && eval_args(net, batch, w, params, true, ea, tiles)) {
+    if (!grad && eval_args(net, batch, w, params, true, dy, net.layer[net.L - 1].out, dx, net.layer[0].in, ea, tiles)) {
         ea.dy = dy;
         ea.dx = dx;
         { ProfScope _ps("mlp_round", s); eval_fragments<true><<<tiles, 256, 0, s>>>(ea); }

@@ -294,3 +294,27 @@ def test_forward_and_input_gradient_match_oracle(sfg, shape_t, batch):
     _close(dx.cpu().numpy(), dxo, 1e-2)
     _close(grad.cpu().numpy(), go, 1e-2)
     assert torch.equal(dx, dx2) and torch.equal(dx, dx3)  # the same products in the same order
+
+
+def test_evaluation_in_overlapping_buffers(sfg):
+    """y over x and dx over dy give what separate buffers give: rows of the
+    output lie over rows of the input that other blocks have still to read."""
+    import torch
+    B = 200_000
+    for shape_t, back in (((10, 64, 34, 2), False), ((34, 64, 10, 2), True)):
+        shape, params, x, t, g = _setup(sfg, shape_t, 1, 3)
+        ws = sfg.workspace(sfg.mlp_workspace_bytes(shape, B))
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        x = torch.randn(B, shape_t[0], device="cuda", generator=gen)
+        dy = torch.randn(B, shape_t[2], device="cuda", generator=gen)
+        y = sfg.mlp_forward(shape, g["params"], x, ws)
+        _, dx = sfg.mlp_backward(shape, g["params"], dy, ws, want_grad=False, want_dx=True)
+        a, want = (dy, dx) if back else (x, y)
+        buf = torch.empty(want.numel(), device="cuda")
+        over = buf[:a.numel()].view(a.shape)
+        over.copy_(a)
+        if back:
+            sfg.mlp_backward(shape, g["params"], over, ws, want_grad=False, dx=buf.view(want.shape), want_dx=True)
+        else:
+            sfg.mlp_forward(shape, g["params"], over, ws, y=buf.view(want.shape))
+        assert torch.equal(buf.view(want.shape), want)
