@@ -1091,11 +1091,12 @@ bool overlap(const float *a, size_t na, const float *b, size_t nb) {
 // split-K scratch; in and out are the call's, [B][cin] and [B][cout].  False, and
 // the unfused kernels run, when the network is not one the fused kernels take or
 // so narrow that its padded fragments do not fit there (below a width of 32 or
-// so), or when out shares memory with in (a block of the fused kernel writes its
-// rows of out while others still have theirs of in to read).
+// so), when out shares memory with in (a block of the fused kernel writes its
+// rows of out while others still have theirs of in to read), or when the scratch
+// is not aligned for the fragments' 16-byte accesses.
 bool eval_args(const Net &net, uint32_t B, const Ws &w, const float *params, bool transposed, const float *in, int cin,
                const float *out, int cout, EvalArgs &a, int &tiles) {
-    if (!fused_ok(net) || overlap(in, (size_t)B * cin, out, (size_t)B * cout)) return false;
+    if (!fused_ok(net) || overlap(in, (size_t)B * cin, out, (size_t)B * cout) || (uintptr_t)w.part % 16) return false;
     memset(&a, 0, sizeof(a));
     a.L = net.L;
     a.B = (int)B;

@@ -318,3 +318,17 @@ def test_evaluation_in_overlapping_buffers(sfg):
         else:
             sfg.mlp_forward(shape, g["params"], over, ws, y=buf.view(want.shape))
         assert torch.equal(buf.view(want.shape), want)
+
+
+def test_evaluation_in_a_workspace_off_16_bytes(sfg):
+    """The workspace's address is the caller's: four bytes past an aligned one
+    gives the same bits."""
+    import torch
+    shape_t, B = (10, 256, 34, 3), 100
+    shape, params, x, t, g = _setup(sfg, shape_t, B, 9)
+    dy = g["t"]
+    y = sfg.mlp_forward(shape, g["params"], g["x"], g["ws"])
+    _, dx = sfg.mlp_backward(shape, g["params"], dy, g["ws"], want_grad=False, want_dx=True)
+    ws = sfg.workspace(g["ws"].numel() + 4)[4:]
+    assert torch.equal(sfg.mlp_forward(shape, g["params"], g["x"], ws), y)
+    assert torch.equal(sfg.mlp_backward(shape, g["params"], dy, ws, want_grad=False, want_dx=True)[1], dx)
