@@ -564,6 +564,7 @@ struct RunArgs {
     const void *run_first, *run_last;
     const uint32_t *tile_dups;
     uint64_t *rp;
+    uint64_t entries;        // rp[n]
     uint8_t *mark;
     uint64_t *dups;
     uint32_t *err;
@@ -624,6 +625,7 @@ __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
     const KeyT *first = static_cast<const KeyT *>(a.run_first);
     const KeyT *last = static_cast<const KeyT *>(a.run_last);
     if (d == 0) s_dup = 0;
+    if (d == 0 && blockIdx.x == 0) a.rp[a.n] = a.entries;
     __syncthreads();
     uint32_t ndup = 0;
     const uint64_t t0 = (uint64_t)blockIdx.x * a.run_tiles;
@@ -1592,8 +1594,9 @@ void clear_csr(const Plan &P, uint64_t *row_ptr, uint64_t *hist, uint64_t *dups,
     }
     c.hist = hist;
     if (dups) c.value(dups, 0);
-    // (with SIMPLE the finish pass writes the values at row n)
-    if (!P.simple || P.fin_tiles == 0) c.value(row_ptr + P.n, P.N);
+    // (the last pass over the entries writes row n's value: the edge list, which
+    // may share memory with row_ptr, has been read by then)
+    if (P.N + P.power == 0) c.value(row_ptr + P.n, 0);
     if (P.hist && P.simple && P.N == 0) c.value(reinterpret_cast<uint64_t *>(ws + P.off_rpraw) + P.n, 0);
     ProfScope _ps("fill", s);
     csr_clear<<<fill_grid(words), 256, 0, s>>>(c);
@@ -1681,7 +1684,7 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
         const int run_tiles = P.pass_tiles >= (uint64_t)kRunTiles * device_cu_count() ? kRunTiles : kRunBatch;
         RunArgs ra{P.pass_tiles, P.n, status, gbase, ghist + last * kRadix, keysA,
                    keysA + P.pass_tiles * kRadix, reinterpret_cast<const uint32_t *>(keysA + 2 * P.pass_tiles * kRadix),
-                   row_ptr, mark, dups, err, P.db, (uint32_t)(last + 1), run_tiles};
+                   row_ptr, P.N, mark, dups, err, P.db, (uint32_t)(last + 1), run_tiles};
         const int rg = (int)((P.pass_tiles + run_tiles - 1) / run_tiles);
         { ProfScope _ps("csr_run_starts", s); csr_run_starts<KeyT><<<rg, kRadix, 0, s>>>(ra); }
     } else if (P.xor_mode) {

@@ -222,3 +222,18 @@ def test_csr_row_fill_short_chunks(sfg, orc, rows, n, flags):
     src = n - 1 - src if rows == "last" else src
     dst = rng.integers(0, min(n, 9), size=E)
     _check(sfg, orc, n, src, dst, flags, 4)
+
+
+@pytest.mark.parametrize("n,flags", [(200, 0), (70_000, 0), (70_000, 1), (70_000, 3)])
+def test_row_starts_over_the_edge_list(sfg, n, flags):
+    """row_ptr in the memory of src: the list is read before any row start is written."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n + flags)
+    E = n + 4_321
+    src = torch.randint(0, n, (E,), device="cuda", generator=g)
+    dst = torch.randint(0, n, (E,), device="cuda", generator=g)
+    want = sfg.edges_to_csr(n, src, dst, flags=flags)
+    got = sfg.edges_to_csr(n, src, dst, flags=flags, row_ptr=src[:n + 1])
+    kept = int(want[0][n])
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1][:kept], want[1][:kept])
+    assert torch.equal(got[2], want[2]) and torch.equal(got[3], want[3])
