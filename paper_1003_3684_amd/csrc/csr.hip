@@ -42,14 +42,21 @@ namespace {
 constexpr int kPassThreads = 1024;
 constexpr int kPassItems = 8;
 constexpr int kPassTile = kPassThreads * kPassItems;  // keys per onesweep tile
-// A list of at most kShortTiles tiles of kShortItems keys per thread is sorted
-// in those: a pass over a few tiles takes as long as one tile, and a tile of two
-// keys per thread is ranked in a quarter of the steps.  The build in us with 8
-// and with 2 keys per thread: 52.8 / 41.1 for 8,192 entries, 63.9 / 61.2 for
-// 65,536, 77.6 / 76.0 for 262,144, 90.2 / 91.2 for 524,288, where the look-back
-// over four times the tiles costs what the ranking saves.
-constexpr int kShortItems = 2;
-constexpr uint64_t kShortTiles = 64;
+// Lists of up to kShortList entries are sorted in shorter tiles: a pass over a
+// few tiles takes as long as one tile, and a tile of two keys per thread is ranked
+// in a quarter of the steps.  The build in us with 8 and with 2 keys per thread: 52.8 /
+// 41.1 for 8,192 entries, 63.9 / 61.2 for 65,536, 77.6 / 76.0 for 262,144, 90.2 /
+// 91.2 for 524,288, where the look-back over four times the tiles costs what the
+// ranking saves.  The short tiles' look-back words are 32-bit, and those of more
+// than kShortTiles tiles would not fit what a plan reserves for the long tiles, so
+// such a list takes kMidItems keys per thread (100,000 directed entries over 3,000
+// vertices: 67.5 with 8, 57.4 with 3, 58.7 with 2).  A workspace that grew for the
+// short tiles would be too small for a list of kShortList entries when it was
+// sized for a longer one.
+constexpr int kShortItems = 2, kMidItems = 3;
+constexpr uint64_t kShortTiles = 30;
+constexpr uint64_t kShortList = 131072;
+constexpr uint64_t kSpareTiles = 7;  // long tiles' look-back words beyond a plan's own
 constexpr int kPassWaves = kPassThreads / 64;
 constexpr int kRadix = 256;
 constexpr int kLookWindow = 2;  // predecessors read per lane and look-back round trip
@@ -85,12 +92,21 @@ constexpr int kPrepMinEdges = 4096;  // edges a workgroup of it has at least
 
 constexpr uint64_t kNoRow = ~0ull;
 
-// Look-back status word: [63:58] pass tag, [57:56] flag, [55:0] count.
+// Look-back status word: pass tag in the top 6 bits, flag in the next 2, then
+// the count: 56 bits, or 24 in a 32-bit word.
 constexpr uint64_t kFlagAgg = 1, kFlagIncl = 2;
-__device__ __forceinline__ uint64_t status_word(uint32_t tag, uint64_t flag, uint64_t v) {
-    return ((uint64_t)tag << 58) | (flag << 56) | v;
+static_assert(kShortList < (1u << 24), "a short list's counts fit 24 bits");
+// (of the passes in tiles of ITEMS keys per thread)
+template <int ITEMS> using StatusWord = typename std::conditional<(ITEMS < kPassItems), uint32_t, uint64_t>::type;
+template <typename WordT> constexpr int kCountBits = sizeof(WordT) * 8 - 8;
+template <typename WordT = uint64_t> __device__ __forceinline__ WordT status_word(uint32_t tag, uint64_t flag, uint64_t v) {
+    return ((WordT)tag << (kCountBits<WordT> + 2)) | ((WordT)flag << kCountBits<WordT>) | (WordT)v;
 }
-
+template <typename WordT> __device__ __forceinline__ uint32_t status_tag(WordT v) { return (uint32_t)(v >> (kCountBits<WordT> + 2)); }
+template <typename WordT> __device__ __forceinline__ uint64_t status_flag(WordT v) { return (v >> kCountBits<WordT>) & 3; }
+template <typename WordT> __device__ __forceinline__ uint64_t status_count(WordT v) {
+    return v & (((WordT)1 << kCountBits<WordT>) - 1);
+}
 
 __device__ __forceinline__ uint32_t count_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
@@ -235,7 +251,7 @@ struct PassArgs {
     const void *src, *dst;  // first pass only
     const void *in;         // later passes
     void *out;
-    uint64_t *status;       // [tiles][256]
+    void *status;           // [tiles][256] look-back words (StatusWord<ITEMS>)
     uint64_t *gbase;        // [256] bucket bases of a FINAL pass, left for csr_run_starts
     const uint64_t *ghist;  // [256] of this pass: digits no entry has skip the look-back
     uint32_t *err;
@@ -273,9 +289,9 @@ __device__ __forceinline__ uint64_t unpack_id(KeyT packed, const uint32_t *dec, 
 // run follows an entry of another tile (or of another digit's bucket); the
 // run's first and last keys go to the run records, and csr_run_starts
 // settles those entries once every tile is done.
-template <typename IdT, typename KeyT, bool SYM, bool FIRST, bool BOUND, bool FINAL, bool SHORT>
-__global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix_pass(PassArgs a) {
-    constexpr int kItems = SHORT ? kShortItems : kPassItems, kTile = kPassThreads * kItems;
+template <typename IdT, typename KeyT, bool SYM, bool FIRST, bool BOUND, bool FINAL, int ITEMS>
+__global__ __launch_bounds__(kPassThreads, ITEMS < kPassItems ? 4 : BOUND ? 6 : 8) void radix_pass(PassArgs a) {
+    constexpr int kItems = ITEMS, kTile = kPassThreads * kItems;
     // s_keys holds the tile's keys in digit order after ranking; during the
     // ranking its first 32 KB serve as the per-wave lane-match tables.
     constexpr size_t kMatchBytes = sizeof(uint64_t) * kPassWaves * kRadix;
@@ -292,6 +308,8 @@ __global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix
     static_assert(kPassThreads % kRadix == 0 && 64 % kLanesPerDigit == 0, "look-back lane groups");
     uint64_t *s_match = reinterpret_cast<uint64_t *>(s_keys) + 0;  // [kPassWaves][256]
 
+    using WordT = StatusWord<ITEMS>;
+    WordT *status = static_cast<WordT *>(a.status);
     const int tid = threadIdx.x;
     const uint32_t lane = tid & 63;
     const int w = tid >> 6;
@@ -425,8 +443,8 @@ __global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix
     const uint32_t dg = (uint32_t)tid / kLanesPerDigit, part = (uint32_t)tid % kLanesPerDigit;
     const uint64_t my_cnt = s_tot[dg];
     if (part == 0 && used)
-        store_agent(a.status + tile * kRadix + dg,
-                    tile == 0 ? status_word(a.tag, kFlagIncl, s_gpos[dg] + my_cnt) : status_word(a.tag, kFlagAgg, my_cnt));
+        store_agent(status + tile * kRadix + dg, tile == 0 ? status_word<WordT>(a.tag, kFlagIncl, s_gpos[dg] + my_cnt)
+                                                           : status_word<WordT>(a.tag, kFlagAgg, my_cnt));
     const bool walk = tile > 0 && used;
 
     uint64_t tot;
@@ -446,12 +464,12 @@ __global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix
         for (;;) {
             // This lane's predecessors: j - 1 - (part kLookWindow + i).  One
             // beyond tile 0 reads as an inclusive zero, which ends the walk.
-            uint64_t v[kLookWindow];
+            WordT v[kLookWindow];
 #pragma unroll
             for (int i = 0; i < kLookWindow; ++i) {
                 const uint64_t back = (uint64_t)part * kLookWindow + i;
-                v[i] = j > back ? load_agent(a.status + (j - 1 - back) * kRadix + dg)
-                                : status_word(a.tag, kFlagIncl, 0);
+                v[i] = j > back ? load_agent(status + (j - 1 - back) * kRadix + dg)
+                                : status_word<WordT>(a.tag, kFlagIncl, 0);
             }
             uint64_t sum = 0;
             bool found = false;
@@ -460,17 +478,17 @@ __global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix
                 if (found) break;
                 const uint64_t back = (uint64_t)part * kLookWindow + i;
                 uint32_t spins = 0;
-                while ((uint32_t)(v[i] >> 58) != a.tag) {
+                while (status_tag(v[i]) != a.tag) {
                     if (++spins > kSpinLimit || ((spins & 1023) == 0 && load_agent(a.err) != 0)) {
                         raise_device_error(a.err, DEVERR_LOOKBACK);
-                        v[i] = status_word(a.tag, kFlagIncl, 0);
+                        v[i] = status_word<WordT>(a.tag, kFlagIncl, 0);
                         break;
                     }
                     __builtin_amdgcn_s_sleep(1);
-                    v[i] = load_agent(a.status + (j - 1 - back) * kRadix + dg);
+                    v[i] = load_agent(status + (j - 1 - back) * kRadix + dg);
                 }
-                sum += v[i] & ((1ull << 56) - 1);
-                found = ((v[i] >> 56) & 3) == kFlagIncl;
+                sum += status_count(v[i]);
+                found = status_flag(v[i]) == kFlagIncl;
             }
             // Combine the group, nearest predecessors first.
             const int lead = (int)(lane & ~(uint32_t)(kLanesPerDigit - 1));
@@ -487,7 +505,7 @@ __global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix
             if (done) break;
             j -= (uint64_t)kLanesPerDigit * kLookWindow;  // else a sentinel had ended the walk
         }
-        if (part == 0) store_agent(a.status + tile * kRadix + dg, status_word(a.tag, kFlagIncl, prefix + my_cnt));
+        if (part == 0) store_agent(status + tile * kRadix + dg, status_word<WordT>(a.tag, kFlagIncl, prefix + my_cnt));
     }
     if (part == 0) s_gpos[dg] = prefix;
     __syncthreads();
@@ -558,7 +576,7 @@ __global__ __launch_bounds__(kPassThreads, SHORT ? 4 : BOUND ? 6 : 8) void radix
 // of d, the last entry of the previous digit that entries have.
 struct RunArgs {
     uint64_t tiles, n;
-    const uint64_t *status;  // [tiles][256] of the FINAL pass
+    const void *status;      // [tiles][256] of the FINAL pass
     const uint64_t *gbase;   // [256] bucket bases of that pass
     const uint64_t *ghist;   // [256] digit counts of that pass
     const void *run_first, *run_last;
@@ -578,37 +596,33 @@ struct RunArgs {
 // one memory latency after the other: 16.4 us for 64 tiles, 9.7 with 4 per workgroup).
 constexpr int kRunTiles = 16;
 
-// The FINAL pass has ended, so its look-back words are read with ordinary
-// (cacheable) loads.
-__device__ __forceinline__ uint64_t incl_of(const RunArgs &a, uint64_t t, uint32_t d) {
-    const uint64_t v = a.status[t * kRadix + d];
-    if ((uint32_t)(v >> 58) != a.tag || ((v >> 56) & 3) != kFlagIncl) {
+// Inclusive count of a look-back word (0 and a device error when the word is
+// not the FINAL pass's inclusive count).
+template <typename WordT> __device__ __forceinline__ uint64_t incl_value(const RunArgs &a, WordT v) {
+    if (status_tag(v) != a.tag || status_flag(v) != kFlagIncl) {
         raise_device_error(a.err, DEVERR_LOOKBACK);
         return 0;
     }
-    return v & ((1ull << 56) - 1);
+    return status_count(v);
+}
+
+// The FINAL pass has ended, so its look-back words are read with ordinary
+// (cacheable) loads.
+template <typename WordT> __device__ __forceinline__ uint64_t incl_of(const RunArgs &a, uint64_t t, uint32_t d) {
+    return incl_value(a, static_cast<const WordT *>(a.status)[t * kRadix + d]);
 }
 
 // Smallest tile x in [lo, hi] with incl(x, d) >= target (incl(hi, d) >= target).
+template <typename WordT>
 __device__ uint64_t first_tile_reaching(const RunArgs &a, uint32_t d, uint64_t lo, uint64_t hi, uint64_t target) {
     while (lo < hi) {
         const uint64_t mid = lo + (hi - lo) / 2;
-        if (incl_of(a, mid, d) >= target)
+        if (incl_of<WordT>(a, mid, d) >= target)
             hi = mid;
         else
             lo = mid + 1;
     }
     return lo;
-}
-
-// Inclusive count of a look-back word read earlier (0 and a device error
-// when the word is not the FINAL pass's inclusive count).
-__device__ __forceinline__ uint64_t incl_value(const RunArgs &a, uint64_t v) {
-    if ((uint32_t)(v >> 58) != a.tag || ((v >> 56) & 3) != kFlagIncl) {
-        raise_device_error(a.err, DEVERR_LOOKBACK);
-        return 0;
-    }
-    return v & ((1ull << 56) - 1);
 }
 
 // A workgroup takes run_tiles consecutive tiles, thread d digit d; the
@@ -617,8 +631,9 @@ __device__ __forceinline__ uint64_t incl_value(const RunArgs &a, uint64_t v) {
 // key of the tile before (the usual predecessor) -- go out together.
 constexpr int kRunBatch = 4;
 
-template <typename KeyT>
+template <typename KeyT, typename WordT>
 __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
+    const WordT *status = static_cast<const WordT *>(a.status);
     __shared__ uint32_t s_dup;
     const uint32_t d = threadIdx.x;
     const bool used = a.ghist[d] != 0;
@@ -631,16 +646,16 @@ __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
     const uint64_t t0 = (uint64_t)blockIdx.x * a.run_tiles;
     // incl(t - 2, d) and incl(t - 1, d) of the current tile t (the base before tile 0)
     const uint64_t base = a.gbase[d];
-    uint64_t c2 = (used && t0 >= 2) ? incl_of(a, t0 - 2, d) : base;
-    uint64_t c1 = (used && t0 >= 1) ? incl_of(a, t0 - 1, d) : base;
+    uint64_t c2 = (used && t0 >= 2) ? incl_of<WordT>(a, t0 - 2, d) : base;
+    uint64_t c1 = (used && t0 >= 1) ? incl_of<WordT>(a, t0 - 1, d) : base;
     for (int i0 = 0; i0 < a.run_tiles; i0 += kRunBatch) {
-        uint64_t raw[kRunBatch];
+        WordT raw[kRunBatch];
         KeyT fk[kRunBatch], lk[kRunBatch];
 #pragma unroll
         for (int u = 0; u < kRunBatch; ++u) {
             const uint64_t t = t0 + i0 + u;
             const bool ok = used && t < a.tiles;
-            raw[u] = ok ? a.status[t * kRadix + d] : 0;
+            raw[u] = ok ? status[t * kRadix + d] : 0;
             fk[u] = ok ? first[t * kRadix + d] : (KeyT)0;
             lk[u] = (ok && t >= 1) ? last[(t - 1) * kRadix + d] : (KeyT)0;
         }
@@ -663,7 +678,7 @@ __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
                 if (t < 2 || before2 < before) {
                     pred = lk[u];
                 } else {
-                    const uint64_t tp = first_tile_reaching(a, d, 0, t - 2, before);
+                    const uint64_t tp = first_tile_reaching<WordT>(a, d, 0, t - 2, before);
                     pred = last[tp * kRadix + d];
                 }
                 has = true;
@@ -671,7 +686,7 @@ __global__ __launch_bounds__(kRadix) void csr_run_starts(RunArgs a) {
                 int dp = (int)d - 1;
                 while (dp >= 0 && a.ghist[dp] == 0) --dp;
                 if (dp >= 0) {
-                    const uint64_t tp = first_tile_reaching(a, (uint32_t)dp, 0, a.tiles - 1, a.gbase[dp] + a.ghist[dp]);
+                    const uint64_t tp = first_tile_reaching<WordT>(a, (uint32_t)dp, 0, a.tiles - 1, a.gbase[dp] + a.ghist[dp]);
                     pred = last[tp * kRadix + dp];
                     has = true;
                 }
@@ -778,7 +793,7 @@ __device__ __forceinline__ uint64_t tile_prefix(const FinArgs &a, uint64_t tile,
             const uint64_t *pj = a.status + (real ? j - 1 - lane : 0);
             uint64_t v = real ? load_agent(pj) : status_word(1, kFlagIncl, 0);
             uint32_t spins = 0;
-            while ((uint32_t)(v >> 58) != 1u) {
+            while (status_tag(v) != 1u) {
                 if (++spins > kSpinLimit || ((spins & 1023) == 0 && load_agent(a.err) != 0)) {
                     raise_device_error(a.err, DEVERR_LOOKBACK);
                     v = status_word(1, kFlagIncl, 0);
@@ -787,9 +802,9 @@ __device__ __forceinline__ uint64_t tile_prefix(const FinArgs &a, uint64_t tile,
                 __builtin_amdgcn_s_sleep(1);
                 v = load_agent(pj);
             }
-            const uint64_t incl = __ballot(((v >> 56) & 3) == kFlagIncl);
+            const uint64_t incl = __ballot(status_flag(v) == kFlagIncl);
             const uint32_t first = incl ? (uint32_t)__builtin_ctzll(incl) : 64u;
-            uint64_t c = lane <= first ? (v & ((1ull << 56) - 1)) : 0;
+            uint64_t c = lane <= first ? status_count(v) : 0;
             for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
             prefix += c;
             if (incl) break;
@@ -1413,14 +1428,37 @@ int bits_for(uint64_t n) {  // bits to hold ids in [0, n)
     return b;
 }
 
+constexpr uint64_t tiles_of(uint64_t entries, int items) {
+    return (entries + kPassThreads * items - 1) / (kPassThreads * items);
+}
+constexpr int pass_items(uint64_t entries) {
+    return entries <= kShortTiles * kPassThreads * kShortItems ? kShortItems : entries <= kShortList ? kMidItems : kPassItems;
+}
+// Bytes of the passes' look-back words that a list uses, and that its plan has.
+constexpr uint64_t words_used(uint64_t entries) {
+    const int items = pass_items(entries);
+    return tiles_of(entries, items) * kRadix * (items < kPassItems ? sizeof(uint32_t) : sizeof(uint64_t));
+}
+constexpr uint64_t words_reserved(uint64_t entries) {
+    return ((entries ? tiles_of(entries, kPassItems) : 1) + kSpareTiles) * kRadix * sizeof(uint64_t);
+}
+constexpr bool words_fit() {
+    for (uint64_t n = 0; n <= kShortList + 1; n += kPassThreads)
+        for (uint64_t e : {n, n + 1})
+            if (words_used(e) > words_reserved(e)) return false;
+    return true;
+}
+static_assert(words_fit(), "no list uses more look-back words than its plan has (checked around every tile's edge)");
+
 struct Plan {
     uint64_t n, E, N;
     int wb, db, kb, passes, key_bytes, dpasses;
     bool sym, simple, hist, directed_hist, xor_mode;
     bool fused_finish;  // the last pass writes the CSR (FINAL) instead of keys
     uint64_t power;  // (XOR) entries of the Kronecker power, beside the N sorted ones
-    bool short_tiles;  // digit passes over tiles of kShortItems keys per thread
+    int items;  // keys per thread of the digit passes' tiles
     uint64_t pass_tiles, fin_tiles, chunks;
+    uint64_t status_bytes;  // of the region of the passes' look-back words
     // workspace carving
     size_t off_keysA, off_keysB, off_status, off_ghist, off_gbase, off_indeg, off_rpraw, off_mark,
         off_cmark, off_cmin, off_fstatus, off_split, off_tables, total;
@@ -1454,9 +1492,9 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.kb = p.wb + p.db;
     p.passes = (p.kb + 7) / 8;
     p.key_bytes = p.kb <= 32 ? 4 : 8;
-    constexpr uint64_t short_tile = kPassThreads * kShortItems;
-    p.short_tiles = p.N <= kShortTiles * short_tile;
-    p.pass_tiles = p.short_tiles ? (p.N + short_tile - 1) / short_tile : (p.N + kPassTile - 1) / kPassTile;
+    p.items = pass_items(p.N);
+    p.pass_tiles = tiles_of(p.N, p.items);
+    p.status_bytes = words_reserved(p.N);
     p.fin_tiles = (p.N + power + fin_tile(xor_mode) - 1) / fin_tile(xor_mode);
     // Without SIMPLE no entry is dropped, so sorted positions are output
     // positions and the last pass can write the columns itself -- unless it
@@ -1474,7 +1512,7 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     const uint64_t records = p.fused_finish ? 2 * p.pass_tiles * kRadix * p.key_bytes + 4 * p.pass_tiles : 0;
     p.off_keysA = take(std::max<uint64_t>(p.N * p.key_bytes, records));
     p.off_keysB = take(p.N * p.key_bytes);
-    p.off_status = take(std::max<uint64_t>(p.pass_tiles, 1) * kRadix * 8);
+    p.off_status = take(p.status_bytes);
     p.off_ghist = take(8 * kRadix * 8);
     p.off_gbase = take(kRadix * 8);
     p.off_indeg = take(p.directed_hist ? (n + 1) * 8 : 0);
@@ -1583,7 +1621,7 @@ void clear_csr(const Plan &P, uint64_t *row_ptr, uint64_t *hist, uint64_t *dups,
         words = std::max(words, c.r[c.regions - 1].words);
     };
     region(P.off_ghist, 8 * kRadix * 8);
-    if (P.N) region(P.off_status, P.pass_tiles * kRadix * 8);
+    if (P.N) region(P.off_status, words_used(P.N));
     if (P.simple && P.fin_tiles) region(P.off_fstatus, P.fin_tiles * 8);
     // Row (and column) starts are written only where a row begins and
     // flagged in the mark bytes; the row fill completes the rest.
@@ -1603,12 +1641,14 @@ void clear_csr(const Plan &P, uint64_t *row_ptr, uint64_t *hist, uint64_t *dups,
 }
 
 template <typename IdT, typename KeyT, bool SYM, bool FIRST, bool BOUND, bool FINAL>
-void launch_pass(const PassArgs &a, int grid, bool short_tiles, hipStream_t s) {
+void launch_pass(const PassArgs &a, int grid, int items, hipStream_t s) {
     ProfScope _ps("radix_pass", s);
-    if (short_tiles)
-        radix_pass<IdT, KeyT, SYM, FIRST, BOUND, FINAL, true><<<grid, kPassThreads, 0, s>>>(a);
+    if (items == kShortItems)
+        radix_pass<IdT, KeyT, SYM, FIRST, BOUND, FINAL, kShortItems><<<grid, kPassThreads, 0, s>>>(a);
+    else if (items == kMidItems)
+        radix_pass<IdT, KeyT, SYM, FIRST, BOUND, FINAL, kMidItems><<<grid, kPassThreads, 0, s>>>(a);
     else
-        radix_pass<IdT, KeyT, SYM, FIRST, BOUND, FINAL, false><<<grid, kPassThreads, 0, s>>>(a);
+        radix_pass<IdT, KeyT, SYM, FIRST, BOUND, FINAL, kPassItems><<<grid, kPassThreads, 0, s>>>(a);
 }
 
 template <typename IdT, typename KeyT>
@@ -1661,16 +1701,16 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
                     a.dec_groups = up->groups;
                     a.dec_bits = up->bits;
                 }
-                launch_pass<IdT, KeyT, false, false, false, true>(a, g, P.short_tiles, s);
+                launch_pass<IdT, KeyT, false, false, false, true>(a, g, P.items, s);
             } else if (csc && p == P.dpasses) {
-                launch_pass<IdT, KeyT, false, false, true, false>(a, g, P.short_tiles, s);
+                launch_pass<IdT, KeyT, false, false, true, false>(a, g, P.items, s);
             } else if (p == 0 && !keys_given) {
                 if (P.sym)
-                    launch_pass<IdT, KeyT, true, true, false, false>(a, g, P.short_tiles, s);
+                    launch_pass<IdT, KeyT, true, true, false, false>(a, g, P.items, s);
                 else
-                    launch_pass<IdT, KeyT, false, true, false, false>(a, g, P.short_tiles, s);
+                    launch_pass<IdT, KeyT, false, true, false, false>(a, g, P.items, s);
             } else {
-                launch_pass<IdT, KeyT, false, false, false, false>(a, g, P.short_tiles, s);
+                launch_pass<IdT, KeyT, false, false, false, false>(a, g, P.items, s);
             }
         }
     }
@@ -1686,7 +1726,11 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
                    keysA + P.pass_tiles * kRadix, reinterpret_cast<const uint32_t *>(keysA + 2 * P.pass_tiles * kRadix),
                    row_ptr, P.N, mark, dups, err, P.db, (uint32_t)(last + 1), run_tiles};
         const int rg = (int)((P.pass_tiles + run_tiles - 1) / run_tiles);
-        { ProfScope _ps("csr_run_starts", s); csr_run_starts<KeyT><<<rg, kRadix, 0, s>>>(ra); }
+        ProfScope _ps("csr_run_starts", s);
+        if (P.items < kPassItems)
+            csr_run_starts<KeyT, uint32_t><<<rg, kRadix, 0, s>>>(ra);
+        else
+            csr_run_starts<KeyT, uint64_t><<<rg, kRadix, 0, s>>>(ra);
     } else if (P.xor_mode) {
         ProfScope _ps("csr_finish", s);
         xor_split<KeyT><<<(int)((P.fin_tiles + 256) / 256), 256, 0, s>>>(
@@ -1716,8 +1760,8 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
     const uint64_t cpad = (P.chunks + kChunkBatch - 1) / kChunkBatch * kChunkBatch;  // (vector loads)
     f.a[1].cmin = status;
     f.a[2].cmin = status + cpad;
-    if ((uint64_t)(f.count - 1) * cpad > std::max<uint64_t>(P.pass_tiles, 1) * kRadix) {
-        // (more rows than 2^19 per tile of entries: one array after the other,
+    if ((uint64_t)(f.count - 1) * cpad * 8 > P.status_bytes) {
+        // (more rows than 2^20 per tile of entries and spare tile: one array after the other,
         // then the histogram from filled arrays)
         for (int q = 0; q < f.count; ++q) {
             FillArrays one = f;
@@ -2181,10 +2225,7 @@ extern "C" int edges_to_csr(uint64_t n, uint64_t num_edges, const void *src, con
 namespace sfg {
 namespace {
 constexpr size_t kNoAllocScratch = 64ull << 20;
-// Room beside it for the look-back words that a list sorted in short tiles has
-// more of, so that the limit is the same for it.
-constexpr size_t kShortExtra = kShortTiles * kRadix * 8;
-__device__ __align__(256) unsigned char scratch[kNoAllocScratch + kShortExtra];
+__device__ __align__(256) unsigned char scratch[kNoAllocScratch];
 
 char *noalloc_scratch() {
     static constexpr int kMaxDevs = 64;
@@ -2210,9 +2251,7 @@ extern "C" int edges_to_csr_noalloc(uint64_t n, uint64_t num_edges, const void *
                                     uint64_t *num_duplicates, void *stream) {
     if (n > 0 && (id_bytes == 4 || id_bytes == 8)) {
         const size_t need = sfg::csr_workspace_bytes(n, num_edges, id_bytes, flags);
-        const bool fits_short = num_edges <= sfg::kShortTiles * sfg::kPassThreads * sfg::kShortItems &&
-                                need <= sfg::kNoAllocScratch + sfg::kShortExtra;
-        if (need > sfg::kNoAllocScratch && !fits_short)
+        if (need > sfg::kNoAllocScratch)
             return fail(SFG_ERANGE,
                         "edges_to_csr_noalloc: %llu vertices and %llu edges need %zu scratch bytes, more than the "
                         "%zu of the static scratch array",
@@ -2221,5 +2260,5 @@ extern "C" int edges_to_csr_noalloc(uint64_t n, uint64_t num_edges, const void *
     char *ws = sfg::noalloc_scratch();
     if (!ws) return fail(SFG_EDEVICE, "edges_to_csr_noalloc: scratch address lookup failed");
     return csr_build(n, num_edges, src, dst, id_bytes, flags, row_ptr, col, degree_hist32, num_duplicates, ws,
-                     sfg::kNoAllocScratch + sfg::kShortExtra, as_stream(stream), nullptr);
+                     sfg::kNoAllocScratch, as_stream(stream), nullptr);
 }

@@ -149,3 +149,45 @@ def test_workspace_sizes_monotone(lib):
     assert 0 < a < b
     assert lib.pba_workspace_bytes(1 << 20, 4, 64, 1000) >= a
     assert lib.edges_to_csr_workspace_bytes(1 << 20, 1 << 22, 4, 0) < lib.edges_to_csr_workspace_bytes(1 << 20, 1 << 22, 4, 1)
+
+
+@pytest.mark.parametrize("flags", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [17, 5000, 100_000, 3_000_000])
+def test_csr_workspace_never_falls_with_the_edges(lib, n, flags):
+    """A workspace made for the longest list serves the shorter ones: no size
+    falls as edges are added, across the lines between the sort's tile sizes
+    too, for 4- and 8-byte keys."""
+    around = [0, 1, 2048, 8192, 30 * 2048, 64 * 2048, 142_784]
+    edges = sorted({max(0, e // d + o) for e in around for d in (1, 2) for o in (-1, 0, 1, 300)})
+    for size in (lambda e: lib.edges_to_csr_workspace_bytes(n, e, 4, flags), lambda e: lib.graph_stats_workspace_bytes(n, e, 4)):
+        got = [size(e) for e in edges]
+        assert got == sorted(got), [(a, b) for a, b, x, y in zip(edges, edges[1:], got, got[1:]) if y < x]
+
+
+def test_xor_workspace_never_falls_with_the_random_pairs(lib):
+    _, w = _W([1, 1, 0, 1, 1, 1, 0, 1, 1])
+    got = [lib.kron_xor_random_workspace_bytes(3, w, 7, r, 4) for r in (0, 1, 60_000, 61_440, 61_441, 131_072, 131_073, 133_230)]
+    assert got == sorted(got)
+
+
+@pytest.mark.parametrize("args,was", [((1024, 16384, 4, 0), 179200), ((5000, 131072, 4, 0), 1164800),
+                                      ((21677, 130578, 4, 0), 1327872), ((19165, 64878, 8, 3), 1277184)])
+def test_csr_workspace_is_no_larger_for_short_tiles(lib, args, was):
+    """Buffers of these sizes have been enough for these lists."""
+    assert lib.edges_to_csr_workspace_bytes(*args) <= was
+
+
+@pytest.mark.parametrize("edges,flags", [(20_000, 0), (60_000, 1), (100_000, 1), (131_072, 0), (1_000_000, 3)])
+def test_noalloc_limit_is_the_queried_size(lib, host_only, edges, flags):
+    """The static array serves exactly the lists whose queried size it holds."""
+    limit = lib.edges_to_csr_noalloc_max_bytes()
+    lo, hi = 1, 1 << 26  # vertices: the first that need more
+    while lo < hi:
+        mid = (lo + hi) // 2
+        if lib.edges_to_csr_workspace_bytes(mid, edges, 4, flags) > limit:
+            hi = mid
+        else:
+            lo = mid + 1
+    d = ctypes.c_void_p(256)
+    assert lib.edges_to_csr_noalloc(lo, edges, d, d, 4, flags, d, d, d, None, None) == -2
+    assert lib.edges_to_csr_noalloc(lo - 1, edges, d, d, 4, flags, d, d, d, None, None) == -4  # no device here

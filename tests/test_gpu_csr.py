@@ -237,3 +237,28 @@ def test_row_starts_over_the_edge_list(sfg, n, flags):
     kept = int(want[0][n])
     assert torch.equal(got[0], want[0]) and torch.equal(got[1][:kept], want[1][:kept])
     assert torch.equal(got[2], want[2]) and torch.equal(got[3], want[3])
+
+
+@pytest.mark.parametrize("id_bytes,n", [(4, 3_000), (8, 300_000)])
+@pytest.mark.parametrize("E", [28 * 2048, 30 * 2048 - 1, 30 * 2048, 30 * 2048 + 1, 31 * 3072 - 1, 31 * 3072, 31 * 3072 + 1])
+def test_csr_longest_short_tile_lists(sfg, orc, E, id_bytes, n):
+    """Directed and symmetrized lists on both sides of the most entries that are
+    sorted in short tiles, whose look-back words are the narrow ones."""
+    rng = np.random.default_rng(E)
+    src = np.minimum(rng.zipf(1.6, size=E) - 1, n - 1)
+    dst = rng.integers(0, n, size=E)
+    _check(sfg, orc, n, src, dst, 0, id_bytes)
+    _check(sfg, orc, n, src[:E // 2], dst[:E // 2], 3, id_bytes)
+
+
+def test_short_lists_in_a_workspace_made_for_a_longer_one(sfg):
+    """One buffer, sized for the longest list, serves every shorter one."""
+    import torch
+    n, longest = 5_000, 142_784
+    ws = sfg.workspace(sfg.edges_to_csr_workspace_bytes(n, longest, 4, 0))
+    src = torch.randint(0, n, (longest,), device="cuda", dtype=torch.int32)
+    dst = torch.randint(0, n, (longest,), device="cuda", dtype=torch.int32)
+    for E in (longest, 131_073, 131_072, 61_441, 61_440, 100, 0):
+        want = sfg.edges_to_csr(n, src[:E], dst[:E])
+        got = sfg.edges_to_csr(n, src[:E], dst[:E], ws=ws)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1][:E], want[1][:E]) and torch.equal(got[2], want[2])
