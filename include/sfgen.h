@@ -80,7 +80,7 @@ int sfg_device_error(void *stream, uint32_t *code);
  * milliseconds; sfg_profile_reset forgets all records.  Launches made while
  * the stream is being captured into a graph are not timed.  Kernel names:
  * "kron_sample", "kron_enumerate", "csr_prepare",
- * "radix_pass", "csr_finish", "csr_rowfill", "degree_hist", "fill",
+ * "radix_pass", "csr_finish", "csr_rowfill", "fill",
  * "pba_fill", "pba_resolve", "pba_tile_table", "pba_count", "pba_scan",
  * "pba_substitute", "stats_chunks", "stats_gamma",
  * "stats_wedge_scan", "stats_wedge", "path_level", "block_count",

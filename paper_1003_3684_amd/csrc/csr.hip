@@ -1192,7 +1192,7 @@ struct FillArrays {
         uint64_t *cmin;  // [chunks]
         bool degree;     // A[v + 1] - A[v] counts towards the degree of v
     } a[3];
-    int count;
+    int count, fills;    // arrays; the first `fills` of them are to be filled, the others only counted
     uint64_t n1, chunks;
     uint64_t *hist;
 };
@@ -1325,10 +1325,12 @@ __device__ __forceinline__ uint64_t marked_from(const FillArrays::One &a, uint64
 // values, the degree of v being the sum of A[v+1] - A[v] over the arrays that
 // count towards it.  SELF: the value after the chunk is looked for in the
 // marks here, not taken from the chunk scan, and the chunks are shorter: such a
-// fill has few of them, and each takes as long as its serial steps.
+// fill has few of them, and each takes as long as its serial steps.  REST: the
+// arrays from f.fills on have been filled before and are read for the degrees (as a
+// flag of the array it cost every fill with a histogram 9%).
 constexpr int kSelfChunk = 1024;
 
-template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_apply(FillArrays f) {
+template <bool HIST, bool SELF, bool REST = false> __global__ __launch_bounds__(256) void rowfill_apply(FillArrays f) {
     constexpr int kChunk = SELF ? kSelfChunk : kScanChunk, per = kChunk / 256;
     // Thread t owns rows t*per .. t*per+per-1 of the chunk; the results go
     // through LDS (one pad word per `per`) so the stores are coalesced.
@@ -1345,7 +1347,17 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
     if (HIST)
 #pragma unroll
         for (int j = 0; j < per; ++j) deg[j] = 0;
-    for (int q = 0; q < f.count; ++q) {
+    if (HIST && REST)
+        for (int q = f.fills; q < f.count; ++q) {
+            const FillArrays::One &a = f.a[q];
+            if (!a.degree) continue;
+#pragma unroll
+            for (int j = 0; j < per; ++j) {
+                const uint64_t v = c0 + 256 * j + tid;
+                if (v + 1 < n1) deg[j] += a.A[v + 1] - a.A[v];
+            }
+        }
+    for (int q = 0; q < (REST ? f.fills : f.count); ++q) {
         const FillArrays::One &a = f.a[q];
         const uint32_t bits = v0 >= n1 ? 0u : SELF ? load_marks4(a.mark, v0, n1) : load_marks16(a.mark, v0, n1);
         uint64_t x[per];
@@ -1400,27 +1412,6 @@ template <bool HIST, bool SELF> __global__ __launch_bounds__(256) void rowfill_a
     }
 }
 
-// The degree histogram from filled arrays.
-__global__ __launch_bounds__(256) void degree_hist(FillArrays f) {
-    __shared__ uint32_t s_h[32];
-    if (threadIdx.x < 32) s_h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
-    for (uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x; v - (threadIdx.x & 63) < f.n1 - 1; v += stride) {
-        const bool row = v < f.n1 - 1;
-        uint64_t deg = 0;
-        for (int q = 0; q < f.count; ++q)
-            if (row && f.a[q].degree) deg += f.a[q].A[v + 1] - f.a[q].A[v];
-        const int b = row ? log2_bin(deg) : 0;
-        const uint64_t zero = __ballot(row && b == 0);
-        if ((threadIdx.x & 63) == 0 && zero) atomicAdd(&s_h[0], (uint32_t)__popcll(zero));
-        if (row && b != 0) atomicAdd(&s_h[b], 1u);
-    }
-    __syncthreads();
-    if (threadIdx.x < 32 && s_h[threadIdx.x])
-        atomicAdd((unsigned long long *)&f.hist[threadIdx.x], (unsigned long long)s_h[threadIdx.x]);
-}
-
 // --------------------------------------------------------------------------- host
 int bits_for(uint64_t n) {  // bits to hold ids in [0, n)
     int b = 1;
@@ -1458,9 +1449,8 @@ struct Plan {
     uint64_t power;  // (XOR) entries of the Kronecker power, beside the N sorted ones
     int items;  // keys per thread of the digit passes' tiles
     uint64_t pass_tiles, fin_tiles, chunks;
-    uint64_t status_bytes;  // of the region of the passes' look-back words
     // workspace carving
-    size_t off_keysA, off_keysB, off_status, off_ghist, off_gbase, off_indeg, off_rpraw, off_mark,
+    size_t off_keysA, off_keysB, off_status, off_ghist, off_gbase, off_indeg, off_rpraw, off_mark,  // in this order
         off_cmark, off_cmin, off_fstatus, off_split, off_tables, total;
 };
 
@@ -1494,7 +1484,6 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.key_bytes = p.kb <= 32 ? 4 : 8;
     p.items = pass_items(p.N);
     p.pass_tiles = tiles_of(p.N, p.items);
-    p.status_bytes = words_reserved(p.N);
     p.fin_tiles = (p.N + power + fin_tile(xor_mode) - 1) / fin_tile(xor_mode);
     // Without SIMPLE no entry is dropped, so sorted positions are output
     // positions and the last pass can write the columns itself -- unless it
@@ -1512,7 +1501,7 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     const uint64_t records = p.fused_finish ? 2 * p.pass_tiles * kRadix * p.key_bytes + 4 * p.pass_tiles : 0;
     p.off_keysA = take(std::max<uint64_t>(p.N * p.key_bytes, records));
     p.off_keysB = take(p.N * p.key_bytes);
-    p.off_status = take(p.status_bytes);
+    p.off_status = take(words_reserved(p.N));
     p.off_ghist = take(8 * kRadix * 8);
     p.off_gbase = take(kRadix * 8);
     p.off_indeg = take(p.directed_hist ? (n + 1) * 8 : 0);
@@ -1589,9 +1578,11 @@ void row_fill(const FillArrays &f, hipStream_t s) {
             rowfill_apply<false, true><<<gs, 256, 0, s>>>(f);
         return;
     }
-    rowfill_first<<<dim3(g, f.count), 256, 0, s>>>(f);
-    rowfill_chunks<<<f.count, 1024, 0, s>>>(f);
-    if (f.hist)
+    rowfill_first<<<dim3(g, f.fills), 256, 0, s>>>(f);
+    rowfill_chunks<<<f.fills, 1024, 0, s>>>(f);
+    if (f.hist && f.fills < f.count)
+        rowfill_apply<true, false, true><<<g, 256, 0, s>>>(f);
+    else if (f.hist)
         rowfill_apply<true, false><<<g, 256, 0, s>>>(f);
     else
         rowfill_apply<false, false><<<g, 256, 0, s>>>(f);
@@ -1754,16 +1745,20 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
     add(row_ptr, mark, hist && !rp_raw_ws);
     if (rp_raw_ws) add(rp_raw_ws, mark, true);
     if (csc) add(csc, cmark, true);
-    // The chunk scans of a second and third array go where the look-back words
-    // were (8 bytes per 4,096 rows against 2 KB per tile).
+    // The chunk scans of a second and third array go where the keys and the
+    // look-back words were (8 bytes per 4,096 rows): nothing reads those any more.
     f.a[0].cmin = reinterpret_cast<uint64_t *>(ws + P.off_cmin);
     const uint64_t cpad = (P.chunks + kChunkBatch - 1) / kChunkBatch * kChunkBatch;  // (vector loads)
-    f.a[1].cmin = status;
-    f.a[2].cmin = status + cpad;
-    if ((uint64_t)(f.count - 1) * cpad * 8 > P.status_bytes) {
-        // (more rows than 2^20 per tile of entries and spare tile: one array after the other,
-        // then the histogram from filled arrays)
-        for (int q = 0; q < f.count; ++q) {
+    f.a[1].cmin = reinterpret_cast<uint64_t *>(ws + P.off_keysA);
+    f.a[2].cmin = f.a[1].cmin + cpad;
+    static_assert(kSelfChunks * 8 * 2 <= kSpareTiles * kRadix * 8, "a fill without a chunk scan needs no room");
+    f.fills = f.count;
+    if ((uint64_t)(f.count - 1) * cpad * 8 > P.off_indeg - P.off_keysA) {
+        // (a few entries over 8 million rows or more: one array after the other, the last
+        // one's launch reading the others' degrees)
+        f.fills = 1;
+        const int last = f.count - 1;
+        for (int q = 0; q < last; ++q) {
             FillArrays one = f;
             one.a[0] = f.a[q];
             one.a[0].cmin = f.a[0].cmin;
@@ -1771,13 +1766,11 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
             one.hist = nullptr;
             row_fill(one, s);
         }
-        if (hist) {
-            ProfScope _ps("degree_hist", s);
-            degree_hist<<<fill_grid(P.n), 256, 0, s>>>(f);
-        }
-    } else {
-        row_fill(f, s);
+        uint64_t *cmin = f.a[0].cmin;
+        std::swap(f.a[0], f.a[last]);
+        f.a[0].cmin = cmin;
     }
+    row_fill(f, s);
     return check_launch("edges_to_csr");
 }
 

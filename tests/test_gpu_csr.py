@@ -262,3 +262,29 @@ def test_short_lists_in_a_workspace_made_for_a_longer_one(sfg):
         want = sfg.edges_to_csr(n, src[:E], dst[:E])
         got = sfg.edges_to_csr(n, src[:E], dst[:E], ws=ws)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1][:E], want[1][:E]) and torch.equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("n", [5_000_011, 8_700_000, 17_400_000, 20_000_003])
+@pytest.mark.parametrize("E", [0, 3, 2_500])
+def test_csr_few_entries_over_many_rows(sfg, n, E):
+    """Row starts, columns and histogram where the row fill's chunk scans are longer
+    than the rest of the workspace (the arrays are then filled one after the
+    other), and where they just fit, with one and with two arrays beside row_ptr."""
+    import torch
+    rng = np.random.default_rng(n + E)
+    src, dst = rng.integers(0, n, E), rng.integers(0, n, E)
+    if E:
+        src[:2], dst[:2] = (0, n - 1), (n - 1, n - 1)
+    for flags in FLAG_SETS:
+        rp, col, hist, _ = _gpu_csr(sfg, n, src, dst, flags, 4)
+        u, v = (np.concatenate([src, dst]), np.concatenate([dst, src])) if flags & 1 else (src, dst)
+        key = np.sort(u * n + v)
+        if flags & 2:
+            key = np.unique(key[key // n != key % n])
+        want = np.zeros(n + 1, np.int64)
+        np.add.at(want, key // n + 1, 1)
+        np.testing.assert_array_equal(rp, np.cumsum(want))
+        np.testing.assert_array_equal(col[:len(key)], key % n)
+        deg = np.bincount(np.concatenate([src, dst]), minlength=n)
+        want = np.bincount(np.where(deg > 0, np.floor(np.log2(np.maximum(deg, 1))) + 1, 0).astype(np.int64), minlength=32)
+        np.testing.assert_array_equal(hist, want)
