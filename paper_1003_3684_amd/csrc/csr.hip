@@ -1787,7 +1787,10 @@ namespace sfg {
 
 size_t csr_workspace_bytes(uint64_t n, uint64_t num_edges, int id_bytes, uint32_t flags) {
     if (n == 0) return 0;
-    return make_plan(n, num_edges, id_bytes, flags, true).total;
+    // With the histogram or without it: a small directed list takes more without,
+    // since its shorter keys then let the last pass write the CSR, whose run records
+    // are longer than a few keys.
+    return std::max(make_plan(n, num_edges, id_bytes, flags, true).total, make_plan(n, num_edges, id_bytes, flags, false).total);
 }
 
 // The argument checks of edges_to_csr; on success P is its plan.

@@ -191,3 +191,15 @@ def test_noalloc_limit_is_the_queried_size(lib, host_only, edges, flags):
     d = ctypes.c_void_p(256)
     assert lib.edges_to_csr_noalloc(lo, edges, d, d, 4, flags, d, d, d, None, None) == -2
     assert lib.edges_to_csr_noalloc(lo - 1, edges, d, d, 4, flags, d, d, d, None, None) == -4  # no device here
+
+
+def test_csr_workspace_serves_calls_without_a_histogram(lib, host_only):
+    """The queried size is enough with and without degree_hist32 (a call that
+    passes every check ends at the missing device)."""
+    d = ctypes.c_void_p(256)
+    for n in list(range(1, 300)) + [1000, 70_000]:
+        for E in (1, 2, 10, 100, 600, 9000):
+            for flags in (0, 1, 2, 3):
+                need = lib.edges_to_csr_workspace_bytes(n, E, 4, flags)
+                for hist in (d, None):
+                    assert lib.edges_to_csr(n, E, d, d, 4, flags, d, d, hist, None, d, need, None) == -4, (n, E, flags, hist)

@@ -288,3 +288,16 @@ def test_csr_few_entries_over_many_rows(sfg, n, E):
         deg = np.bincount(np.concatenate([src, dst]), minlength=n)
         want = np.bincount(np.where(deg > 0, np.floor(np.log2(np.maximum(deg, 1))) + 1, 0).astype(np.int64), minlength=32)
         np.testing.assert_array_equal(hist, want)
+
+
+@pytest.mark.parametrize("n", [17, 40, 191])
+@pytest.mark.parametrize("E", [1, 10, 100, 600])
+def test_csr_without_a_histogram_in_the_queried_workspace(sfg, orc, n, E):
+    import torch
+    rng = np.random.default_rng(n + E)
+    src, dst = rng.integers(0, n, E), rng.integers(0, n, E)
+    rp, col, _, dups = sfg.edges_to_csr(n, torch.tensor(src).cuda(), torch.tensor(dst).cuda(), want_hist=False)
+    orp, ocol, odups = orc.edges_to_csr(n, src, dst)
+    np.testing.assert_array_equal(rp.cpu().numpy().astype(np.uint64), orp)
+    np.testing.assert_array_equal(col.cpu().numpy(), ocol)
+    assert int(dups.item()) == odups
