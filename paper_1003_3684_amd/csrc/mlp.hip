@@ -1058,7 +1058,8 @@ Ws carve(const Net &net, uint32_t B, void *base) {
 // every block reads from L2 cost more than the blocks' latency.  A step of
 // the 3 x 256 network in us with 1 / 2 / 4 tiles: 39 / 44 / 54 at batch 4,096,
 // 56 / 51 / 61 at 8,192, 85 / 87 / 75 at 12,000, 98 / 90 / 78 at 16,384, 428 /
-// 394 / 341 at 65,536.
+// 394 / 341 at 65,536.  (256 is the card's CU count, but a constant: the order of
+// the bias sums and the workspace's size are the same on every device.)
 int row_tiles(int Bp) {
     const int tiles = Bp / 16;
     return tiles <= 256 ? 1 : tiles <= 512 ? 2 : 4;
@@ -1288,6 +1289,9 @@ TrainWs carve_train(const Net &net, uint32_t B, void *base) {
     const int Bp = (int)((B + kFR - 1) / kFR * kFR);
     w.mt = row_tiles(Bp);
     w.blocks = Bp / (16 * w.mt);
+    // (room for as many blocks as any smaller batch has: fewer row tiles per block
+    // are more blocks, and a workspace sized for a longer batch serves those too)
+    const int room = std::max(w.blocks, std::min(Bp / 16, 256));
     w.slices = (Bp + kWSlice - 1) / kWSlice;
     w.t.L = net.L;
     w.t.B = (int)B;
@@ -1311,10 +1315,10 @@ TrainWs carve_train(const Net &net, uint32_t B, void *base) {
         w.t.xb[l] = c.take<bf16>(pin * Bp);
         w.t.z[l] = l + 1 < net.L ? c.take<float>(pout * Bp) : nullptr;
         w.t.dzb[l] = c.take<bf16>(pout * Bp);
-        w.t.dbp[l] = c.take<float>((size_t)w.blocks * net.layer[l].out);
+        w.t.dbp[l] = c.take<float>((size_t)room * net.layer[l].out);
         w.t.db[l] = c.take<float>(net.layer[l].out);
     }
-    w.t.lossp = c.take<float>(w.blocks);
+    w.t.lossp = c.take<float>(room);
     w.part = c.take<float>((size_t)w.slices * net.nparams);
     w.total = c.used;
     return w;

@@ -203,3 +203,14 @@ def test_csr_workspace_serves_calls_without_a_histogram(lib, host_only):
                 need = lib.edges_to_csr_workspace_bytes(n, E, 4, flags)
                 for hist in (d, None):
                     assert lib.edges_to_csr(n, E, d, d, 4, flags, d, d, hist, None, d, need, None) == -4, (n, E, flags, hist)
+
+
+def test_train_workspace_never_falls_with_the_batch(lib):
+    """Across the batches at which a block takes more rows, for narrow networks
+    above all: their block sums are more than a few rows' activations."""
+    from paper_1003_3684_amd.native import MlpShape
+    for d_in, width, d_out, hidden in ((1, 1, 34, 1), (10, 16, 34, 3), (10, 256, 34, 3), (1, 1, 256, 1), (3, 8, 5, 7)):
+        s = MlpShape(d_in, width, d_out, hidden)
+        got = [lib.mlp_train_workspace_bytes(ctypes.byref(s), b)
+               for b in (1, 64, 65, 4032, 4096, 4097, 4160, 4352, 8192, 8193, 8256, 16_384, 16_385)]
+        assert got == sorted(got), (d_in, width, d_out, hidden, got)
