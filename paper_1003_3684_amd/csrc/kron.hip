@@ -26,9 +26,9 @@ namespace sfg {
 namespace {
 
 constexpr int kBlock = 256;
-// The register-path sampler's LDS (byte counters, guide and packing tables,
-// about 53 KB) allows three workgroups per CU: 1,024-thread workgroups give
-// it the full 32 waves per CU to hide its LDS latency with.
+// The register-path sampler's LDS (byte counters and guide table: 64 to 66 KB)
+// allows two workgroups per CU: of 1,024 threads each they are the full 32 waves per
+// CU to hide its LDS latency with.
 constexpr int kFastBlock = 1024;
 
 }  // namespace
@@ -188,18 +188,28 @@ __global__ __launch_bounds__(kFastBlock) void kron_sample_fast(FastArgs a, IdT *
     auto entry_of = [&](uint32_t b) {
         return ((uint32_t)(a.lut_row >> (4 * b)) & 15u) | (((uint32_t)(a.lut_col >> (4 * b)) & 15u) << kColAt);
     };
+    // (without the guide table: the four buckets' entries, in scalar registers)
+    const uint32_t e0 = entry_of(0), e1 = entry_of(1), e2 = entry_of(2), e3 = entry_of(3);
     if (kGuide) {
-        for (uint32_t i = threadIdx.x; i < kGuideSize; i += kFastBlock) {
-            const uint32_t lo = i << (32 - kGuideBits), hi = lo | ((1u << (32 - kGuideBits)) - 1u);
-            const uint32_t blo = bucket_of<NT>(lo, a.tm1), bhi = bucket_of<NT>(hi, a.tm1);
-            s_guide[i] = (uint16_t)(blo == bhi ? entry_of(blo) : blo | kStraddle);
-        }
         if (threadIdx.x == 0) {
 #pragma unroll
             for (int i = 0; i <= NT; ++i) {
                 s_tm1[i] = i < NT ? a.tm1[i < NT ? i : 0] : 0xFFFFFFFFu;
                 s_entry[i] = (uint16_t)entry_of((uint32_t)i);
             }
+        }
+        __syncthreads();
+        // Every prefix's first word is compared, then the prefixes that a threshold
+        // lies inside are marked: with the last words compared as well the table
+        // of a launch over 2^20 edges took longer than its edges (see below).
+        constexpr uint32_t kRange = 32 - kGuideBits;
+        for (uint32_t i = threadIdx.x; i < kGuideSize; i += kFastBlock)
+            s_guide[i] = s_entry[bucket_of<NT>(i << kRange, a.tm1)];
+        __syncthreads();
+        if (threadIdx.x < NT) {
+            const uint32_t t = s_tm1[threadIdx.x];  // the last word below the threshold
+            if (((t + 1) & ((1u << kRange) - 1)) != 0)
+                s_guide[t >> kRange] = (uint16_t)(bucket_of<NT>(t >> kRange << kRange, a.tm1) | kStraddle);
         }
     }
     if (kGuide || CNT) __syncthreads();
@@ -236,18 +246,19 @@ __global__ __launch_bounds__(kFastBlock) void kron_sample_fast(FastArgs a, IdT *
         // prefix holds a threshold are decoded by comparison.
         uint32_t e[5];
 #pragma unroll
-        for (int i = 0; i < 5; ++i) e[i] = kGuide ? (uint32_t)s_guide[ws[i] >> (32 - kGuideBits)] : kStraddle;
-        if ((e[0] | e[1] | e[2] | e[3] | e[4]) & kStraddle) {
+        for (int i = 0; i < 5; ++i)
+            e[i] = kGuide                ? (uint32_t)s_guide[ws[i] >> (32 - kGuideBits)]
+                   : ws[i] > a.tm1[2]    ? e3
+                   : ws[i] > a.tm1[1]    ? e2
+                   : ws[i] > a.tm1[0]    ? e1
+                                         : e0;
+        if (kGuide && ((e[0] | e[1] | e[2] | e[3] | e[4]) & kStraddle)) {
 #pragma unroll
             for (int i = 0; i < 5; ++i)
                 if (e[i] & kStraddle) {
-                    if (kGuide) {
-                        uint32_t b = e[i] & 15u;
-                        while (ws[i] > s_tm1[b]) ++b;
-                        e[i] = s_entry[b];
-                    } else {
-                        e[i] = entry_of(bucket_of<NT>(ws[i], a.tm1));
-                    }
+                    uint32_t b = e[i] & 15u;
+                    while (ws[i] > s_tm1[b]) ++b;
+                    e[i] = s_entry[b];
                 }
         }
         if (FORM == Form::Packed) {
@@ -534,19 +545,29 @@ int grid_for(uint64_t items) {
     return (int)std::max<uint64_t>(1, std::min(want, cap));
 }
 
-int grid_fast(uint64_t items) {
+// Workgroups of the register-path sampler.  Below 2^25 edges, with a guide table
+// (each workgroup builds its own), at most the two per CU that are resident at
+// once: 2^20 edges of a 3 x 3 initiator 16.5 us, 21.7 with four per CU.  Otherwise
+// four, which end more evenly: 2^24 edges of a 2 x 2 initiator 172.7 us, 177.7 with
+// two; 2^26 of the 3 x 3 one 483 and 494.
+int grid_fast(uint64_t items, bool guide) {
     const uint64_t want = (items + kFastBlock - 1) / kFastBlock;
-    const uint64_t cap = (uint64_t)device_cu_count() * 4;
+    const uint64_t cap = (uint64_t)device_cu_count() * (guide && items < (1ull << 25) ? 2 : 4);
     return (int)std::max<uint64_t>(1, std::min(want, cap));
 }
 
 template <typename IdT, typename AccT, Form FORM, bool POW2, bool CNT>
 void launch_fast(const FastArgs &a, uint32_t nt, void *src, void *dst, hipStream_t s) {
-    const int g = grid_fast(a.num_edges);
+    // (three comparisons are cheaper than the table's look-ups and its building, but
+    // not than the two wide digits' extraction once the building is paid: four cells of
+    // a 5 x 5 initiator, compared / looked up, 10.7 / 14.3 us at 2^20 edges, 27.4 / 29.1 at
+    // 2^22, 48.7 / 46.8 at 2^23, 97.4 / 83.1 at 2^24)
+    const bool guide = FORM != Form::Bits && (nt > 3 || (FORM == Form::Wide && a.num_edges >= (1ull << 23)));
+    const int g = grid_fast(a.num_edges, guide);
     IdT *S = static_cast<IdT *>(src), *D = static_cast<IdT *>(dst);
     ProfScope _ps("kron_sample", s);
-    if (FORM == Form::Bits || (nt <= 3 && FORM != Form::Wide))
-        kron_sample_fast<IdT, AccT, FORM, POW2, FORM == Form::Wide ? 8 : 3, CNT><<<g, kFastBlock, 0, s>>>(a, S, D);
+    if (!guide)
+        kron_sample_fast<IdT, AccT, FORM, POW2, 3, CNT><<<g, kFastBlock, 0, s>>>(a, S, D);
     else if (nt <= 8)
         kron_sample_fast<IdT, AccT, FORM, POW2, FORM == Form::Bits ? 3 : 8, CNT><<<g, kFastBlock, 0, s>>>(a, S, D);
     else
@@ -555,8 +576,8 @@ void launch_fast(const FastArgs &a, uint32_t nt, void *src, void *dst, hipStream
 
 template <typename IdT, typename AccT, bool POW2, bool CNT>
 void launch_fast_form(const FastArgs &a, Form form, uint32_t nt, void *src, void *dst, hipStream_t s) {
-    if (form == Form::Bits)
-        launch_fast<IdT, AccT, Form::Bits, POW2, CNT>(a, nt, src, dst, s);
+    if (form == Form::Bits)  // (n0 = 2)
+        launch_fast<IdT, AccT, POW2 ? Form::Bits : Form::Narrow, POW2, CNT>(a, nt, src, dst, s);
     else if (form == Form::Packed)
         launch_fast<IdT, AccT, POW2 && CNT ? Form::Packed : Form::Narrow, POW2, CNT>(a, nt, src, dst, s);
     else if (form == Form::Narrow)
@@ -606,7 +627,7 @@ bool count_ok(const ByteCount &bc, uint64_t count, int id_bytes) {
     if (bc.pack_groups && (bc.pack_groups < 1 || bc.pack_bits < 1 || bc.pack_bits > 12 || !bc.pack_tab || bc.key_sym ||
                            (1 << bc.pack_bits) > kPackTabMax))
         return false;
-    const uint64_t threads = (uint64_t)grid_fast(count) * kFastBlock;
+    const uint64_t threads = (uint64_t)grid_fast(count, true) * kFastBlock;
     const uint64_t per_group = (count + threads - 1) / threads * kFastBlock;
     return 2 * per_group < (1ull << 32);
 }

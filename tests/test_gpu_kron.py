@@ -217,3 +217,36 @@ def test_kron_decodes_match_oracle(sfg, orc, n0, cells, k):
         np.testing.assert_array_equal(d1.cpu().numpy().astype(np.int64), od)
         assert torch.equal(rp1, rp2) and torch.equal(col1, col2) and torch.equal(h1, h2) and torch.equal(q1, q2)
     assert sfg.device_error() == 0
+
+
+@pytest.mark.parametrize("n0,weights", [
+    (3, [1, 2, 1, 4, 8, 16, 8, 16, 8]),                       # thresholds on the table's prefixes
+    (3, [16384 + 1, 65536 - 2, 3, 9, 1, 1, 1, 16384, 7]),     # beside them, and several in one prefix
+    (4, [1] * 16),                                            # 15 of them, each on a prefix
+    (4, [3, 1, 2, 1, 5, 1, 1, 1, 9, 1, 4, 1, 1, 60000, 1, 1]),
+    (5, [0, 7, 0, 0, 1, 0, 0, 2, 0, 0, 30, 0, 0, 0, 1, 1, 0, 0, 50, 0, 0, 3, 0, 0, 0]),
+])
+def test_kron_guide_table_thresholds(sfg, orc, n0, weights):
+    """Initiators whose thresholds lie on the first word of a guide-table prefix,
+    just beside one, or several within one prefix."""
+    W = np.array(weights, np.float32).reshape(n0, n0)
+    c = dict(n0=n0, initiator=W, k=7, num_edges=400_003, seed=5, graph_id=3, id_bytes=4)
+    src, dst = _gpu(sfg, c)
+    os_, od = orc.kron_sample(n0, W, 7, 400_003, 5, 3)
+    np.testing.assert_array_equal(src.cpu().numpy(), os_)
+    np.testing.assert_array_equal(dst.cpu().numpy(), od)
+
+
+@pytest.mark.parametrize("n0", [5, 16])
+@pytest.mark.parametrize("cells", [1, 2, 4])
+def test_kron_wide_sparse_initiators(sfg, n0, cells):
+    """At most three thresholds over a wide initiator: compared in launches of fewer
+    than 2^23 edges, looked up from there on, with the same ids."""
+    import torch
+    pick = np.random.default_rng(n0 + cells).choice(n0 * n0, cells, replace=False)
+    W = _support(n0, [divmod(int(c), n0) for c in pick], n0 + cells)
+    E, k = (1 << 23) + 5, 5
+    src, dst = sfg.kron_generate(n0, W, k, E, seed=21)
+    for e0, count in ((0, 1 << 22), (1 << 22, (1 << 23) - 1 - (1 << 22)), (E - 6, 6)):
+        a, b = sfg.kron_generate_range(n0, W, k, E, e0, count, seed=21)
+        assert torch.equal(a, src[e0:e0 + count]) and torch.equal(b, dst[e0:e0 + count])
