@@ -1139,12 +1139,19 @@ static int enqueue(const PbaPlan &pl, const Graphs &G, const Factions &fac, uint
     const int cus = device_cu_count();
     const int res_grid = cus * 8 / kXcd * kXcd;  // (a multiple of the XCDs)
     const uint32_t S = pl.S, items = resolve_items(pl.E, cus);
-    // Tickets from kTicketRounds tiles per resident workgroup on.  Both phases
-    // in us, tickets / tiles by workgroup id (m = 5): 404 / 29 at 65,536
-    // vertices (m = 4), 422 / 135 at 10^6, 667 / 369 at 4 10^6, 893 / 760 at
-    // 8 10^6 (4.8 tiles each), 1,304 / 1,414 (64 partitions) and 1,460 / 1,339
-    // (1,024) at 16 10^6, 4,765 / 6,351 at 64 10^6.
-    const bool tickets = pl.E > kTicketRounds * (uint64_t)items * kResThreads * (uint64_t)res_grid;
+    // Tickets from kTicketRounds tiles per resident workgroup on, from half as many
+    // where the partitions spread unevenly over the queues (more than one in eight
+    // places empty): tiles of all queues taken in turn lie further apart in their
+    // segments.  One to three partitions are the exception, measured below.
+    // The whole generation in us, tickets / tiles by workgroup id (m = 5): 556 / 200 at 10^6
+    // vertices in 8 partitions, 1,451 / 1,001 at 8 10^6 (4.8 tiles each), 2,229 / 1,750 at 13 10^6
+    // (7.8), both phases alone 4,765 / 6,351 at 64 10^6; in 12 partitions 556 / 293 at 10^6, 1,178 /
+    // 1,125 at 6 10^6 (3.6), 1,435 / 1,537 at 8 10^6, 2,174 / 2,258 at 13 10^6; in one 1,747 /
+    // 1,476 at 8 10^6, 2,672 / 2,450 at 13 10^6.  (At 16 10^6, 9.5 tiles each, both ways are within a
+    // tenth of each other: 1,304 / 1,414 for the phases with 64 partitions, 1,460 / 1,339 with 1,024.)
+    const uint64_t places = (uint64_t)(S + kXcd - 1) / kXcd * kXcd;
+    const uint64_t rounds = S > 3 && places * 8 > (uint64_t)S * 9 ? kTicketRounds / 2 : kTicketRounds;
+    const bool tickets = pl.E > rounds * items * kResThreads * (uint64_t)res_grid;
 
     // Phase 1: every slot's label, drawn and resolved in one pass over
     // sentinel-initialised labels.

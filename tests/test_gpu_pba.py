@@ -121,3 +121,14 @@ def test_substitution_tiles_match_oracle(sfg, orc, n, m, P, id_bytes):
     assert sfg.device_error() == 0
     es, ed = orc.pba_generate(n, m, P, 0.3, n)
     assert np.array_equal(src.cpu().numpy(), es) and np.array_equal(dst.cpu().numpy(), ed)
+
+
+@pytest.mark.parametrize("P", [3, 12, 16])
+def test_tile_dealing_between_the_lines_matches_oracle(sfg, orc, P):
+    """Between 4 and 8 tiles per resident workgroup: tickets where the partitions
+    spread unevenly over the queues, by workgroup id where they are few or even."""
+    n, m = 7_000_003, 5
+    src, dst = sfg.pba_generate(n, m, P, 0.2, seed=P)
+    es, ed = orc.pba_generate(n, m, P, 0.2, P)
+    assert np.array_equal(src.cpu().numpy(), es) and np.array_equal(dst.cpu().numpy(), ed)
+    assert sfg.device_error() == 0
