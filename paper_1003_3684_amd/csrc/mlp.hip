@@ -866,20 +866,23 @@ template <bool TR> __global__ __launch_bounds__(256) void eval_fragments(EvalArg
 // values also to keep (row-major) when given.
 template <int MT>
 __device__ __forceinline__ void stage_rows(const float *v, int cols, int r0, int B, bf16 (*sA)[kFMax + 8], bf16 *keep) {
-    const int K = round32(cols), n = 16 * MT * K;
-    for (int i0 = 0; i0 < n; i0 += 64 * kRW * 4) {
-        float t[4];
+    // A thread takes one column of every 32-column piece, rows 16 apart: no division
+    // per value (one row-column pair per thread and step took 1,246 us of a forward
+    // pass of 2^20 rows of 256, now 962).
+    constexpr int kStep = 64 * kRW / 32;
+    const int c0 = (int)threadIdx.x % 32, r1 = (int)threadIdx.x / 32;
+    for (int c = c0; c < round32(cols); c += 32) {
+        float t[MT];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = i0 + 64 * kRW * u + (int)threadIdx.x, r = i / K, c = i % K;
-            const bool ok = i < n && c < cols && r0 + r < B;
+        for (int u = 0; u < MT; ++u) {
+            const int r = r1 + kStep * u;
+            const bool ok = c < cols && r0 + r < B;
             t[u] = v[ok ? (size_t)(r0 + r) * cols + c : 0];
             if (!ok) t[u] = 0.f;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = i0 + 64 * kRW * u + (int)threadIdx.x, r = i / K, c = i % K;
-            if (i >= n) break;
+        for (int u = 0; u < MT; ++u) {
+            const int r = r1 + kStep * u;
             const bf16 b = f2bf(t[u]);
             sA[r][c] = b;
             if (keep && c < cols && r0 + r < B) keep[(size_t)(r0 + r) * cols + c] = b;
@@ -1083,6 +1086,28 @@ template <typename F> void launch_rows(uint32_t B, F f) {
         f(std::integral_constant<int, 4>(), blocks);
 }
 
+// Whether the fused evaluation of B rows is the faster.  It takes a time per row
+// and layer that hardly depends on the widths, the unfused one a time per value
+// that its kernels pass on between them (and a few us per launch): narrow layers
+// are cheaper unfused from some batch on.  Measured in us, unfused / fused, widths in x
+// hidden out:
+//   forward   3 16 5: 20 / 11 at 16,384, 22 / 32 at 65,536, 40 / 114 at 262,144;
+//             10 3x32 34: 31 / 19, 57 / 57, 116 / 208; 10 3x64 34: 39 / 20, 80 / 60, 173 / 227;
+//             10 3x96 34: 48 / 21, 84 / 62, 268 / 238; 256 64 5: 27 / 19, 47 / 56, 194 / 258
+//   backward  3 16 5: 15 / 10, 17 / 23, 34 / 82; 10 3x32 34: 27 / 15, 52 / 46, 118 / 168;
+//             10 3x64 34: 34 / 15, 72 / 49, 203 / 180
+// The lines are fitted to those and 14 more networks at 16,384 to 2^20 rows: with 76
+// values passed on per layer forward and 36 backward both take the same in the
+// limit; the staged columns weigh an eighth against the fused kernel forward, a
+// sixth for it backward.
+bool fused_is_faster(const Net &net, uint64_t B, bool backward) {
+    const int64_t in = net.layer[0].in, out = net.layer[net.L - 1].out;
+    int64_t hidden = 0;
+    for (int l = 1; l < net.L; ++l) hidden += net.layer[l].in;
+    const int64_t lack = backward ? 36 * net.L - hidden - out / 6 : 76 * net.L + in / 8 - hidden - out;
+    return lack <= 0 || B * (uint64_t)lack <= (uint64_t)net.L * (backward ? 1 << 20 : 7 << 18);
+}
+
 bool overlap(const float *a, size_t na, const float *b, size_t nb) {
     const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
     return pa < pb + nb * sizeof(float) && pb < pa + na * sizeof(float);
@@ -1090,14 +1115,14 @@ bool overlap(const float *a, size_t na, const float *b, size_t nb) {
 
 // The evaluation's arguments for a network and workspace, its fragments in the
 // split-K scratch; in and out are the call's, [B][cin] and [B][cout].  False, and
-// the unfused kernels run, when the network is not one the fused kernels take or
-// so narrow that its padded fragments do not fit there (below a width of 32 or
-// so), when out shares memory with in (a block of the fused kernel writes its
+// the unfused kernels run, when the network is not one the fused kernels take, too
+// narrow for the batch, or so narrow that its padded fragments do not fit there
+// (below a width of 16 or so), when out shares memory with in (a block of the fused kernel writes its
 // rows of out while others still have theirs of in to read), or when the scratch
 // is not aligned for the fragments' 16-byte accesses.
 bool eval_args(const Net &net, uint32_t B, const Ws &w, const float *params, bool transposed, const float *in, int cin,
                const float *out, int cout, EvalArgs &a, int &tiles) {
-    if (!fused_ok(net) || overlap(in, (size_t)B * cin, out, (size_t)B * cout) || (uintptr_t)w.part % 16) return false;
+    if (!fused_ok(net) || !fused_is_faster(net, B, transposed) || overlap(in, (size_t)B * cin, out, (size_t)B * cout) || (uintptr_t)w.part % 16) return false;
     memset(&a, 0, sizeof(a));
     a.L = net.L;
     a.B = (int)B;

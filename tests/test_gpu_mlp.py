@@ -332,3 +332,26 @@ def test_evaluation_in_a_workspace_off_16_bytes(sfg):
     ws = sfg.workspace(g["ws"].numel() + 4)[4:]
     assert torch.equal(sfg.mlp_forward(shape, g["params"], g["x"], ws), y)
     assert torch.equal(sfg.mlp_backward(shape, g["params"], dy, ws, want_grad=False, want_dx=True)[1], dx)
+
+
+@pytest.mark.parametrize("shape_t,batches", [((3, 16, 5, 1), (28015, 28016, 37449, 37450)),
+                                             ((10, 32, 34, 3), (41943, 41944, 97541, 97542)),
+                                             ((256, 16, 5, 1), (22515, 22516))])
+def test_evaluation_of_narrow_networks_at_large_batches(sfg, shape_t, batches):
+    """Both sides of the batches from which narrow networks are evaluated unfused:
+    the first and the last rows give the bits that they give alone."""
+    import torch
+    for B in batches:
+        shape, params, x, t, g = _setup(sfg, shape_t, 1, 3)
+        gen = torch.Generator(device="cuda").manual_seed(B)
+        x = torch.randn(B, shape_t[0], device="cuda", generator=gen)
+        dy = torch.randn(B, shape_t[2], device="cuda", generator=gen)
+        ws = sfg.workspace(sfg.mlp_workspace_bytes(shape, B))
+        y = sfg.mlp_forward(shape, g["params"], x, ws)
+        _, dx = sfg.mlp_backward(shape, g["params"], dy, ws, want_grad=False, want_dx=True)
+        for rows in (slice(0, 100), slice(B - 77, B)):
+            part = x[rows].contiguous()
+            ws1 = sfg.workspace(sfg.mlp_workspace_bytes(shape, part.shape[0]))
+            assert torch.equal(sfg.mlp_forward(shape, g["params"], part, ws1), y[rows])
+            _, dx1 = sfg.mlp_backward(shape, g["params"], dy[rows].contiguous(), ws1, want_grad=False, want_dx=True)
+            assert torch.equal(dx1, dx[rows])
