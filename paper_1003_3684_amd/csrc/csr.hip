@@ -73,8 +73,21 @@ constexpr int kPlainThreads = 256;
 // 1e8 entries at 256 x 16 / 512 x 8 / 512 x 12 / 512 x 16: 2,562 / 2,469 / 2,605 /
 // 2,398.
 constexpr int kFinThreads = 512, kFinItems = 16;
+constexpr int kFinTile = kFinThreads * kFinItems;
 constexpr int kXorThreads = 512, kXorItems = 16;
-constexpr int fin_tile(bool xor_mode) { return xor_mode ? kXorThreads * kXorItems : kFinThreads * kFinItems; }
+// Fewer entries make shorter tiles: a thread's entries are walked one after the
+// other, and over a power of sparse rows most of them are looked up from the top, so
+// that a tile is a long chain which a few tiles do not hide.  The whole graph in us
+// with 16 / 8 / 4 entries per thread: 8,192 entries in rows of one, with 50,000 random pairs, 157 /
+// 131 / 116; 248,832 with as many, rows of 12^5 / 8^5, 129 / 114 / 106; 1,771,561 with 50,000
+// 97 / 91 / 95, with 7,086,244 314 / 300 / 323; 19,487,171 alone 112 / 121 / 181, with as many random
+// pairs 922 / 919 / 1,043.
+constexpr int kXorMidItems = 8, kXorShortItems = 4;
+constexpr uint64_t kXorShort = 1 << 20, kXorMid = 1 << 24;  // entries, at most
+constexpr int xor_items(uint64_t entries) {
+    return entries <= kXorShort ? kXorShortItems : entries <= kXorMid ? kXorMidItems : kXorItems;
+}
+constexpr uint64_t xor_tiles(uint64_t entries, int items) { return (entries + kXorThreads * items - 1) / (kXorThreads * items); }
 
 constexpr int kScanChunk = 4096;  // vertices per chunk of the row fill scan
 constexpr int kPrepThreads = 1024;
@@ -721,7 +734,7 @@ struct FinArgs {
     int wb;
     // XOR: `keys` are the random graph's `random` sorted pairs; N counts them
     // and the power's entries together.  split[t]: how many of the random pairs
-    // come before merged position t kFinTile.
+    // come before the first position of tile t.
     uint64_t random;
     const uint64_t *split;
 };
@@ -839,11 +852,11 @@ __global__ __launch_bounds__(kFinThreads, 4) void csr_finish(FinArgs a) {
     constexpr int kWaves = kFinThreads / 64;
     __shared__ uint32_t s_counts[kWaves];  // kept entries of a wave | repeats << 16
     __shared__ uint64_t s_base;
-    static_assert(fin_tile(false) < (1 << 16), "a tile's counts fit 16 bits");
+    static_assert(kFinTile < (1 << 16), "a tile's counts fit 16 bits");
     const uint32_t lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t tile = blockIdx.x;  // dispatch order (see radix_pass)
-    const uint64_t base = tile * fin_tile(false) + (uint64_t)w * 64 * kFinItems;  // of the wave
+    const uint64_t base = tile * kFinTile + (uint64_t)w * 64 * kFinItems;  // of the wave
     const KeyT *K = static_cast<const KeyT *>(a.keys);
     const KeyT mask = ((KeyT)1 << a.wb) - 1;
     KeyT k[kFinItems];
@@ -901,7 +914,7 @@ __global__ __launch_bounds__(kFinThreads, 4) void csr_finish(FinArgs a) {
     if (threadIdx.x == 0) {
         if (a.dups && (all >> 16)) atomicAdd((unsigned long long *)a.dups, (unsigned long long)(all >> 16));
         // The last tile closes row n.
-        if ((tile + 1) * fin_tile(false) >= a.N) {
+        if ((tile + 1) * kFinTile >= a.N) {
             a.rp[a.n] = s_base + tot;
             if (a.rp_raw) a.rp_raw[a.n] = a.N;
             a.mark[a.n] = 1;
@@ -920,14 +933,14 @@ __device__ __forceinline__ uint64_t merged_position(const Power &p, const CountT
 
 // split[t] for every tile boundary t = 0 .. tiles, by binary search.
 template <typename KeyT>
-__global__ __launch_bounds__(256) void xor_split(Power p, const KeyT *R, uint64_t random, uint64_t N, uint64_t tiles, int wb,
-                                                 uint64_t *split) {
+__global__ __launch_bounds__(256) void xor_split(Power p, const KeyT *R, uint64_t random, uint64_t N, uint64_t tiles, int tile,
+                                                 int wb, uint64_t *split) {
     __shared__ CountTables s_t;
     power_load(p, &s_t);
     __syncthreads();
     const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     if (t > tiles) return;
-    const uint64_t d = min(t * fin_tile(true), N);
+    const uint64_t d = min(t * tile, N);
     uint64_t lo = d > p.entries ? d - p.entries : 0, hi = min(d, random);
     while (lo < hi) {
         const uint64_t mid = lo + (hi - lo) / 2;
@@ -952,9 +965,9 @@ __global__ __launch_bounds__(256) void xor_split(Power p, const KeyT *R, uint64_
 // its table loads.  Counting what it keeps only after the walk made every tile
 // wait for the slowest one in flight (3.0 ms; 2.4 with the counts published
 // before it), and a walk that waited for each middle column itself 2.4.
-template <typename IdT, typename RawT>
+template <typename IdT, typename RawT, int ITEMS>
 __global__ __launch_bounds__(kXorThreads, 4) void csr_finish_xor(FinArgs a, Power pw) {
-    constexpr int kThreads = kXorThreads, kItems = kXorItems, kTile = fin_tile(true);
+    constexpr int kThreads = kXorThreads, kItems = ITEMS, kTile = kThreads * kItems;
     using KeyT = uint64_t;
     // The walk writes kItems consecutive entries per thread, which would hit few
     // LDS banks across the wave; one pad slot per 16 entries spreads them.  Slot
@@ -1448,6 +1461,7 @@ struct Plan {
     bool fused_finish;  // the last pass writes the CSR (FINAL) instead of keys
     uint64_t power;  // (XOR) entries of the Kronecker power, beside the N sorted ones
     int items;  // keys per thread of the digit passes' tiles
+    int xor_items;  // entries per thread of the XOR finish's tiles
     uint64_t pass_tiles, fin_tiles, chunks;
     // workspace carving
     size_t off_keysA, off_keysB, off_status, off_ghist, off_gbase, off_indeg, off_rpraw, off_mark,  // in this order
@@ -1484,7 +1498,8 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.key_bytes = p.kb <= 32 ? 4 : 8;
     p.items = pass_items(p.N);
     p.pass_tiles = tiles_of(p.N, p.items);
-    p.fin_tiles = (p.N + power + fin_tile(xor_mode) - 1) / fin_tile(xor_mode);
+    p.xor_items = xor_items(p.N + power);
+    p.fin_tiles = xor_mode ? xor_tiles(p.N + power, p.xor_items) : (p.N + kFinTile - 1) / kFinTile;
     // Without SIMPLE no entry is dropped, so sorted positions are output
     // positions and the last pass can write the columns itself -- unless it
     // is also the first pass or the pass that marks column starts.
@@ -1509,8 +1524,13 @@ Plan make_plan(uint64_t n, uint64_t E, int id_bytes, uint32_t flags, bool want_h
     p.off_mark = take(n + 1);
     p.off_cmark = take(p.directed_hist ? n + 1 : 0);
     p.off_cmin = take(std::max<uint64_t>(p.chunks, 1) * 8);
-    p.off_fstatus = take(p.simple ? std::max<uint64_t>(p.fin_tiles, 1) * 8 : 0);
-    p.off_split = take(xor_mode ? (p.fin_tiles + 1) * 8 : 0);
+    // (XOR: room for as many tiles as any fewer entries have)
+    uint64_t most = std::max<uint64_t>(p.fin_tiles, 1);
+    if (xor_mode)
+        most = std::max({most, xor_tiles(std::min(p.N + power, kXorShort), kXorShortItems),
+                         xor_tiles(std::min(p.N + power, kXorMid), kXorMidItems)});
+    p.off_fstatus = take(p.simple ? most * 8 : 0);
+    p.off_split = take(xor_mode ? (most + 1) * 8 : 0);
     p.off_tables = take(xor_mode ? sizeof(PowerTables) : 0);
     p.total = o;
     (void)id_bytes;
@@ -1725,8 +1745,13 @@ int run_csr(const Plan &P, const void *src, const void *dst, uint64_t *row_ptr, 
     } else if (P.xor_mode) {
         ProfScope _ps("csr_finish", s);
         xor_split<KeyT><<<(int)((P.fin_tiles + 256) / 256), 256, 0, s>>>(
-            *pw, keysA, P.N, entries, P.fin_tiles, P.db, reinterpret_cast<uint64_t *>(ws + P.off_split));
-        csr_finish_xor<IdT, KeyT><<<(int)P.fin_tiles, kXorThreads, 0, s>>>(fa, *pw);
+            *pw, keysA, P.N, entries, P.fin_tiles, kXorThreads * P.xor_items, P.db, reinterpret_cast<uint64_t *>(ws + P.off_split));
+        if (P.xor_items == kXorItems)
+            csr_finish_xor<IdT, KeyT, kXorItems><<<(int)P.fin_tiles, kXorThreads, 0, s>>>(fa, *pw);
+        else if (P.xor_items == kXorMidItems)
+            csr_finish_xor<IdT, KeyT, kXorMidItems><<<(int)P.fin_tiles, kXorThreads, 0, s>>>(fa, *pw);
+        else
+            csr_finish_xor<IdT, KeyT, kXorShortItems><<<(int)P.fin_tiles, kXorThreads, 0, s>>>(fa, *pw);
     } else if (P.simple) {
         ProfScope _ps("csr_finish", s);
         csr_finish<IdT, KeyT><<<(int)P.fin_tiles, kFinThreads, 0, s>>>(fa);

@@ -214,3 +214,10 @@ def test_train_workspace_never_falls_with_the_batch(lib):
         got = [lib.mlp_train_workspace_bytes(ctypes.byref(s), b)
                for b in (1, 64, 65, 4032, 4096, 4097, 4160, 4352, 8192, 8193, 8256, 16_384, 16_385)]
         assert got == sorted(got), (d_in, width, d_out, hidden, got)
+
+
+def test_xor_workspace_never_falls_across_its_tile_sizes(lib):
+    _, w = _W([1, 1, 0, 1])  # 3^k entries
+    got = [lib.kron_xor_random_workspace_bytes(2, w, 12, r - 3 ** 12, 4)
+           for r in (1 << 20, (1 << 20) + 1, (1 << 20) + 4097, 1 << 24, (1 << 24) + 1, (1 << 24) + 8193)]
+    assert got == sorted(got), got

@@ -67,3 +67,21 @@ def test_xor_errors(sfg):
         sfg.kron_xor_random(3, np.zeros((3, 3), np.float32), 2, 10)
     with pytest.raises(SfgenError):
         sfg.kron_xor_random(2, np.ones((2, 2), np.float32), 32, 10)  # 2^32 vertices
+
+
+@pytest.mark.parametrize("seed_m,k,M", [
+    (np.array([[1, 1], [0, 0]]), 11, 0),               # exactly one of the shortest tiles, and one entry more
+    (np.array([[1, 1], [0, 0]]), 11, 1),
+    (np.array([[1, 1], [1, 0]]), 12, 2**20 - 3**12),   # the most entries in them, and one more
+    (np.array([[1, 1], [1, 0]]), 12, 2**20 - 3**12 + 1),
+    (np.array([[0, 1], [1, 0]]), 20, 1),
+    (np.array([[1, 1], [1, 0]]), 15, 2**24 - 3**15),   # the same of the middle ones
+    (np.array([[1, 1], [1, 0]]), 15, 2**24 - 3**15 + 1),
+])
+def test_xor_tile_sizes_match_oracle(sfg, orc, seed_m, k, M):
+    seed_m = np.asarray(seed_m, np.float32)
+    rp, col = sfg.kron_xor_random(2, seed_m, k, M, seed=29, graph_id=1, id_bytes=4)
+    orp, ocol = orc.kron_xor_random(seed_m, k, M, 29, 1)
+    np.testing.assert_array_equal(rp.cpu().numpy().astype(np.uint64), orp)
+    np.testing.assert_array_equal(col[:int(orp[-1])].cpu().numpy().astype(np.int64), ocol)
+    assert sfg.device_error() == 0
