@@ -68,7 +68,7 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // whole tile, so they are moved from LDS into scalar registers: the Philox key
 // schedule and the bucket thresholds then cost no vector instructions.  The
 // decode is chosen by the tile's own member: a 2 x 2 initiator takes its bits
-// from three comparisons (Form::Bits in kron.hip), others compare with 8 or 15
+// from three comparisons (Form::Bits in kron.hip), others compare with 3, 8 or 15
 // thresholds.  Bound by vector instructions; with 15 comparisons for every word
 // of a batch that holds a 3 x 3 member it took 1.64 ms for the 96 graphs of a
 // table, now 1.18.
@@ -141,6 +141,8 @@ __global__ __launch_bounds__(kKronThreads) void kron_batch(const KGraph *G, uint
         };
         if (decode == kDecodeBits)
             sample(std::integral_constant<int, 0>{});
+        else if (decode <= 3)
+            sample(std::integral_constant<int, 3>{});
         else if (decode <= 8)
             sample(std::integral_constant<int, 8>{});
         else

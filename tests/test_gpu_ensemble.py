@@ -177,3 +177,23 @@ def test_captured_graph_replays_equal_eager(sfg):
         sfg.ensemble_generate(other, num_samples=700, stat_seed=9, ws=ws, check=True,
                               tuning=sfg.ensemble_tuning(1 << 16, 8, 4, graph=False))
         torch.cuda.synchronize()
+
+
+def test_members_of_every_decode_equal_plain(sfg):
+    """One batch of members with 1 to 16 cells in 2 x 2, 3 x 3 and 4 x 4 initiators, the
+    first cell among them or not: 0, up to 3, up to 8 and more thresholds."""
+    rng = np.random.default_rng(8)
+    rows = []
+    for n0, k in ((2, 9), (3, 6), (4, 5)):
+        for cells in range(1, n0 * n0 + 1):
+            for first in (True, False) if cells < n0 * n0 else (True,):
+                at = rng.permutation(np.arange(1, n0 * n0))[:cells - first]
+                W = np.zeros(n0 * n0, np.float32)
+                W[np.concatenate([at, [0] if first else []]).astype(int)] = rng.uniform(0.1, 1.0, cells)
+                rows.append(dict(kind="kron", graph_id=len(rows), seed=31, n0=n0, k=k, num_edges=2_311,
+                                 initiator=W.reshape(n0, n0)))
+    hist, gamma, closed = (x.cpu().numpy() for x in sfg.ensemble_generate(
+        sfg.graph_descs(rows), num_samples=500, stat_seed=STAT_SEED, max_batch_edges=1 << 20, check=True))
+    for i, (h, g, c) in enumerate(_plain(sfg, rows, 500)):
+        np.testing.assert_array_equal(hist[i], h, err_msg=f"member {i}")
+        assert closed[i] == c and _same_gamma(float(gamma[i]), g), i
