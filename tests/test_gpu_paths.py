@@ -142,3 +142,37 @@ def test_listed_only_by_others_matches_oracle(sfg, orc, id_bytes):
         exp = orc.path_stats(n, trp, t[:, 1], np.array(srcs))
         assert exp[1] > 50
         assert _gpu(sfg, n, rp, a[:, 1], srcs, id_bytes) == tuple(int(x) for x in exp)
+
+
+@pytest.mark.parametrize("n", [2**18 - 1, 2**18, 2**18 + 1, 2**19, 2**19 + 33, 2**20 + 77, 2**22 - 5])
+@pytest.mark.parametrize("id_bytes", [4, 8])
+def test_coarse_bitmap_sizes_match_oracle(sfg, orc, n, id_bytes):
+    """Vertices on both sides of the sizes at which a bit of the coarse bitmap stands
+    for 1, 2, 4, 8 and 16 of them.  Half of them hang on a few hubs (more than 4,096
+    edges) and on each other, so that the frontier fills, passes an eighth of the
+    vertices and empties again; a path of 40 behind the last, some cycles far from
+    the hubs, and idle vertices between; two groups of sources."""
+    import torch
+    rng = np.random.default_rng(n)
+    core = n // 2
+    u = np.concatenate([rng.integers(0, 6, core), rng.integers(0, core, core // 2), rng.integers(6, 300, core // 8)])
+    v = np.concatenate([np.arange(core), rng.integers(0, core, core // 2), rng.integers(0, core, core // 8)])
+    tail = np.arange(n - 41, n - 1)
+    ring = np.arange(core + 1000, core + 1200)
+    u = np.concatenate([u, tail, [core - 1], ring, [ring[-1]]])
+    v = np.concatenate([v, tail + 1, [n - 41], ring + 1, [ring[0]]])
+    src, dst = torch.tensor(u).cuda(), torch.tensor(v).cuda()
+    rp, col, _, _ = sfg.edges_to_csr(n, src, dst, flags=sfg.CSR_SYMMETRIZE | sfg.CSR_SIMPLE)
+    kept = int(rp[-1])
+    col = col[:kept].to(torch.int32) if id_bytes == 4 else col[:kept]
+    sources = np.concatenate([rng.integers(0, core, 3), [n - 1, int(ring[7]), n - 50, 2]])
+    if id_bytes == 4:  # a second group, in which most sources are near
+        sources = np.concatenate([np.resize(sources[:4], 64), sources[4:]])
+    out = sfg.path_stats(n, rp, col, sources)
+    got = tuple(int(x) for x in out.cpu().numpy())
+    uniq, times = np.unique(sources, return_counts=True)
+    parts = [orc.path_stats(n, rp.cpu().numpy().astype(np.uint64), col.cpu().numpy().astype(np.int64), np.array([s])) for s in uniq]
+    want = (sum(int(p[0]) * int(t) for p, t in zip(parts, times)), sum(int(p[1]) * int(t) for p, t in zip(parts, times)),
+            max(int(p[2]) for p in parts))
+    assert got == want
+    assert want[2] >= 42
