@@ -79,3 +79,39 @@ def test_capacity_error(sfg):
         sfg.kron_perturbed(5, FIG2, 4, 0.0, 0.0, 11 ** 4 - 1)
     with pytest.raises(SfgenError):
         sfg.kron_perturbed(9, np.ones((9, 9), np.float32), 2, 0.0, 0.0, 100)
+
+
+@pytest.mark.parametrize("n0,cells,k,p_add,p_del", [(2, 1, 12, 0.4, 0.1), (3, 4, 7, 0.1, 0.2), (4, 16, 5, 0.0, 0.3),
+                                                    (7, 49, 3, 0.0, 0.5), (3, 3, 9, 0.0, 0.6), (3, 3, 9, 0.0, 1.0)])
+def test_capacity_decides_by_the_first_level_above_it(sfg, orc, n0, cells, k, p_add, p_del):
+    """The first iteration above the capacity is named, with its size, and no output is
+    touched; a capacity that every level fits gives the edges.  The sizes are the oracle's,
+    of the powers by fewer levels."""
+    import ctypes
+    import re
+    import torch
+    m = np.zeros(n0 * n0, np.float32)
+    m[np.random.default_rng(n0 * 100 + cells).permutation(n0 * n0)[:cells]] = 1
+    m = m.reshape(n0, n0)
+    edges = [orc.kron_perturbed(m, it, p_add, p_del, 23, 1, cap=3_000_000) for it in range(1, k + 1)]
+    sizes = [len(e[0]) for e in edges]
+    lib = sfg.load()
+    for capacity in sorted({cells, sizes[-1], max(sizes) - 1, max(sizes), max(sizes) + 7, max(sizes[:-1])} - {0}):
+        if capacity < cells:
+            continue
+        src = torch.full((capacity,), -7, dtype=torch.int32, device="cuda")
+        dst, count = src.clone(), torch.full((1,), -7, dtype=torch.int64, device="cuda")
+        ws = sfg.workspace(lib.kron_perturbed_workspace_bytes(capacity))
+        p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+        rc = lib.kron_perturbed(n0, m.ctypes.data_as(ctypes.c_void_p), k, p_add, p_del, 23, 1, 4, capacity, p(src), p(dst),
+                                p(count), p(ws), ws.numel(), None)
+        above = [it for it in range(2, k + 1) if sizes[it - 1] > capacity]
+        if above:
+            assert rc == sfg.SFG_ENOSPACE
+            assert re.search(f"iteration {above[0]} has {sizes[above[0] - 1]} edges, capacity is {capacity}$",
+                             lib.sfg_last_error().decode())
+            assert int(count) == -7 and bool((src == -7).all()) and bool((dst == -7).all())
+        else:
+            assert rc == 0 and int(count) == sizes[-1]
+            np.testing.assert_array_equal(src[:sizes[-1]].cpu().numpy(), edges[-1][0])
+            np.testing.assert_array_equal(dst[:sizes[-1]].cpu().numpy(), edges[-1][1])
