@@ -176,3 +176,47 @@ def test_coarse_bitmap_sizes_match_oracle(sfg, orc, n, id_bytes):
             max(int(p[2]) for p in parts))
     assert got == want
     assert want[2] >= 42
+
+
+def test_more_vertices_than_32_bit_ids(sfg):
+    """Above 2^32 vertices (nearly all idle): 64-bit lists, no bitmaps.  A hub shared by
+    several wavefronts, one swept by a wavefront, one of 40 edges and a path across
+    2^32; 68 sources, some repeated, against a search over the few rows with entries."""
+    import collections
+    import torch
+    n = (1 << 32) + 70_001
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 175 << 30:
+        pytest.skip("needs 175 GiB of GPU memory")
+    hub, leaf, path = n - 1, n - 60_000, n - 40_000
+    pairs = [(hub, leaf + i) for i in range(5_000)] + [(17, v) for v in range((1 << 32) - 300, (1 << 32) + 300)]
+    pairs += [(23, v) for v in range(100, 140)] + [(path + i, path + i + 1) for i in range(12)]
+    pairs += [(leaf, 17), (23, 17), (path, 100)]
+    a = np.array(pairs, np.int64)
+    a = np.concatenate([a, a[:, ::-1]])
+    a = a[np.lexsort((a[:, 1], a[:, 0]))]
+    ids, counts = np.unique(a[:, 0], return_counts=True)
+    starts = np.cumsum(counts)
+    rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    for v, end, at in zip(ids, np.append(ids[1:], n), starts):
+        rp[int(v) + 1:int(end) + 1] = int(at)
+    neighbours = collections.defaultdict(list)
+    for u, v in a.tolist():
+        neighbours[u].append(v)
+
+    def search(s):
+        dist, queue = {s: 0}, collections.deque([s])
+        while queue:
+            u = queue.popleft()
+            for v in neighbours[u]:
+                if v not in dist:
+                    dist[v] = dist[u] + 1
+                    queue.append(v)
+        return sum(dist.values()), len(dist) - 1, max(dist.values())
+
+    sources = [hub, 17, path + 10, 23, 50, leaf + 7] + [leaf + 1] * 62
+    found = [search(s) for s in sources]
+    out = sfg.path_stats(n, rp, torch.tensor(a[:, 1], device="cuda"), sources)
+    assert tuple(out.tolist()) == (sum(f[0] for f in found), sum(f[1] for f in found), max(f[2] for f in found))
+    del rp, out
+    torch.cuda.empty_cache()
