@@ -290,7 +290,7 @@ template <int LANES, typename Above> __device__ __forceinline__ uint64_t first_a
     return lo;
 }
 
-constexpr int kWedgeLanes = 16;  // lanes of a sample, where all of them fit the GPU at once
+constexpr int kWedgeLanes = 16;  // lanes of a sample, where all of them fit half the GPU at once
 
 struct WedgeArgs {
     const StatGraph *G;
@@ -304,9 +304,11 @@ struct WedgeArgs {
 
 // Sample i of graph g: Philox block (i, 0, 0, WEDGE | gid << 8).  Two searches,
 // one load after the other: few samples take LANES lanes each, which shortens
-// both (2,000 samples over 16,384 vertices 14.3 us with one lane, 8.3 with 16);
-// more samples than fit the GPU that way hide the latency behind one another
-// (9.6e5 over 1.7e7 vertices: 156 us).
+// both (2,000 samples over 16,384 vertices 14.3 us with one lane, 8.3 with 16); from
+// the number on whose lanes take half the GPU one lane each is as fast, since the
+// samples hide the latency behind one another.  The statistics of 2^18 edges in us
+// with one lane / 16: 112.0 / 108.4 for 16,384 samples, 112.0 / 110.3 for 32,768, 112.6 /
+// 113.3 for 40,000, 113.8 / 117.1 for 65,536, 116.2 / 123.0 for 100,000.
 template <typename IdT, int LANES> __global__ __launch_bounds__(256) void wedge_sample(WedgeArgs a) {
     const uint64_t total_items = (uint64_t)a.count * a.samples;
     const uint64_t stride = (uint64_t)gridDim.x * (256 / LANES);
@@ -421,7 +423,7 @@ int stats_enqueue(StatGraph *G_dev, uint32_t count, uint64_t total_chunks, uint6
                      reinterpret_cast<unsigned long long *>(closed), nv};
         const uint64_t items = (uint64_t)count * samples;
         const uint64_t resident = (uint64_t)device_cu_count() * 16;  // workgroups
-        const int lanes = items * kWedgeLanes <= resident * 256 ? kWedgeLanes : 1;
+        const int lanes = items * kWedgeLanes * 2 <= resident * 256 ? kWedgeLanes : 1;
         const unsigned g = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((items * lanes + 255) / 256, resident));
         ProfScope _ps("stats_wedge", s);
         if (id_bytes == 4 && lanes > 1)

@@ -80,3 +80,13 @@ def test_stats_sample_lanes(sfg, orc, samples):
     src = np.minimum(rng.zipf(1.5, size=E) - 1, n - 1)
     dst = np.minimum(rng.zipf(1.3, size=E) - 1, n - 1)
     _check(sfg, orc, n, src, dst, samples, 11, 6, 8 if samples % 2 else 4)
+
+
+@pytest.mark.parametrize("samples", [32_767, 32_768, 32_769])
+def test_stats_sample_lanes_at_their_line(sfg, orc, samples):
+    """The last sample counts at 16 lanes each and the first at one (on 256 CUs)."""
+    rng = np.random.default_rng(samples)
+    n, E = 20_000, 60_000
+    src = np.minimum(rng.zipf(1.5, size=E) - 1, n - 1)
+    dst = np.minimum(rng.zipf(1.3, size=E) - 1, n - 1)
+    _check(sfg, orc, n, src, dst, samples, 11, 6, 8 if samples % 2 else 4)
