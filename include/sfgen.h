@@ -81,8 +81,8 @@ int sfg_device_error(void *stream, uint32_t *code);
  * the stream is being captured into a graph are not timed.  Kernel names:
  * "kron_sample", "kron_enumerate", "csr_prepare",
  * "radix_pass", "csr_finish", "csr_rowfill", "fill",
- * "pba_fill", "pba_resolve", "pba_tile_table", "pba_count", "pba_scan",
- * "pba_substitute", "stats_chunks", "stats_gamma",
+ * "pba_fill", "pba_resolve", "pba_count", "pba_scan", "pba_substitute",
+ * "csr_run_starts", "stats_chunks", "stats_gamma",
  * "stats_wedge_scan", "stats_wedge", "path_level", "block_count",
  * "random_pairs", "perturb_expand", "mlp_gemm", "mlp_elementwise",
  * "mlp_adam", "mlp_round", "mlp_rows", "mlp_wgrad", "mlp_update". */
@@ -535,7 +535,7 @@ int adam_step_device(uint64_t count, float *params, const float *grad, float *m,
  * weighted squared-error loss and its gradient, the backward pass and Adam
  * (with the learning rate and the step counter in device memory, as
  * adam_step_device), with the rounding points above.  The first launch
- * rounds the weights to bfloat16 (row-major and transposed); the second
+ * rounds the weights to bfloat16 (and their transposes); the second
  * runs, for every block of 16 to 64 rows, the forward pass, the loss gradient and
  * the chain of activation gradients on the matrix cores with the layer
  * operand in LDS; the third computes every weight-gradient tile over each

@@ -704,7 +704,7 @@ __global__ __launch_bounds__(256) void mlp_wgrad(WgradArgs a) {
             }
             rem -= groups;
         }
-        // The losses: lane c sums those of blocks c, c + 64, ..
+        // The losses: thread i sums those of blocks i, i + 256, ..
         float x = 0.f;
         for (int b = tid; b < a.blocks; b += 256) x += a.t.lossp[b];
         for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
